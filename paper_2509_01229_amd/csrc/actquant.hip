@@ -7,14 +7,13 @@
 //     Q[m,k]  = clamp(rint(x'[m,k] / s_x[m]), -127, 127)
 //
 // Every operation is one correctly rounded FP32 operation, so the INT8 result is determined
-// bit for bit; the kernel reproduces it exactly (see round8 for how the second division is
-// avoided where it cannot matter).
+// bit for bit; the kernel reproduces it exactly (see div_by and round8 for how the two divisions
+// are shortened where that cannot matter).
 //
-// One block of 256 threads per token (or per R consecutive tokens, one after the other, so
-// that the reciprocals of the smooth scales are computed once for R tokens).  A token of up
-// to 32768 elements is read from HBM once and kept in registers between the max pass and the
-// rounding pass (from 16392 elements on, on blocks of 512 or 1024 threads); longer tokens are
-// read twice (the second read hits L2).  Traffic: 2 bytes in, 1 byte out per element.
+// One block per token (or per R consecutive tokens, one after the other, so that the reciprocals
+// of the smooth scales are computed once for R tokens).  A token of up to 32768 elements is read
+// from HBM once and kept in registers between the max pass and the rounding pass; longer tokens
+// are read twice (the second read hits L2).  Traffic: 2 bytes in, 1 byte out per element.
 #include <algorithm>
 
 #include <hip/hip_fp16.h>
@@ -27,65 +26,7 @@ namespace lqq {
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kQuantThreads = 256;
-
-// 8 FP16 values (one 16-byte load) -> FP32, optionally divided by their smooth scales
-struct Raw8 {
-    u32x4 x;
-    float4 s0, s1;
-};
-template <bool SMOOTH>
-__device__ __forceinline__ Raw8 load8(const u32x4 *xrow, const float *smooth, int i)
-{
-    Raw8 r;
-    r.x = xrow[i];
-    if (SMOOTH) {
-        r.s0 = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)i);
-        r.s1 = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)i + 4);
-    }
-    return r;
-}
-template <bool SMOOTH>
-__device__ __forceinline__ void convert8(const Raw8 &r, float (&f)[8])
-{
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t w = r.x[d];
-        const f16x2 h = __builtin_bit_cast(f16x2, w);
-        f[2 * d] = (float)h[0];
-        f[2 * d + 1] = (float)h[1];
-    }
-    if (SMOOTH) {
-        f[0] /= r.s0.x, f[1] /= r.s0.y, f[2] /= r.s0.z, f[3] /= r.s0.w;
-        f[4] /= r.s1.x, f[5] /= r.s1.y, f[6] /= r.s1.z, f[7] /= r.s1.w;
-    }
-}
-
-// x / s, correctly rounded, from a reciprocal refined once per smooth scale.  This is the
-// instruction sequence of the IEEE division without its scaling and special-case steps
-// (y1 = rcp refined by one Newton step; quotient x * y1 corrected twice with exact
-// residuals), which change nothing while s is within [2^-40, 2^40] and x is zero or an FP16
-// magnitude (2^-24 .. 65504): no intermediate leaves the normal range.  Callers check s.
-struct Recip {
-    float s, y1;
-};
-__device__ __forceinline__ Recip refine_recip(float s)
-{
-    const float y0 = __builtin_amdgcn_rcpf(s);
-    const float e = __builtin_fmaf(-s, y0, 1.0f);
-    return Recip{s, __builtin_fmaf(e, y0, y0)};
-}
-__device__ __forceinline__ float div_by(float x, const Recip r)
-{
-    const float q0 = x * r.y1;
-    const float r0 = __builtin_fmaf(-r.s, q0, x);
-    const float q1 = __builtin_fmaf(r0, r.y1, q0);
-    const float r1 = __builtin_fmaf(-r.s, q1, x);
-    return __builtin_fmaf(r1, r.y1, q1);
-}
-__device__ __forceinline__ bool recip_is_safe(float s) { return s >= 0x1p-40f && s <= 0x1p40f; }
-
-// 8 FP16 values -> FP32 (no smooth divide)
+// 8 FP16 values (one 16-byte load) -> FP32
 __device__ __forceinline__ void widen8(const u32x4 x, float (&f)[8])
 {
 #pragma unroll
@@ -97,49 +38,82 @@ __device__ __forceinline__ void widen8(const u32x4 x, float (&f)[8])
     }
 }
 
+// the smooth scales of piece i (8 columns)
+__device__ __forceinline__ void load_smooth8(const float *smooth, int i, float (&s)[8])
+{
+    const float4 a = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)i);
+    const float4 b = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)i + 4);
+    s[0] = a.x, s[1] = a.y, s[2] = a.z, s[3] = a.w;
+    s[4] = b.x, s[5] = b.y, s[6] = b.z, s[7] = b.w;
+}
+
+// x / s, correctly rounded, with y = the correctly rounded 1 / s: one exact residual corrects the
+// quotient x * y.  For a general x that can miss by one unit; for the 11-bit significand of an
+// FP16 x it never does (tests/native/short_division.c goes through all 2^23 x 2^10 pairs of
+// significands).  No intermediate leaves the normal range while s is within [2^-40, 2^40]
+// (x is zero or 2^-24 .. 65504); callers check that.
+__device__ __forceinline__ float div_by(float x, float s, float y)
+{
+    const float q = x * y;
+    return __builtin_fmaf(__builtin_fmaf(-s, q, x), y, q);
+}
+__device__ __forceinline__ bool short_division_is_exact(float s) { return s >= 0x1p-40f && s <= 0x1p40f; }
+
 __device__ __forceinline__ float max_abs8(const float (&f)[8], float m)
 {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(f[e]));
+    for (int e = 0; e < 8; e += 2) m = fmaxf(fmaxf(m, fabsf(f[e])), fabsf(f[e + 1]));
     return m;
 }
 
-// Q = clamp(rint(f / s)) for 8 values.  The FP32 quotient is only needed to decide an
-// integer, so the common case multiplies by an approximate reciprocal: that product and
-// the correctly rounded quotient both lie within 127 * (2^-23 + 2^-24 + 2^-24) < 3.1e-5 of
-// the exact quotient (|f / s| <= 127), hence they round to the same integer unless the
-// product is within 1e-4 of a tie.  Only then (about 1 lane-visit in 600) the 8 values
-// are redone with the full IEEE division, so the result is always that of the division.
+// Q = clamp(rint(f / s)) for 8 values.  The FP32 quotient is only needed to decide an integer, so
+// the common case multiplies by an approximate reciprocal, in one FMA with 1.5 * 2^23: the sum is
+// rounded to an integer, which is its low byte.  The exact product and the correctly rounded
+// quotient both lie within 127 * (2^-23 + 2^-24) < 2.3e-5 of the exact quotient (|f / s| <= 127),
+// hence they round to the same integer unless the product is within 1e-4 of a tie.  Only then
+// (about 1 lane-visit in 600; also where a value is not finite) the 8 values are redone with the
+// IEEE division, so the result is always that of the division.
 __device__ __forceinline__ uint2 round8(const float (&f)[8], float s, float rcp_s)
 {
-    float q[8];
+    constexpr float kMagic = 0x1.8p23f;
+    uint32_t u[8];
     bool near_tie = false;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const float t = f[e] * rcp_s;
-        q[e] = __builtin_rintf(t);
-        near_tie |= fabsf(t - q[e]) > 0.5f - 1e-4f;
+        const float t = __builtin_fmaf(f[e], rcp_s, kMagic);
+        const float off = __builtin_fmaf(f[e], rcp_s, -(t - kMagic));
+        near_tie |= !(fabsf(off) <= 0.5f - 1e-4f);  // (true for NaN)
+        u[e] = __builtin_bit_cast(uint32_t, t);
     }
-    if (near_tie) {
+    // (a branch the compiler must not turn into 8 divisions and selects for everybody)
+    if (__builtin_expect_with_probability(near_tie, 0, 0.999)) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = __builtin_rintf(f[e] / s);
+        for (int e = 0; e < 8; ++e) u[e] = (uint32_t)(int)fminf(fmaxf(__builtin_rintf(f[e] / s), -127.0f), 127.0f);
     }
-    uint32_t w[2] = {0, 0};
+    uint32_t w[2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float c = fminf(fmaxf(q[e], -127.0f), 127.0f);
-        w[e >> 2] |= ((uint32_t)(int)c & 0xffu) << (8 * (e & 3));
-    }
+    for (int h = 0; h < 2; ++h)  // the low bytes of four registers
+        w[h] = __builtin_amdgcn_perm(u[4 * h + 1], u[4 * h], 0x0c0c0400u) |
+               __builtin_amdgcn_perm(u[4 * h + 3], u[4 * h + 2], 0x04000c0cu);
     return uint2{w[0], w[1]};
 }
 
-// maximum over the block of NWAVES waves; every thread gets the result
-template <int NWAVES = 4>
+// maximum (of values >= 0) over the block of NWAVES waves; every thread gets the result
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float lane_shift_or_0(float m)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), CTRL, ROWS, 0xf, ROWS == 0xf));
+}
+template <int NWAVES>
 __device__ __forceinline__ float block_max(float m, float *s_part)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = m;
+    m = fmaxf(m, lane_shift_or_0<0x111, 0xf>(m));  // row_shr 1, 2, 4, 8: lane 15 of each row of 16
+    m = fmaxf(m, lane_shift_or_0<0x112, 0xf>(m));
+    m = fmaxf(m, lane_shift_or_0<0x114, 0xf>(m));
+    m = fmaxf(m, lane_shift_or_0<0x118, 0xf>(m));
+    m = fmaxf(m, lane_shift_or_0<0x142, 0xa>(m));  // row_bcast 15, 31: lane 63 of the wave
+    m = fmaxf(m, lane_shift_or_0<0x143, 0xc>(m));
+    if ((threadIdx.x & 63) == 63) s_part[threadIdx.x >> 6] = m;
     __syncthreads();
     float r = s_part[0];
 #pragma unroll
@@ -150,8 +124,9 @@ __device__ __forceinline__ float block_max(float m, float *s_part)
 // Tokens of any length, one per block, read twice.  Loads of a pass are issued four pieces at
 // a time, with indices past the end clamped to the last piece and their values ignored, so
 // that no load waits behind a branch.
+constexpr int kLongThreads = 256;
 template <bool SMOOTH>
-__global__ __launch_bounds__(kQuantThreads) void quantize_act_long_kernel(
+__global__ __launch_bounds__(kLongThreads) void quantize_act_long_kernel(
     int K, const __half *__restrict__ X, const float *__restrict__ smooth, int8_t *__restrict__ Q,
     float *__restrict__ sx)
 {
@@ -162,199 +137,176 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_long_kernel(
     const int n8 = K >> 3;
     constexpr int U = 4;  // pieces in flight per thread
 
-    float amax = 0.0f;
-    float f[U][8];
-    for (int i0 = tid; i0 < n8; i0 += U * kQuantThreads) {
-        Raw8 raw[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) raw[u] = load8<SMOOTH>(xrow, smooth, min(i0 + u * kQuantThreads, n8 - 1));
+    float f[U][8], sm[SMOOTH ? U : 1][8];
+    auto load = [&](int i0) {
+        u32x4 raw[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            convert8<SMOOTH>(raw[u], f[u]);
-            if (i0 + u * kQuantThreads < n8) amax = max_abs8(f[u], amax);
+            const int i = min(i0 + u * kLongThreads, n8 - 1);
+            raw[u] = xrow[i];
+            if (SMOOTH) load_smooth8(smooth, i, sm[u]);
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            widen8(raw[u], f[u]);
+            if (SMOOTH) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f[u][e] /= sm[u][e];
+            }
+        }
+    };
+    float amax = 0.0f;
+    for (int i0 = tid; i0 < n8; i0 += U * kLongThreads) {
+        load(i0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) amax = max_abs8(f[u], amax);  // (a piece read twice changes nothing)
     }
-    amax = block_max(amax, s_part);
+    amax = block_max<4>(amax, s_part);
     const float s = amax > 0.0f ? amax / 127.0f : 1.0f;
     if (tid == 0) sx[m] = s;
     const float rcp_s = __builtin_amdgcn_rcpf(s);
-    for (int i0 = tid; i0 < n8; i0 += U * kQuantThreads) {
-        Raw8 raw[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) raw[u] = load8<SMOOTH>(xrow, smooth, min(i0 + u * kQuantThreads, n8 - 1));
+    for (int i0 = tid; i0 < n8; i0 += U * kLongThreads) {
+        load(i0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            convert8<SMOOTH>(raw[u], f[u]);
-            const int i = i0 + u * kQuantThreads;
+            const int i = i0 + u * kLongThreads;
             if (i < n8) qrow[i] = round8(f[u], s, rcp_s);
         }
     }
 }
 
-// Register-resident tokens (K <= ITERS x NT x 8), R consecutive tokens per block.  Thread t owns
-// the 16-byte pieces t, t + NT, ... of every token of its block, i.e. fixed columns: their
-// smooth scales and refined reciprocals are loaded and computed once.
-// KEEP = false (tokens of 16392..32768 elements, on 512 or 1024 threads): what would not fit in
-// registers is not kept -- with smooth scales the reciprocals (the scales are re-read for
-// every token and divided by with the IEEE division), without them the widened values.
-template <bool SMOOTH, int ITERS, int NT, bool KEEP = true>
+// Register-resident tokens (K <= ITERS x NT x 8).  Thread t owns the 16-byte pieces t, t + NT, ...
+// of a token, i.e. fixed columns; pieces past the end repeat the last one, which leaves the maximum
+// alone, and are not stored.
+//   SEVERAL: a block takes R consecutive tokens; the smooth scales and their reciprocals are loaded
+//     and computed once, and the loads of the next two tokens are in flight while one is worked on.
+//     The loads and stores of that loop are all unconditional (past the end: the last token once
+//     more, the last piece once more with the same bytes), so that the compiler can count them and
+//     a token waits for its own loads only.
+//   Otherwise one token per block, and with gridDim.y > 1 a share of its pieces: every block of a
+//     token finds the maximum of the whole token and rounds and stores ITERS / gridDim.y of its
+//     pieces per thread.
+// About 10 instructions per element with smooth scales, 6 without; large calls move their bytes at
+// the rate of a copy or near it, small ones take the launch, one load and one store.
+template <bool SMOOTH, int ITERS, int NT, bool SEVERAL>
 __global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
     int M, int K, int R, const __half *__restrict__ X, const float *__restrict__ smooth,
     int8_t *__restrict__ Q, float *__restrict__ sx)
 {
-    __shared__ float s_part[2][NT / 64];
+    __shared__ __attribute__((aligned(16))) float s_part[2][NT / 64];
     const int tid = threadIdx.x;
     const int n8 = K >> 3;
+    const int it_begin = ITERS * (int)blockIdx.y / (int)gridDim.y, it_end = ITERS * ((int)blockIdx.y + 1) / (int)gridDim.y;
     int piece[ITERS];
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) piece[it] = min(it * NT + tid, n8 - 1);
+    const int m_begin = (int)blockIdx.x * (SEVERAL ? R : 1), m_end = SEVERAL ? min(M, m_begin + R) : m_begin + 1;
 
-    // the first token's loads go out before anything waits for the smooth scales
-    const int m_begin = blockIdx.x * R, m_end = min(M, m_begin + R);
-    u32x4 raw[ITERS];
-    if (m_begin < m_end) {
-        const u32x4 *xrow = reinterpret_cast<const u32x4 *>(X + (size_t)m_begin * K);
+    u32x4 raw[SEVERAL ? 2 : 1][ITERS];  // this token and the next
+    auto load = [&](int m, u32x4 (&r)[ITERS]) {
+        const u32x4 *xrow = reinterpret_cast<const u32x4 *>(X + (size_t)min(m, m_end - 1) * K);
 #pragma unroll
-        for (int it = 0; it < ITERS; ++it) raw[it] = xrow[piece[it]];
-    }
+        for (int it = 0; it < ITERS; ++it) r[it] = xrow[piece[it]];
+    };
+    // (the loads of the first tokens go out before anything waits for the smooth scales)
+    load(m_begin, raw[0]);
+    if constexpr (SEVERAL) load(m_begin + 1, raw[1]);
 
-    Recip rc[SMOOTH && KEEP ? ITERS : 1][8];
+    float sm[SMOOTH ? ITERS : 1][8], rc[SMOOTH && SEVERAL ? ITERS : 1][8];
     bool safe = true;  // every smooth scale of this thread allows the short division
-    if (SMOOTH && KEEP) {
+    if (SMOOTH) {
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            const float4 a = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)piece[it]);
-            const float4 b = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)piece[it] + 4);
-            const float sm[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            load_smooth8(smooth, piece[it], sm[it]);
+            if (SEVERAL) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                rc[it][e] = refine_recip(sm[e]);
-                safe &= recip_is_safe(sm[e]);
+                for (int e = 0; e < 8; ++e) {
+                    rc[SEVERAL ? it : 0][e] = 1.0f / sm[it][e];
+                    safe &= short_division_is_exact(sm[it][e]);
+                }
             }
         }
     }
 
-    for (int m = m_begin; m < m_end; ++m) {
-        uint2 *qrow = reinterpret_cast<uint2 *>(Q + (size_t)m * K);
-        if (!SMOOTH && !KEEP) {
-            // Long tokens without smooth scales: only the FP16 token itself stays in registers
-            // between the two passes (4 registers per piece instead of 12) and widening is
-            // repeated, so that several blocks still share a CU (34 instead of 41 us for
-            // 2048 x 28672; shorter tokens are 5 % faster with the widened values kept).
-            if (m > m_begin) {
-                const u32x4 *xrow = reinterpret_cast<const u32x4 *>(X + (size_t)m * K);
-#pragma unroll
-                for (int it = 0; it < ITERS; ++it) raw[it] = xrow[piece[it]];
-            }
-            float amax = 0.0f;
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) {
-                float f[8];
-                widen8(raw[it], f);
-                if (it * NT + tid < n8) amax = max_abs8(f, amax);
-            }
-            amax = block_max<NT / 64>(amax, s_part[(m - m_begin) & 1]);
-            const float s = amax > 0.0f ? amax / 127.0f : 1.0f;
-            if (tid == 0) sx[m] = s;
-            const float rcp_s = __builtin_amdgcn_rcpf(s);
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) {
-                // (opaque to the compiler, so that it widens again instead of keeping the first pass's values)
-                asm volatile("" : "+v"(raw[it]));
-                float f[8];
-                widen8(raw[it], f);
-                const int i = it * NT + tid;
-                if (i < n8) qrow[i] = round8(f, s, rcp_s);
-            }
-            continue;
-        }
+    auto token = [&](int m, u32x4 (&r)[ITERS], float *part) {
         float f[ITERS][8];
         float amax = 0.0f;
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            widen8(raw[it], f[it]);
-            if (!SMOOTH) {
-            } else if (KEEP) {
-                if (safe) {
+            widen8(r[it], f[it]);
+            if (SMOOTH) {
+                if (SEVERAL && safe) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) f[it][e] = div_by(f[it][e], rc[KEEP ? it : 0][e]);
+                    for (int e = 0; e < 8; ++e) f[it][e] = div_by(f[it][e], sm[it][e], rc[SEVERAL ? it : 0][e]);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) f[it][e] = f[it][e] / rc[KEEP ? it : 0][e].s;
+                    for (int e = 0; e < 8; ++e) f[it][e] /= sm[it][e];
                 }
-            } else {
-                const float4 a = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)piece[it]);
-                const float4 b = *reinterpret_cast<const float4 *>(smooth + 8 * (size_t)piece[it] + 4);
-                const float sm[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) f[it][e] = f[it][e] / sm[e];
             }
-            if (it * NT + tid < n8) amax = max_abs8(f[it], amax);
+            amax = max_abs8(f[it], amax);
         }
-        if (m + 1 < m_end) {  // the next token's loads fly while this one is reduced, rounded and stored
-            const u32x4 *xrow = reinterpret_cast<const u32x4 *>(X + (size_t)(m + 1) * K);
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) raw[it] = xrow[piece[it]];
-        }
-        amax = block_max<NT / 64>(amax, s_part[(m - m_begin) & 1]);
+        if (SEVERAL) load(m + 2, r);
+        amax = block_max<NT / 64>(amax, part);
         const float s = amax > 0.0f ? amax / 127.0f : 1.0f;
-        if (tid == 0) sx[m] = s;
+        if (tid == 0 && blockIdx.y == 0) sx[m] = s;
         const float rcp_s = __builtin_amdgcn_rcpf(s);
+        uint2 *qrow = reinterpret_cast<uint2 *>(Q + (size_t)m * K);
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            const int i = it * NT + tid;
-            if (i < n8) qrow[i] = round8(f[it], s, rcp_s);
+            if (!SEVERAL && (it < it_begin || it >= it_end)) continue;  // (block-uniform)
+            const uint2 q = round8(f[it], s, rcp_s);
+            if (SEVERAL || it * NT + tid < n8) qrow[piece[it]] = q;
+        }
+    };
+    token(m_begin, raw[0], s_part[0]);
+    if constexpr (SEVERAL) {
+        for (int m = m_begin + 1; m < m_end; m += 2) {
+            token(m, raw[1], s_part[1]);
+            if (m + 1 == m_end) break;
+            token(m + 1, raw[0], s_part[0]);
         }
     }
 }
 
-template <bool SMOOTH>
-static void launch_quantize(int M, int K, const __half *X, const float *smooth, int8_t *Q, float *sx,
-                            hipStream_t st)
+template <bool SMOOTH, int ITERS, int NT, bool SEVERAL = false>
+static void launch_rows(int M, int K, int R, int shares, const __half *X, const float *smooth, int8_t *Q, float *sx,
+                        hipStream_t st)
 {
-    const dim3 block(kQuantThreads);
-    const int pieces = (K / 8 + kQuantThreads - 1) / kQuantThreads;  // 16-byte pieces per thread
-    // tokens per block: as many as leave four blocks per CU (with smooth scales only: without
-    // them there is nothing to share between tokens; three blocks of this kernel fit a CU, and
-    // 1024 blocks measured 3 to 12 % faster than 512 on 4096 tokens of 8192 and 4096 elements)
-    const int R = !SMOOTH ? 1 : std::max(1, (M + 1023) / 1024);
-    const dim3 grid((unsigned)((M + R - 1) / R));
-#define LQ_LAUNCH_Q(ITERS) \
-    hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, ITERS, kQuantThreads>), grid, block, 0, st, M, K, R, X, \
-                       smooth, Q, sx)
-    if (pieces <= 1)
-        LQ_LAUNCH_Q(1);
-    else if (pieces <= 2)
-        LQ_LAUNCH_Q(2);
-    else if (pieces <= 4)
-        LQ_LAUNCH_Q(4);
-    else if (pieces <= 8) {
-        // 8193..16384 columns.  With smooth scales the reciprocals triple the registers per
-        // piece: blocks of 512 threads keep twice the waves on a CU (64 instead of 72 us for
-        // 4096 x 16384, 32 instead of 38 for 2048 x 14336).
-        if constexpr (SMOOTH) {
-            if (pieces <= 6)
-                hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, 3, 512>), grid, dim3(512), 0, st, M, K, R, X,
-                                   smooth, Q, sx);
-            else
-                hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, 4, 512>), grid, dim3(512), 0, st, M, K, R, X,
-                                   smooth, Q, sx);
-        } else {
-            if (pieces <= 6)
-                LQ_LAUNCH_Q(6);
-            else
-                LQ_LAUNCH_Q(8);
-        }
-    } else if (pieces <= 16) {  // up to 32768 columns: still register-resident, on larger blocks
-        if constexpr (SMOOTH)
-            hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, 4, 1024, false>), dim3((unsigned)M), dim3(1024), 0, st,
-                               M, K, 1, X, smooth, Q, sx);
-        else
-            hipLaunchKernelGGL((quantize_act_rows_kernel<false, 8, 512, false>), dim3((unsigned)M), dim3(512), 0, st, M,
-                               K, 1, X, smooth, Q, sx);
-    } else
-        hipLaunchKernelGGL((quantize_act_long_kernel<SMOOTH>), dim3((unsigned)M), block, 0, st, K, X, smooth, Q, sx);
-#undef LQ_LAUNCH_Q
+    hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, ITERS, NT, SEVERAL>), dim3((unsigned)((M + R - 1) / R), (unsigned)shares),
+                       dim3(NT), 0, st, M, K, R, X, smooth, Q, sx);
+}
+
+// Block shapes, from sweeps of threads x pieces per thread x tokens per block over M = 4..8192 and
+// K = 2048..28672 (microseconds of the rule / of blocks of 256 threads with all pieces of a token):
+//   many tokens, no smooth scales: 512 threads above 4096 columns (13.0 / 13.8 on 2048 x 11008, 40.2 /
+//     43.5 on 6000 x 14336), 256 up to there (13.3 / 13.5 on 6000 x 4096; 512 threads: 15.6) and one
+//     piece per thread up to 2048 (11.0 / 15.5 on 8192 x 2048);
+//   many tokens with smooth scales: from 1024 tokens on several tokens per block, as many as leave two
+//     blocks of 1024 threads per CU (one where a thread holds two pieces: 98 registers) -- 20.1 / 26.8
+//     on 4096 x 8192 (5.0 TB/s, a copy runs at 5.2), 38 / 60 on 4096 x 16384, 9.3 / 11.2 on 1024 x 8192;
+//     with at most 2048 columns a token is too short for that (16.0 / 20.2 on 8192 x 2048);
+//   few tokens: as many threads as a token has pieces, up to 512, and with at most 128 (token, share)
+//     pairs the pieces of a thread shared out over blocks (2.0 / 3.0 on 4 x 11008, 4.0 / 5.6 on 16 x 28672).
+template <bool SMOOTH>
+static void launch_quantize(int M, int K, const __half *X, const float *smooth, int8_t *Q, float *sx, hipStream_t st)
+{
+    const int n8 = K / 8;  // 16-byte pieces of a token
+    if (SMOOTH && M >= 1024 && K > 2048 && K <= 16384) {
+        const int R = (M + 511) / 512;
+        if (n8 <= 512) return launch_rows<SMOOTH, 1, 512, SMOOTH>(M, K, R, 1, X, smooth, Q, sx, st);
+        if (n8 <= 1024) return launch_rows<SMOOTH, 1, 1024, SMOOTH>(M, K, R, 1, X, smooth, Q, sx, st);
+        return launch_rows<SMOOTH, 2, 1024, SMOOTH>(M, K, (M + 255) / 256, 1, X, smooth, Q, sx, st);
+    }
+    if (n8 <= 256) return launch_rows<SMOOTH, 1, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+    if (n8 <= 512)
+        return M <= 512 ? launch_rows<SMOOTH, 1, 512>(M, K, 1, 1, X, smooth, Q, sx, st)
+                        : launch_rows<SMOOTH, 2, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+    auto shares = [&](int iters) { return M * iters <= 128 ? iters : 1; };
+    if (n8 <= 1024) return launch_rows<SMOOTH, 2, 512>(M, K, 1, shares(2), X, smooth, Q, sx, st);
+    if (n8 <= 1536) return launch_rows<SMOOTH, 3, 512>(M, K, 1, shares(3), X, smooth, Q, sx, st);
+    if (n8 <= 2048) return launch_rows<SMOOTH, 4, 512>(M, K, 1, shares(4), X, smooth, Q, sx, st);
+    if (n8 <= 4096) return launch_rows<SMOOTH, 4, 1024>(M, K, 1, shares(4), X, smooth, Q, sx, st);
+    hipLaunchKernelGGL((quantize_act_long_kernel<SMOOTH>), dim3((unsigned)M), dim3(kLongThreads), 0, st, K, X, smooth, Q, sx);
 }
 
 }  // namespace lqq

@@ -64,6 +64,33 @@ def test_several_tokens_per_block(M, K):
     assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
 
 
+# the block shapes change at these columns (pieces of 8 per thread and threads per token), with 1024
+# tokens (several per block) and with 128 (token, share) pairs (a token's pieces shared between blocks)
+@pytest.mark.parametrize("K", [2040, 2056, 4096, 4104, 8192, 8200, 12296, 16384, 16392, 32768])
+@pytest.mark.parametrize("M", [1, 32, 43, 65, 513])
+@pytest.mark.parametrize("with_smooth", [False, True])
+def test_edges_of_the_block_shapes(M, K, with_smooth):
+    _say(f"actquant block shapes M={M} K={K} smooth={with_smooth}")
+    X16 = WL.make_activations_f16(M, K, outlier_frac=0.001, seed=M * 7 + K)
+    smooth = WL.make_smooth(K, seed=K + 2) if with_smooth else None
+    q_ref, s_ref = O.quantize_activations(X16, smooth)
+    q, s = _run(X16, smooth)
+    assert np.array_equal(s.view(np.uint32), s_ref.view(np.uint32)), "per-token scales differ"
+    assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
+
+
+@pytest.mark.parametrize("M,K", [(1023, 2056), (1024, 2056), (1025, 4104), (1537, 8200), (1024, 8192), (1025, 16384), (1030, 12296)])
+def test_edges_of_several_tokens_per_block(M, K):
+    """Odd and even numbers of tokens per block, ragged last blocks and ragged last pieces."""
+    _say(f"actquant several tokens M={M} K={K}")
+    X16 = WL.make_activations_f16(M, K, outlier_frac=0.001, seed=M + 1)
+    smooth = WL.make_smooth(K, seed=K + 3)
+    q_ref, s_ref = O.quantize_activations(X16, smooth)
+    q, s = _run(X16, smooth)
+    assert np.array_equal(s.view(np.uint32), s_ref.view(np.uint32)), "per-token scales differ"
+    assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
+
+
 def test_smooth_scales_outside_the_short_division_range():
     """Smooth scales below 2^-40 or above 2^40 (and FP32 subnormals) take the full IEEE
     division; scales at the edges of the range and powers of two take the short one."""
