@@ -88,6 +88,7 @@ __device__ __forceinline__ __half scale_to_half(int acc, float sx, float sw)
 
 #include "kernels_common.h"
 #include "kernels_stream.h"
+#include "kernels_panel.h"
 #include "kernels_tiled.h"
 #include "kernels_tiled_dl.h"
 #include "kernels_tiled_pt.h"
@@ -169,81 +170,6 @@ static size_t stream_ws_bytes(int M, int N, int S, int MF = 1)
     return kTicketBytes + (size_t)S * (N / 32) * MF * rmax * 64 * sizeof(int32_t);
 }
 
-// S = requested number of K slices; `named` = the variant names its split (then a missing
-// workspace is an error instead of a fall-back to one slice).
-template <int F, int NW, int MF, bool XL = false>
-static int launch_stream_as(const Args &a, int S, bool named)
-{
-    if (a.M > 32 * MF) return fail(LQ_ERR_INVALID, "this stream variant handles M <= %d, got %d", 32 * MF, a.M);
-    if ((a.N / 32) % F != 0) return fail(LQ_ERR_INVALID, "N/32 not a multiple of F=%d", F);
-    const int groups = a.N / (32 * F);
-    S = std::max(1, std::min(S, a.K / 128));
-    if (S > 1 && groups > kMaxTicketGroups) S = 1;
-    size_t need = stream_ws_bytes(a.M, a.N, S, MF);
-    if (a.query) return *a.query = need, LQ_OK;
-    if (need > 0 && (!a.ws || a.ws_bytes < need)) {
-        if (named)
-            return fail(LQ_ERR_WORKSPACE, "split-K needs %zu bytes of workspace, got %zu", need,
-                        a.ws ? a.ws_bytes : 0);
-        S = 1;
-        need = 0;
-    }
-    const dim3 grid(groups, S), block(NW * 64);
-    const int rmax = MF == 1 ? 4 * ((a.M + 7) / 8) : 16;
-    // reduction buffer; with XL the waves' X regions (32 MF rows x 128 k each) come first in the same memory
-    const size_t lds_bytes = std::max((size_t)NW * F * MF * rmax * 64 * sizeof(int), XL ? (size_t)NW * MF * 4096 : 0);
-    unsigned int *tickets = static_cast<unsigned int *>(a.ws);
-    int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
-    if (a.group == 128) {
-        if (int rc = allow_lds(&w4a8_stream_kernel<F, NW, MF, true, XL>, lds_bytes)) return rc;
-        hipLaunchKernelGGL((w4a8_stream_kernel<F, NW, MF, true, XL>), grid, block, lds_bytes, a.stream, a.M, a.N, a.K,
-                           a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
-    } else {
-        if (int rc = allow_lds(&w4a8_stream_kernel<F, NW, MF, false, XL>, lds_bytes)) return rc;
-        hipLaunchKernelGGL((w4a8_stream_kernel<F, NW, MF, false, XL>), grid, block, lds_bytes, a.stream, a.M, a.N, a.K,
-                           a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
-    }
-    return LQ_OK;
-}
-
-// SPLIT: 0 = choose with stream_split(), otherwise the fixed number of K slices.
-template <int F, int NW, int SPLIT, int MF = 1, bool XL = false>
-static int launch_stream(const Args &a)
-{
-    return launch_stream_as<F, NW, MF, XL>(a, SPLIT ? SPLIT : stream_split(a.N, a.K, F, NW), SPLIT != 0);
-}
-
-// 32-row (MF = 1) and 64-row (MF = 2) stream kernels with the block shape chosen from N.
-// Measured for both: the best grid is the largest one of at most 256 blocks of 8 waves --
-// one tile per block while N / 32 <= 256, else two -- with K split across blocks while
-// that still fits and leaves every wave at least four units of 128 k.
-template <int MF, bool XL>
-static int launch_stream_shaped(const Args &a)
-{
-    const int tiles = a.N / 32;
-    // long K with no room for K slices: two tiles per block share the X fragments and two
-    // K slices halve each wave's walk (29 vs 31 us at 32 rows, 39 vs 42 at 64 rows on 8192 x 28672)
-    if (tiles > 128 && tiles <= 256 && a.K >= 24576) return launch_stream_as<2, 8, MF, XL>(a, 2, false);
-    if (tiles <= 256) {
-        const int s_units = std::max(1, a.K / (128 * 8 * 4));
-        return launch_stream_as<1, 8, MF, XL>(a, std::min({4, 256 / tiles, s_units}), false);
-    }
-    return launch_stream_as<2, 8, MF, XL>(a, 1, false);
-}
-
-// X through LDS (XL) pays whenever a wave holds two row fragments; with one it is worth
-// 4-9 % once most of the 32 rows exist and N is small enough for one tile per block (or, with
-// two tiles per block, K is long: 21.5 against 22.8 us at 32 rows on 12288 x 12288), and
-// costs a few per cent otherwise (measured at 20..32 rows on 36 weight shapes).
-template <int MF>
-static int launch_stream_auto(const Args &a)
-{
-    if (MF == 2) return launch_stream_shaped<2, true>(a);
-    const int tiles = a.N / 32;
-    const bool xl = a.M > 24 && (tiles <= 256 || (tiles <= 512 && a.K >= 12288));
-    return xl ? launch_stream_shaped<1, true>(a) : launch_stream_shaped<1, false>(a);
-}
-
 template <int F, int NW, int SPLIT, int UU = 1>
 static int launch_stream16(const Args &a)
 {
@@ -279,6 +205,106 @@ static int launch_stream16(const Args &a)
                            a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
     }
     return LQ_OK;
+}
+
+// Panel kernel: 32 MF rows x 32 F channels per block, S slices of K across blocks, NW waves per
+// block (two per SIMD while the accumulators leave room for that, i.e. up to 64 rows).
+constexpr long long kAssumedCUs = 256;  // the shape rules of the dispatcher are written for the MI355X
+static long long panel_blocks(int M, int N, int F, int MF)
+{
+    return (long long)((M + 32 * MF - 1) / (32 * MF)) * ((N / 32 + F - 1) / F);
+}
+static size_t panel_ws_bytes(int blocks, int F, int MF, int S)
+{
+    return S <= 1 ? 0 : kTicketBytes + (size_t)blocks * S * F * MF * 1024 * sizeof(int32_t);
+}
+static size_t workspace_limit(const Args &a)  // (a query names its limit, if it has one, in ws_bytes)
+{
+    return a.query ? (a.ws_bytes ? a.ws_bytes : SIZE_MAX) : a.ws ? a.ws_bytes : 0;
+}
+template <int F, int NW, int MF>
+static int launch_panel(const Args &a, int S)
+{
+    const int blocks_m = (a.M + 32 * MF - 1) / (32 * MF), blocks_n = (a.N / 32 + F - 1) / F;
+    S = std::max(1, std::min(S, a.K / 128));
+    if (S > 1 && blocks_m * blocks_n > kMaxTicketGroups) S = 1;
+    const size_t need = panel_ws_bytes(blocks_m * blocks_n, F, MF, S);
+    if (a.query) return *a.query = need, LQ_OK;
+    if (need > 0 && (!a.ws || a.ws_bytes < need))
+        return fail(LQ_ERR_WORKSPACE, "split-K needs %zu bytes of workspace, got %zu", need, a.ws ? a.ws_bytes : 0);
+    const dim3 grid((unsigned)(blocks_m * blocks_n * S)), block(NW * 64);
+    const size_t lds_bytes = (size_t)NW * MF * 4096 * (F % 2 == 0 ? 2 : 1);
+    unsigned int *tickets = static_cast<unsigned int *>(a.ws);
+    int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
+    if (a.group == 128) {
+        if (int rc = allow_lds(&w4a8_panel_kernel<F, NW, MF, true>, lds_bytes)) return rc;
+        hipLaunchKernelGGL((w4a8_panel_kernel<F, NW, MF, true>), grid, block, lds_bytes, a.stream, a.M, a.N, a.K, a.X,
+                           a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets, blocks_m, blocks_n, S);
+    } else {
+        if (int rc = allow_lds(&w4a8_panel_kernel<F, NW, MF, false>, lds_bytes)) return rc;
+        hipLaunchKernelGGL((w4a8_panel_kernel<F, NW, MF, false>), grid, block, lds_bytes, a.stream, a.M, a.N, a.K, a.X,
+                           a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets, blocks_m, blocks_n, S);
+    }
+    return LQ_OK;
+}
+struct PanelForm {
+    int F, NW, MF;
+    int (*launch)(const Args &, int S);
+};
+static const PanelForm kPanelForms[] = {
+    {1, 8, 1, &launch_panel<1, 8, 1>}, {2, 8, 1, &launch_panel<2, 8, 1>}, {4, 8, 1, &launch_panel<4, 8, 1>},
+    {1, 8, 2, &launch_panel<1, 8, 2>}, {2, 8, 2, &launch_panel<2, 8, 2>}, {3, 8, 2, &launch_panel<3, 8, 2>},
+    {4, 8, 2, &launch_panel<4, 8, 2>}, {3, 4, 4, &launch_panel<3, 4, 4>}, {4, 4, 4, &launch_panel<4, 4, 4>},
+};
+struct PanelChoice {
+    const PanelForm *form = nullptr;  // null: no form takes the shape
+    int S = 1;
+    double us = 1e30;
+};
+// The form and the number of K slices for a shape.  The time of a form is linear in what it does,
+// fitted to 14 row counts (17 to 512) x 17 weight shapes (1024 to 28672 channels and k) x all forms
+// and 1 to 4 slices, 8 % rms; the form it picks is 1.5 % behind the best one on average:
+//   2.26 us of launch and first loads
+//   + 0.61 us per accumulator tile (32 x 32) of a block: the sum over the waves and the epilogue
+//   + 9.8 ns per KB of X and 19.1 ns per KB of W that a CU takes in (X comes from L2; W is also dequantised)
+//   + 75 ns per MB of packed weights, streamed from HBM once
+//   + with K slices 1.33 us for the exchange and 0.85 us per 1024 (block, accumulator tile) pairs of its volume
+// Beyond 64 rows, no more than two rounds of blocks were fitted (more never paid); 128-row panels
+// with K slices were never among the best, nor slices that leave a wave less than two units (1024 x
+// 4096 at 45 rows: 5.8 us with one slice, 6.2 / 6.4 / 6.7 with two, three, four).
+static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
+{
+    PanelChoice best;
+    for (const PanelForm &f : kPanelForms) {
+        const long long blocks = panel_blocks(M, N, f.F, f.MF);
+        const int tiles = f.F * f.MF;
+        for (int S = 1; S <= 4 && S <= K / 128; ++S) {
+            if (S > 1 && (f.MF == 4 || K / 128 < 2 * f.NW * S || blocks * S > 2 * kAssumedCUs ||
+                          panel_ws_bytes((int)blocks, f.F, f.MF, S) > ws_limit)) break;
+            if (M > 64 && blocks * S > 2 * kAssumedCUs) break;
+            const double rounds = (double)((blocks * S + kAssumedCUs - 1) / kAssumedCUs);
+            const int units = (K / 128 + S - 1) / S, walked = (units + f.NW - 1) / f.NW * f.NW;
+            const double x_kb = rounds * walked * 4.096 * f.MF, w_kb = rounds * walked * 2.048 * f.F;
+            const double us = 2.26 + 0.611 * rounds * tiles + 0.00983 * x_kb + 0.0191 * w_kb + 0.0753 * (0.5e-6 * N * K) +
+                              (S > 1 ? 1.33 + 0.00085 * (double)(blocks * S * tiles) : 0.0);
+            if (us < best.us) best = PanelChoice{&f, S, us};
+        }
+    }
+    return best;
+}
+// 17..32 and 33..64 rows (MAX_M): always (measured against 32- and 64-row kernels that prefetched one
+// unit and split K across blocks only for small N: 10 to 30 % ahead, at worst equal)
+template <int MAX_M>
+static int launch_panel_auto(const Args &a)
+{
+    if (a.M > MAX_M) return fail(LQ_ERR_INVALID, "this stream variant handles M <= %d, got %d", MAX_M, a.M);
+    const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
+    return c.form->launch(a, c.S);
+}
+template <int F, int NW, int MF, int SPLIT>
+static int launch_panel_named(const Args &a)
+{
+    return launch_panel<F, NW, MF>(a, SPLIT);
 }
 
 // Grid-level split of K for the duo kernel with two k groups per block (grids of at most
@@ -397,7 +423,6 @@ static int launch_duo_dl(const Args &a)
     return LQ_OK;
 }
 
-constexpr long long kAssumedCUs = 256;  // the shape rules of the dispatcher are written for the MI355X
 // Compute units of the current device (the grid of the persistent kernels), asked once per device.
 static int cu_count()
 {
@@ -595,15 +620,40 @@ static int launch_duo64(const Args &a)
 // two k groups per block (microseconds; u = 256-k units per k group, S = K slices):
 //   128-row tiles: 13.9 + 1.95 u + 2.3 (S - 1)       64-row tiles: 8.1 + 1.76 u + c (S - 1),
 //   c = 0.8 + 1.6 * blocks / 256 (a slice costs less when few blocks exchange at once)
+static double duo_us(int M, int N, int K)
+{
+    const int s = duo_split(M, N, K), units = K / 256;
+    return 13.9 + 1.95 * units / (2.0 * s) + 2.3 * (s - 1);
+}
+static double duo64_us(int M, int N, int K)
+{
+    const int t64 = ((M + 63) / 64) * ((N + 255) / 256), s = duo64_split(M, N, K), units = K / 256;
+    return 8.1 + 1.76 * units / (2.0 * s) + (0.8 + 1.6 * t64 * s / 256.0) * (s - 1);
+}
 static bool prefer_64_row_tiles(int M, int N, int K)
 {
     const int bn = (N + 255) / 256;
     const int t128 = ((M + 127) / 128) * bn, t64 = ((M + 63) / 64) * bn, units = K / 256;
     if (K < 512 || t64 > 256 || t128 > 256) return false;
-    const int s128 = duo_split(M, N, K), s64 = duo64_split(M, N, K);
-    const double est128 = 13.9 + 1.95 * units / (2.0 * s128) + 2.3 * (s128 - 1);
-    const double est64 = 8.1 + 1.76 * units / (2.0 * s64) + (0.8 + 1.6 * t64 * s64 / 256.0) * (s64 - 1);
+    const double est128 = duo_us(M, N, K), est64 = duo64_us(M, N, K);
     return est64 < est128;
+}
+
+// duo_m64 and duo_m128: the tiles, or a panel form where that is estimated to be faster.  The
+// estimate of the tiles is 2.5 us below its terms (the fits above include more launch time) and low by
+// up to half for some shapes, by 18 % on average; with a factor of 1.15 the choice is 0.8 % from
+// the better of both over 128 shapes of 96 to 512 rows (256 x 8192 x 8192: 27.2 against 30.6 us,
+// 128 x 4096 x 11008: 15.8 against 21.2, 192 x 5120 x 5120: 12.8 against 18.3).  With more rows and
+// more than 64 tiles of 128 x 256 the tiles stay ahead (384 x 6144 x 2048: 12.9 against 14.8 us,
+// 1024 x 3072 x 3072: 17.5 against 18.9; with 64 tiles 500 x 4096 x 4096: 18.6 against 15.3).
+static double few_tiles_us(int M, int N, int K);
+template <LaunchFn TILES>
+static int launch_few_tiles(const Args &a)
+{
+    if (a.M > 256 && (long long)((a.M + 127) / 128) * ((a.N + 255) / 256) > 64) return TILES(a);
+    const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
+    if (c.form && c.us < 1.15 * few_tiles_us(a.M, a.N, a.K)) return c.form->launch(a, c.S);
+    return TILES(a);
 }
 
 struct Variant {
@@ -615,9 +665,11 @@ struct Variant {
     int min_k = 256;
 };
 
-// stream*_f<F>_w<NW>[_s<S>]: F tiles per block, NW waves splitting the block's K slice,
+// stream_m32, stream_m64: the panel forms for up to 32 and 64 rows.  panel_f<F>_m<rows>[_s<S>]: F tiles
+// and 32, 64 or 128 rows per block.  duo_m64, duo_m128: few 64- or 128-row tiles, or a panel form
+// where that is faster.  stream16_f<F>_w<NW>[_s<S>]: F tiles per block, NW waves splitting the block's K slice,
 // S grid-level K slices (chosen from the shape when not named); _u4 = four 128-k units per
-// pipeline step; x = X fragments through LDS; g2 = two k groups per block.
+// pipeline step; g2 = two k groups per block.
 static const Variant kVariants[] = {
     // --- dispatched (select_variant) ---
     {"stream16_f1_w16_s1", &launch_stream16<1, 16, 1>, 16, 1, 1},
@@ -626,10 +678,10 @@ static const Variant kVariants[] = {
     {"stream16_f2_w8", &launch_stream16<2, 8, 0>, 16, 2, 1},
     {"stream16_f2_w16_s1", &launch_stream16<2, 16, 1>, 16, 2, 1},
     {"stream16_f2_w4", &launch_stream16<2, 4, 0>, 16, 2, 1},
-    {"stream_m32", &launch_stream_auto<1>, 32, 2, 1},
-    {"stream_m64", &launch_stream_auto<2>, 64, 2, 1},
-    {"duo_m64", &launch_duo64<0>, 0, 1, 1, 512},
-    {"duo_m128", &launch_duo<0, 0>, 0, 1, 1},
+    {"stream_m32", &launch_panel_auto<32>, 32, 2, 1},
+    {"stream_m64", &launch_panel_auto<64>, 64, 2, 1},
+    {"duo_m64", &launch_few_tiles<&launch_duo64<0>>, 0, 1, 1, 512},
+    {"duo_m128", &launch_few_tiles<&launch_duo<0, 0>>, 0, 1, 1},
     {"duo_dl_m128", &launch_duo_dl<0>, 0, 1, 1},
     {"duo_pt_m128", &launch_duo_pt, 0, 1, 8, 512},
     {"solo16_pt_m256", &launch_solo_pt<1, 0, true>, 0, 1, 4},
@@ -642,11 +694,17 @@ static const Variant kVariants[] = {
     //     dispatcher would not split (parity tests) ---
     {"stream16_f2_w8_s2", &launch_stream16<2, 8, 2>, 16, 2, 1},
     {"stream16_f1_w8_u4_s2", &launch_stream16<1, 8, 2, 4>, 16, 1, 8},
-    {"stream_f2_w8_s2", &launch_stream<2, 8, 2>, 32, 2, 1},
-    {"stream_x_f1_w8_s2", &launch_stream<1, 8, 2, 1, true>, 32, 1, 1},
-    {"stream_m64x_f1_w8_s2", &launch_stream<1, 8, 2, 2, true>, 64, 1, 1},
-    {"stream_m64x_f2_w8_s4", &launch_stream<2, 8, 4, 2, true>, 64, 2, 1},
+    {"panel_f1_m32_s2", &launch_panel_named<1, 8, 1, 2>, 0, 1, 1},
+    {"panel_f4_m32_s2", &launch_panel_named<4, 8, 1, 2>, 0, 1, 1},
+    {"panel_f2_m64_s4", &launch_panel_named<2, 8, 2, 4>, 0, 1, 1, 512},
+    {"panel_f3_m64_s2", &launch_panel_named<3, 8, 2, 2>, 0, 1, 1},
     {"duo_m64_s2", &launch_duo64<2>, 0, 1, 1, 512},
+    // (... and the panel forms without slices)
+    {"panel_f1_m64", &launch_panel_named<1, 8, 2, 1>, 0, 1, 1},
+    {"panel_f2_m32", &launch_panel_named<2, 8, 1, 1>, 0, 1, 1},
+    {"panel_f4_m64", &launch_panel_named<4, 8, 2, 1>, 0, 1, 1},
+    {"panel_f3_m128", &launch_panel_named<3, 4, 4, 1>, 0, 1, 1},
+    {"panel_f4_m128", &launch_panel_named<4, 4, 4, 1>, 0, 1, 1},
     {"duo_m128_s1", &launch_duo<1, 1>, 0, 1, 1},
     {"duo_m128_s2", &launch_duo<2, 1>, 0, 1, 1},
     {"duo_m128_g2_s2", &launch_duo<2, 2>, 0, 1, 1},
@@ -726,6 +784,17 @@ static TiledCosts tiled_costs(int M, int N, int K)
     const long long bm256 = (M + 255) / 256;
     return tiled_costs((long long)((M + 127) / 128) * ((N + 255) / 256), bm256 * ((N + 255) / 256),
                        bm256 * ((N + 127) / 128), K, K % 512 == 0);
+}
+static double few_tiles_us(int M, int N, int K)
+{
+    const int bn = (N + 255) / 256, t128 = ((M + 127) / 128) * bn, t64 = ((M + 63) / 64) * bn;
+    const TiledCosts c = tiled_costs(M, N, K);
+    const double round_us = 60.0 * K / 8192;
+    double us = std::min(c.solo, c.g2) * round_us + 4;
+    if (t128 > 128) us = std::min(us, c.duo * round_us + 4);
+    else us = std::min(us, duo_us(M, N, K));
+    if (t128 <= 128 && t64 <= 256) us = std::min(us, duo64_us(M, N, K));
+    return us - 2.5;
 }
 static int solo_form_of(const TiledCosts &c)
 {

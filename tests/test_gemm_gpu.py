@@ -608,3 +608,29 @@ def test_two_launch_plans(M, N, K, g):
     torch.cuda.synchronize()
     assert np.array_equal(ACC.cpu().numpy().astype(np.float64), ref), "accumulators differ"
     H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref, s_x, s_w), "two launches")
+
+
+# ---------------------------------------------------------------------------------------
+# The panel forms as the dispatcher picks them: edges of their row tiles (32, 64, 128), channel
+# tiles that do not fill a block, fewer units than waves, K slices and a workspace too small for them
+# ---------------------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,g", [
+    (17, 2112, 2304, 64), (32, 4160, 256, 128), (33, 192, 4608, 64), (63, 7232, 512, 128), (64, 1088, 6912, 64),
+    (65, 3264, 1280, 64), (96, 1600, 8192, 128), (127, 5184, 768, 64), (129, 64, 4352, 128), (193, 2880, 2048, 64),
+    (257, 1216, 2816, 128), (511, 3008, 768, 64)])
+def test_panel_dispatch_edges(M, N, K, g):
+    import torch
+
+    _say(f"panel M={M} N={N} K={K} g={g} -> {api.w4a8_variant_name(api.w4a8_select_variant(M, N, K, g))}")
+    P = H.Problem(N, K, g, seed=M)
+    X, s_x = I.make_activations(M, K, outlier_frac=0.01, seed=K)
+    ref = torch.from_numpy(X.astype(np.float64)) @ torch.from_numpy(P.oracle_wd()[0].astype(np.float64)).t()
+    dX, dsx = torch.from_numpy(X).cuda(), torch.from_numpy(s_x).cuda()
+    tiny = torch.zeros(16, dtype=torch.uint8, device="cuda")
+    want = ref.to(torch.int32)
+    for ws in (None, None, tiny):   # twice with the full workspace: the tickets reset themselves
+        ACC = api.w4a8_gemm_i32(dX, P.d_packed, P.d_gparams, N, K, g, workspace=ws)
+        assert torch.equal(ACC.cpu(), want)
+    Y = api.w4a8_gemm(dX, dsx, P.d_packed, P.d_gparams, P.d_w_scales, N, K, g)
+    H.assert_fp16_close(Y.cpu().numpy(), ref.numpy() * s_x[:, None].astype(np.float64) * P.oracle_wd()[1][None, :].astype(np.float64),
+                        "panel")
