@@ -41,23 +41,23 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_grouped_kernel(const Gr
                                     nullptr);
 }
 
-template <int NW, bool G128>
-__global__ __launch_bounds__(NW * 64) void w4a8_stream_grouped_kernel(const GroupTable g, const GroupedPtrs p,
-                                                                      int N, int K, int groups)
+// block_end counts row tiles x column groups of every entry.  As in w4a8_panel_kernel each XCD gets a
+// run of blocks, in which the row tiles of one column group are neighbours.
+template <int F, int MF, bool G128>
+__global__ __launch_bounds__(512) void w4a8_panel_grouped_kernel(const GroupTable g, const GroupedPtrs p, int N, int K)
 {
-    const int i = blockIdx.x / groups, gx = blockIdx.x % groups;
-    const int e = g.expert[i], r0 = g.row_off[i];
-    if (g.rows[i] > 24) {  // block-uniform: X through LDS once most of the 32 rows exist (57 -> 51 us for 8 x 32 rows on 4096 x 14336)
-        stream_block<2, NW, 1, G128, true>(Place{gx, groups, 0, 1, nullptr}, g.rows[i], N, K, p.X + (size_t)r0 * K,
-                                           p.sx + r0, p.Wp + e * p.w_stride, p.gp + e * p.gp_stride,
-                                           p.sw + (size_t)e * N, p.Y ? p.Y + (size_t)r0 * N : nullptr,
-                                           p.ACC ? p.ACC + (size_t)r0 * N : nullptr, nullptr);
-        return;
-    }
-    stream_block<2, NW, 1, G128>(Place{gx, groups, 0, 1, nullptr}, g.rows[i], N, K, p.X + (size_t)r0 * K, p.sx + r0,
-                              p.Wp + e * p.w_stride, p.gp + e * p.gp_stride, p.sw + (size_t)e * N,
-                              p.Y ? p.Y + (size_t)r0 * N : nullptr, p.ACC ? p.ACC + (size_t)r0 * N : nullptr,
-                              nullptr);
+    const int total = g.block_end[g.count - 1];
+    const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
+    const int lid = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
+    int i = 0;
+    while (i < g.count - 1 && lid >= g.block_end[i]) ++i;
+    const int local = lid - (i ? g.block_end[i - 1] : 0);
+    const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
+    const int blocks_m = (M + 32 * MF - 1) / (32 * MF), groups = (N / 32 + F - 1) / F;
+    panel_block<F, 8, MF, G128>(Place{local / blocks_m, groups, 0, 1, nullptr}, local % blocks_m, M, N, K,
+                                p.X + (size_t)r0 * K, p.sx + r0, p.Wp + e * p.w_stride, p.gp + e * p.gp_stride,
+                                p.sw + (size_t)e * N, p.Y ? p.Y + (size_t)r0 * N : nullptr,
+                                p.ACC ? p.ACC + (size_t)r0 * N : nullptr, nullptr, 0);
 }
 
 // TM = rows per row tile (128, or 64: twice the blocks for launches that would leave CUs idle)

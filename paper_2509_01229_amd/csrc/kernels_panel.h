@@ -18,7 +18,11 @@
 // 256 x 8192 x 8192 30.6 / 27.2, 24 x 10240 x 8192 17.1 / 13.6.
 //
 // X goes through a region of LDS that belongs to the wave: a load covers 8 whole rows (8 cache
-// lines per KiB instead of the 32 of a fragment load); see stream_block for the layout.
+// lines per KiB instead of the 32 of a fragment load).  Load i (i = 0 .. 4 MF - 1) fills the 1 KiB
+// piece i of the region in lane order; lane p brings row 8 i + r, 16-byte column c with
+// r = (p >> 3) ^ (i & 1), c = (p & 7) ^ r.  Fragment row j' = 32 mf + j is then found in piece j' >> 3
+// at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): neither the stores nor the fragment reads
+// meet bank conflicts.
 // ------------------------------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t buf_t;
 __device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
@@ -184,7 +188,7 @@ __device__ __forceinline__ void panel_block(
             }
     }
     if (S > 1) {
-        // the partial tiles meet in memory: same protocol as stream_block, 16 bytes per thread
+        // the partial tiles meet in memory: same protocol as stream16_block, 16 bytes per thread
         const size_t group_ints = (size_t)F * ITEMS * 4;
         int32_t *const base = partials + (size_t)tile_group * S * group_ints;
 #pragma unroll

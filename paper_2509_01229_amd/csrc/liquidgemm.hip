@@ -633,7 +633,7 @@ static double duo64_us(int M, int N, int K)
 static bool prefer_64_row_tiles(int M, int N, int K)
 {
     const int bn = (N + 255) / 256;
-    const int t128 = ((M + 127) / 128) * bn, t64 = ((M + 63) / 64) * bn, units = K / 256;
+    const int t128 = ((M + 127) / 128) * bn, t64 = ((M + 63) / 64) * bn;
     if (K < 512 || t64 > 256 || t128 > 256) return false;
     const double est128 = duo_us(M, N, K), est64 = duo64_us(M, N, K);
     return est64 < est128;
@@ -983,8 +983,8 @@ static int run(int variant, const Args &a)
 
 // ------------------------------------------------------------------------------------
 // Grouped GEMM: experts are sorted by their number of rows into the three kernel families
-// (<= 16 rows: 16-row stream kernel, <= 32: 32-row stream kernel, more: 128 x 256 tiles),
-// and each family that is not empty gets one launch over all of its experts.
+// (16-row stream kernel, 32- or 64-row panels, tiles), and each family that is not empty gets
+// one launch over all of its experts.
 // ------------------------------------------------------------------------------------
 struct GroupedArgs {
     int E, N, K, group;
@@ -1064,13 +1064,51 @@ static int grouped_tiles_run(const GroupedArgs &a, GroupTable &big)
                                  a.p, a.N, a.K);
 }
 
+// Experts of up to 64 rows as panels: one launch for all of them.
+template <int F, int MF>
+static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
+{
+    const int groups = (a.N / 32 + F - 1) / F;
+    long long blocks = 0;
+    for (int i = 0; i < t.count; ++i) {
+        blocks += (long long)((t.rows[i] + 32 * MF - 1) / (32 * MF)) * groups;
+        if (blocks > 0x7fffffff) return fail(LQ_ERR_INVALID, "grouped GEMM too large for one launch");
+        t.block_end[i] = (int)blocks;
+    }
+    const size_t lds = (size_t)8 * MF * 4096 * (F % 2 == 0 ? 2 : 1);
+    const dim3 grid((unsigned)blocks);
+    return a.group == 128 ? launch_checked("grouped panel", w4a8_panel_grouped_kernel<F, MF, true>, grid, dim3(512), lds,
+                                           a.stream, t, a.p, a.N, a.K)
+                          : launch_checked("grouped panel", w4a8_panel_grouped_kernel<F, MF, false>, grid, dim3(512), lds,
+                                           a.stream, t, a.p, a.N, a.K);
+}
+
 static int grouped_run(const GroupedArgs &a)
 {
+    // Up to 32 rows: as one launch of 32-row panels if any expert has more than 16 rows or K is long (8
+    // experts of 10..24 rows: 41.6 against 55.7 us in two launches on 14336 x 4096, 40.2 / 51.8 on
+    // 4096 x 14336, where experts of 1..7 rows take 40.7 / 43.8; short K 14.7 / 13.9 on 4 x 8192 x 3584).
+    // 33..64 rows, if no expert has more: 64-row panels of 128 channels for all experts where these
+    // are one round of blocks (8 experts of 36..55 rows on 4096 x 14336: 44.9 / 59.0 us, 17..35 rows:
+    // 42.4 / 93.3; with 3.5 rounds on 14336 x 4096 64.5 / 50.9), else 32-row panels for all where at
+    // least half of them have no more than 32 rows (16..33 rows: 43.5 / 71.9, 36..55 rows: 65.2 / 50.9).
+    int used = 0, upto32 = 0, most = 0, most32 = 0;
+    for (int e = 0; e < a.E; ++e) {
+        const int rows = a.row_offsets[e + 1] - a.row_offsets[e];
+        if (rows == 0) continue;
+        ++used;
+        most = std::max(most, rows);
+        if (rows <= 32) ++upto32, most32 = std::max(most32, rows);
+    }
+    const bool up_to_64 = most > 32 && most <= 64;
+    const bool panel64 = up_to_64 && (long long)used * ((a.N / 32 + 3) / 4) <= kAssumedCUs;
+    const int panel_max = panel64 || (up_to_64 && 2 * upto32 >= used) ? 64 : 32;
+    const bool panels = panel_max == 64 || most32 > 16 || a.K >= 8192;
     GroupTable small{}, mid{}, big{};
     for (int e = 0; e < a.E; ++e) {
         const int r0 = a.row_offsets[e], rows = a.row_offsets[e + 1] - r0;
         if (rows == 0) continue;
-        GroupTable &t = rows <= 16 ? small : (rows <= 32 ? mid : big);
+        GroupTable &t = rows > panel_max ? big : panels ? mid : small;
         const int i = t.count++;
         t.expert[i] = e, t.row_off[i] = r0, t.rows[i] = rows;
     }
@@ -1095,12 +1133,7 @@ static int grouped_run(const GroupedArgs &a)
         if (rc) return rc;
     }
     if (mid.count) {
-        const dim3 grid((unsigned)(mid.count * groups));
-        const size_t lds = (size_t)8 * 2 * 16 * 64 * sizeof(int);
-        const int rc = g128 ? launch_checked("grouped stream", w4a8_stream_grouped_kernel<8, true>, grid, dim3(512), lds,
-                                             a.stream, mid, a.p, a.N, a.K, groups)
-                            : launch_checked("grouped stream", w4a8_stream_grouped_kernel<8, false>, grid, dim3(512),
-                                             lds, a.stream, mid, a.p, a.N, a.K, groups);
+        const int rc = panel64 ? grouped_panel_run<4, 2>(a, mid) : grouped_panel_run<2, 1>(a, mid);
         if (rc) return rc;
     }
     if (!big.count) return LQ_OK;

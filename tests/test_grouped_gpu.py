@@ -192,3 +192,16 @@ def test_grouped_large_experts_take_256_row_tiles(K):
         assert np.array_equal(ACC[r0:r1].astype(np.float64), ref), f"expert {e}: accumulators differ"
         H.assert_fp16_close(Y[r0:r1], ref * s_x[r0:r1, None].astype(np.float64) * q["s_w"][None, :].astype(np.float64),
                             f"expert {e}")
+
+
+@pytest.mark.parametrize("E,N,K,g,rows", [
+    (4, 320, 512, 64, [16, 17, 0, 32]),            # 32-row panels
+    (3, 192, 8192, 128, [1, 9, 16]),               # ... long K: also for the smallest experts
+    (3, 320, 768, 128, [33, 64, 5]),               # 64-row panels of 128 channels, a ragged last column group
+    (6, 5824, 256, 64, [40, 3, 31, 17, 64, 1]),    # more blocks than one round: 32-row panels, two row tiles for some
+    (6, 5824, 256, 128, [40, 33, 64, 50, 20, 1]),  # ... most experts above 32 rows: panels and tiles
+    (3, 320, 512, 64, [65, 40, 20]),               # an expert of more than 64 rows: panels up to 32 rows only
+])
+def test_panel_groups(E, N, K, g, rows):
+    _say(f"panel groups E={E} N={N} K={K} g={g} rows={rows}")
+    Experts(E, N, K, g, seed=K).check(rows, seed=N, what=f"rows {rows}")
