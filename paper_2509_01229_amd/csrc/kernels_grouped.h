@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_grouped_kernel(const Gr
 
 // block_end counts row tiles x column groups of every entry.  As in w4a8_panel_kernel each XCD gets a
 // run of blocks, in which the row tiles of one column group are neighbours.
-template <int F, int MF, bool G128>
+template <int F, int MF, bool G128, bool ONCE>
 __global__ __launch_bounds__(512) void w4a8_panel_grouped_kernel(const GroupTable g, const GroupedPtrs p, int N, int K)
 {
     const int total = g.block_end[g.count - 1];
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(512) void w4a8_panel_grouped_kernel(const GroupTabl
     const int local = lid - (i ? g.block_end[i - 1] : 0);
     const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
     const int blocks_m = (M + 32 * MF - 1) / (32 * MF), groups = (N / 32 + F - 1) / F;
-    panel_block<F, 8, MF, G128>(Place{local / blocks_m, groups, 0, 1, nullptr}, local % blocks_m, M, N, K,
+    panel_block<F, 8, MF, G128, ONCE>(Place{local / blocks_m, groups, 0, 1, nullptr}, local % blocks_m, M, N, K,
                                 p.X + (size_t)r0 * K, p.sx + r0, p.Wp + e * p.w_stride, p.gp + e * p.gp_stride,
                                 p.sw + (size_t)e * N, p.Y ? p.Y + (size_t)r0 * N : nullptr,
                                 p.ACC ? p.ACC + (size_t)r0 * N : nullptr, nullptr, 0);

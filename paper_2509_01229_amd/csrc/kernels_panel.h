@@ -30,7 +30,11 @@ __device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
 }
 
-template <int F, int NW, int MF, bool G128>
+// ONCE = the weights are read by one row tile only (M <= 32 MF): loaded without keeping them in the
+// caches (8 experts of 10..24 rows on 14336 x 4096, weights in HBM: 46.6 against 51.8 us; where row
+// tiles share them the plain loads win, 16 experts of 18..36 rows on 2816 x 2048 16.8 against 18.6; the
+// same weights again while the memory-side cache holds them all are slower, 6.9 against 6.1 us on 32 x 4096 x 4096).
+template <int F, int NW, int MF, bool G128, bool ONCE>
 __device__ __forceinline__ void panel_block(
     const Place pl, int bm, int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
@@ -78,7 +82,7 @@ __device__ __forceinline__ void panel_block(
         for (int i = 0; i < 4 * MF; ++i) xr[i] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, xoff[i], u * 128, 0);
     };
     auto load_w = [&](int u, int f, int c) {
-        wr[f][c] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, wl + 1024 * c, (min(f, nf - 1) * units + u) * 2048, 0);
+        wr[f][c] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, wl + 1024 * c, (min(f, nf - 1) * units + u) * 2048, ONCE ? 2 : 0);
     };
     auto load_p = [&](int u, int f) {
         const int po = (min(f, nf - 1) * units + u) * PB;
@@ -263,7 +267,7 @@ __device__ __forceinline__ void panel_block(
     }
 }
 
-template <int F, int NW, int MF, bool G128>
+template <int F, int NW, int MF, bool G128, bool ONCE>
 __global__ __launch_bounds__(NW * 64) void w4a8_panel_kernel(
     int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
@@ -276,6 +280,6 @@ __global__ __launch_bounds__(NW * 64) void w4a8_panel_kernel(
     const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
     const int lid = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
     const int tg = lid / S, ks = lid % S;
-    panel_block<F, NW, MF, G128>(Place{tg / blocks_m, blocks_n, ks, S, tickets}, tg % blocks_m, M, N, K, X, sx, Wp, gp,
+    panel_block<F, NW, MF, G128, ONCE>(Place{tg / blocks_m, blocks_n, ks, S, tickets}, tg % blocks_m, M, N, K, X, sx, Wp, gp,
                                        sw, Y, ACC, partials, tg);
 }

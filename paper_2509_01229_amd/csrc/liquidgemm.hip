@@ -236,16 +236,15 @@ static int launch_panel(const Args &a, int S)
     const size_t lds_bytes = (size_t)NW * MF * 4096 * (F % 2 == 0 ? 2 : 1);
     unsigned int *tickets = static_cast<unsigned int *>(a.ws);
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
-    if (a.group == 128) {
-        if (int rc = allow_lds(&w4a8_panel_kernel<F, NW, MF, true>, lds_bytes)) return rc;
-        hipLaunchKernelGGL((w4a8_panel_kernel<F, NW, MF, true>), grid, block, lds_bytes, a.stream, a.M, a.N, a.K, a.X,
-                           a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets, blocks_m, blocks_n, S);
-    } else {
-        if (int rc = allow_lds(&w4a8_panel_kernel<F, NW, MF, false>, lds_bytes)) return rc;
-        hipLaunchKernelGGL((w4a8_panel_kernel<F, NW, MF, false>), grid, block, lds_bytes, a.stream, a.M, a.N, a.K, a.X,
-                           a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets, blocks_m, blocks_n, S);
-    }
-    return LQ_OK;
+    auto go = [&](auto kernel) {
+        if (int rc = allow_lds(kernel, lds_bytes)) return rc;
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, a.stream, a.M, a.N, a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC,
+                           partials, tickets, blocks_m, blocks_n, S);
+        return (int)LQ_OK;
+    };
+    if (blocks_m == 1)
+        return a.group == 128 ? go(&w4a8_panel_kernel<F, NW, MF, true, true>) : go(&w4a8_panel_kernel<F, NW, MF, false, true>);
+    return a.group == 128 ? go(&w4a8_panel_kernel<F, NW, MF, true, false>) : go(&w4a8_panel_kernel<F, NW, MF, false, false>);
 }
 struct PanelForm {
     int F, NW, MF;
@@ -1077,10 +1076,14 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
     }
     const size_t lds = (size_t)8 * MF * 4096 * (F % 2 == 0 ? 2 : 1);
     const dim3 grid((unsigned)blocks);
-    return a.group == 128 ? launch_checked("grouped panel", w4a8_panel_grouped_kernel<F, MF, true>, grid, dim3(512), lds,
-                                           a.stream, t, a.p, a.N, a.K)
-                          : launch_checked("grouped panel", w4a8_panel_grouped_kernel<F, MF, false>, grid, dim3(512), lds,
-                                           a.stream, t, a.p, a.N, a.K);
+    auto go = [&](auto kernel) {
+        return launch_checked("grouped panel", kernel, grid, dim3(512), lds, a.stream, t, a.p, a.N, a.K);
+    };
+    if (blocks == (long long)t.count * groups)  // one row tile each
+        return a.group == 128 ? go(&w4a8_panel_grouped_kernel<F, MF, true, true>)
+                              : go(&w4a8_panel_grouped_kernel<F, MF, false, true>);
+    return a.group == 128 ? go(&w4a8_panel_grouped_kernel<F, MF, true, false>)
+                          : go(&w4a8_panel_grouped_kernel<F, MF, false, false>);
 }
 
 static int grouped_run(const GroupedArgs &a)
