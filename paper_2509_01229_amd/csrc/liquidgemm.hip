@@ -664,7 +664,8 @@ struct Variant {
     int min_k = 256;
 };
 
-// stream_m32, stream_m64: the panel forms for up to 32 and 64 rows.  panel_f<F>_m<rows>[_s<S>]: F tiles
+// stream_m32, stream_m64, stream_f*, stream_x*, stream_m64x*: panel forms for up to 32 and 64 rows
+// (the names of the kernels they took the place of).  panel_f<F>_m<rows>[_s<S>]: F tiles
 // and 32, 64 or 128 rows per block.  duo_m64, duo_m128: few 64- or 128-row tiles, or a panel form
 // where that is faster.  stream16_f<F>_w<NW>[_s<S>]: F tiles per block, NW waves splitting the block's K slice,
 // S grid-level K slices (chosen from the shape when not named); _u4 = four 128-k units per
@@ -693,9 +694,11 @@ static const Variant kVariants[] = {
     //     dispatcher would not split (parity tests) ---
     {"stream16_f2_w8_s2", &launch_stream16<2, 8, 2>, 16, 2, 1},
     {"stream16_f1_w8_u4_s2", &launch_stream16<1, 8, 2, 4>, 16, 1, 8},
-    {"panel_f1_m32_s2", &launch_panel_named<1, 8, 1, 2>, 0, 1, 1},
+    {"stream_f2_w8_s2", &launch_panel_named<2, 8, 1, 2>, 32, 2, 1},
+    {"stream_x_f1_w8_s2", &launch_panel_named<1, 8, 1, 2>, 32, 1, 1},
+    {"stream_m64x_f1_w8_s2", &launch_panel_named<1, 8, 2, 2>, 64, 1, 1},
+    {"stream_m64x_f2_w8_s4", &launch_panel_named<2, 8, 2, 4>, 64, 2, 1},
     {"panel_f4_m32_s2", &launch_panel_named<4, 8, 1, 2>, 0, 1, 1},
-    {"panel_f2_m64_s4", &launch_panel_named<2, 8, 2, 4>, 0, 1, 1, 512},
     {"panel_f3_m64_s2", &launch_panel_named<3, 8, 2, 2>, 0, 1, 1},
     {"duo_m64_s2", &launch_duo64<2>, 0, 1, 1, 512},
     // (... and the panel forms without slices)
