@@ -41,6 +41,15 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_grouped_kernel(const Gr
                                     nullptr);
 }
 
+// The entry that block `lid` belongs to: one lane per entry compares, instead of a walk through the
+// table (one dependent scalar load after the other, which a short block of a late entry waits for).
+static_assert(kMaxExperts == 64, "one lane per entry");
+__device__ __forceinline__ int entry_of(const GroupTable &g, int lid)
+{
+    const int lane = threadIdx.x & 63;
+    return __popcll(__ballot(lane < g.count - 1 && lid >= g.block_end[lane]));
+}
+
 // block_end counts row tiles x column groups of every entry.  As in w4a8_panel_kernel each XCD gets a
 // run of blocks, in which the row tiles of one column group are neighbours.
 template <int F, int MF, bool G128, bool ONCE>
@@ -49,8 +58,7 @@ __global__ __launch_bounds__(512) void w4a8_panel_grouped_kernel(const GroupTabl
     const int total = g.block_end[g.count - 1];
     const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
     const int lid = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
-    int i = 0;
-    while (i < g.count - 1 && lid >= g.block_end[i]) ++i;
+    const int i = entry_of(g, lid);
     const int local = lid - (i ? g.block_end[i - 1] : 0);
     const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
     const int blocks_m = (M + 32 * MF - 1) / (32 * MF), groups = (N / 32 + F - 1) / F;

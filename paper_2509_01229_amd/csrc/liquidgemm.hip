@@ -1092,29 +1092,40 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
 static int grouped_run(const GroupedArgs &a)
 {
     // Up to 32 rows: as one launch of 32-row panels if any expert has more than 16 rows or K is long (8
-    // experts of 10..24 rows: 41.6 against 55.7 us in two launches on 14336 x 4096, 40.2 / 51.8 on
-    // 4096 x 14336, where experts of 1..7 rows take 40.7 / 43.8; short K 14.7 / 13.9 on 4 x 8192 x 3584).
+    // experts of 10..24 rows: 45.8 against 52.9 us in two launches on 14336 x 4096, 64 experts of 7..25 rows
+    // on 1408 x 2048 25.2 / 29.5; 16 of 3..15 rows on 3072 x 8192 36.2 / 37.9) -- unless the experts of up to
+    // 16 rows alone are more than nine rounds of blocks with short K: a panel costs more than a 16-row block
+    // there, and nothing is idle in either launch (64 experts on 4096 x 1536, 60 of them up to 16 rows: 54.5
+    // us in one launch, 44.9 in two; 36 of them: 54.5 / 52.8; on 2816 x 2048 52 of them, 8.9 rounds: 43.2 / 45.6).
     // 33..64 rows, if no expert has more: 64-row panels of 128 channels for all experts where these
     // are one round of blocks (8 experts of 36..55 rows on 4096 x 14336: 44.9 / 59.0 us, 17..35 rows:
     // 42.4 / 93.3; with 3.5 rounds on 14336 x 4096 64.5 / 50.9), else 32-row panels for all where at
-    // least half of them have no more than 32 rows (16..33 rows: 43.5 / 71.9, 36..55 rows: 65.2 / 50.9).
-    int used = 0, upto32 = 0, most = 0, most32 = 0;
+    // least half of them have no more than 32 rows and the second row tiles of the others are less than two
+    // rounds of blocks (0.9 rounds, 16 experts of 24..36 rows on 3072 x 8192: 52.5 / 67.0 us; 1.9, 64 experts of
+    // 17..40 on 2048 x 1536: 36.3 / 39.3; 2.0, 32 of 16..39 on 4096 x 2560: 50.2 / 47.7; 5.2, 64 of 20..47 on
+    // 2816 x 2048: 59.9 / 52.5).
+    int used = 0, upto16 = 0, upto32 = 0, most = 0, most32 = 0;
     for (int e = 0; e < a.E; ++e) {
         const int rows = a.row_offsets[e + 1] - a.row_offsets[e];
         if (rows == 0) continue;
         ++used;
         most = std::max(most, rows);
+        if (rows <= 16) ++upto16;
         if (rows <= 32) ++upto32, most32 = std::max(most32, rows);
     }
+    const long long panel_groups = a.N / 64;  // blocks of a 32-row panel's row tile
     const bool up_to_64 = most > 32 && most <= 64;
     const bool panel64 = up_to_64 && (long long)used * ((a.N / 32 + 3) / 4) <= kAssumedCUs;
-    const int panel_max = panel64 || (up_to_64 && 2 * upto32 >= used) ? 64 : 32;
-    const bool panels = panel_max == 64 || most32 > 16 || a.K >= 8192;
+    const bool panels_for_all = panel64 || (up_to_64 && 2 * upto32 >= used && (used - upto32) * panel_groups < 2 * kAssumedCUs);
+    const int panel_max = panels_for_all ? 64 : 32;
+    const bool split16 = !panels_for_all && a.K < 4096 && upto16 * panel_groups > 9 * kAssumedCUs;
+    const bool panels16 = panels_for_all || most32 > 16 || a.K >= 8192;  // panels also for the experts of up to 16 rows
+    const int stream16_max = panels16 && !split16 ? 0 : 16;
     GroupTable small{}, mid{}, big{};
     for (int e = 0; e < a.E; ++e) {
         const int r0 = a.row_offsets[e], rows = a.row_offsets[e + 1] - r0;
         if (rows == 0) continue;
-        GroupTable &t = rows > panel_max ? big : panels ? mid : small;
+        GroupTable &t = rows > panel_max ? big : rows > stream16_max ? mid : small;
         const int i = t.count++;
         t.expert[i] = e, t.row_off[i] = r0, t.rows[i] = rows;
     }

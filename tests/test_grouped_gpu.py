@@ -205,3 +205,82 @@ def test_grouped_large_experts_take_256_row_tiles(K):
 def test_panel_groups(E, N, K, g, rows):
     _say(f"panel groups E={E} N={N} K={K} g={g} rows={rows}")
     Experts(E, N, K, g, seed=K).check(rows, seed=N, what=f"rows {rows}")
+
+
+@pytest.mark.parametrize("E,N,K,g,rows", [
+    (64, 192, 256, 64, [(7 * e) % 33 for e in range(64)]),       # the whole table: panels of up to 32 rows
+    (64, 192, 512, 128, [5 + (11 * e) % 60 for e in range(64)]),  # ... 33..64 rows: one or two row tiles an expert
+    (64, 2816, 256, 64, [1 + (5 * e) % 18 for e in range(64)]),   # 9.8 rounds of experts of up to 16 rows: two launches
+    (2, 64, 256, 64, [17, 1]),
+])
+def test_many_experts_in_the_panel_table(E, N, K, g, rows):
+    """Every expert against its rows as a call of its own."""
+    import torch
+
+    _say(f"panel table E={E} N={N} K={K} g={g}")
+    cb, gb = api.liquidquant_packed_size(N, K, g)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    codes = torch.randint(0, 256, (cb * E,), dtype=torch.uint8, device="cuda", generator=gen)
+    pairs = [torch.randint(lo, hi, (gb // 2 * E,), device="cuda", generator=gen) for lo, hi in ((1, 17), (0, 16))]
+    gparams = torch.stack(pairs, 1).to(torch.uint8).reshape(-1).contiguous()   # code * s + a <= 255
+    scales = torch.rand((E, N), device="cuda", generator=gen)
+    offsets = [0] + [int(v) for v in np.cumsum(rows)]
+    X = torch.randint(-127, 128, (offsets[-1], K), dtype=torch.int8, device="cuda", generator=gen)
+    sx = torch.rand(offsets[-1], device="cuda", generator=gen) * 1e-3
+    Y, ACC = api.w4a8_grouped_gemm(offsets, X, sx, codes, gparams, scales, N, K, g, want_y=True, want_acc=True)
+    for e in range(E):
+        lo, hi = offsets[e], offsets[e + 1]
+        if lo == hi:
+            continue
+        Wd = api.w4a8_dequant_dump(codes[e * cb:(e + 1) * cb].clone(), gparams[e * gb:(e + 1) * gb].clone(), N, K, g)
+        ref = X[lo:hi].cpu().numpy().astype(np.int64) @ Wd.cpu().numpy().astype(np.int64).T
+        assert np.array_equal(ACC[lo:hi].cpu().numpy(), ref), f"expert {e}"
+        H.assert_fp16_close(Y[lo:hi].cpu().numpy(), O.scale_epilogue_f64(ref, sx[lo:hi].cpu().numpy(), scales[e].cpu().numpy()),
+                            f"expert {e}")
+
+
+def test_many_small_experts_are_not_slower_together():
+    """64 experts of a decode batch in one call against the same rows in two calls (up to 16 rows, more than
+    16 rows).  A block that walked through the table of experts, or one launch of 32-row panels for all
+    of them, took 1.4 times as long as the two calls here; 1.25 leaves room for the noise of both."""
+    import torch
+
+    E, N, K, g = 64, 2048, 1536, 64
+    _say(f"many small experts E={E} N={N} K={K}")
+    rows = np.random.Generator(np.random.PCG64(11)).multinomial(11 * E, [1 / E] * E)
+    assert rows.max() > 16 and rows.max() <= 32
+    cb, gb = api.liquidquant_packed_size(N, K, g)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    weights = [torch.randint(0, 256, (cb * E,), dtype=torch.uint8, device="cuda", generator=gen) for _ in range(4)]
+    gparams = torch.tensor([3, 5], dtype=torch.uint8, device="cuda").repeat(gb // 2 * E)
+    scales = torch.rand((E, N), device="cuda", generator=gen)
+
+    def calls(*parts):
+        out = []
+        for part in parts:
+            offsets = [0] + [int(v) for v in np.cumsum(part)]
+            X = torch.randint(-127, 128, (offsets[-1], K), dtype=torch.int8, device="cuda", generator=gen)
+            out.append((offsets, X, torch.rand(offsets[-1], device="cuda", generator=gen)))
+        return lambda i: [api.w4a8_grouped_gemm(o, X, sx, weights[i % 4], gparams, scales, N, K, g) for o, X, sx in out]
+
+    def best_us(call, n=8):
+        call(0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for i in range(n):
+                call(i)
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3 / n)
+        return min(times)
+
+    together, apart = calls(rows), calls(np.where(rows <= 16, rows, 0), np.where(rows > 16, rows, 0))
+    t, u = best_us(together), best_us(apart)
+    _say(f"  one call {t:.1f} us, two calls {u:.1f} us")
+    assert t < 1.25 * u
