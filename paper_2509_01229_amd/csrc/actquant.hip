@@ -278,9 +278,11 @@ static void launch_rows(int M, int K, int R, int shares, const __half *X, const 
 
 // Block shapes, from sweeps of threads x pieces per thread x tokens per block over M = 4..8192 and
 // K = 2048..28672 (microseconds of the rule / of blocks of 256 threads with all pieces of a token):
-//   many tokens, no smooth scales: 512 threads above 4096 columns (13.0 / 13.8 on 2048 x 11008, 40.2 /
-//     43.5 on 6000 x 14336), 256 up to there (13.3 / 13.5 on 6000 x 4096; 512 threads: 15.6) and one
-//     piece per thread up to 2048 (11.0 / 15.5 on 8192 x 2048);
+//   many tokens, no smooth scales: 256 threads up to 8192 columns (13.3 / 13.5 on 6000 x 4096, 512 threads:
+//     15.6), with three pieces each up to 6144 (11.9 on 4096 x 4104, 13.3 on 4096 x 5120; 512 threads of
+//     two pieces, nearly half of them past the end: 15.0 and 15.8) and four from there on (18.2 on 4096 x
+//     8192, 512 threads: 19.0; with 1024 tokens 7.7 and 7.5, hence from 2048 tokens), one up to 2048 columns
+//     (11.0 / 15.5 on 8192 x 2048); 512 threads above (40.2 / 43.5 on 6000 x 14336);
 //   many tokens with smooth scales: from 1024 tokens on several tokens per block, as many as leave two
 //     blocks of 1024 threads per CU (one where a thread holds two pieces: 98 registers) -- 20.1 / 26.8
 //     on 4096 x 8192 (5.0 TB/s, a copy runs at 5.2), 38 / 60 on 4096 x 16384, 9.3 / 11.2 on 1024 x 8192;
@@ -302,6 +304,10 @@ static void launch_quantize(int M, int K, const __half *X, const float *smooth, 
         return M <= 512 ? launch_rows<SMOOTH, 1, 512>(M, K, 1, 1, X, smooth, Q, sx, st)
                         : launch_rows<SMOOTH, 2, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
     auto shares = [&](int iters) { return M * iters <= 128 ? iters : 1; };
+    if constexpr (!SMOOTH) {
+        if (n8 <= 768 && M >= 1024) return launch_rows<SMOOTH, 3, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+        if (n8 <= 1024 && M >= 2048) return launch_rows<SMOOTH, 4, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+    }
     if (n8 <= 1024) return launch_rows<SMOOTH, 2, 512>(M, K, 1, shares(2), X, smooth, Q, sx, st);
     if (n8 <= 1536) return launch_rows<SMOOTH, 3, 512>(M, K, 1, shares(3), X, smooth, Q, sx, st);
     if (n8 <= 2048) return launch_rows<SMOOTH, 4, 512>(M, K, 1, shares(4), X, smooth, Q, sx, st);
