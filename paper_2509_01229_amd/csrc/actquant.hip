@@ -268,12 +268,13 @@ __global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
     }
 }
 
+// (lds: dynamic LDS that nothing uses, to keep fewer blocks on a CU)
 template <bool SMOOTH, int ITERS, int NT, bool SEVERAL = false>
 static void launch_rows(int M, int K, int R, int shares, const __half *X, const float *smooth, int8_t *Q, float *sx,
-                        hipStream_t st)
+                        hipStream_t st, size_t lds = 0)
 {
     hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, ITERS, NT, SEVERAL>), dim3((unsigned)((M + R - 1) / R), (unsigned)shares),
-                       dim3(NT), 0, st, M, K, R, X, smooth, Q, sx);
+                       dim3(NT), lds, st, M, K, R, X, smooth, Q, sx);
 }
 
 // Block shapes, from sweeps of threads x pieces per thread x tokens per block over M = 4..8192 and
@@ -282,7 +283,9 @@ static void launch_rows(int M, int K, int R, int shares, const __half *X, const 
 //     15.6), with three pieces each up to 6144 (11.9 on 4096 x 4104, 13.3 on 4096 x 5120; 512 threads of
 //     two pieces, nearly half of them past the end: 15.0 and 15.8) and four from there on (18.2 on 4096 x
 //     8192, 512 threads: 19.0; with 1024 tokens 7.7 and 7.5, hence from 2048 tokens), one up to 2048 columns
-//     (11.0 / 15.5 on 8192 x 2048); 512 threads above (40.2 / 43.5 on 6000 x 14336);
+//     (11.0 / 15.5 on 8192 x 2048); 512 threads above (40.2 / 43.5 on 6000 x 14336), three blocks
+//     of them on a CU instead of four where the call moves more than the memory-side cache holds (72.3 / 74.5 on
+//     8192 x 16384, 62.5 / 64.2 on 8192 x 14336; below that four are ahead, 32.9 / 33.8 on 4096 x 16384);
 //   many tokens with smooth scales: from 1024 tokens on several tokens per block, as many as leave two
 //     blocks of 1024 threads per CU (one where a thread holds two pieces: 98 registers) -- 20.1 / 26.8
 //     on 4096 x 8192 (5.0 TB/s, a copy runs at 5.2), 38 / 60 on 4096 x 16384, 9.3 / 11.2 on 1024 x 8192;
@@ -307,6 +310,8 @@ static void launch_quantize(int M, int K, const __half *X, const float *smooth, 
     if constexpr (!SMOOTH) {
         if (n8 <= 768 && M >= 1024) return launch_rows<SMOOTH, 3, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
         if (n8 <= 1024 && M >= 2048) return launch_rows<SMOOTH, 4, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+        if (n8 > 1536 && n8 <= 2048 && (size_t)M * K >= (96u << 20))
+            return launch_rows<SMOOTH, 4, 512>(M, K, 1, 1, X, smooth, Q, sx, st, 48 * 1024);
     }
     if (n8 <= 1024) return launch_rows<SMOOTH, 2, 512>(M, K, 1, shares(2), X, smooth, Q, sx, st);
     if (n8 <= 1536) return launch_rows<SMOOTH, 3, 512>(M, K, 1, shares(3), X, smooth, Q, sx, st);

@@ -101,6 +101,19 @@ def test_edges_of_many_tokens_without_smooth_scales(M, K):
     assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
 
 
+@pytest.mark.parametrize("M,K", [(6200, 16384), (8192, 12296)])
+def test_large_calls_equal_their_parts(M, K):
+    """From 96 M elements on fewer blocks share a CU (without smooth scales, 12289 to 16384 columns)."""
+    import torch
+
+    _say(f"actquant large call M={M} K={K}")
+    X = torch.randn((M, K), device="cuda").half()
+    q, s = api.w4a8_quantize_activations(X)
+    for lo, hi in ((0, M // 2), (M // 2, M)):
+        qp, sp = api.w4a8_quantize_activations(X[lo:hi].clone())
+        assert torch.equal(q[lo:hi], qp) and torch.equal(s[lo:hi], sp)
+
+
 def test_a_few_columns_more_do_not_cost_a_larger_block():
     """8192 tokens of 4104 columns against 4096: blocks with twice the threads for one piece more took 1.37
     times as long; 1.2 leaves room for the noise of both."""
