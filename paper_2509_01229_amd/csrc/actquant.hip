@@ -47,15 +47,27 @@ __device__ __forceinline__ void load_smooth8(const float *smooth, int i, float (
     s[4] = b.x, s[5] = b.y, s[6] = b.z, s[7] = b.w;
 }
 
-// x / s, correctly rounded, with y = the correctly rounded 1 / s: one exact residual corrects the
-// quotient x * y.  For a general x that can miss by one unit; for the 11-bit significand of an
-// FP16 x it never does (tests/native/short_division.c goes through all 2^23 x 2^10 pairs of
-// significands).  No intermediate leaves the normal range while s is within [2^-40, 2^40]
-// (x is zero or 2^-24 .. 65504); callers check that.
-__device__ __forceinline__ float div_by(float x, float s, float y)
+// x / s, correctly rounded, for x = the lower (H = 0) or upper half of xx and y = the correctly rounded
+// 1 / s: one exact residual corrects the quotient x * y.  For a general x that can miss by one unit;
+// for the 11-bit significand of an FP16 x it never does (tests/native/short_division.c goes through
+// all 2^23 x 2^10 pairs of significands).  No intermediate leaves the normal range while s is within
+// [2^-40, 2^40] (x is zero or 2^-24 .. 65504); callers check that.  The residual of an infinite x is
+// not a number: the fix-up instruction that ends the IEEE sequence gives the quotient that x * y then
+// is, infinite (NaN for a NaN).  The mixed-precision FMA takes x as it is, which pays for the fix-up
+// (4096 x 8192 22.9 us, 22.9 without either, 23.7 with the fix-up and a conversion of x; 8192 x 2056, bound by
+// its instructions, 20.6, 20.2 and 21.8).
+template <int H>
+__device__ __forceinline__ float div_by(uint32_t xx, float s, float y)
 {
-    const float q = x * y;
-    return __builtin_fmaf(__builtin_fmaf(-s, q, x), y, q);
+    float q, r;
+    if (H == 0) {
+        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(q) : "v"(xx), "v"(y));
+        asm("v_fma_mix_f32 %0, -%1, %2, %3 op_sel_hi:[0,0,1]" : "=v"(r) : "v"(s), "v"(q), "v"(xx));
+    } else {
+        asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(q) : "v"(xx), "v"(y));
+        asm("v_fma_mix_f32 %0, -%1, %2, %3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r) : "v"(s), "v"(q), "v"(xx));
+    }
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(r, y, q), s, q);
 }
 __device__ __forceinline__ bool short_division_is_exact(float s) { return s >= 0x1p-40f && s <= 0x1p40f; }
 
@@ -233,12 +245,16 @@ __global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
         float amax = 0.0f;
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            widen8(r[it], f[it]);
-            if (SMOOTH) {
-                if (SEVERAL && safe) {
+            if (SMOOTH && SEVERAL && safe) {
+                const float *const y = rc[SEVERAL ? it : 0];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) f[it][e] = div_by(f[it][e], sm[it][e], rc[SEVERAL ? it : 0][e]);
-                } else {
+                for (int d = 0; d < 4; ++d) {
+                    f[it][2 * d] = div_by<0>(r[it][d], sm[it][2 * d], y[2 * d]);
+                    f[it][2 * d + 1] = div_by<1>(r[it][d], sm[it][2 * d + 1], y[2 * d + 1]);
+                }
+            } else {
+                widen8(r[it], f[it]);
+                if (SMOOTH) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) f[it][e] /= sm[it][e];
                 }

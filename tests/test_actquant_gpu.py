@@ -172,6 +172,29 @@ def test_smooth_scales_outside_the_short_division_range():
     assert np.array_equal(q, q_ref)
 
 
+def test_infinite_activations_do_not_depend_on_the_batch():
+    """A token's scale is that of the definition, x / smooth in FP32, however many tokens share the call:
+    infinite where an activation is, and unmoved by the NaN of another channel (the codes of such
+    tokens are unspecified)."""
+    import torch
+
+    _say("actquant infinite activations")
+    for K in (2056, 8192, 12296):
+        X16 = WL.make_activations_f16(1031, K, seed=K)
+        X16[3, 5], X16[500, K - 1], X16[1030, 0], X16[7, 9] = np.inf, -np.inf, np.inf, np.nan
+        smooth = WL.make_smooth(K, seed=K + 4)
+        q, s = _run(X16, smooth)
+        some = [0, 3, 7, 8, 500, 1029, 1030]
+        q_few, s_few = _run(X16[some], smooth)
+        assert np.isinf(s[[3, 500, 1030]]).all() and np.isfinite(np.delete(s, [3, 500, 1030])).all()
+        assert np.array_equal(s[some], s_few) and np.array_equal(q[some], q_few)
+        x = X16.copy()
+        x[[3, 500, 1030, 7]] = 0
+        q_ref, s_ref = O.quantize_activations(x, smooth)
+        keep = np.delete(np.arange(1031), [3, 7, 500, 1030])
+        assert np.array_equal(s[keep], s_ref[keep]) and np.array_equal(q[keep], q_ref[keep])
+
+
 def test_quantize_activations_edge_values():
     _say("actquant edge values")
     K = 512
