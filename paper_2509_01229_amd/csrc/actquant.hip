@@ -352,10 +352,15 @@ extern "C" int w4a8_quantize_activations(int M, int K, const uint16_t *X_f16, co
     const __half *X = reinterpret_cast<const __half *>(X_f16);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
-    if (smooth)
-        launch_quantize<true>(M, K, X, smooth, X_i8, act_scales, st);
-    else
-        launch_quantize<false>(M, K, X, smooth, X_i8, act_scales, st);
+    // A launch holds fewer than 2^32 threads, and a token takes up to 1024 of them.
+    constexpr int kTokensPerLaunch = 1 << 21;
+    for (long long m = 0; m < M; m += kTokensPerLaunch) {
+        const int rows = (int)std::min<long long>(kTokensPerLaunch, M - m);
+        if (smooth)
+            launch_quantize<true>(rows, K, X + m * K, smooth, X_i8 + m * K, act_scales + m, st);
+        else
+            launch_quantize<false>(rows, K, X + m * K, smooth, X_i8 + m * K, act_scales + m, st);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(LQ_ERR_HIP, "activation quantisation launch failed: %s", hipGetErrorString(e));
     return LQ_OK;

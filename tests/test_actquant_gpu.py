@@ -237,6 +237,22 @@ def test_quantize_activations_near_ties():
         assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
 
 
+@pytest.mark.parametrize("with_smooth", [False, True])
+def test_more_tokens_than_a_launch_takes(with_smooth):
+    """2^24 tokens of one block of 256 threads each would be 2^32 threads: several launches, with the
+    results of calls of their own."""
+    import torch
+
+    M, K = (1 << 24) + 5, 8
+    _say(f"actquant M={M} K={K} smooth={with_smooth}")
+    X = torch.randn((M, K), device="cuda").half()
+    smooth = torch.from_numpy(WL.make_smooth(K, seed=K)).cuda() if with_smooth else None
+    q, s = api.w4a8_quantize_activations(X, smooth)
+    for lo, hi in ((0, 70), ((1 << 21) - 3, (1 << 21) + 5), ((1 << 23) - 3, (1 << 23) + 5), (M - 70, M)):
+        qp, sp = api.w4a8_quantize_activations(X[lo:hi].clone(), smooth)
+        assert torch.equal(q[lo:hi], qp) and torch.equal(s[lo:hi], sp)
+
+
 def test_empty_and_bad_arguments():
     import torch
 
