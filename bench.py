@@ -169,8 +169,7 @@ def point(shape, M, ms, api, calib=None, ms_same=None):
         "tops": round(ops / t / 1e12, 3), "gbs": round(byt / t / 1e9, 1),
         "bound": "hbm" if t_mem >= t_mma else "mfma",
         "frac_of_roofline": round(max(t_mem, t_mma) / t, 4),
-        "variant": "+".join(api.w4a8_variant_name(v) + (f"[{rows} rows]" if rows != M else "")
-                            for rows, v in api.w4a8_select_plan(M, shape.N, shape.K, shape.group)),
+        "variant": api.w4a8_describe_launch(M, shape.N, shape.K, shape.group)[0],
     }
     if ms_same is not None:
         p["us_same_buffer"] = round(ms_same * 1e3, 3)
@@ -186,7 +185,7 @@ def point(shape, M, ms, api, calib=None, ms_same=None):
         rates = CM.Rates(calib["stream_read_gbs"] * 1e9, calib["mfma_i8_random_tops"] * 1e12,
                          CM.NOMINAL_VALU_LANE_OPS_PER_S)
         first = p["variant"].split("+")[0]
-        m_tile = 16 if M <= 16 else 32 if M <= 32 else 256 if first.startswith("solo") else 64 if "m64" in first else 128
+        m_tile = next((t for t in (32, 64, 128, 256) if f"_m{t}" in first), 16)   # (the 16-row kernels name no tile)
         pr = CM.predict(M, shape.N, shape.K, shape.group, rates, m_tile)
         p["model_us"] = {"eq6_serial": round(pr["serial"] * 1e6, 2), "overlapped": round(pr["overlapped"] * 1e6, 2)}
     return p

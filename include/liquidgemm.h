@@ -174,6 +174,14 @@ int w4a8_select_variant(int M, int N, int K, int group); /* the dispatcher's cho
  * <0 on error. */
 int w4a8_select_plan(int M, int N, int K, int group, int *rows_first, int *variant_rest);
 
+/* What one launch (or two) of a named variant, or of the dispatcher (-1), runs for a shape when the
+ * workspace holds all K slices: the kernel's name -- for the dispatcher also the panel form that takes
+ * the place of the few tiles of duo_m64 / duo_m128 or that stream_m32 / stream_m64 stand for, with its
+ * K slices ("panel_f4_m64_s3") -- and the workspace bytes it uses (0: no K slices across blocks).  Host
+ * only; text (cut to text_bytes, always terminated) and workspace_bytes may be NULL. */
+int w4a8_describe_launch(int variant, int M, int N, int K, int group, char *text, size_t text_bytes,
+                         size_t *workspace_bytes);
+
 /* Layout hook: dequantise the whole packed matrix on the device with the kernels' own
  * unpack + Eq. 12 code path into Wd [N,K] INT8 row-major (device). */
 int w4a8_dequant_dump(const void *W_packed, const uint8_t *gparams, int N, int K, int group,

@@ -76,6 +76,8 @@ def lib() -> ctypes.CDLL:
     L.w4a8_select_variant.argtypes = [i, i, i, i]
     L.w4a8_select_plan.restype = i
     L.w4a8_select_plan.argtypes = [i, i, i, i, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
+    L.w4a8_describe_launch.restype = i
+    L.w4a8_describe_launch.argtypes = [i, i, i, i, i, ctypes.c_char_p, sz, ctypes.POINTER(sz)]
     L.w4a8_dequant_dump.restype = i
     L.w4a8_dequant_dump.argtypes = [vp, vp, i, i, i, vp, vp]
     L.w4a8_grouped_gemm.restype = i
@@ -350,6 +352,13 @@ def w4a8_select_plan(M: int, N: int, K: int, group: int):
     if rest.value >= 0:
         plan.append((M - int(rows_first.value), int(rest.value)))
     return plan
+
+
+def w4a8_describe_launch(M: int, N: int, K: int, group: int, variant: int = -1):
+    """(name of the kernel that runs, workspace bytes it uses) for the dispatcher or a named variant."""
+    text, need = ctypes.create_string_buffer(160), ctypes.c_size_t()
+    _check(lib().w4a8_describe_launch(variant, M, N, K, group, text, len(text), ctypes.byref(need)))
+    return text.value.decode(), int(need.value)
 
 
 def w4a8_dequant_dump(W_packed, gparams, N: int, K: int, group: int, out=None, stream=None):

@@ -291,12 +291,9 @@ static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
     }
     return best;
 }
-// 17..32 and 33..64 rows (MAX_M): always (measured against 32- and 64-row kernels that prefetched one
-// unit and split K across blocks only for small N: 10 to 30 % ahead, at worst equal)
-template <int MAX_M>
+// 17..64 rows: always
 static int launch_panel_auto(const Args &a)
 {
-    if (a.M > MAX_M) return fail(LQ_ERR_INVALID, "this stream variant handles M <= %d, got %d", MAX_M, a.M);
     const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
     return c.form->launch(a, c.S);
 }
@@ -638,21 +635,19 @@ static bool prefer_64_row_tiles(int M, int N, int K)
     return est64 < est128;
 }
 
-// duo_m64 and duo_m128: the tiles, or a panel form where that is estimated to be faster.  The
-// estimate of the tiles is 2.5 us below its terms (the fits above include more launch time) and low by
-// up to half for some shapes, by 18 % on average; with a factor of 1.15 the choice is 0.8 % from
-// the better of both over 128 shapes of 96 to 512 rows (256 x 8192 x 8192: 27.2 against 30.6 us,
-// 128 x 4096 x 11008: 15.8 against 21.2, 192 x 5120 x 5120: 12.8 against 18.3).  With more rows and
-// more than 64 tiles of 128 x 256 the tiles stay ahead (384 x 6144 x 2048: 12.9 against 14.8 us,
+// Where the dispatcher arrives at duo_m64 or duo_m128 it runs a panel form instead if that is estimated to
+// be faster (a null form: it is not).  The estimate of the tiles is 2.5 us below its terms (the fits above
+// include more launch time) and low by up to half for some shapes, by 18 % on average; with a factor of
+// 1.15 the choice is 0.8 % from the better of both over 128 shapes of 96 to 512 rows (256 x 8192 x 8192:
+// 27.2 against 30.6 us, 128 x 4096 x 11008: 15.8 against 21.2, 192 x 5120 x 5120: 12.8 against 18.3).  With
+// more rows and more than 64 tiles of 128 x 256 the tiles stay ahead (384 x 6144 x 2048: 12.9 against 14.8 us,
 // 1024 x 3072 x 3072: 17.5 against 18.9; with 64 tiles 500 x 4096 x 4096: 18.6 against 15.3).
 static double few_tiles_us(int M, int N, int K);
-template <LaunchFn TILES>
-static int launch_few_tiles(const Args &a)
+static PanelChoice panel_instead_of_tiles(const Args &a)
 {
-    if (a.M > 256 && (long long)((a.M + 127) / 128) * ((a.N + 255) / 256) > 64) return TILES(a);
+    if (a.M > 256 && (long long)((a.M + 127) / 128) * ((a.N + 255) / 256) > 64) return PanelChoice{};
     const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
-    if (c.form && c.us < 1.15 * few_tiles_us(a.M, a.N, a.K)) return c.form->launch(a, c.S);
-    return TILES(a);
+    return c.form && c.us < 1.15 * few_tiles_us(a.M, a.N, a.K) ? c : PanelChoice{};
 }
 
 struct Variant {
@@ -666,8 +661,8 @@ struct Variant {
 
 // stream_m32, stream_m64, stream_f*, stream_x*, stream_m64x*: panel forms for up to 32 and 64 rows
 // (the names of the kernels they took the place of).  panel_f<F>_m<rows>[_s<S>]: F tiles
-// and 32, 64 or 128 rows per block.  duo_m64, duo_m128: few 64- or 128-row tiles, or a panel form
-// where that is faster.  stream16_f<F>_w<NW>[_s<S>]: F tiles per block, NW waves splitting the block's K slice,
+// and 32, 64 or 128 rows per block.  duo_m64, duo_m128: few 64- or 128-row tiles, K split over blocks (the
+// dispatcher runs a panel form in their place where that is faster).  stream16_f<F>_w<NW>[_s<S>]: F tiles per block, NW waves splitting the block's K slice,
 // S grid-level K slices (chosen from the shape when not named); _u4 = four 128-k units per
 // pipeline step; g2 = two k groups per block.
 static const Variant kVariants[] = {
@@ -678,10 +673,10 @@ static const Variant kVariants[] = {
     {"stream16_f2_w8", &launch_stream16<2, 8, 0>, 16, 2, 1},
     {"stream16_f2_w16_s1", &launch_stream16<2, 16, 1>, 16, 2, 1},
     {"stream16_f2_w4", &launch_stream16<2, 4, 0>, 16, 2, 1},
-    {"stream_m32", &launch_panel_auto<32>, 32, 2, 1},
-    {"stream_m64", &launch_panel_auto<64>, 64, 2, 1},
-    {"duo_m64", &launch_few_tiles<&launch_duo64<0>>, 0, 1, 1, 512},
-    {"duo_m128", &launch_few_tiles<&launch_duo<0, 0>>, 0, 1, 1},
+    {"stream_m32", &launch_panel_auto, 32, 2, 1},
+    {"stream_m64", &launch_panel_auto, 64, 2, 1},
+    {"duo_m64", &launch_duo64<0>, 0, 1, 1, 512},
+    {"duo_m128", &launch_duo<0, 0>, 0, 1, 1},
     {"duo_dl_m128", &launch_duo_dl<0>, 0, 1, 1},
     {"duo_pt_m128", &launch_duo_pt, 0, 1, 8, 512},
     {"solo16_pt_m256", &launch_solo_pt<1, 0, true>, 0, 1, 4},
@@ -731,6 +726,11 @@ static int find_variant(const char *name)
     for (int i = 0; i < kNumVariants; ++i)
         if (!strcmp(kVariants[i].name, name)) return i;
     return -1;
+}
+
+static bool is_few_tiles(int variant)
+{
+    return kVariants[variant].fn == &launch_duo64<0> || kVariants[variant].fn == &launch_duo<0, 0>;
 }
 
 // The 256-row tiles with one wave per SIMD (solo16_pt_m256: 256 x 256; solo16_g2_m256: 256 x 128
@@ -930,7 +930,8 @@ static int check_device_args(const Args &a)
 
 static int run_rows(int variant, const Args &a)
 {
-    if (variant < 0) variant = select_variant(a.M, a.N, a.K);
+    const bool dispatched = variant < 0;
+    if (dispatched) variant = select_variant(a.M, a.N, a.K);
     if (variant < 0 || variant >= kNumVariants) return fail(LQ_ERR_INVALID, "unknown variant %d", variant);
     if (!variant_supports(variant, a.M, a.N, a.K))
         return fail(LQ_ERR_INVALID, "variant %s cannot run M=%d N=%d K=%d", kVariants[variant].name, a.M, a.N,
@@ -951,7 +952,8 @@ static int run_rows(int variant, const Args &a)
         if (a.sx) c.sx = a.sx + r0;
         if (a.Y) c.Y = a.Y + r0 * a.N;
         if (a.ACC) c.ACC = a.ACC + r0 * a.N;
-        if (int rc = kVariants[variant].fn(c)) return rc;
+        const PanelChoice panel = dispatched && is_few_tiles(variant) ? panel_instead_of_tiles(c) : PanelChoice{};
+        if (int rc = panel.form ? panel.form->launch(c, panel.S) : kVariants[variant].fn(c)) return rc;
         need_max = std::max(need_max, need);
     }
     if (a.query) return *a.query = need_max, LQ_OK;
@@ -981,6 +983,25 @@ static int run(int variant, const Args &a)
     if (int rc = run_rows(-1, rest)) return rc;
     if (a.query) *a.query = std::max(need_head, need_rest);
     return LQ_OK;
+}
+
+// The name of the kernel that a launch over the given rows runs (with all K slices), to `text`.
+static void launch_name(int variant, int M, int N, int K, char *text, size_t text_bytes)
+{
+    Args a{};
+    size_t unused = 0;
+    a.M = M, a.N = N, a.K = K, a.query = &unused;
+    const bool dispatched = variant < 0;
+    if (dispatched) variant = select_variant(M, N, K);
+    PanelChoice panel{};
+    if (kVariants[variant].fn == &launch_panel_auto) panel = choose_panel(M, N, K, workspace_limit(a));
+    else if (dispatched && is_few_tiles(variant)) panel = panel_instead_of_tiles(a);
+    if (!panel.form)
+        snprintf(text, text_bytes, "%s", kVariants[variant].name);
+    else if (panel.S == 1)
+        snprintf(text, text_bytes, "panel_f%d_m%d", panel.form->F, 32 * panel.form->MF);
+    else
+        snprintf(text, text_bytes, "panel_f%d_m%d_s%d", panel.form->F, 32 * panel.form->MF, panel.S);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1349,6 +1370,35 @@ int w4a8_select_plan(int M, int N, int K, int group, int *rows_first, int *varia
     *rows_first = first;
     *variant_rest = first == M ? -1 : select_variant(M - first, N, K);
     return first == M ? select_variant(M, N, K) : find_variant("solo16_pt_m256");
+}
+
+int w4a8_describe_launch(int variant, int M, int N, int K, int group, char *text, size_t text_bytes,
+                         size_t *workspace_bytes)
+{
+    if (variant < -1 || variant >= kNumVariants) return fail(LQ_ERR_INVALID, "unknown variant %d", variant);
+    if (M < 0 || !shape_ok(N, K, group)) return fail(LQ_ERR_INVALID, "bad shape");
+    if (variant >= 0 && !variant_supports(variant, M, N, K))
+        return fail(LQ_ERR_INVALID, "variant %s cannot run M=%d N=%d K=%d", kVariants[variant].name, M, N, K);
+    size_t need[2] = {0, 0};
+    char words[160] = "";
+    if (M > 0) {
+        const int first = variant < 0 ? rows_of_first_launch(M, N, K) : M;
+        char name[64];
+        Args a{};
+        a.M = first, a.N = N, a.K = K, a.group = group, a.query = &need[0];
+        if (int rc = run_rows(first == M ? variant : find_variant("solo16_pt_m256"), a)) return rc;
+        launch_name(first == M ? variant : -1, M - (first == M ? 0 : first), N, K, name, sizeof(name));
+        if (first == M) {
+            snprintf(words, sizeof(words), "%s", name);
+        } else {
+            a.M = M - first, a.query = &need[1];
+            if (int rc = run_rows(-1, a)) return rc;
+            snprintf(words, sizeof(words), "solo16_pt_m256[%d rows]+%s[%d rows]", first, name, M - first);
+        }
+    }
+    if (workspace_bytes) *workspace_bytes = std::max(need[0], need[1]);
+    if (text && text_bytes) snprintf(text, text_bytes, "%s", words);
+    return LQ_OK;
 }
 
 int w4a8_dequant_dump(const void *W_packed, const uint8_t *gparams, int N, int K, int group,

@@ -176,6 +176,36 @@ def test_variant_table_is_consistent():
     assert not api.w4a8_variant_supports(len(names), 8, 256, 1024, 64)
 
 
+def test_reported_kernels():
+    """What w4a8_describe_launch says runs: a named variant is the kernel of that name (stream_m32 and
+    stream_m64 stand for panel forms); the dispatcher takes tiles or a panel where the plan says duo_m64 or duo_m128."""
+    names = api.w4a8_variant_names()
+    for M, N, K in [(8, 256, 512), (77, 448, 768), (200, 256, 512), (130, 576, 1280), (300, 320, 1792), (256, 8192, 8192),
+                    (160, 512, 2048), (200, 1024, 4096)]:
+        for v, name in enumerate(names):
+            if api.w4a8_variant_supports(v, M, N, K, 64) and name not in ("stream_m32", "stream_m64"):
+                assert api.w4a8_describe_launch(M, N, K, 64, v)[0] == name
+    assert api.w4a8_describe_launch(45, 4096, 4096, 64, names.index("stream_m64"))[0].startswith("panel_f")
+    with pytest.raises(api.LiquidGemmError):
+        api.w4a8_describe_launch(65, 4096, 4096, 64, names.index("stream_m64"))
+    with pytest.raises(api.LiquidGemmError):
+        api.w4a8_describe_launch(8, 100, 512, 64)
+    # both are duo_m64 to w4a8_select_variant
+    assert _pick(256, 8192, 8192) == _pick(64, 28672, 8192) == "duo_m64"
+    assert api.w4a8_describe_launch(256, 8192, 8192, 64) == ("panel_f4_m64", 0)
+    assert api.w4a8_describe_launch(64, 28672, 8192, 64) == ("duo_m64", 32768 + 112 * 2 * 131072)   # two K slices
+    assert api.w4a8_describe_launch(64, 1088, 6912, 64)[0] == "panel_f1_m32_s3"
+    assert api.w4a8_describe_launch(4096 + 40, 8192, 8192, 64)[0] == "solo16_pt_m256[4096 rows]+panel_f2_m32[40 rows]"
+    assert api.w4a8_describe_launch(0, 8192, 8192, 64) == ("", 0)
+    for s in WL.ALL_SHAPES:
+        name, _ = api.w4a8_describe_launch(s.M, s.N, s.K, s.group)
+        plan = api.w4a8_select_plan(s.M, s.N, s.K, s.group)
+        for part, (rows, v) in zip(name.split("+"), plan):
+            picked = names[v]
+            assert part.split("[")[0] == picked or (picked in ("duo_m64", "duo_m128", "stream_m32", "stream_m64")
+                                                    and part.startswith("panel_f")), (s.name, name)
+
+
 def test_workspace_sizes():
     ws = api.w4a8_gemm_workspace_size
     assert ws(0, 4096, 4096, 64) == 0 and ws(16, 100, 4096, 64) == 0     # nothing to do / bad shape
