@@ -103,6 +103,10 @@ int liquidquant_unpack_weights(const void *W_packed, const uint8_t *gparams, int
  * the shape splits K across blocks): 32 KiB of arrival tickets followed by room for the INT32
  * partial tiles of the grid-level split-K (the 256-row tile kernels with K slices keep a whole
  * [M,N] INT32 matrix per slice there, at most four).
+ *   - It is enough for the dispatcher (the rest of a batch in two launches takes the slices that fit),
+ *     for every variant of up to 256 rows and, while the output has fewer than 192 tiles of 128 x 256,
+ *     for every variant that can run the shape.  A variant that names its K slices may ask for more
+ *     on a larger output: w4a8_describe_launch says how much.
  *   - The first 32 KiB (or the whole buffer if smaller) must be zero before the first call
  *     that uses the buffer: zero it yourself or enqueue w4a8_workspace_init() once.  The
  *     kernels leave the tickets zero again, so one initialisation serves any number of calls,

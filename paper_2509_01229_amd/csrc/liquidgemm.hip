@@ -163,13 +163,6 @@ static int stream_split(int N, int K, int F, int NW)
     return std::max(1, s);
 }
 
-static size_t stream_ws_bytes(int M, int N, int S, int MF = 1)
-{
-    if (S <= 1) return 0;
-    const int rmax = MF == 1 ? 4 * ((M + 7) / 8) : 16;
-    return kTicketBytes + (size_t)S * (N / 32) * MF * rmax * 64 * sizeof(int32_t);
-}
-
 template <int F, int NW, int SPLIT, int UU = 1>
 static int launch_stream16(const Args &a)
 {
@@ -1253,13 +1246,13 @@ extern "C" {
 size_t w4a8_gemm_workspace_size(int M, int N, int K, int group)
 {
     if (M <= 0 || !shape_ok(N, K, group)) return 0;
-    // Enough for any variant that can run the shape.  Tiled kernels split K only while the
-    // output has fewer tiles than CUs (at most 8 slices); stream kernels take at most 16
-    // slices (the 16-row kernels always exchange 8 values per lane and tile).
+    // Enough for the dispatcher, for any variant that can run a shape of fewer than 192 tiles of
+    // 128 x 256 (tiled kernels and panels split K only there, into at most 8 slices) and for the variants of
+    // up to 64 rows (panels of at most 4 slices; the 16-row kernels take up to 16 and exchange 8 values per
+    // lane and tile).
     const int tiles = ((M + 127) / 128) * ((N + 255) / 256);
     size_t need = tiles >= 192 ? 0 : std::max(duo_ws_bytes(M, N, 8), duo_ws_bytes(M, N, 8, 64));
-    if (M <= 32) need = std::max(need, stream_ws_bytes(M, N, 16));
-    if (M <= 64) need = std::max(need, stream_ws_bytes(M, N, 16, 2));
+    if (M <= 64) need = std::max(need, panel_ws_bytes(N / 32 + 3, 1, 2, 4));
     if (M <= 16) need = std::max(need, kTicketBytes + (size_t)16 * (N / 32) * 8 * 64 * sizeof(int32_t));
     if (K % 512 == 0) {
         // the 256-row tiles with K slices: a whole INT32 matrix per slice, at most one round of blocks

@@ -219,6 +219,30 @@ def test_workspace_sizes():
     assert ws(128, 4096, 4096, 64) <= 1 << 30
 
 
+def test_workspace_size_covers_what_it_promises():
+    """w4a8_gemm_workspace_size is enough for the dispatcher, for the variants of up to 256 rows and, on fewer than
+    192 tiles of 128 x 256, for every variant that can run the shape."""
+    names = api.w4a8_variant_names()
+    shapes = [(M, N, K) for M in (1, 16, 17, 32, 33, 64, 65, 128, 257, 512, 1000, 2048, 4096, 12000)
+              for N in (64, 192, 256, 1536, 4096, 8192, 28672, 65600) for K in (256, 512, 768, 1024, 2048, 8192, 28672)]
+    for M, N, K in shapes:
+        room = api.w4a8_gemm_workspace_size(M, N, K, 64)
+        few_tiles = -(-M // 128) * -(-N // 256) < 192
+        for v in range(-1, len(names)):
+            if v >= 0 and not api.w4a8_variant_supports(v, M, N, K, 64):
+                continue
+            if v >= 0 and not few_tiles and api.w4a8_variant_supports(v, 4096, N, 2048, 64):
+                continue   # (no row limit: may name K slices of a larger output)
+            name, need = api.w4a8_describe_launch(M, N, K, 64, v)
+            if "+" in name:
+                continue   # (the rest of a batch in two launches takes the slices that fit)
+            assert need <= room, (M, N, K, names[v] if v >= 0 else name, need, room)
+    # what it points to for the others
+    v = names.index("panel_f4_m32_s2")
+    assert api.w4a8_describe_launch(2048, 8192, 512, 64, v)[1] == 32768 + 64 * 64 * 2 * 4 * 4096
+    assert api.w4a8_gemm_workspace_size(2048, 8192, 512, 64) < 32768 + 64 * 64 * 2 * 4 * 4096
+
+
 def test_workload_names():
     # the listed shapes by name, and any other shape spelled <label>_M.._N.._K..[_g..]
     s = WL.by_name("l70b_up_M16_N28672_K8192")
