@@ -312,11 +312,13 @@ template <bool SMOOTH>
 static void launch_quantize(int M, int K, const __half *X, const float *smooth, int8_t *Q, float *sx, hipStream_t st)
 {
     const int n8 = K / 8;  // 16-byte pieces of a token
-    if (SMOOTH && M >= 1024 && K > 2048 && K <= 16384) {
-        const int R = (M + 511) / 512;
-        if (n8 <= 512) return launch_rows<SMOOTH, 1, 512, SMOOTH>(M, K, R, 1, X, smooth, Q, sx, st);
-        if (n8 <= 1024) return launch_rows<SMOOTH, 1, 1024, SMOOTH>(M, K, R, 1, X, smooth, Q, sx, st);
-        return launch_rows<SMOOTH, 2, 1024, SMOOTH>(M, K, (M + 255) / 256, 1, X, smooth, Q, sx, st);
+    if constexpr (SMOOTH) {
+        if (M >= 1024 && K > 2048 && K <= 16384) {
+            const int R = (M + 511) / 512;
+            if (n8 <= 512) return launch_rows<SMOOTH, 1, 512, true>(M, K, R, 1, X, smooth, Q, sx, st);
+            if (n8 <= 1024) return launch_rows<SMOOTH, 1, 1024, true>(M, K, R, 1, X, smooth, Q, sx, st);
+            return launch_rows<SMOOTH, 2, 1024, true>(M, K, (M + 255) / 256, 1, X, smooth, Q, sx, st);
+        }
     }
     if (n8 <= 256) return launch_rows<SMOOTH, 1, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
     if (n8 <= 512)

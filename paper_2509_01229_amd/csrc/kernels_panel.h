@@ -6,10 +6,13 @@
 // A block owns 32 MF rows x F tiles (32 F channels) of the output and one of S slices of K; its
 // NW waves take the slice's units of 128 k round-robin, so a wave shares nothing with the others
 // until the end: no barrier in the loop, and the registers of the whole CU hold loads in flight
-// (128 KB with F = 4, MF = 2).  Loading further ahead gained nothing (one to four units, F = 1): what
-// bounds the loop is the rate at which a CU takes in X from L2 and W, 55 to 60 bytes per ns
-// whatever the form (64 x 8192 x 8192 F = 1 and 256 x 8192 x 8192 F = 4 alike), hence forms
-// from 1 x 1 to 4 x 4 accumulator tiles, which trade that volume against the sum over the waves at
+// (128 KB with F = 4, MF = 2).  Loading further ahead gained nothing (one to four units, F = 1).  Shader
+// counters: on 256 x 8192 x 8192 (F = 4, MF = 2, 256 blocks) vector and matrix instructions add up to
+// 37.6 of the 51.3 thousand cycles that the two waves of a SIMD live, on 45 x 13824 x 5120 (F = 2, MF = 2, 216
+// blocks) 12.8 of 25.6; the waves wait for loads 31 and 37 % of their time, at 21 and 16 bytes per
+// cycle and CU (L2 answers in 390 and 480 cycles).  So no one unit is the bound: the dequantisation of W
+// for few rows and the latency of X and W both are, hence forms from 1 x 1 to 4 x 4 accumulator tiles, which
+// trade the volume of X and the repeated dequantisation against the sum over the waves at
 // the end (0.6 us per tile) and the number of blocks.  Starting every column group at another
 // unit takes 1 to 3 us off large batches (35.8 to 32.9 us on 256 x 10240 x 8192): rows are a power of
 // two apart, and the blocks of an XCD would all ask the same channels of its L2.
@@ -22,7 +25,7 @@
 // piece i of the region in lane order; lane p brings row 8 i + r, 16-byte column c with
 // r = (p >> 3) ^ (i & 1), c = (p & 7) ^ r.  Fragment row j' = 32 mf + j is then found in piece j' >> 3
 // at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): neither the stores nor the fragment reads
-// meet bank conflicts.
+// meet bank conflicts (the counter says 0 for both shapes above).
 // ------------------------------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t buf_t;
 __device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
@@ -31,9 +34,13 @@ __device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
 }
 
 // ONCE = the weights are read by one row tile only (M <= 32 MF): loaded without keeping them in the
-// caches (8 experts of 10..24 rows on 14336 x 4096, weights in HBM: 46.6 against 51.8 us; where row
-// tiles share them the plain loads win, 16 experts of 18..36 rows on 2816 x 2048 16.8 against 18.6; the
-// same weights again while the memory-side cache holds them all are slower, 6.9 against 6.1 us on 32 x 4096 x 4096).
+// caches.  That pays where the weights come from HBM, as those of a model larger than the memory-side cache (256 MB)
+// do: with 550 MB of weights in rotation 4 to 13 % over 23 shapes of 0.5 to 117 MB at 17..64 rows (1024 x 2048 at 17
+// rows 4.5 against 5.1 us, 10240 x 8192 12.9 / 13.7, 28672 x 8192 at 64 rows 30.7 / 32.3; 6144 x 16384 equal).  It
+// costs where that cache still holds them all when they are asked for again: 9 to 14 % on 24 matrices of 4096 x
+// 4096 in turn (6.9 / 6.1 us at 32 rows), nothing on one matrix of up to 25 MB, up to 17 % on a larger one
+// (10240 x 8192 11.9 / 10.9, 28672 x 8192 24.0 / 21.9).  Where row tiles share the weights the plain loads
+// win (16 experts of 18..36 rows on 2816 x 2048 16.8 against 18.6).
 template <int F, int NW, int MF, bool G128, bool ONCE>
 __device__ __forceinline__ void panel_block(
     const Place pl, int bm, int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,

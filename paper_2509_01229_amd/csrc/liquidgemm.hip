@@ -1,15 +1,18 @@
 // gfx950 kernels and the C-ABI dispatcher of the LiquidQuant W4A8 GEMM.
 //
-// Two kernel families share the packed layout of lqq_layout.h and the dequantisation of
+// Three kernel families share the packed layout of lqq_layout.h and the dequantisation of
 // lqq_device.h (paper Sec. 5.3):
 //
-//   stream  (M <= 64): the memory-bound regime of the paper's cost model (Sec. 3.2,
+//   stream16 (M <= 16): the memory-bound regime of the paper's cost model (Sec. 3.2,
 //           T_LD dominates).  A block owns F tiles of 32 output channels; its NW waves
 //           split K between them (in-block split-K), stream the packed weights straight
 //           from HBM into registers with one 16-byte load per lane, dequantise, feed the
-//           MFMA, and reduce their INT32 partials through LDS -- integer sums, so the
-//           result does not depend on the order.  stream16 is the same on the 16-row MFMA
-//           shape for M <= 16.  Optional grid-level split-K through a workspace.
+//           16-row MFMA, and reduce their INT32 partials through LDS -- integer sums, so the
+//           result does not depend on the order.  Optional grid-level split-K through a workspace.
+//
+//   panel   (17 rows to a few hundred): the same split of K between the waves of a block, with
+//           32, 64 or 128 rows and 32 to 128 channels per block on the 32-row MFMA and X passed
+//           through LDS a wave at a time.
 //
 //   tiled   (larger M): the compute-bound regime (T_DQ + T_MMA dominates).  A block owns
 //           128 rows of X and 256 output channels; the X tile is staged in LDS (double
@@ -151,8 +154,7 @@ static int allow_lds(Kernel kernel, size_t bytes)
     return allow_lds_once(reinterpret_cast<const void *>(kernel), bytes);
 }
 
-// Grid-level split of K for the stream kernels: enough blocks for every CU to hold two
-// (about 512), each wave keeping at least two units of 128 k.
+// Grid-level split of K for the 16-row kernel, each wave keeping at least two units of 128 k.
 static int stream_split(int N, int K, int F, int NW)
 {
     const int groups = N / (32 * F), units = K / 128;
@@ -255,7 +257,10 @@ struct PanelChoice {
 };
 // The form and the number of K slices for a shape.  The time of a form is linear in what it does,
 // fitted to 14 row counts (17 to 512) x 17 weight shapes (1024 to 28672 channels and k) x all forms
-// and 1 to 4 slices, 8 % rms; the form it picks is 1.5 % behind the best one on average:
+// and 1 to 4 slices, 8 % rms.  Audited on 19 row counts x 23 weight shapes (channels and k up to 28672, 550 MB of
+// weights in rotation): at 17..64 rows the form it picks is 1.4 % behind the best one (geometric mean) and at
+// worst 14 % (33 x 4096 x 14336: 14.8 against 13.0 us), at 65..512 rows 0.4 % and 9 %; 12 and 19 % ahead of the
+// 32- and 64-row kernels that prefetched one unit, and nowhere more than 1 % behind them:
 //   2.26 us of launch and first loads
 //   + 0.61 us per accumulator tile (32 x 32) of a block: the sum over the waves and the epilogue
 //   + 9.8 ns per KB of X and 19.1 ns per KB of W that a CU takes in (X comes from L2; W is also dequantised)
@@ -284,7 +289,7 @@ static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
     }
     return best;
 }
-// 17..64 rows: always
+// 17..64 rows: the form that choose_panel picks
 static int launch_panel_auto(const Args &a)
 {
     const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
@@ -803,10 +808,9 @@ static int solo_form_for(long long t128, long long t256, long long t2, int K)
 }
 static int solo_form_that_pays(int M, int N, int K) { return solo_form_of(tiled_costs(M, N, K)); }
 
-// Shape -> kernel.  Up to 32 rows the weights are streamed once with X fragments in
-// registers (16-row MFMA shape up to 16 rows); anything larger runs the 128 x 256 tiles of
-// the duo kernel, whose launcher adds in-block and grid-level split-K while the output
-// alone gives at most one tile per CU.
+// Shape -> kernel.  Up to 16 rows the 16-row kernel, up to 64 the panels while N alone does not fill the
+// chip with tiles, then tiles of 256, 128 or 64 rows by cost; where these are few (duo_m64, duo_m128) the
+// dispatcher compares a panel form once more (panel_instead_of_tiles).
 static int select_variant(int M, int N, int K)
 {
     if (M <= 16) {
@@ -836,10 +840,9 @@ static int select_variant(int M, int N, int K)
         return find_variant("stream16_f2_w8");
     }
     if (M <= 32) return find_variant("stream_m32");
-    // up to 64 rows the weights are still best streamed once per block column (X through LDS)
-    // unless N alone fills the chip with 128 x 256 tiles
-    // (except 129..256 tiles with very long K from 48 rows on: no room for K slices across blocks,
-    // and the tiles' split-K grid is 8-16 % ahead, 32.8 against 38.1 us at 64 rows on 6144 x 28672)
+    // up to 64 rows the panels, unless N alone fills the chip with 128 x 256 tiles.  (48 rows and more on
+    // 129..256 tiles of 32 channels with very long K arrive at duo_m64 / duo_m128 below, where the estimates
+    // pick a panel again: 26.2 against 31.2 us on the tiles for 48 x 6144 x 28672, 31.6 / 35.2 for 64 x 8192 x 28672.)
     if (M <= 64 && N / 32 <= 512 && !(M >= 48 && N / 32 > 128 && N / 32 <= 256 && K >= 24576))
         return find_variant("stream_m64");
     // 256-row tiles with one wave per SIMD where their whole rounds come out ahead
