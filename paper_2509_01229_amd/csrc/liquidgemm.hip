@@ -693,6 +693,7 @@ static const Variant kVariants[] = {
     {"stream_m64x_f2_w8_s4", &launch_panel_named<2, 8, 2, 4>, 64, 2, 1},
     {"panel_f4_m32_s2", &launch_panel_named<4, 8, 1, 2>, 0, 1, 1},
     {"panel_f3_m64_s2", &launch_panel_named<3, 8, 2, 2>, 0, 1, 1},
+    {"panel_f4_m64_s3", &launch_panel_named<4, 8, 2, 3>, 0, 1, 1},
     {"duo_m64_s2", &launch_duo64<2>, 0, 1, 1, 512},
     // (... and the panel forms without slices)
     {"panel_f1_m64", &launch_panel_named<1, 8, 2, 1>, 0, 1, 1},

@@ -102,3 +102,34 @@ def assert_fp16_close(Y, ref_f64, what=""):
 def variants_for(M, N, K, group):
     """Indices of every kernel variant able to run this shape."""
     return [i for i in range(api.w4a8_variant_count()) if api.w4a8_variant_supports(i, M, N, K, group)]
+
+
+class RandomWeights:
+    """Packed weights made on the GPU (any codes, admissible group parameters: code * s + a <= 255), for shapes
+    whose quantisation on the host would take longer than the test; `product` is exact, from the
+    library's own dequantised matrix (which test_dequant_dump_* compares with the oracle)."""
+
+    def __init__(self, N, K, group, seed=0):
+        import torch
+
+        self.N, self.K, self.group = N, K, group
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        cb, gb = api.liquidquant_packed_size(N, K, group)
+        self.codes = torch.randint(0, 256, (cb,), dtype=torch.uint8, device="cuda", generator=gen)
+        pairs = [torch.randint(lo, hi, (gb // 2,), device="cuda", generator=gen) for lo, hi in ((1, 17), (0, 16))]
+        self.gparams = torch.stack(pairs, 1).to(torch.uint8).reshape(-1).contiguous()
+        self.scales = torch.rand(N, device="cuda", generator=gen) * 1e-3
+        self._gen = gen
+
+    def activations(self, M):
+        import torch
+
+        X = torch.randint(-127, 128, (M, self.K), dtype=torch.int8, device="cuda", generator=self._gen)
+        return X, torch.rand(M, device="cuda", generator=self._gen) * 1e-2
+
+    def product(self, X):
+        """X . Wd^T in INT32: sums of integers below 2^53 in float64."""
+        import torch
+
+        Wd = api.w4a8_dequant_dump(self.codes, self.gparams, self.N, self.K, self.group)
+        return torch.matmul(X.double(), Wd.double().t().contiguous()).to(torch.int32)

@@ -53,8 +53,9 @@ def test_quantize_activations_bit_exact(M, K, with_smooth):
 
 @pytest.mark.parametrize("M,K", [(1027, 2048), (2051, 4096), (4096, 512), (1027, 12288), (600, 16384)])
 def test_several_tokens_per_block(M, K):
-    """From 1024 tokens on a block quantises 2 or 4 consecutive tokens (ragged last block) and
-    shares the reciprocals of the smooth scales between them."""
+    """From 1024 tokens of 2049 to 16384 columns on a block quantises several consecutive tokens (here 5,
+    with a ragged last block) and shares the reciprocals of the smooth scales between them: the second and
+    fourth case.  The others were such cases once and are blocks of one token."""
     _say(f"actquant rows per block M={M} K={K}")
     X16 = WL.make_activations_f16(M, K, outlier_frac=0.001, seed=M)
     smooth = WL.make_smooth(K, seed=K + 1)
@@ -142,29 +143,35 @@ def test_a_few_columns_more_do_not_cost_a_larger_block():
     assert t < 1.2 * u
 
 
-def test_smooth_scales_outside_the_short_division_range():
+# (up to 1023 tokens every division is the IEEE one; the other shapes are the three block shapes of several tokens,
+# which take the short division where all scales of a thread are in range)
+@pytest.mark.parametrize("M,K", [(5, 2048), (1025, 2056), (1025, 8192), (1030, 12296)])
+def test_smooth_scales_outside_the_short_division_range(M, K):
     """Smooth scales below 2^-40 or above 2^40 (and FP32 subnormals) take the full IEEE
     division; scales at the edges of the range and powers of two take the short one."""
-    _say("actquant extreme smooth scales")
-    K = 2048
+    _say(f"actquant extreme smooth scales M={M} K={K}")
     rng = np.random.default_rng(5)
-    X16 = (rng.standard_normal((5, K)) * 3).astype(np.float16)
+    X16 = (rng.standard_normal((M, K)) * 3).astype(np.float16)
     X16[1] = (rng.standard_normal(K) * 1e-4).astype(np.float16)       # FP16 subnormals among them
-    smooth = np.exp2(rng.integers(-45, 46, size=K)).astype(np.float32)
+    X16[2, ::3] = np.float16(65504.0)
+    smooth = np.exp2(rng.integers(-45, 46, size=K)).astype(np.float32)   # in and out of range within a thread's columns
     smooth[::7] *= np.float32(1.2345)
-    smooth[3] = np.float32(2.0 ** -40)
-    smooth[4] = np.float32(2.0 ** 40)
+    smooth[K // 2:] = np.exp2(rng.uniform(-40, 40, size=K - K // 2))     # ... and whole threads in range
+    smooth[3] = smooth[K - 3] = np.float32(2.0 ** -40)
+    smooth[4] = smooth[K - 4] = np.float32(2.0 ** 40)
     smooth[5] = np.float32(1e-38)      # the quotients overflow or are huge: codes saturate
     smooth[6] = np.float32(1e-44)      # FP32 subnormal
-    X16[:3, 5:7] = 0                   # tokens 0..2 stay finite; 3 and 4 overflow (unspecified codes)
+    X16[:-2, 5:7] = 0                  # all but the last two tokens stay finite; those overflow (unspecified codes)
+    X16[-2:, 5:7] = 1
     with np.errstate(over="ignore", invalid="ignore"):
         q_ref, s_ref = O.quantize_activations(X16, smooth)
     finite = np.isfinite(s_ref)
-    assert finite[:3].all() and not finite[3:].any()
+    assert finite[:-2].all() and not finite[-2:].any()
     q, s = _run(X16, smooth)
     assert np.array_equal(s.view(np.uint32)[finite], s_ref.view(np.uint32)[finite])
     assert np.array_equal(q[finite], q_ref[finite])
-    # and a moderate range, where every token stays finite and every thread takes the short division
+    assert np.isinf(s[~finite]).all()
+    # and a moderate range, where every token stays finite and every thread may take the short division
     smooth = np.exp2(rng.uniform(-12, 12, size=K)).astype(np.float32)
     q_ref, s_ref = O.quantize_activations(X16, smooth)
     q, s = _run(X16, smooth)

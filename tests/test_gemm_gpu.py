@@ -70,10 +70,10 @@ SMALL = [
     (16, 320, 768, 128),     # N not a multiple of 256
     (13, 192, 1024, 64),     # ragged M inside one fragment
     (31, 128, 512, 128),
-    (50, 192, 768, 64),      # two row fragments of the 64-row stream kernel, ragged
+    (50, 192, 768, 64),      # two row fragments of the 64-row panels, ragged
     (64, 128, 512, 128),     # exactly 64 rows
     (77, 448, 768, 64),      # ragged M over several row tiles, N tail
-    (128, 64, 512, 64),      # exactly 128 rows: four row fragments of the stream kernel
+    (128, 64, 512, 64),      # exactly 128 rows: one 128-row panel, one row tile
     (200, 256, 256, 64),     # one k unit only
     (130, 576, 1280, 128),
     (300, 320, 1792, 64),    # 14 stages of 128 k; last row tile with 44 rows, N tail
@@ -199,7 +199,7 @@ def test_workspace_is_optional_for_the_dispatcher():
     variant that names its split reports the missing workspace."""
     import torch
 
-    for M, N, K, g in [(8, 256, 2048, 64), (160, 512, 2048, 128)]:
+    for M, N, K, g in [(8, 256, 2048, 64), (160, 512, 2048, 128)]:   # a 16-row kernel with slices, a panel without
         _say(f"small workspace M={M} N={N} K={K}")
         assert api.w4a8_gemm_workspace_size(M, N, K, g) > 16
         P = H.Problem(N, K, g, seed=11)
@@ -217,6 +217,27 @@ def test_workspace_is_optional_for_the_dispatcher():
                 api.w4a8_gemm_variant(v, dX, torch.from_numpy(s_x).cuda(), P.d_packed, P.d_gparams,
                                       P.d_w_scales, N, K, g, workspace=tiny)
             assert e.value.code == -3
+
+
+@pytest.mark.parametrize("M,N,K,g,kernel", [(64, 1088, 6912, 64, "panel_f1_m32_s3"), (100, 12672, 2304, 128, "duo_m64"),
+                                            (256, 10240, 8192, 64, "duo_m128"), (256, 6144, 16384, 64, "solo16_g2_sk_m256")])
+def test_dispatcher_without_room_for_its_slices(M, N, K, g, kernel):
+    """K slices with the workspace the library asks for (twice: the tickets reset themselves), then
+    with 16 bytes and with nothing: the same accumulators."""
+    import torch
+
+    name, need = api.w4a8_describe_launch(M, N, K, g)
+    _say(f"no room for slices M={M} N={N} K={K} -> {name}, {need} bytes")
+    assert name == kernel and need > 32768
+    W = H.RandomWeights(N, K, g, seed=M)
+    X, _ = W.activations(M)
+    ref = W.product(X)
+    full = torch.zeros(api.w4a8_gemm_workspace_size(M, N, K, g), dtype=torch.uint8, device="cuda")
+    assert full.numel() >= need
+    for ws in (full, full, torch.zeros(16, dtype=torch.uint8, device="cuda"), torch.zeros(0, dtype=torch.uint8, device="cuda")):
+        ACC = api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g, workspace=ws)
+        assert torch.equal(ACC, ref), f"{ws.numel()} bytes"
+    assert not full[:32768].any()
 
 
 def test_calibration_kernels_run():
@@ -389,12 +410,15 @@ def test_hip_graph_replays_of_split_k_kernels():
     reproduce the eager result."""
     import torch
 
-    # stream16 / stream_m64 / duo_m64 / 256-row tiles with K slices and their finish kernel
-    cases = [(8, 2048, 4096, 64), (48, 4096, 2048, 64), (200, 1024, 4096, 128), (256, 6144, 16384, 128)]
+    # without slices: a 16-row kernel and panels; with K slices: 256-row tiles and their finish kernel, then with
+    # tickets a 16-row kernel, a panel, 64- and 128-row tiles
+    cases = [(8, 2048, 4096, 64, False), (48, 4096, 2048, 64, False), (200, 1024, 4096, 128, False), (256, 6144, 16384, 128, True),
+             (16, 2048, 8192, 64, True), (64, 1088, 6912, 64, True), (70, 12672, 2304, 64, True), (130, 12352, 5376, 128, True)]
     stream = torch.cuda.Stream()
-    for M, N, K, g in cases:
-        picked = api.w4a8_variant_name(api.w4a8_select_variant(M, N, K, g))
-        _say(f"graph replay M={M} N={N} K={K} -> {picked}")
+    for M, N, K, g, slices in cases:
+        picked, need = api.w4a8_describe_launch(M, N, K, g)
+        _say(f"graph replay M={M} N={N} K={K} -> {picked}, workspace {need}")
+        assert (need > 0) == slices
         P = H.Problem(N, K, g, seed=M)
         X, s_x = I.make_activations(M, K, seed=M + 1)
         X2, s_x2 = I.make_activations(M, K, seed=M + 2)
@@ -590,8 +614,8 @@ def test_k_slices_through_the_dispatcher():
                                      (2048 + 700, 8192, 4096, 64), (2048 + 512, 8192, 4096, 128)])
 def test_two_launch_plans(M, N, K, g):
     """Batches that the dispatcher runs as two launches over consecutive rows (whole rounds of
-    256 x 256 tiles, then the rest with its own kernel; the last cases rests of several row tiles, on
-    256 x 128 tiles with a ragged one and on 64-row tiles with K slices): every accumulator and every FP16 output
+    256 x 256 tiles, then the rest with its own kernel, a panel in the first three; the last cases rests of several
+    row tiles, on 256 x 128 tiles with a ragged one and on 64-row tiles): every accumulator and every FP16 output
     against the exact float64 product, through both public entry points."""
     import torch
 
@@ -611,8 +635,8 @@ def test_two_launch_plans(M, N, K, g):
 
 
 # ---------------------------------------------------------------------------------------
-# The panel forms as the dispatcher picks them: edges of their row tiles (32, 64, 128), channel
-# tiles that do not fill a block, fewer units than waves, K slices and a workspace too small for them
+# Panels through the dispatcher at small ragged sizes: few channel tiles, few units, a workspace too small
+# (one case with K slices; 511 x 3008 x 768 is beyond the panels and runs on tiles)
 # ---------------------------------------------------------------------------------------
 @pytest.mark.parametrize("M,N,K,g", [
     (17, 2112, 2304, 64), (32, 4160, 256, 128), (33, 192, 4608, 64), (63, 7232, 512, 128), (64, 1088, 6912, 64),
@@ -621,7 +645,7 @@ def test_two_launch_plans(M, N, K, g):
 def test_panel_dispatch_edges(M, N, K, g):
     import torch
 
-    _say(f"panel M={M} N={N} K={K} g={g} -> {api.w4a8_variant_name(api.w4a8_select_variant(M, N, K, g))}")
+    _say(f"panel M={M} N={N} K={K} g={g} -> {api.w4a8_describe_launch(M, N, K, g)[0]}")
     P = H.Problem(N, K, g, seed=M)
     X, s_x = I.make_activations(M, K, outlier_frac=0.01, seed=K)
     ref = torch.from_numpy(X.astype(np.float64)) @ torch.from_numpy(P.oracle_wd()[0].astype(np.float64)).t()
@@ -634,3 +658,32 @@ def test_panel_dispatch_edges(M, N, K, g):
     Y = api.w4a8_gemm(dX, dsx, P.d_packed, P.d_gparams, P.d_w_scales, N, K, g)
     H.assert_fp16_close(Y.cpu().numpy(), ref.numpy() * s_x[:, None].astype(np.float64) * P.oracle_wd()[1][None, :].astype(np.float64),
                         "panel")
+
+
+# ---------------------------------------------------------------------------------------
+# Every panel form that the dispatcher picks, with the number of K slices it picks, on a ragged last row tile and,
+# where channel tiles are grouped by three or four, a last column group that is not full
+# ---------------------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,form", [
+    (33, 192, 256, "panel_f1_m32"), (17, 64, 5632, "panel_f1_m32_s2"), (17, 64, 6912, "panel_f1_m32_s3"), (31, 64, 8192, "panel_f1_m32_s4"),
+    (33, 4224, 256, "panel_f2_m32"), (17, 5568, 13568, "panel_f2_m32_s2"), (17, 4160, 8704, "panel_f2_m32_s3"),
+    (31, 2816, 10496, "panel_f2_m32_s4"), (65, 8256, 768, "panel_f4_m32"), (17, 8320, 8448, "panel_f4_m32_s3"),
+    (33, 8256, 256, "panel_f2_m64"), (33, 6272, 11520, "panel_f2_m64_s2"), (33, 4224, 7424, "panel_f2_m64_s3"),
+    (33, 2752, 11520, "panel_f2_m64_s4"), (65, 11008, 1024, "panel_f3_m64"), (33, 8448, 7424, "panel_f3_m64_s2"),
+    (33, 6208, 14592, "panel_f3_m64_s3"), (45, 5504, 10496, "panel_f3_m64_s4"), (65, 12352, 1536, "panel_f4_m64"),
+    (33, 8256, 8448, "panel_f4_m64_s3"), (125, 5120, 8448, "panel_f4_m64_s3"), (164, 3264, 8960, "panel_f4_m64_s3"),
+    (129, 11008, 2560, "panel_f3_m128"), (193, 8320, 3072, "panel_f3_m128")])
+def test_every_dispatched_panel_form(M, N, K, form):
+    import torch
+
+    g = 64 if K % 512 else 128
+    name, need = api.w4a8_describe_launch(M, N, K, g)
+    _say(f"panel form M={M} N={N} K={K} g={g} -> {name}, {need} bytes")
+    assert name == form and (need > 0) == ("_s" in form)
+    W = H.RandomWeights(N, K, g, seed=M)
+    X, sx = W.activations(M)
+    ref = W.product(X)
+    for rep in range(2):   # (the tickets reset themselves)
+        assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g), ref), f"accumulators differ, call {rep}"
+    Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
+    H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
