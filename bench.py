@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the LiquidQuant W4A8 GEMM on one MI355X.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--details FILE]
                     [--no-curve] [--no-configs] [--no-calib] [--no-cpu]
 
 A step is one pass of the whole hot path (load packed W4 + group parameters, unpack,
@@ -9,19 +9,23 @@ LiquidQuant dequantisation, INT8 MFMA, per-token x per-channel scaling, FP16 sto
 one batch of synthetic activations, with every input already resident in HBM.  Weights
 rotate through enough distinct copies (> 512 MB in total) that the 256 MB Infinity Cache
 cannot serve them.  The headline workload is the compute-bound end of the metric's M
-range (prefill, M=4096, N=K=8192, group 64).  The same JSON line carries
+range (prefill, M=4096, N=K=8192, group 64).  The same JSON line, short enough to survive in the
+tail of a log, carries
   * roofline / roofline_hbm: the dominant kernel of the headline and of the HBM-bound
     point (70B up-projection at M=16) against the nominal peaks;
   * calibration: what this GPU reaches on a pure streaming read and on a register-only
     INT8 MFMA loop (constant and random operands);
-  * curve_N8192_K8192, curve_N4096_K4096: TOPS and fraction of the roofline for M = 1..4096;
+  * curve_N8192_K8192: [M, TOPS, fraction of the roofline] for M = 1..4096;
+  * cpu_baseline: the CPU oracle timed on a bounded sample.
+With --details FILE everything else is measured too and written there, with the above in full:
+  * curve_N4096_K4096: the same for decode-sized weights;
   * configs: every workload row (decode, 7B MLP, 70B layers, prefill sweep), median of five
     batches, with rotating weights and with one weight buffer (cache-warm) side by side;
   * activation_quant: the per-token FP16 -> INT8 quantisation kernel upstream of the GEMM;
   * ablation_pipeline, ablation_dequant, mfma_shape: the headline shape on the explicit
     producer / consumer form, with the widened dequantisation, and on the other MFMA shape;
-  * grouped_moe: mixture-of-experts layers in one grouped call vs one call per expert;
-  * cpu_baseline: the CPU oracle timed on a bounded sample.
+  * reference_w8a8_own, reference_w8a8_vendor: INT8 weights without dequantisation;
+  * grouped_moe: mixture-of-experts layers in one grouped call vs one call per expert.
 """
 from __future__ import annotations
 
@@ -46,6 +50,9 @@ ROTATE_BYTES = 512 << 20
 # the same counters read for a plain 1 GiB copy, --copy-ref) cannot be read from inside a timed
 # run: they are carried per (workload, kernel) in profiles/traffic.json, the data file the
 # summaries under profiles/ are written from, and are null for anything not profiled.
+HBM_WORKLOAD = "l70b_up_M16_N28672_K8192"   # the HBM-bound point of the result line
+
+
 def measured_traffic(workload, kernel):
     try:
         with open(os.path.join(ROOT, "profiles", "traffic.json")) as f:
@@ -389,6 +396,19 @@ def cpu_baseline(prob, M, budget_s=12.0):
     }
 
 
+def short_line(out):
+    """The result line: the contract's keys and one figure or two of each section."""
+    line = {k: v for k, v in out.items() if k not in ("configs", "activation_quant", "grouped_moe")
+            and not k.startswith(("curve_", "reference_", "ablation_", "mfma_shape"))}
+    if "curve_N8192_K8192" in out:
+        line["curve_N8192_K8192"] = [[p["M"], p["tops"], p["frac_of_roofline"]] for p in out["curve_N8192_K8192"]]
+    if "calibration" in out:
+        line["calibration"] = {k: v for k, v in out["calibration"].items() if k != "note"}
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -400,6 +420,7 @@ def main():
     ap.add_argument("--no-configs", action="store_true")
     ap.add_argument("--no-calib", action="store_true")
     ap.add_argument("--no-cpu", action="store_true")
+    ap.add_argument("--details", metavar="FILE", help="measure every section and write it to FILE as JSON")
     ap.add_argument("--copy-ref", action="store_true",
                     help="only run a plain device-to-device copy of 1 GiB five times (reference "
                          "for scaling the profiler's FETCH_SIZE / WRITE_SIZE counters)")
@@ -481,6 +502,8 @@ def main():
         rows = []
         groups = []
         for s in WL.DECODE + WL.MLP_7B + WL.LAYERS_70B + WL.PREFILL:
+            if not args.details and s.name != HBM_WORKLOAD:
+                continue
             key = (s.N, s.K, s.group, s.seed)
             if not groups or groups[-1][0] != key:
                 groups.append((key, []))
@@ -497,7 +520,7 @@ def main():
                         for M in extra_Ms]
             # the oracle beside every family of configs: a bounded row sample of its largest batch
             fam_cpu = None
-            if not args.no_cpu and p2 is not prob:
+            if args.details and not args.no_cpu and p2 is not prob:
                 fam_cpu = cpu_baseline(p2, max(s.M for s in shapes if s.M in p2.dX), budget_s=2.5)
             for s in shapes:
                 if s.M not in p2.dX:
@@ -513,7 +536,7 @@ def main():
                 del p2
                 torch.cuda.empty_cache()
         out["configs"] = rows
-        hb = next((r for r in rows if r["workload"] == "l70b_up_M16_N28672_K8192"), None)
+        hb = next((r for r in rows if r["workload"] == HBM_WORKLOAD), None)
         if hb:
             out["roofline_hbm"] = {
                 "bound": "hbm", "achieved": hb["gbs"], "peak": PEAK_HBM_GBS, "unit": "GB/s",
@@ -524,7 +547,7 @@ def main():
             if calib:
                 out["roofline_hbm"]["frac_of_measured_stream_read"] = round(hb["gbs"] / calib["stream_read_gbs"], 4)
 
-    if not args.no_configs:
+    if args.details and not args.no_configs:
         out["activation_quant"] = activation_quant_points(torch, api, WL, stream, calib)
         out["reference_w8a8_own"] = own_w8a8_reference(prob, torch, api, stream)
         # Fig. 13's pipeline comparison on this chip: the dispatcher's implicit form against the
@@ -567,7 +590,10 @@ def main():
         for r in out.get("configs", []):
             r.setdefault("cpu_oracle", out["cpu_baseline"])  # rows of the headline's own family
 
-    print(json.dumps(out), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(short_line(out)), flush=True)
 
 
 if __name__ == "__main__":
