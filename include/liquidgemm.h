@@ -175,7 +175,8 @@ int w4a8_select_variant(int M, int N, int K, int group); /* the dispatcher's cho
  * hundred on smaller tiles) runs as two launches over consecutive rows: returns the variant
  * of the first, writes its rows to *rows_first (= M when there is one launch only) and the
  * variant of the launch over the remaining rows to *variant_rest (-1 when there is none).
- * <0 on error. */
+ * Where the answer is duo_m64 or duo_m128 the dispatcher may run a panel form in its place
+ * (w4a8_describe_launch names it); w4a8_gemm_variant runs the tiles.  <0 on error. */
 int w4a8_select_plan(int M, int N, int K, int group, int *rows_first, int *variant_rest);
 
 /* What one launch (or two) of a named variant, or of the dispatcher (-1), runs for a shape when the
