@@ -9,8 +9,10 @@
 // moves half the accumulator registers per operation).  This is the solo kernel (one wave per
 // SIMD, wave tile 256 x 64, 256 accumulator registers, every dequantised operand reused by all
 // 256 rows; paper Sec. 3.2, Eq. 6: T_DQ per MMA shrinks with that reuse) with the small shape:
-//   * a k-step is one chunk of 64 k: 64 MFMAs, token fragment i / 4 (16 rows) times channel
-//     fragment i % 4 (16 channels);
+//   * a k-step is one chunk of 64 k: 64 MFMAs, token fragment i / 4 (16 rows) times the four channel
+//     fragments (16 channels), back and forth: from one MFMA to the next only one operand changes,
+//     which draws less power (register-only loop on Gaussian int8 values 4.05 / 4.12 POP/s; 4096 x 8192 x
+//     8192 188.6 / 186.6 us, 1024 x 8192 x 8192 53.6 / 52.9);
 //   * the channel operands of a chunk come from the same two 16-byte lane loads as before: the
 //     low and the high nibbles are dequantised as for the 32x32x32 order (Sec. 5.3, 7
 //     instructions per 8 codes) and one v_permlane16_swap per register regroups them into the
@@ -198,16 +200,17 @@ __device__ __forceinline__ void solo16_body(const Src &src, const int N, const i
     // other registers than its addend, and with all 256 accumulation registers taken it then
     // moves accumulators through vector registers and memory.  Nothing here reads an accumulator
     // sooner than 63 MFMAs after it was written; the epilogue waits by itself.)
+    auto chan = [](int i) /* channel fragment of slot i */ { return (i & 4) ? 3 - (i & 3) : i & 3; };
     auto mm = [&](int i, const v4i (&b)[4]) {
-        asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[i >> 2][i & 3]) : "v"(b[i & 3]), "v"(ax[(i >> 2) & 7]));
+        asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[i >> 2][chan(i)]) : "v"(b[chan(i)]), "v"(ax[(i >> 2) & 7]));
     };
     // The same with piece xi of LDS stage buf of the X prefetch behind it: the MFMA is the wait
     // state the load needs after the write of m0.
     auto mm_x = [&](int i, const v4i (&b)[4], int buf, int xi) {
         asm volatile("s_mov_b32 m0, %4\n\tv_mfma_i32_16x16x64_i8 %0, %5, %6, %0\n\tglobal_load_lds_dwordx4 %2, %3"
-                     : "+a"(acc[i >> 2][i & 3]), "+v"(wl)
+                     : "+a"(acc[i >> 2][chan(i)]), "+v"(wl)
                      : "v"(xg[xi]), "s"(ld_X + (size_t)l_e * 128), "s"(lds0 + buf * STAGE + (4 * xi + wave) * 1024),
-                       "v"(b[i & 3]), "v"(ax[(i >> 2) & 7])
+                       "v"(b[chan(i)]), "v"(ax[(i >> 2) & 7])
                      : "memory", "m0");
     };
     auto rd = [&](int buf, int c, int tf) {
