@@ -81,26 +81,33 @@ __device__ __forceinline__ float max_abs8(const float (&f)[8], float m)
 // Q = clamp(rint(f / s)) for 8 values.  The FP32 quotient is only needed to decide an integer, so
 // the common case multiplies by an approximate reciprocal, in one FMA with 1.5 * 2^23: the sum is
 // rounded to an integer, which is its low byte.  The exact product and the correctly rounded
-// quotient both lie within 127 * (2^-23 + 2^-24) < 2.3e-5 of the exact quotient (|f / s| <= 127),
-// hence they round to the same integer unless the product is within 1e-4 of a tie.  Only then
-// (about 1 lane-visit in 600; also where a value is not finite) the 8 values are redone with the
-// IEEE division, so the result is always that of the division.
+// quotient both lie within 127 * (2^-23 + 2^-24) < 2.3e-5 of the exact quotient (|f / s| <= 127,
+// reciprocal within one unit), hence they round to the same integer unless the product is within 3e-5
+// of a tie.  Only then (or where a value is not finite) that value is redone with the IEEE division,
+// so the result is always that of the division.  A wave of 512 values meets one 3 times in 100, and a small call
+// lasts as long as its slowest wave: redoing one value at a time, where it redid all 8 of the lane within
+// 1e-4 of a tie, takes 2.77 us to 2.50 on 128 x 4096, 3.55 to 3.17 on 128 x 8192, 8.3 to 7.7 on 1000 x 8192.
 __device__ __forceinline__ uint2 round8(const float (&f)[8], float s, float rcp_s)
 {
     constexpr float kMagic = 0x1.8p23f;
-    uint32_t u[8];
-    bool near_tie = false;
+    uint32_t u[8], ties = 0;  // bit e: value e needs the division
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const float t = __builtin_fmaf(f[e], rcp_s, kMagic);
         const float off = __builtin_fmaf(f[e], rcp_s, -(t - kMagic));
-        near_tie |= !(fabsf(off) <= 0.5f - 1e-4f);  // (true for NaN)
+        ties |= fabsf(off) <= 0.5f - 3e-5f ? 0u : 1u << e;  // (set for NaN)
         u[e] = __builtin_bit_cast(uint32_t, t);
     }
-    // (a branch the compiler must not turn into 8 divisions and selects for everybody)
-    if (__builtin_expect_with_probability(near_tie, 0, 0.999)) {
+    // (a branch the compiler must not turn into divisions and selects for everybody)
+    while (__builtin_expect_with_probability(ties != 0, 0, 0.999)) {
+        const uint32_t first = ties & -ties;
+        float x = f[0];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = (uint32_t)(int)fminf(fmaxf(__builtin_rintf(f[e] / s), -127.0f), 127.0f);
+        for (int e = 1; e < 8; ++e) x = first == 1u << e ? f[e] : x;
+        const uint32_t q = (uint32_t)(int)fminf(fmaxf(__builtin_rintf(x / s), -127.0f), 127.0f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = first == 1u << e ? q : u[e];
+        ties ^= first;
     }
     uint32_t w[2];
 #pragma unroll
@@ -195,24 +202,28 @@ __global__ __launch_bounds__(kLongThreads) void quantize_act_long_kernel(
 //     The loads and stores of that loop are all unconditional (past the end: the last token once
 //     more, the last piece once more with the same bytes), so that the compiler can count them and
 //     a token waits for its own loads only.
-//   Otherwise one token per block, and with gridDim.y > 1 a share of its pieces: every block of a
-//     token finds the maximum of the whole token and rounds and stores ITERS / gridDim.y of its
-//     pieces per thread.
+//   Otherwise one token per block, and with lg_shares > 0 a share of its pieces: each of the token's
+//     2^lg_shares blocks finds the maximum of the whole token and rounds and stores its part of every
+//     thread's ITERS pieces.  These blocks are 8 ids apart, on one XCD, whose L2 then fetches the
+//     token once.
 // About 10 instructions per element with smooth scales, 6 without; large calls move their bytes at
 // the rate of a copy or near it, small ones take the launch, one load and one store.
 template <bool SMOOTH, int ITERS, int NT, bool SEVERAL>
 __global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
-    int M, int K, int R, const __half *__restrict__ X, const float *__restrict__ smooth,
+    int M, int K, int R, int lg_shares, const __half *__restrict__ X, const float *__restrict__ smooth,
     int8_t *__restrict__ Q, float *__restrict__ sx)
 {
     __shared__ __attribute__((aligned(16))) float s_part[2][NT / 64];
     const int tid = threadIdx.x;
     const int n8 = K >> 3;
-    const int it_begin = ITERS * (int)blockIdx.y / (int)gridDim.y, it_end = ITERS * ((int)blockIdx.y + 1) / (int)gridDim.y;
+    const int row = (int)blockIdx.x >> 3, share = row & ((1 << lg_shares) - 1);
+    const int m_first = SEVERAL ? (int)blockIdx.x * R : (row >> lg_shares) * 8 + ((int)blockIdx.x & 7);
+    if (m_first >= M) return;  // (several shares: the grid is padded to 8 tokens)
+    const int it_begin = ITERS * share >> lg_shares, it_end = ITERS * (share + 1) >> lg_shares;
     int piece[ITERS];
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) piece[it] = min(it * NT + tid, n8 - 1);
-    const int m_begin = (int)blockIdx.x * (SEVERAL ? R : 1), m_end = SEVERAL ? min(M, m_begin + R) : m_begin + 1;
+    const int m_begin = m_first, m_end = SEVERAL ? min(M, m_begin + R) : m_begin + 1;
 
     u32x4 raw[SEVERAL ? 2 : 1][ITERS];  // this token and the next
     auto load = [&](int m, u32x4 (&r)[ITERS]) {
@@ -264,7 +275,7 @@ __global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
         if (SEVERAL) load(m + 2, r);
         amax = block_max<NT / 64>(amax, part);
         const float s = amax > 0.0f ? amax / 127.0f : 1.0f;
-        if (tid == 0 && blockIdx.y == 0) sx[m] = s;
+        if (tid == 0 && share == 0) sx[m] = s;
         const float rcp_s = __builtin_amdgcn_rcpf(s);
         uint2 *qrow = reinterpret_cast<uint2 *>(Q + (size_t)m * K);
 #pragma unroll
@@ -286,28 +297,33 @@ __global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
 
 // (lds: dynamic LDS that nothing uses, to keep fewer blocks on a CU)
 template <bool SMOOTH, int ITERS, int NT, bool SEVERAL = false>
-static void launch_rows(int M, int K, int R, int shares, const __half *X, const float *smooth, int8_t *Q, float *sx,
+static void launch_rows(int M, int K, int R, int lg_shares, const __half *X, const float *smooth, int8_t *Q, float *sx,
                         hipStream_t st, size_t lds = 0)
 {
-    hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, ITERS, NT, SEVERAL>), dim3((unsigned)((M + R - 1) / R), (unsigned)shares),
-                       dim3(NT), lds, st, M, K, R, X, smooth, Q, sx);
+    const int blocks = lg_shares ? ((M + 7) / 8 * 8) << lg_shares : (M + R - 1) / R;
+    hipLaunchKernelGGL((quantize_act_rows_kernel<SMOOTH, ITERS, NT, SEVERAL>), dim3((unsigned)blocks), dim3(NT), lds, st, M, K,
+                       R, lg_shares, X, smooth, Q, sx);
 }
 
 // Block shapes, from sweeps of threads x pieces per thread x tokens per block over M = 4..8192 and
-// K = 2048..28672 (microseconds of the rule / of blocks of 256 threads with all pieces of a token):
+// K = 2048..28672 (microseconds of the rule / of blocks of 256 threads with all pieces of a token, unless said):
 //   many tokens, no smooth scales: 256 threads up to 8192 columns (13.3 / 13.5 on 6000 x 4096, 512 threads:
 //     15.6), with three pieces each up to 6144 (11.9 on 4096 x 4104, 13.3 on 4096 x 5120; 512 threads of
 //     two pieces, nearly half of them past the end: 15.0 and 15.8) and four from there on (18.2 on 4096 x
 //     8192, 512 threads: 19.0; with 1024 tokens 7.7 and 7.5, hence from 2048 tokens), one up to 2048 columns
-//     (11.0 / 15.5 on 8192 x 2048); 512 threads above (40.2 / 43.5 on 6000 x 14336), three blocks
+//     (11.0 / 15.5 on 8192 x 2048); 768 threads of two pieces up to 12288 (36.8 on 6000 x 11008, 512 threads of
+//     three: 37.9); 512 threads above (40.2 / 43.5 on 6000 x 14336), three blocks
 //     of them on a CU instead of four where the call moves more than the memory-side cache holds (72.3 / 74.5 on
 //     8192 x 16384, 62.5 / 64.2 on 8192 x 14336; below that four are ahead, 32.9 / 33.8 on 4096 x 16384);
 //   many tokens with smooth scales: from 1024 tokens on several tokens per block, as many as leave two
 //     blocks of 1024 threads per CU (one where a thread holds two pieces: 98 registers) -- 20.1 / 26.8
 //     on 4096 x 8192 (5.0 TB/s, a copy runs at 5.2), 38 / 60 on 4096 x 16384, 9.3 / 11.2 on 1024 x 8192;
 //     with at most 2048 columns a token is too short for that (16.0 / 20.2 on 8192 x 2048);
-//   few tokens: as many threads as a token has pieces, up to 512, and with at most 128 (token, share)
-//     pairs the pieces of a thread shared out over blocks (2.0 / 3.0 on 4 x 11008, 4.0 / 5.6 on 16 x 28672).
+//   few tokens: at most two pieces per thread up to 1536 pieces of a token (45 x 5120 2.64 to 2.30, 200 x 11008
+//     4.5 to 3.9 against blocks of 512 threads) and beyond 128 tokens up to 2048 (200 x 14336 5.0 to 4.3); up to
+//     64 tokens four blocks, up to 128 two share the pieces of a token (60 x 14336 3.6 to 2.8, 128 x 11008 4.3 to
+//     3.2, 16 x 28672 3.1 to 2.9; with 200 tokens two blocks a token are as fast as one, or slower).  These times
+//     are what a call adds to a replayed graph behind a kernel that moves 24 MB; an empty kernel adds 1.7.
 template <bool SMOOTH>
 static void launch_quantize(int M, int K, const __half *X, const float *smooth, int8_t *Q, float *sx, hipStream_t st)
 {
@@ -315,26 +331,29 @@ static void launch_quantize(int M, int K, const __half *X, const float *smooth, 
     if constexpr (SMOOTH) {
         if (M >= 1024 && K > 2048 && K <= 16384) {
             const int R = (M + 511) / 512;
-            if (n8 <= 512) return launch_rows<SMOOTH, 1, 512, true>(M, K, R, 1, X, smooth, Q, sx, st);
-            if (n8 <= 1024) return launch_rows<SMOOTH, 1, 1024, true>(M, K, R, 1, X, smooth, Q, sx, st);
-            return launch_rows<SMOOTH, 2, 1024, true>(M, K, (M + 255) / 256, 1, X, smooth, Q, sx, st);
+            if (n8 <= 512) return launch_rows<SMOOTH, 1, 512, true>(M, K, R, 0, X, smooth, Q, sx, st);
+            if (n8 <= 1024) return launch_rows<SMOOTH, 1, 1024, true>(M, K, R, 0, X, smooth, Q, sx, st);
+            return launch_rows<SMOOTH, 2, 1024, true>(M, K, (M + 255) / 256, 0, X, smooth, Q, sx, st);
         }
     }
-    if (n8 <= 256) return launch_rows<SMOOTH, 1, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+    const int two = M <= 128 ? 1 : 0, four = M <= 64 ? 2 : two;  // log2 of the blocks that share a token
+    if (n8 <= 256) return launch_rows<SMOOTH, 1, 256>(M, K, 1, 0, X, smooth, Q, sx, st);
     if (n8 <= 512)
-        return M <= 512 ? launch_rows<SMOOTH, 1, 512>(M, K, 1, 1, X, smooth, Q, sx, st)
-                        : launch_rows<SMOOTH, 2, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
-    auto shares = [&](int iters) { return M * iters <= 128 ? iters : 1; };
+        return M <= 512 ? launch_rows<SMOOTH, 1, 512>(M, K, 1, 0, X, smooth, Q, sx, st)
+                        : launch_rows<SMOOTH, 2, 256>(M, K, 1, 0, X, smooth, Q, sx, st);
+    if (n8 <= 768 && (SMOOTH || (M > 128 && M <= 512))) return launch_rows<SMOOTH, 1, 768>(M, K, 1, 0, X, smooth, Q, sx, st);
     if constexpr (!SMOOTH) {
-        if (n8 <= 768 && M >= 1024) return launch_rows<SMOOTH, 3, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
-        if (n8 <= 1024 && M >= 2048) return launch_rows<SMOOTH, 4, 256>(M, K, 1, 1, X, smooth, Q, sx, st);
+        if (n8 <= 768 && M >= 1024) return launch_rows<SMOOTH, 3, 256>(M, K, 1, 0, X, smooth, Q, sx, st);
+        if (n8 <= 1024 && M >= 2048) return launch_rows<SMOOTH, 4, 256>(M, K, 1, 0, X, smooth, Q, sx, st);
         if (n8 > 1536 && n8 <= 2048 && (size_t)M * K >= (96u << 20))
-            return launch_rows<SMOOTH, 4, 512>(M, K, 1, 1, X, smooth, Q, sx, st, 48 * 1024);
+            return launch_rows<SMOOTH, 4, 512>(M, K, 1, 0, X, smooth, Q, sx, st, 48 * 1024);
     }
-    if (n8 <= 1024) return launch_rows<SMOOTH, 2, 512>(M, K, 1, shares(2), X, smooth, Q, sx, st);
-    if (n8 <= 1536) return launch_rows<SMOOTH, 3, 512>(M, K, 1, shares(3), X, smooth, Q, sx, st);
-    if (n8 <= 2048) return launch_rows<SMOOTH, 4, 512>(M, K, 1, shares(4), X, smooth, Q, sx, st);
-    if (n8 <= 4096) return launch_rows<SMOOTH, 4, 1024>(M, K, 1, shares(4), X, smooth, Q, sx, st);
+    if (n8 <= 1024) return launch_rows<SMOOTH, 2, 512>(M, K, 1, two, X, smooth, Q, sx, st);
+    if (n8 <= 1536) return launch_rows<SMOOTH, 2, 768>(M, K, 1, two, X, smooth, Q, sx, st);
+    if (n8 <= 2048)
+        return M > 128 && (SMOOTH || M <= 512) ? launch_rows<SMOOTH, 2, 1024>(M, K, 1, 0, X, smooth, Q, sx, st)
+                                               : launch_rows<SMOOTH, 4, 512>(M, K, 1, four, X, smooth, Q, sx, st);
+    if (n8 <= 4096) return launch_rows<SMOOTH, 4, 1024>(M, K, 1, four, X, smooth, Q, sx, st);
     hipLaunchKernelGGL((quantize_act_long_kernel<SMOOTH>), dim3((unsigned)M), dim3(kLongThreads), 0, st, K, X, smooth, Q, sx);
 }
 

@@ -65,8 +65,8 @@ def test_several_tokens_per_block(M, K):
     assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
 
 
-# the block shapes change at these columns (pieces of 8 per thread and threads per token), with 1024
-# tokens (several per block) and with 128 (token, share) pairs (a token's pieces shared between blocks)
+# the block shapes change at these columns (pieces of 8 per thread and threads per token) and with 1024
+# tokens (several per block)
 @pytest.mark.parametrize("K", [2040, 2056, 4096, 4104, 8192, 8200, 12296, 16384, 16392, 32768])
 @pytest.mark.parametrize("M", [1, 32, 43, 65, 513])
 @pytest.mark.parametrize("with_smooth", [False, True])
@@ -74,6 +74,25 @@ def test_edges_of_the_block_shapes(M, K, with_smooth):
     _say(f"actquant block shapes M={M} K={K} smooth={with_smooth}")
     X16 = WL.make_activations_f16(M, K, outlier_frac=0.001, seed=M * 7 + K)
     smooth = WL.make_smooth(K, seed=K + 2) if with_smooth else None
+    q_ref, s_ref = O.quantize_activations(X16, smooth)
+    q, s = _run(X16, smooth)
+    assert np.array_equal(s.view(np.uint32), s_ref.view(np.uint32)), "per-token scales differ"
+    assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
+
+
+# four blocks share a token up to 64 tokens, two up to 128 (in grids padded to 8 tokens); 768 threads from 4104 to
+# 6144 and from 8200 to 12288 columns, 1024 threads of two pieces up to 16384; the outlier channels put most
+# values of a token near few integers, the values +-k/2 of the first columns on and next to ties of scale 1
+@pytest.mark.parametrize("K", [4104, 6144, 6152, 8200, 12288, 16384, 28680])
+@pytest.mark.parametrize("M", [9, 64, 65, 128, 129, 512])
+@pytest.mark.parametrize("with_smooth", [False, True])
+def test_edges_of_shared_tokens(M, K, with_smooth):
+    _say(f"actquant shared tokens M={M} K={K} smooth={with_smooth}")
+    X16 = WL.make_activations_f16(M, K, outlier_frac=0.001, seed=M * 3 + K)
+    ties = (np.arange(1024) % 255 - 127).astype(np.float16) / 2
+    X16[:, :1024] = ties
+    X16[0::2, 1] = 127.0
+    smooth = np.ones(K, dtype=np.float32) if with_smooth else None
     q_ref, s_ref = O.quantize_activations(X16, smooth)
     q, s = _run(X16, smooth)
     assert np.array_equal(s.view(np.uint32), s_ref.view(np.uint32)), "per-token scales differ"
