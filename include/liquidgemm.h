@@ -194,7 +194,7 @@ int w4a8_dequant_dump(const void *W_packed, const uint8_t *gparams, int N, int K
 
 /* ------------------------------------------------------------------------------------
  * Grouped GEMM (device; mixture-of-experts layers, Sec. 7.3): E independent W4A8 GEMMs that
- * share N, K and group, over disjoint runs of tokens, in at most four kernel launches.
+ * share N, K and group, over disjoint runs of tokens, in at most five kernel launches.
  * ------------------------------------------------------------------------------------ */
 
 /*   row_offsets host [E+1], row_offsets[0] = 0, non-decreasing: expert e owns rows

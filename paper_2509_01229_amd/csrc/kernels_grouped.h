@@ -115,9 +115,9 @@ __global__ __launch_bounds__(256, 2) void w4a8_duo_dl_grouped_kernel(const Group
         duo_dl_tile<G128, 4>(pl, bm, bn, M, N, K, X, sx, Wp, gp, sw, Y, ACC, nullptr);
 }
 
-// The 256 x 256 tiles (one wave per SIMD, see kernels_tiled_solo.h) of all experts of a launch as
-// one persistent stream: resident blocks walk the tiles of every expert, prefetching across the
-// boundaries between them.  block_end counts 256 x 256 tiles here.
+// The 256-row tiles (one wave per SIMD, see kernels_tiled_solo16.h) of all experts of a launch as
+// one persistent stream: resident blocks walk the tiles of every expert, with 256 x 256 tiles (KG = 1)
+// prefetching across the boundaries between them.  block_end counts 256 x 256 / KG tiles here.
 struct SoloGrouped {
     const GroupTable &g;
     const GroupedPtrs &p;
@@ -146,8 +146,9 @@ struct SoloGrouped {
                         p.ACC ? p.ACC + (size_t)r0 * N : nullptr};
     }
 };
-template <bool G128>
+template <bool G128, int KG>
 __global__ __launch_bounds__(256, 1) void w4a8_solo_grouped_kernel(const GroupTable g, const GroupedPtrs p, int N, int K)
 {
-    solo16_body<G128, 1>(SoloGrouped{g, p, N, K, (N + 255) / 256}, N, K);
+    constexpr int TN = 256 / KG;
+    solo16_body<G128, KG>(SoloGrouped{g, p, N, K, (N + TN - 1) / TN}, N, K);
 }

@@ -1107,6 +1107,92 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
                           : go(&w4a8_panel_grouped_kernel<F, MF, false, false>);
 }
 
+// Up to 128 rows of each expert (experts of 33 to 128 rows, and what larger ones leave over): 32-row
+// panels, 64-row panels of 128 channels or tiles, whichever a fitted cost (us) finds cheapest.  Fitted
+// to 8 to 128 rows of 1 to 16 experts on five weight shapes (2816 x 2048 to 4096 x 14336), 4 to 8 % rms;
+// the choice is 0.8 % behind the best of the three (geometric mean; 15 % at worst), tiles alone 37 %: a few
+// experts are few tiles, and the tiles of a grouped launch have no K slices across blocks (us on tiles / as
+// picked: one expert of 8..128 rows on 4096 x 14336 51 / 20, four of 64 rows 53 / 32, eight 71 / 51, two of 64
+// on 14336 x 4096 24 / 20; eight of 64 there stay on tiles, 59 against 69).
+static double grouped_panel_us(const GroupTable &t, int N, int K, int F, int MF)
+{
+    long long blocks = 0;
+    for (int i = 0; i < t.count; ++i) blocks += panel_blocks(t.rows[i], N, F, MF);
+    const double fill = (double)blocks / kAssumedCUs, rounds = 0.5 * (std::ceil(fill) + std::max(fill, 1.0));
+    const double k = K / 1024.0, mb = 0.5e-6 * N * K * t.count;
+    return MF == 1 ? 7.11 + rounds * (0.21 + 0.864 * k) - 0.306 * std::min(fill, 1.0) * k + 0.0683 * mb
+                   : 3.05 + rounds * (5.50 + 1.605 * k) - 0.071 * std::min(fill, 1.0) * k + 0.0784 * mb;
+}
+// ... as 128- or 64-row tiles, also of experts of more rows (the last line: the rounds of a single GEMM, 6 % off
+// on 264 to 3584 tiles with K from 2048 to 14336)
+static double grouped_tiles_us(const GroupTable &t, int N, int K)
+{
+    long long tiles[2] = {0, 0}, b64 = 0;  // 128-row tiles with up to 64 and with more rows; 64-row tiles
+    const int bn = (N + 255) / 256;
+    bool few_rows = true;
+    for (int i = 0; i < t.count; ++i) {
+        const int last = t.rows[i] % 128;
+        tiles[1] += (long long)(t.rows[i] / 128 + (last > 64)) * bn;
+        tiles[0] += last > 0 && last <= 64 ? bn : 0;
+        b64 += (long long)((t.rows[i] + 63) / 64) * bn;
+        few_rows = few_rows && t.rows[i] <= 128;
+    }
+    if (b64 <= kAssumedCUs) tiles[0] = b64, tiles[1] = 0;
+    const long long all = tiles[0] + tiles[1];
+    const double k = K / 1024.0, mb = 0.5e-6 * N * K * t.count;
+    if (all <= kAssumedCUs || few_rows)
+        return 8.24 + k * (all <= kAssumedCUs ? 2.365 : 5.378) + k * (2.033 * tiles[0] + 4.451 * tiles[1]) / kAssumedCUs + 0.061 * mb;
+    return 9 + 0.95 * 64.0 * K / 8192 * tiled_costs(all, 0, 0, K, true).duo;
+}
+static double grouped_few_rows_us(const GroupTable &t, int N, int K)
+{
+    return t.count == 0 ? 0.0 : std::min({grouped_panel_us(t, N, K, 2, 1), grouped_panel_us(t, N, K, 4, 2), grouped_tiles_us(t, N, K)});
+}
+// (t: every entry at most 128 rows; mid: entries of at most 32 rows, which run as 32-row panels, in the
+// same launch where t does too; either may be empty)
+static int grouped_few_rows_run(const GroupedArgs &a, GroupTable &t, GroupTable &mid)
+{
+    int most = 0;
+    for (int i = 0; i < t.count; ++i) most = std::max(most, t.rows[i]);
+    const double p32 = grouped_panel_us(t, a.N, a.K, 2, 1), p64 = grouped_panel_us(t, a.N, a.K, 4, 2);
+    const double tiles = 0.95 * grouped_tiles_us(t, a.N, a.K);  // (panels have to win by 5 %, the fit is no better)
+    const bool as_p32 = most <= 32 || (p32 <= p64 && p32 <= tiles);
+    for (int i = 0; as_p32 && i < t.count; ++i) {
+        const int k = mid.count++;
+        mid.expert[k] = t.expert[i], mid.row_off[k] = t.row_off[i], mid.rows[k] = t.rows[i];
+    }
+    if (mid.count)
+        if (int rc = grouped_panel_run<2, 1>(a, mid)) return rc;
+    if (as_p32) return LQ_OK;
+    return p64 <= tiles ? grouped_panel_run<4, 2>(a, t) : grouped_tiles_run(a, t);
+}
+
+// 256 x 256 / KG tiles of the one-wave-per-SIMD kernel, all entries of the table in one launch
+template <int KG>
+static int grouped_solo_run(const GroupedArgs &a, const GroupTable &t)
+{
+    const dim3 grid((unsigned)std::min(t.block_end[t.count - 1], std::max(cu_count(), 1)));
+    const size_t lds = 4 * (size_t)256 * 128 + 4 * 1024;
+    return a.group == 128 ? launch_checked("grouped solo", w4a8_solo_grouped_kernel<true, KG>, grid, dim3(256), lds, a.stream,
+                                           t, a.p, a.N, a.K)
+                          : launch_checked("grouped solo", w4a8_solo_grouped_kernel<false, KG>, grid, dim3(256), lds, a.stream,
+                                           t, a.p, a.N, a.K);
+}
+// The larger experts' row blocks of 256: time (us) of 256 x 256 and of 256 x 128 tiles, from 65
+// calls on five weight shapes (2816 x 2048 to 4096 x 14336; 4 to 64 row blocks).  A round that leaves CUs
+// idle takes 62 % of a full one plus its part of the rest (the others clock higher): 1.06 rounds of 256 x 256
+// tiles with K = 14336 took 275 us, 1.5 rounds 287, two 323.  Hence the rows that fill whole rounds go to
+// 256 x 256 tiles, a last round of up to about half to 256 x 128 tiles: 24 row blocks on 4096 x 14336
+// 274 us (287 on 256 x 256 tiles alone, 281 on 256 x 128, 347 on 128-row tiles), 20 on 14336 x 4096 226 / 237 / 263
+// / 259, 16 of 256 rows on 8192 x 5120 128 on 256 x 256 tiles / 152 / 143, eight of 129..256 on 4096 x 14336 92 on
+// 256 x 128 / 124 / 110.
+static double rounds_us(long long tiles, double round)
+{
+    const double part = (double)(tiles % kAssumedCUs) / kAssumedCUs;
+    return round * ((double)(tiles / kAssumedCUs) + (part > 0 ? 0.62 + 0.30 * part : 0.0));
+}
+static double grouped_solo_us(long long t256, int K) { return t256 ? 6 + rounds_us(t256, 6 + 11.1 * K / 1024) : 0.0; }
+static double grouped_g2_us(long long t2, int K) { return t2 ? 3 + rounds_us(t2, 9 + 5.8 * K / 1024) : 0.0; }
 static int grouped_run(const GroupedArgs &a)
 {
     // Up to 32 rows: as one launch of 32-row panels if any expert has more than 16 rows or K is long (8
@@ -1167,48 +1253,71 @@ static int grouped_run(const GroupedArgs &a)
                                        lds, a.stream, small, a.p, a.N, a.K, groups);
         if (rc) return rc;
     }
-    if (mid.count) {
+    if (mid.count && (panel64 || !big.count)) {
         const int rc = panel64 ? grouped_panel_run<4, 2>(a, mid) : grouped_panel_run<2, 1>(a, mid);
         if (rc) return rc;
     }
     if (!big.count) return LQ_OK;
-    // The larger experts: whole 256-row blocks of them (and a last block of more than 128 rows) as
-    // 256 x 256 tiles of the one-wave-per-SIMD kernel, one persistent launch over all experts, where
-    // those tiles pay; what is left of each expert (at most 128 rows) and everything else as 128- or
-    // 64-row tiles in a launch of their own.
-    const int blocks_n = (a.N + 255) / 256;
-    GroupTable main{}, rest{};
-    long long main_t128 = 0, main_t256 = 0;
+    // The larger experts: whole 256-row blocks of them (and a last block of more than 128 rows) on the
+    // one-wave-per-SIMD tiles where these pay, what is left of each expert (at most 128 rows) as panels
+    // or tiles in a launch of its own; everything on 128- or 64-row tiles otherwise.
+    const int blocks_n = (a.N + 255) / 256, blocks_n2 = (a.N + 127) / 128;
+    GroupTable rest{};
+    long long row_blocks = 0, main_t128 = 0;
     bool fits = a.N <= (1 << 26);
     for (int i = 0; i < big.count; ++i) {
         const int rows = big.rows[i], tail = rows % 256;
         const int rows_rest = tail > 0 && tail <= 128 ? tail : 0, rows_main = rows - rows_rest;
         fits = fits && (long long)rows * a.K < (1ll << 32);
-        if (rows_main) {
-            const int k = main.count++;
-            main.expert[k] = big.expert[i], main.row_off[k] = big.row_off[i], main.rows[k] = rows_main;
-            main_t128 += (long long)((rows_main + 127) / 128) * blocks_n;
-            main_t256 += (long long)((rows_main + 255) / 256) * blocks_n;
-            if (main_t256 > 0x7fffffff) return fail(LQ_ERR_INVALID, "grouped GEMM too large for one launch");
-            main.block_end[k] = (int)main_t256;
-        }
+        row_blocks += (rows_main + 255) / 256;
+        main_t128 += (long long)((rows_main + 127) / 128) * blocks_n;
+        if (row_blocks * blocks_n > 0x7fffffff) return fail(LQ_ERR_INVALID, "grouped GEMM too large for one launch");
         if (rows_rest) {
             const int k = rest.count++;
             rest.expert[k] = big.expert[i], rest.row_off[k] = big.row_off[i] + rows_main, rest.rows[k] = rows_rest;
         }
     }
-    if (main.count && fits && solo_form_for(main_t128, main_t256, 0, a.K) == 1) {
-        const int cus = cu_count();
-        const dim3 grid((unsigned)std::min<long long>(main_t256, std::max(cus, 1)));
-        const size_t lds = 4 * (size_t)256 * 128 + 4 * 1024;
-        const int rc = g128 ? launch_checked("grouped solo", w4a8_solo_grouped_kernel<true>, grid, dim3(256), lds,
-                                             a.stream, main, a.p, a.N, a.K)
-                            : launch_checked("grouped solo", w4a8_solo_grouped_kernel<false>, grid, dim3(256), lds,
-                                             a.stream, main, a.p, a.N, a.K);
-        if (rc) return rc;
-        return rest.count ? grouped_tiles_run(a, rest) : LQ_OK;
+    if (row_blocks == 0) return grouped_few_rows_run(a, rest, mid);
+    long long first = -1;  // row blocks on 256 x 256 tiles; the others on 256 x 128
+    // (the estimates are good to about 5 %: what the rule of single GEMMs picks has to lose by that)
+    const double rest_us = grouped_few_rows_us(rest, a.N, a.K);
+    const bool solo_by_rule = solo_form_for(main_t128, row_blocks * blocks_n, 0, a.K) == 1;
+    double us = grouped_tiles_us(big, a.N, a.K) * (solo_by_rule && fits ? 1.0 : 0.95);
+    const long long rounds = row_blocks * blocks_n / kAssumedCUs;
+    for (const long long rb : {0ll, (rounds - 1) * kAssumedCUs / blocks_n, rounds * kAssumedCUs / blocks_n, row_blocks}) {
+        if (!fits || rb < 0 || (row_blocks - rb) * blocks_n2 > 0x7fffffff) continue;
+        const double t = grouped_solo_us(rb * blocks_n, a.K) + grouped_g2_us((row_blocks - rb) * blocks_n2, a.K) + rest_us;
+        const double biased = solo_by_rule && rb == row_blocks ? 0.95 * t : t;
+        if (biased < us) us = biased, first = rb;
     }
-    return grouped_tiles_run(a, big);
+    if (first < 0) {
+        if (mid.count)
+            if (int rc = grouped_panel_run<2, 1>(a, mid)) return rc;
+        return grouped_tiles_run(a, big);
+    }
+    GroupTable solo{}, g2{};
+    long long left = first;
+    int solo_tiles = 0, g2_tiles = 0;
+    for (int i = 0; i < big.count; ++i) {
+        const int tail = big.rows[i] % 256, rows_main = big.rows[i] - (tail <= 128 ? tail : 0);
+        const int rb = (rows_main + 255) / 256, rb1 = (int)std::min<long long>(rb, left), rows1 = std::min(rows_main, 256 * rb1);
+        left -= rb1;
+        if (rows1) {
+            const int k = solo.count++;
+            solo.expert[k] = big.expert[i], solo.row_off[k] = big.row_off[i], solo.rows[k] = rows1;
+            solo.block_end[k] = solo_tiles += rb1 * blocks_n;
+        }
+        if (rows1 < rows_main) {
+            const int k = g2.count++;
+            g2.expert[k] = big.expert[i], g2.row_off[k] = big.row_off[i] + rows1, g2.rows[k] = rows_main - rows1;
+            g2.block_end[k] = g2_tiles += (rb - rb1) * blocks_n2;
+        }
+    }
+    if (solo.count)
+        if (int rc = grouped_solo_run<1>(a, solo)) return rc;
+    if (g2.count)
+        if (int rc = grouped_solo_run<2>(a, g2)) return rc;
+    return rest.count || mid.count ? grouped_few_rows_run(a, rest, mid) : LQ_OK;
 }
 
 // ------------------------------------------------------------------------------------

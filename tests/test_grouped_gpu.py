@@ -207,6 +207,39 @@ def test_panel_groups(E, N, K, g, rows):
     Experts(E, N, K, g, seed=K).check(rows, seed=N, what=f"rows {rows}")
 
 
+@pytest.mark.parametrize("N,K,g,rows", [
+    # 24 row blocks: 16 on 256 x 256 tiles, 8 on 256 x 128; the rests of 1 and 120 rows join the expert of 20 as panels
+    (4096, 4096, 64, [1500, 20, 1537, 1400, 1700]),
+    (4096, 4864, 128, [1000, 900]),                # 256 x 128 tiles alone, K % 512 == 256
+    (4096, 4096, 64, [100, 12, 97, 128, 65]),      # 64-row panels of two row tiles, the smallest expert on 32-row panels
+    (8192, 1024, 128, [100, 97, 128, 66, 90, 100, 3, 120, 113]),   # tiles, and the smallest expert on panels
+])
+def test_row_blocks_and_rests(N, K, g, rows):
+    """Larger experts as two kinds of 256-row tiles and what they leave over, against the float64 product
+    (exact: |ACC| < 2^53) of the weights that the layout hook dequantises."""
+    import torch
+
+    _say(f"grouped row blocks N={N} K={K} g={g} rows={rows}")
+    E = len(rows)
+    cb, gb = api.liquidquant_packed_size(N, K, g)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    codes = torch.randint(0, 256, (cb * E,), dtype=torch.uint8, device="cuda", generator=gen)
+    pairs = [torch.randint(lo, hi, (gb // 2 * E,), device="cuda", generator=gen) for lo, hi in ((1, 17), (0, 16))]
+    gparams = torch.stack(pairs, 1).to(torch.uint8).reshape(-1).contiguous()   # code * s + a <= 255
+    scales = torch.rand((E, N), device="cuda", generator=gen)
+    offsets = [0] + [int(v) for v in np.cumsum(rows)]
+    X = torch.randint(-127, 128, (offsets[-1], K), dtype=torch.int8, device="cuda", generator=gen)
+    sx = torch.rand(offsets[-1], device="cuda", generator=gen) * 1e-3
+    Y, ACC = api.w4a8_grouped_gemm(offsets, X, sx, codes, gparams, scales, N, K, g, want_y=True, want_acc=True)
+    for e in range(E):
+        lo, hi = offsets[e], offsets[e + 1]
+        Wd = api.w4a8_dequant_dump(codes[e * cb:(e + 1) * cb].clone(), gparams[e * gb:(e + 1) * gb].clone(), N, K, g)
+        ref = X[lo:hi].double() @ Wd.double().t()
+        assert torch.equal(ACC[lo:hi].double(), ref), f"expert {e}"
+        ref = ref * sx[lo:hi, None].double() * scales[e].double()
+        H.assert_fp16_close(Y[lo:hi].cpu().numpy(), ref.cpu().numpy(), f"expert {e}")
+
+
 @pytest.mark.parametrize("E,N,K,g,rows", [
     (64, 192, 256, 64, [(7 * e) % 33 for e in range(64)]),       # the whole table: panels of up to 32 rows
     (64, 192, 512, 128, [5 + (11 * e) % 60 for e in range(64)]),  # ... 33..64 rows: one or two row tiles an expert
