@@ -5,32 +5,40 @@
 // ------------------------------------------------------------------------------------
 // A block owns 32 MF rows x F tiles (32 F channels) of the output and one of S slices of K; its
 // NW waves take the slice's units of 128 k round-robin, so a wave shares nothing with the others
-// until the end: no barrier in the loop, and the registers of the whole CU hold loads in flight
-// (128 KB with F = 4, MF = 2).  Loading further ahead gained nothing (one to four units, F = 1).  Shader
-// counters: on 256 x 8192 x 8192 (F = 4, MF = 2, 256 blocks) vector and matrix instructions add up to
-// 37.6 of the 51.3 thousand cycles that the two waves of a SIMD live, on 45 x 13824 x 5120 (F = 2, MF = 2, 216
-// blocks) 12.8 of 25.6; the waves wait for loads 31 and 37 % of their time, at 21 and 16 bytes per
-// cycle and CU (L2 answers in 390 and 480 cycles).  So no one unit is the bound: the dequantisation of W
-// for few rows and the latency of X and W both are, hence forms from 1 x 1 to 4 x 4 accumulator tiles, which
-// trade the volume of X and the repeated dequantisation against the sum over the waves at
-// the end (0.6 us per tile) and the number of blocks.  Starting every column group at another
-// unit takes 1 to 3 us off large batches (35.8 to 32.9 us on 256 x 10240 x 8192): rows are a power of
-// two apart, and the blocks of an XCD would all ask the same channels of its L2.
-// Measured with the dispatcher's choice, before and after, in us: 45 x 13824 x 5120 17.4 / 14.2,
-// 45 x 5120 x 13824 20.8 / 16.1, 128 x 11008 x 4096 18.5 / 15.2, 128 x 4096 x 11008 21.2 / 15.8,
-// 256 x 8192 x 8192 30.6 / 27.2, 24 x 10240 x 8192 17.1 / 13.6.
+// until the end: no barrier in the loop.  No one unit of the CU is the bound: built without its loads the kernel
+// takes 20.6 us on 256 x 8192 x 8192 (of 26.5; F = 4, MF = 2), without dequantisation and MFMA 22.5, and 10.2 and
+// 12.5 of 13.7 on 45 x 13824 x 5120 (F = 2, MF = 2) -- the dequantisation of W for few rows, the way of X and W from
+// L2 (64 KB per us and CU, what a CU draws from beyond its L2) and 5 to 7 us of launch, first loads and sum, which
+// do not depend on K; hence forms from 1 x 1 to 4 x 4 accumulator tiles, which trade the volume of X and the
+// repeated dequantisation against the sum over the waves and the number of blocks.  Two things keep the loads ahead:
+//   * W sits in two sets of registers: a unit's is loaded while the unit two before it is computed, as the
+//     registers of that one are used up;
+//   * X goes straight into LDS, into the half of the wave's region that the unit before the last has left, a
+//     whole unit ahead.
+// Starting every column group at another unit takes 1 to 3 us off large batches (35.8 to 32.9 us on 256 x 10240 x
+// 8192): rows are a power of two apart, and the blocks of an XCD would all ask the same channels of its L2.
+// The waves add their accumulators to the block's sums in LDS, each when it is through.  Measured against one set
+// of W registers (loaded for the next unit), X through registers and a sum of eight copies in LDS, in us: 45 x 5120 x
+// 5120 9.5 / 9.0, 45 x 13824 x 5120 13.7 / 13.0, 128 x 4096 x 11008 16.7 / 15.7, 24 x 8192 x 4096 8.7 / 8.1, 64 x 28672
+// x 8192 33.1 / 30.5; 128 x 11008 x 4096 and 256 x 8192 x 8192 (row tiles share W) equal to 1 %.
+// The code is written out per position of a unit (first of an odd count, pair in the loop, last two): a load that
+// may or may not have been issued would make the compiler wait for all of them.
 //
-// X goes through a region of LDS that belongs to the wave: a load covers 8 whole rows (8 cache
-// lines per KiB instead of the 32 of a fragment load).  Load i (i = 0 .. 4 MF - 1) fills the 1 KiB
-// piece i of the region in lane order; lane p brings row 8 i + r, 16-byte column c with
+// X: a load covers 8 whole rows (8 cache lines per KiB instead of the 32 of a fragment load).  Load i (i = 0 .. 4
+// MF - 1) fills the 1 KiB piece i of the region in lane order; lane p brings row 8 i + r, 16-byte column c with
 // r = (p >> 3) ^ (i & 1), c = (p & 7) ^ r.  Fragment row j' = 32 mf + j is then found in piece j' >> 3
-// at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): neither the stores nor the fragment reads
-// meet bank conflicts (the counter says 0 for both shapes above).
+// at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): the fragment reads meet no bank conflicts (counted).
 // ------------------------------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t buf_t;
 __device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+
+constexpr bool panel_sums_apart(int F, int NW, int MF) { return (2 * NW + F) * MF * 4096 <= 160 * 1024; }
+constexpr size_t panel_lds_bytes(int F, int NW, int MF)
+{
+    return (size_t)(2 * NW + (panel_sums_apart(F, NW, MF) ? F : 0)) * MF * 4096;
 }
 
 // ONCE = the weights are read by one row tile only (M <= 32 MF): loaded without keeping them in the
@@ -47,8 +55,7 @@ __device__ __forceinline__ void panel_block(
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials, int tile_group)
 {
-    extern __shared__ __attribute__((aligned(16))) int8_t panel_lds[];  // the waves' X regions, then the reduction
-    __shared__ int s_last;
+    extern __shared__ __attribute__((aligned(16))) int8_t panel_lds[];  // the waves' X regions and the block's sums
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int j = lane & 31, kb = lane >> 5;
@@ -66,10 +73,14 @@ __device__ __forceinline__ void panel_block(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[f][mf][r] = 0;
 
-    int8_t *const xregion = panel_lds + wave * (MF * 4096);
+    // X of two units in the wave's region; the sums behind all regions where there is room
+    constexpr bool kSumsApart = panel_sums_apart(F, NW, MF);
+    int8_t *const xregion = panel_lds + wave * (2 * MF * 4096);
+    int *const block_sums = reinterpret_cast<int *>(panel_lds + (kSumsApart ? 2 * NW * MF * 4096 : 0));  // [F][MF][register][lane]
     const int8_t *const xfrag = xregion + (j >> 3) * 1024 + 128 * ((j & 7) ^ ((j >> 3) & 1));
+    const uint32_t xlds = (uint32_t)(size_t)(__attribute__((address_space(3))) void *)xregion;
     const int rows = min(32 * MF, M - m0);
-    const buf_t xbuf = make_buf(X + (size_t)m0 * K, (uint32_t)rows * (uint32_t)K);
+    const int8_t *const xbase = X + (size_t)m0 * K;
     uint32_t xoff[4 * MF];
 #pragma unroll
     for (int i = 0; i < 4 * MF; ++i) {
@@ -82,60 +93,33 @@ __device__ __forceinline__ void panel_block(
     const buf_t pbuf = make_buf(gp + (size_t)t0 * units * PB, (uint32_t)nf * (uint32_t)units * PB);
     const uint32_t wl = lane * 16, pofl = j * (PB / 32);
 
-    u32x4 xr[4 * MF], wr[F][2];
-    uint32_t pr[F];
-    auto load_x = [&](int u) {
+    u32x4 wr[2][F][2];  // [parity of the unit]
+    uint32_t pr[2][F];
+    // X of unit u straight into half `par` of the wave's region
+    auto load_x = [&](int u, int par) {
 #pragma unroll
-        for (int i = 0; i < 4 * MF; ++i) xr[i] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, xoff[i], u * 128, 0);
+        for (int i = 0; i < 4 * MF; ++i)
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                         :
+                         : "v"(xoff[i]), "s"(xbase + (size_t)u * 128), "s"(xlds + par * (MF * 4096) + i * 1024)
+                         : "memory", "m0");
     };
-    auto load_w = [&](int u, int f, int c) {
-        wr[f][c] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, wl + 1024 * c, (min(f, nf - 1) * units + u) * 2048, ONCE ? 2 : 0);
+    // (off: the lane's offset, or kNoLoad: a load past the end of the buffer, which asks memory for nothing)
+    constexpr uint32_t kNoLoad = 1u << 30;
+    auto load_w = [&](int u, int par, int f, int c, uint32_t off) {
+        wr[par][f][c] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, off + 1024 * c, (min(f, nf - 1) * units + u) * 2048, ONCE ? 2 : 0);
     };
-    auto load_p = [&](int u, int f) {
+    auto load_p = [&](int u, int par, int f, uint32_t off) {
         const int po = (min(f, nf - 1) * units + u) * PB;
-        pr[f] = G128 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pbuf, pofl, po, 0)
-                     : __builtin_amdgcn_raw_buffer_load_b32(pbuf, pofl, po, 0);
+        pr[par][f] = G128 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pbuf, off, po, 0)
+                          : __builtin_amdgcn_raw_buffer_load_b32(pbuf, off, po, 0);
     };
-    // One unit in 4 F steps of one k-step (32 k) and tile each: the B operand of the next step is
-    // dequantised and, at the first tile of a k-step, the X fragments of the next k-step are read
-    // while the MFMAs of this one run.  MORE: the registers are loaded again, from unit `next`, as
-    // soon as they are used up.
-    auto unit = [&](auto more_tag, int next) {
-        constexpr bool MORE = decltype(more_tag)::value;
-        v4i a[2][MF], b[2];
-        uint32_t s2[F], a4[F];
-        auto read_a = [&](int t, v4i (&to)[MF]) {
+    auto load_unit_w = [&](int u, int par, uint32_t w_off, uint32_t p_off) {
 #pragma unroll
-            for (int mf = 0; mf < MF; ++mf)
-                to[mf] = *reinterpret_cast<const v4i *>(xfrag + mf * 4096 + 16 * ((2 * t + kb) ^ (j & 7)));
-        };
-        auto build = [&](int t, int f, v4i &to) {
-            if (G128 ? t == 0 : (t & 1) == 0) {
-                UnitParams<G128> p;
-                p.raw = pr[f];
-                p.get(t >> 1, s2[f], a4[f]);
-            }
-            dequant_half(wr[f][t >> 1], s2[f], a4[f], t & 1, to);
-        };
+        for (int f = 0; f < F; ++f) load_p(u, par, f, p_off), load_w(u, par, f, 0, w_off);
 #pragma unroll
-        for (int i = 0; i < 4 * MF; ++i) *reinterpret_cast<u32x4 *>(xregion + i * 1024 + 16 * lane) = xr[i];
-        if (MORE) load_x(next);
-        read_a(0, a[0]);
-        build(0, 0, b[0]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int st = 0; st < 4 * F; ++st) {
-            const int t = st / F, f = st % F;
-            if (f == 0 && t < 3) read_a(t + 1, a[(t + 1) & 1]);
-            if (st + 1 < 4 * F) build((st + 1) / F, (st + 1) % F, b[(st + 1) & 1]);
-            if (MORE && (t & 1)) load_w(next, f, t >> 1);  // (the B operand of this step was their last use)
-            if (MORE && t == 3) load_p(next, f);
-#pragma unroll
-            for (int mf = 0; mf < MF; ++mf) acc[f][mf] = mfma_i8(a[t & 1][mf], b[st & 1], acc[f][mf]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int f = 0; f < F; ++f) load_w(u, par, f, 1, w_off);
     };
-
     // the scales that this thread's outputs need, fetched before its last unit
     constexpr int ITEMS = MF * 4 * 64, PER = (ITEMS + NW * 64 - 1) / (NW * 64);
     float pre_sx[PER][4], pre_sw[F];
@@ -147,57 +131,153 @@ __device__ __forceinline__ void panel_block(
 #pragma unroll
             for (int e = 0; e < 4; ++e) pre_sx[i][e] = sx[min(m0 + 8 * ((wave + i * NW) % (MF * 4)) + 4 * kb + e, M - 1)];
     };
-    // unit i of the slice, in an order that starts elsewhere for every column group
+    // The units of this wave are wave + k NW of the slice (in an order that starts elsewhere for every column
+    // group), k = 0 .. count - 1; only the last may be past the end (is_unit).
     const int n = u_end - u_begin, rot = (int)(((unsigned)pl.gx * NW) % (unsigned)n);
-    auto nth = [&](int i) { return u_begin + i + rot - (i + rot >= n ? n : 0); };
-    int i = wave;
-    if (i < n) {
-        const int u = nth(i);
-        load_x(u);
+    auto is_unit = [&](int k) { return wave + k * NW < n; };
+    auto nth = [&](int k) {
+        const int i = min(wave + k * NW, n - 1);
+        return u_begin + i + rot - (i + rot >= n ? n : 0);
+    };
+    // Unit k in 4 F steps of one k-step (32 k) and tile each: the B operand of the next step is
+    // dequantised and, at the first tile of a k-step, the X fragments of the next k-step are read
+    // while the MFMAs of this one run.  On entry the loads of this unit's W, then its X, then the next
+    // unit's W (3 F loads) are in flight.  X of the next unit is loaded at the start, the W registers are loaded
+    // again (MORE_W), from unit k + 2, as soon as they are used up.
+    auto unit = [&](auto par_tag, auto pending_tag, auto more_w_tag, int k) {
+        constexpr int P = decltype(par_tag)::value;
+        constexpr bool MORE_W = decltype(more_w_tag)::value, LAST = P == 1 && !MORE_W;
+        v4i a[2][MF], b[2];
+        uint32_t s2[F], a4[F];
+        auto read_a = [&](int t, v4i (&to)[MF]) {
 #pragma unroll
-        for (int f = 0; f < F; ++f) load_p(u, f), load_w(u, f, 0);
+            for (int mf = 0; mf < MF; ++mf)
+                to[mf] = *reinterpret_cast<const v4i *>(xfrag + (P * MF + mf) * 4096 + 16 * ((2 * t + kb) ^ (j & 7)));
+        };
+        // phase ph (0..3) of the dequantisation of step (t, f): four independent instructions each
+        auto build = [&](int t, int f, int ph, v4i &to) {
+            if (ph == 0 && (G128 ? t == 0 : (t & 1) == 0)) {
+                UnitParams<G128> p;
+                p.raw = pr[P][f];
+                p.get(t >> 1, s2[f], a4[f]);
+            }
 #pragma unroll
-        for (int f = 0; f < F; ++f) load_w(u, f, 1);
+            for (int d = 0; d < 4; ++d) {
+                if (ph == 0) to[d] = (int)((t & 1) ? wr[P][f][t >> 1][d] >> 4 : wr[P][f][t >> 1][d] & 0x0F0F0F0Fu);
+                if (ph == 1 && (t & 1)) to[d] &= 0x0F0F0F0F;
+                if (ph == 2) to[d] = (int)pk_mad_u16((uint32_t)to[d], s2[f], a4[f]);
+                if (ph == 3) to[d] ^= (int)0x80808080;
+            }
+        };
+        // X of this unit is in LDS, and W (older) in the registers
+        wait_vmcnt<decltype(pending_tag)::value>();
+#pragma unroll
+        for (int f = 0; f < F; ++f) asm volatile("" : "+v"(wr[P][f][0]), "+v"(wr[P][f][1]), "+v"(pr[P][f]));
+        if (F * MF == 16) {  // (all accumulation registers: held where they are, a copy would need more)
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+#pragma unroll
+                for (int mf = 0; mf < MF; ++mf) asm volatile("" : "+a"(acc[f][mf]));
+        }
+        if (LAST) {
+            if (Y) load_scales();
+        } else if (is_unit(k + 1)) {
+            load_x(nth(k + 1), P ^ 1);
+        }
+        const int next2 = nth(k + 2);
+        const uint32_t w_off = is_unit(k + 2) ? wl : kNoLoad, p_off = is_unit(k + 2) ? pofl : kNoLoad;
+        read_a(0, a[0]);
+#pragma unroll
+        for (int ph = 0; ph < 4; ++ph) build(0, 0, ph, b[0]);
         __builtin_amdgcn_sched_barrier(0);
-        for (; i + NW < n; i += NW) unit(std::true_type{}, nth(i + NW));
-    }
-    if (Y) load_scales();
-    __builtin_amdgcn_sched_barrier(0);
-    if (i < n) unit(std::false_type{}, 0);
-
-    // Sum over the waves through LDS, FG tiles at a time: element quadruple q of (tile, fragment) as 16
-    // bytes per lane.  Item it = (mf * 4 + q) * 64 + lane of a tile is rows 32 mf + 8 q + 4 (lane / 32)
-    // + 0..3 of the slot lane % 32.
-    constexpr int FG = F % 2 == 0 ? 2 : 1;
-    v4i *const red = reinterpret_cast<v4i *>(panel_lds);  // [NW][FG][ITEMS]
-    v4i sums[F][PER];
 #pragma unroll
-    for (int f0 = 0; f0 < F; f0 += FG) {
+        for (int st = 0; st < 4 * F; ++st) {
+            const int t = st / F, f = st % F;
+            v4i &to = b[(st + 1) & 1];
+            if (f == 0 && t < 3) read_a(t + 1, a[(t + 1) & 1]);
+#pragma unroll
+            for (int mf = 0; mf < MF; ++mf) {
+                acc[f][mf] = mfma_i8(a[t & 1][mf], b[st & 1], acc[f][mf]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ph = 4 * mf / MF; ph < 4 * (mf + 1) / MF; ++ph)
+                    if (st + 1 < 4 * F) build((st + 1) / F, (st + 1) % F, ph, to);
+                // (complete before the registers it comes from are loaded again: these then stay the same ones)
+                asm volatile("" : "+v"(to));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (MORE_W && (t & 1)) load_w(next2, P, f, t >> 1, w_off);  // (the B operand of this step was their last use)
+            if (MORE_W && t == 3) load_p(next2, P, f, p_off);
+        }
+    };
+
+    // (an odd count: unit 0 goes first, on the second set of registers)
+    const int count = (n + NW - 1) / NW, odd = count & 1;
+    if (is_unit(0)) load_x(nth(0), odd);
+    load_unit_w(nth(odd), 0, is_unit(odd) ? wl : kNoLoad, is_unit(odd) ? pofl : kNoLoad);
+    load_unit_w(nth(odd ^ 1), 1, is_unit(odd ^ 1) ? wl : kNoLoad, is_unit(odd ^ 1) ? pofl : kNoLoad);
+    __builtin_amdgcn_sched_barrier(0);
+    if (kSumsApart) {
+#pragma unroll
+        for (int z = 0; z < F * MF * 256; z += NW * 64)
+            if (z + (int)threadIdx.x < F * MF * 256) reinterpret_cast<v4i *>(block_sums)[z + threadIdx.x] = v4i{0, 0, 0, 0};
+        // (no wave adds before all are past this; the loads above need not have arrived)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    const std::integral_constant<int, 3 * F> next_w{};
+    if (odd && count > 1) unit(c1, c0, std::true_type{}, 0);
+    for (int k = odd; k + 2 < count; k += 2) {
+        unit(c0, next_w, std::true_type{}, k);
+        unit(c1, next_w, std::true_type{}, k + 1);
+    }
+    if (count > 1) unit(c0, next_w, std::false_type{}, count - 2);
+    if (is_unit(count - 1))
+        unit(c1, c0, std::false_type{}, count - 1);
+    else if (Y)
+        load_scales();
+    __builtin_amdgcn_sched_barrier(0);
+
+    if (!kSumsApart) {
         __syncthreads();
 #pragma unroll
-        for (int g = 0; g < FG; ++g)
+        for (int z = 0; z < F * MF * 256; z += NW * 64)
+            if (z + (int)threadIdx.x < F * MF * 256) reinterpret_cast<v4i *>(block_sums)[z + threadIdx.x] = v4i{0, 0, 0, 0};
+        __syncthreads();
+    }
+    // Sum over the waves: each adds its accumulators to the block's sums in LDS as soon as it is through
+    // with its units.  Item it = (mf * 4 + q) * 64 + lane of a tile is rows 32 mf + 8 q + 4 (lane / 32)
+    // + 0..3 of the slot lane % 32.
+    constexpr int FG = F % 2 == 0 ? 2 : 1;
+    if (is_unit(0)) {
+        // (16 tiles fill the accumulation registers: their elements are read one at a time where they sit, behind the
+        // wait states that an MFMA's result needs)
+        if (F * MF == 16) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+        for (int f = 0; f < F; ++f)
 #pragma unroll
             for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v16i &t = acc[f0 + g][mf];
-                    red[(wave * FG + g) * ITEMS + (mf * 4 + q) * 64 + lane] =
-                        v4i{t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]};
+                for (int r = 0; r < 16; ++r) {
+                    int x = acc[f][mf][r];
+                    if (F * MF == 16) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[f][mf][r]));
+                    __hip_atomic_fetch_add(&block_sums[((f * MF + mf) * 16 + r) * 64 + lane], x, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
-        __syncthreads();
-#pragma unroll
-        for (int g = 0; g < FG; ++g)
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int it = threadIdx.x + i * NW * 64;
-                v4i s = {0, 0, 0, 0};
-                if (it < ITEMS) {
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) s += red[(w * FG + g) * ITEMS + it];
-                }
-                sums[f0 + g][i] = s;
-            }
     }
+    __syncthreads();
+    v4i sums[F][PER];
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int it = threadIdx.x + i * NW * 64;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sums[f][i][e] = it < ITEMS ? block_sums[((f * MF * 4 + (it >> 6)) * 4 + e) * 64 + lane] : 0;
+        }
     if (S > 1) {
         // the partial tiles meet in memory: same protocol as stream16_block, 16 bytes per thread
         const size_t group_ints = (size_t)F * ITEMS * 4;
@@ -209,14 +289,15 @@ __device__ __forceinline__ void panel_block(
                 const int it = threadIdx.x + i * NW * 64;
                 if (it < ITEMS) store_sc1_x4(base + ks * group_ints + (size_t)(f * ITEMS + it) * 4, sums[f][i]);
             }
+        int *const s_last = reinterpret_cast<int *>(panel_lds);  // (X and sums are read)
         wait_vmcnt0();
         __syncthreads();
         if (threadIdx.x == 0) {
             const unsigned t = __hip_atomic_fetch_add(&pl.tickets[tile_group], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_last = (t == (unsigned)(S - 1));
+            *s_last = (t == (unsigned)(S - 1));
         }
         __syncthreads();
-        if (!s_last) return;
+        if (!*s_last) return;
         for (int k2 = 0; k2 < S; ++k2) {
             if (k2 == ks) continue;
             const unsigned long long *other = reinterpret_cast<const unsigned long long *>(base + k2 * group_ints);
