@@ -176,13 +176,15 @@ int w4a8_select_variant(int M, int N, int K, int group); /* the dispatcher's cho
  * of the first, writes its rows to *rows_first (= M when there is one launch only) and the
  * variant of the launch over the remaining rows to *variant_rest (-1 when there is none).
  * Where the answer is duo_m64 or duo_m128 the dispatcher may run a panel form in its place
- * (w4a8_describe_launch names it); w4a8_gemm_variant runs the tiles.  <0 on error. */
+ * (w4a8_describe_launch names it); w4a8_gemm_variant runs the tiles.  In the same way a 16-row kernel of
+ * whole tiles may have half tiles or a panel run in its place.  <0 on error. */
 int w4a8_select_plan(int M, int N, int K, int group, int *rows_first, int *variant_rest);
 
 /* What one launch (or two) of a named variant, or of the dispatcher (-1), runs for a shape when the
  * workspace holds all K slices: the kernel's name -- for the dispatcher also the panel form that takes
  * the place of the few tiles of duo_m64 / duo_m128 or that stream_m32 / stream_m64 stand for, with its
- * K slices ("panel_f4_m64_s3") -- and the workspace bytes it uses (0: no K slices across blocks).  Host
+ * K slices ("panel_f4_m64_s3"), and behind the name of a 16-row kernel of whole tiles what runs in its place
+ * ("stream16_f1_w8[as stream16_h_w16_d3]") -- and the workspace bytes it uses (0: no K slices across blocks).  Host
  * only; text (cut to text_bytes, always terminated) and workspace_bytes may be NULL. */
 int w4a8_describe_launch(int variant, int M, int N, int K, int group, char *text, size_t text_bytes,
                          size_t *workspace_bytes);

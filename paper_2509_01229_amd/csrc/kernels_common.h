@@ -42,6 +42,15 @@ __device__ __forceinline__ void wait_vmcnt0(v4i &a, v4i &b, v4i &c, v4i &d)
     asm volatile("s_waitcnt vmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)::"memory");
 }
 
+// Buffers whose loads past the end ask memory for nothing and return zero; kNoLoad as a lane's offset is past
+// the end of any of them.
+typedef __amdgpu_buffer_rsrc_t buf_t;
+__device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+constexpr uint32_t kNoLoad = 1u << 30;
+
 // Where a block works: gx = its tile group (or output tile) among gnx, ks = its slice of S
 // K slices.  Plain launches take these from the grid (blockIdx.x, gridDim.x, blockIdx.y,
 // gridDim.y); grouped launches compute them per expert.

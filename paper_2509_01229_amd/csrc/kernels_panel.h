@@ -29,12 +29,6 @@
 // r = (p >> 3) ^ (i & 1), c = (p & 7) ^ r.  Fragment row j' = 32 mf + j is then found in piece j' >> 3
 // at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): the fragment reads meet no bank conflicts (counted).
 // ------------------------------------------------------------------------------------
-typedef __amdgpu_buffer_rsrc_t buf_t;
-__device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
-}
-
 constexpr bool panel_sums_apart(int F, int NW, int MF) { return (2 * NW + F) * MF * 4096 <= 160 * 1024; }
 constexpr size_t panel_lds_bytes(int F, int NW, int MF)
 {
@@ -104,8 +98,7 @@ __device__ __forceinline__ void panel_block(
                          : "v"(xoff[i]), "s"(xbase + (size_t)u * 128), "s"(xlds + par * (MF * 4096) + i * 1024)
                          : "memory", "m0");
     };
-    // (off: the lane's offset, or kNoLoad: a load past the end of the buffer, which asks memory for nothing)
-    constexpr uint32_t kNoLoad = 1u << 30;
+    // (off: the lane's offset, or kNoLoad)
     auto load_w = [&](int u, int par, int f, int c, uint32_t off) {
         wr[par][f][c] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, off + 1024 * c, (min(f, nf - 1) * units + u) * 2048, ONCE ? 2 : 0);
     };

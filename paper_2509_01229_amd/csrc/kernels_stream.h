@@ -1,4 +1,4 @@
-// stream16 kernel (M <= 16): weights streamed once, K split between the waves of a block.
+// stream16 kernels (M <= 16): weights streamed once, K split between the waves of a block.
 // (part of liquidgemm.hip: included there, inside namespace lqq)
 #pragma once
 
@@ -25,6 +25,75 @@ struct Stream16Regs {
     u32x4 x[2 * UU];
 };
 
+// The waves' accumulators are in red[NW][VALS][64]: sum over the waves, over the K slices where there are
+// several, and epilogue.  Value v of lane l is row 4 (l / 16) + v % 4, channel chan(v, l); thread i's outputs are
+// idx = 64 v + l = i, i + 64 NW, ...; their scales are in pre_sx and pre_sw.
+template <int VALS, int NW, class Chan>
+__device__ __forceinline__ void stream16_finish(
+    const Place pl, int M, int N, const int *red, const float *pre_sx, const float *pre_sw, Chan chan,
+    __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials)
+{
+    constexpr int OUTS = (VALS * 64 + NW * 64 - 1) / (NW * 64);
+    __shared__ int s_last;
+    const int S = pl.S, ks = pl.ks;
+    __syncthreads();
+    auto block_sum = [&](int idx) {
+        int sum = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += red[(w * VALS + (idx >> 6)) * 64 + (idx & 63)];
+        return sum;
+    };
+    auto finish = [&](int i, int idx, int sum) {
+        const int v = idx >> 6, l = idx & 63;
+        const int m = 4 * (l >> 4) + (v & 3);
+        if (m < M) {
+            const int n = chan(v, l);
+            if (ACC) ACC[(size_t)m * N + n] = sum;
+            if (Y) Y[(size_t)m * N + n] = scale_to_half(sum, pre_sx[i], pre_sw[i]);
+        }
+    };
+    if (S == 1) {
+#pragma unroll
+        for (int i = 0; i < OUTS; ++i) {
+            const int idx = threadIdx.x + i * NW * 64;
+            if (idx < VALS * 64) finish(i, idx, block_sum(idx));
+        }
+    } else {
+        // Partial tile of this slice: [ks][blockIdx.x][VALS * 64], coalesced.  The tiles are
+        // written and read with device-scope atomics, which act at the memory side common to
+        // all XCDs, so no cache has to be flushed or invalidated.  Every wave waits for the
+        // acknowledgement of its own stores (a block barrier alone does not: it orders LDS
+        // traffic only) before the barrier that precedes the ticket, so a block that sees
+        // the last ticket also sees every partial tile.
+        int32_t *mine = partials + ((size_t)ks * pl.gnx + pl.gx) * (size_t)(VALS * 64);
+        for (int idx = threadIdx.x; idx < VALS * 64; idx += NW * 64)
+            __hip_atomic_store(mine + idx, block_sum(idx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_vmcnt0();
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned t = __hip_atomic_fetch_add(&pl.tickets[pl.gx], 1u, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+            s_last = (t == (unsigned)(S - 1));
+        }
+        __syncthreads();
+        if (s_last) {
+#pragma unroll
+            for (int i = 0; i < OUTS; ++i) {
+                const int idx = threadIdx.x + i * NW * 64;
+                if (idx >= VALS * 64) break;
+                int sum = 0;
+                for (int k2 = 0; k2 < S; ++k2)
+                    sum += __hip_atomic_load(
+                        partials + ((size_t)k2 * pl.gnx + pl.gx) * (size_t)(VALS * 64) + idx,
+                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                finish(i, idx, sum);
+            }
+            if (threadIdx.x == 0)
+                __hip_atomic_store(&pl.tickets[pl.gx], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 template <int F, int NW, int UU, bool G128>
 __device__ __forceinline__ void stream16_block(
     const Place pl, int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
@@ -33,7 +102,6 @@ __device__ __forceinline__ void stream16_block(
 {
     constexpr int VALS = F * 8;  // accumulator registers per lane
     extern __shared__ __attribute__((aligned(16))) int red[];  // [NW][VALS][64]
-    __shared__ int s_last;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 31;
     const int t0 = pl.gx * F;
@@ -56,6 +124,7 @@ __device__ __forceinline__ void stream16_block(
     // The outputs this thread will finish (idx = threadIdx.x + i * blockDim.x) are known
     // now: fetch their scales here, so that the epilogue does not end on a cold load.
     constexpr int OUTS = (VALS * 64 + NW * 64 - 1) / (NW * 64);
+    auto chan = [&](int v, int l) { return channel_of(t0 + (v >> 3), 16 * ((v >> 2) & 1) + (l & 15)); };
     float pre_sx[OUTS], pre_sw[OUTS];
     if (Y) {
 #pragma unroll
@@ -63,7 +132,7 @@ __device__ __forceinline__ void stream16_block(
             const int idx = threadIdx.x + i * NW * 64;
             const int v = min(idx >> 6, VALS - 1), l = idx & 63;
             pre_sx[i] = sx[min(4 * (l >> 4) + (v & 3), M - 1)];
-            pre_sw[i] = sw[channel_of(t0 + (v >> 3), 16 * ((v >> 2) & 1) + (l & 15))];
+            pre_sw[i] = sw[chan(v, l)];
         }
     }
 
@@ -116,62 +185,7 @@ __device__ __forceinline__ void stream16_block(
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[(wave * VALS + (f * 2 + h) * 4 + r) * 64 + lane] = acc[f][h][r];
-    __syncthreads();
-    auto block_sum = [&](int idx) {
-        int sum = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) sum += red[(w * VALS + (idx >> 6)) * 64 + (idx & 63)];
-        return sum;
-    };
-    auto finish = [&](int i, int idx, int sum) {
-        const int v = idx >> 6, l = idx & 63;
-        const int m = 4 * (l >> 4) + (v & 3);
-        if (m < M) {
-            const int n = channel_of(t0 + (v >> 3), 16 * ((v >> 2) & 1) + (l & 15));
-            if (ACC) ACC[(size_t)m * N + n] = sum;
-            if (Y) Y[(size_t)m * N + n] = scale_to_half(sum, pre_sx[i], pre_sw[i]);
-        }
-    };
-    if (S == 1) {
-#pragma unroll
-        for (int i = 0; i < OUTS; ++i) {
-            const int idx = threadIdx.x + i * NW * 64;
-            if (idx < VALS * 64) finish(i, idx, block_sum(idx));
-        }
-    } else {
-        // Partial tile of this slice: [ks][blockIdx.x][VALS * 64], coalesced.  The tiles are
-        // written and read with device-scope atomics, which act at the memory side common to
-        // all XCDs, so no cache has to be flushed or invalidated.  Every wave waits for the
-        // acknowledgement of its own stores (a block barrier alone does not: it orders LDS
-        // traffic only) before the barrier that precedes the ticket, so a block that sees
-        // the last ticket also sees every partial tile.
-        int32_t *mine = partials + ((size_t)ks * pl.gnx + pl.gx) * (size_t)(VALS * 64);
-        for (int idx = threadIdx.x; idx < VALS * 64; idx += NW * 64)
-            __hip_atomic_store(mine + idx, block_sum(idx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_vmcnt0();
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const unsigned t = __hip_atomic_fetch_add(&pl.tickets[pl.gx], 1u, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
-            s_last = (t == (unsigned)(S - 1));
-        }
-        __syncthreads();
-        if (s_last) {
-#pragma unroll
-            for (int i = 0; i < OUTS; ++i) {
-                const int idx = threadIdx.x + i * NW * 64;
-                if (idx >= VALS * 64) break;
-                int sum = 0;
-                for (int k2 = 0; k2 < S; ++k2)
-                    sum += __hip_atomic_load(
-                        partials + ((size_t)k2 * pl.gnx + pl.gx) * (size_t)(VALS * 64) + idx,
-                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                finish(i, idx, sum);
-            }
-            if (threadIdx.x == 0)
-                __hip_atomic_store(&pl.tickets[pl.gx], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    stream16_finish<VALS, NW>(pl, M, N, red, pre_sx, pre_sw, chan, Y, ACC, partials);
 }
 
 template <int F, int NW, int UU, bool G128>
@@ -184,3 +198,102 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_kernel(
     stream16_block<F, NW, UU, G128>(grid_place(tickets), M, N, K, X, sx, Wp, gp, sw, Y, ACC, partials);
 }
 
+
+// ------------------------------------------------------------------------------------
+// Half a tile (16 channels) per block: twice the blocks where N alone leaves CUs idle, and no exchange of K
+// slices where these would fill them.  Such calls are bound by launch, the latency of the first loads and the sum over the
+// waves: 4 x 4096 x 4096 takes 4.2 us (whole tiles 5.1), 4 x 4096 x 11008 7.2 (two slices of K 8.9), 4.3 TB/s with weights
+// from HBM.  A unit of 128 k is one 16-byte load per lane: lane l takes slot 16 half + l % 16, k-half (l / 16) % 2, of chunk
+// l / 32.  Its low nibbles are then, without any regrouping, the B operand of a 16x16x64 MFMA over the first k-steps of
+// both chunks and its high nibbles over the second; X is read in that order.  All loads of D units per wave
+// are issued together and twice that are in flight; units past the end are loads past the end of the buffers (zero X, so
+// they add nothing), and the waves do not branch on them.
+// ------------------------------------------------------------------------------------
+template <int D>
+struct HalfRegs {
+    u32x4 w[D], x[D][2];
+    uint32_t p[D];
+};
+
+template <int NW, int D, bool G128>
+__device__ __forceinline__ void stream16_half_block(
+    const Place pl, int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
+    const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
+    __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials)
+{
+    __shared__ int red[NW * 4 * 64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile = pl.gx >> 1, slot = 16 * (pl.gx & 1) + (lane & 15);
+    const int chunk = lane >> 5, kb = (lane >> 4) & 1;
+    const int units = K >> 7;
+    const int u_begin = (int)((long long)units * pl.ks / pl.S), u_end = (int)((long long)units * (pl.ks + 1) / pl.S);
+    constexpr int PB = G128 ? 64 : 128;  // parameter bytes of a tile's unit
+    const buf_t wbuf = make_buf(Wp + (size_t)tile * (K >> 6) * 64, (uint32_t)K * 16u);
+    const buf_t pbuf = make_buf(gp + (size_t)tile * units * PB, (uint32_t)units * PB);
+    const buf_t xbuf = make_buf(X, (uint32_t)M * (uint32_t)K);
+    const uint32_t w_off = 1024 * chunk + 512 * kb + 16 * slot, p_off = slot * (PB / 32);
+    const uint32_t x_off = (uint32_t)min(lane & 15, M - 1) * (uint32_t)K + 64 * chunk + 16 * kb;
+
+    auto load = [&](HalfRegs<D> &r, int k0) {  // the wave's units k0 .. k0 + D - 1
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int u = u_begin + wave + (k0 + d) * NW;
+            const bool is_unit = u < u_end;
+            const int at = is_unit ? u : 0;
+            r.w[d] = __builtin_amdgcn_raw_buffer_load_b128(wbuf, is_unit ? w_off : kNoLoad, at * 2048, 2);
+            r.p[d] = G128 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pbuf, is_unit ? p_off : kNoLoad, at * PB, 0)
+                          : __builtin_amdgcn_raw_buffer_load_b32(pbuf, is_unit ? p_off : kNoLoad, at * PB, 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                r.x[d][h] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (is_unit ? x_off : kNoLoad) + 32 * h, at * 128, 0);
+        }
+    };
+    v4i acc = {0, 0, 0, 0};
+    auto compute = [&](const HalfRegs<D> &r) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            uint32_t s2, a4;
+            expand_params(G128 ? r.p[d] : r.p[d] >> (16 * chunk), 0, s2, a4);
+            v4i lo, hi;
+            dequant_chunk(r.w[d], s2, a4, lo, hi);
+            acc = mfma16_i8(__builtin_bit_cast(v4i, r.x[d][0]), lo, acc);
+            acc = mfma16_i8(__builtin_bit_cast(v4i, r.x[d][1]), hi, acc);
+        }
+    };
+    const int passes = (u_end - u_begin + NW * D - 1) / (NW * D);  // (the same for every wave)
+    HalfRegs<D> a, b;
+    auto chan = [&](int, int l) { return channel_of(tile, 16 * (pl.gx & 1) + (l & 15)); };
+    float pre_sx = 0, pre_sw = 0;  // (four waves finish one output per thread)
+    load(a, 0);
+    load(b, D);
+    if (Y && threadIdx.x < 256) {
+        pre_sx = sx[min(4 * (lane >> 4) + wave, M - 1)];
+        pre_sw = sw[chan(0, lane)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    int p = 0;
+    for (; p + 2 < passes; p += 2) {
+        compute(a);
+        load(a, (p + 2) * D);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(b);
+        load(b, (p + 3) * D);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    compute(a);
+    if (p + 1 < passes) compute(b);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[(wave * 4 + r) * 64 + lane] = acc[r];
+    stream16_finish<4, NW>(pl, M, N, red, &pre_sx, &pre_sw, chan, Y, ACC, partials);
+}
+
+template <int NW, int D, bool G128>
+__global__ __launch_bounds__(NW * 64) void w4a8_stream16_half_kernel(
+    int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
+    const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
+    __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials,
+    unsigned int *__restrict__ tickets)
+{
+    stream16_half_block<NW, D, G128>(grid_place(tickets), M, N, K, X, sx, Wp, gp, sw, Y, ACC, partials);
+}

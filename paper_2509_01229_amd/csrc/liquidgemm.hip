@@ -202,6 +202,27 @@ static int launch_stream16(const Args &a)
     return LQ_OK;
 }
 
+// The 16-row kernel with half a tile per block.
+template <int NW, int D, int SPLIT>
+static int launch_stream16_half(const Args &a)
+{
+    if (a.M > 16) return fail(LQ_ERR_INVALID, "stream16 variants handle M <= 16, got %d", a.M);
+    const int groups = a.N / 16;
+    const int S = groups > kMaxTicketGroups ? 1 : std::min(SPLIT, a.K / 128);
+    const size_t need = S > 1 ? kTicketBytes + (size_t)S * groups * 4 * 64 * sizeof(int32_t) : 0;
+    if (a.query) return *a.query = need, LQ_OK;
+    if (need > 0 && (!a.ws || a.ws_bytes < need))
+        return fail(LQ_ERR_WORKSPACE, "split-K needs %zu bytes of workspace, got %zu", need, a.ws ? a.ws_bytes : 0);
+    unsigned int *tickets = static_cast<unsigned int *>(a.ws);
+    int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(groups, S), dim3(NW * 64), 0, a.stream, a.M, a.N, a.K, a.X, a.sx, a.Wp, a.gp, a.sw,
+                           a.Y, a.ACC, partials, tickets);
+        return (int)LQ_OK;
+    };
+    return a.group == 128 ? go(&w4a8_stream16_half_kernel<NW, D, true>) : go(&w4a8_stream16_half_kernel<NW, D, false>);
+}
+
 // Panel kernel: 32 MF rows x 32 F channels per block, S slices of K across blocks, NW waves per
 // block (two per SIMD while the accumulators leave room for that, i.e. up to 64 rows).
 constexpr long long kAssumedCUs = 256;  // the shape rules of the dispatcher are written for the MI355X
@@ -662,7 +683,7 @@ struct Variant {
 // and 32, 64 or 128 rows per block.  duo_m64, duo_m128: few 64- or 128-row tiles, K split over blocks (the
 // dispatcher runs a panel form in their place where that is faster).  stream16_f<F>_w<NW>[_s<S>]: F tiles per block, NW waves splitting the block's K slice,
 // S grid-level K slices (chosen from the shape when not named); _u4 = four 128-k units per
-// pipeline step; g2 = two k groups per block.
+// pipeline step; stream16_h_w<NW>_d<D>: half a tile per block, D units per step (in_place_of_stream16); g2 = two k groups per block.
 static const Variant kVariants[] = {
     // --- dispatched (select_variant) ---
     {"stream16_f1_w16_s1", &launch_stream16<1, 16, 1>, 16, 1, 1},
@@ -671,6 +692,15 @@ static const Variant kVariants[] = {
     {"stream16_f2_w8", &launch_stream16<2, 8, 0>, 16, 2, 1},
     {"stream16_f2_w16_s1", &launch_stream16<2, 16, 1>, 16, 2, 1},
     {"stream16_f2_w4", &launch_stream16<2, 4, 0>, 16, 2, 1},
+    {"stream16_h_w8_d2", &launch_stream16_half<8, 2, 1>, 16, 1, 1},
+    {"stream16_h_w8_d3", &launch_stream16_half<8, 3, 1>, 16, 1, 1},
+    {"stream16_h_w8_d4", &launch_stream16_half<8, 4, 1>, 16, 1, 1},
+    {"stream16_h_w16_d3", &launch_stream16_half<16, 3, 1>, 16, 1, 1},
+    {"stream16_h_w16_d4", &launch_stream16_half<16, 4, 1>, 16, 1, 1},
+    {"stream16_h_w8_d2_s2", &launch_stream16_half<8, 2, 2>, 16, 1, 1},
+    {"stream16_h_w8_d3_s2", &launch_stream16_half<8, 3, 2>, 16, 1, 1},
+    {"stream16_h_w8_d4_s2", &launch_stream16_half<8, 4, 2>, 16, 1, 1},
+    {"panel_f1_m32", &launch_panel_named<1, 8, 1, 1>, 0, 1, 1},
     {"stream_m32", &launch_panel_auto, 32, 2, 1},
     {"stream_m64", &launch_panel_auto, 64, 2, 1},
     {"duo_m64", &launch_duo64<0>, 0, 1, 1, 512},
@@ -874,6 +904,53 @@ static int select_variant(int M, int N, int K)
     return find_variant(prefer_64_row_tiles(M, N, K) ? "duo_m64" : "duo_m128");
 }
 
+// Up to 16 rows: the kernel that runs where select_variant names a stream16 variant of whole tiles (that variant
+// itself where nothing is faster).  Measured on 52 weight shapes (N 1024..12288, K 2048..20480) at 1, 4, 8 and 16 rows and 20
+// (N to 28672, K to 28672) at 1, 4, 8, 12 and 16, 560 MB of weights in rotation, us whole tiles / what runs here:
+//   * up to 128 tiles of 32 channels, half tiles: 256 instead of 128 blocks at N = 4096, and no K slices.  At 4 rows 4096 x
+//     4096 5.1 / 4.2, 4096 x 11008 8.9 / 7.2, 4096 x 8192 8.0 / 5.8, 1024 x 4096 5.0 / 3.8, 4096 x 14336 10.5 / 8.4.  D is
+//     the number of units that leaves the fewest loads past the end: K / 128 units over 8 waves are at most 2 x 2, 2 x
+//     3 or 2 x 4 each (4096 x 5120: 4.9 with 3, 5.4 with 4), above that over 16 waves, with very long K 2 in any number of passes.
+//     X is read twice as often, so from 13 rows long K keeps whole tiles (4096 x 11008 at 16 rows 9.1, half tiles 9.3).
+//   * up to 64 tiles two slices of K fill the CUs where K is long (2048 x 14336 at 4 rows 8.1 / 7.2; one slice 7.6)
+//   * 129..384 tiles: with a whole number of passes and few rows half tiles again (8192 x 8192 at 4 rows 9.8 / 9.0, 10240 x
+//     8192 12.9 / 11.3), else up to 320 tiles the 32-row panels, whose loads run two units ahead (8192 x 11008 at 8
+//     rows 12.6 / 11.9, 10240 x 8192 at 16 13.5 / 12.8, 6656 x 16384 at 16 16.6 / 15.1; groups of 128: 12.7 / 12.3,
+//     13.3 / 13.1, 16.4 / 15.6).  K below 6144, up to 8 rows with K from 12288 and K beyond 16384 stay (5120 x
+//     5120 6.7 against 7.5, 5120 x 13824 at 8 rows 12.1 against 12.2, 8192 x 28672 at 16 rows, groups of 128, 25.7 against 26.5).
+static int in_place_of_stream16(int variant, const Args &a)
+{
+    const int tiles = a.N / 32, M = a.M, K = a.K;
+    const char *name = nullptr;
+    if (tiles <= 128) {
+        if (K <= 4096) name = "stream16_h_w8_d2";
+        else if (K <= 6144) name = "stream16_h_w8_d3";
+        else if (K <= 8192) name = tiles <= 64 && M > 12 ? "stream16_h_w8_d2_s2" : "stream16_h_w8_d4";
+        else if (tiles <= 64) {
+            if (K <= 12288) name = M <= 12 ? "stream16_h_w8_d3_s2" : nullptr;
+            else if (K <= 16384) name = M <= 12 ? "stream16_h_w8_d4_s2" : nullptr;
+            else if (K <= 20480) name = M <= 4 ? "stream16_h_w8_d2_s2" : nullptr;
+        } else if (K <= 16384) {
+            if (M <= 12) name = K <= 12288 ? "stream16_h_w16_d3" : "stream16_h_w16_d4";
+        } else if (K <= 20480 && M <= 4) {
+            name = "stream16_h_w8_d2";
+        }
+    } else if (tiles <= 384 && K >= 6144 && K <= 8192 && M <= 4) {
+        name = K == 6144 ? "stream16_h_w8_d3" : "stream16_h_w8_d4";
+    } else if (tiles <= 256) {
+        if (K > 6144 && K <= 16384 && (M >= 9 || (K > 8192 && K < 12288))) name = "panel_f1_m32";
+    } else if (tiles <= 320) {
+        if (K >= 6144 && K < 12288 && (M >= 5 || K > 8192)) name = "panel_f2_m32";
+    }
+    if (!name) return variant;
+    const int other = find_variant(name);
+    Args query = a;
+    size_t need = 0;
+    query.query = &need;
+    if (kVariants[other].fn(query) || need > workspace_limit(a)) return variant;
+    return other;
+}
+
 // A batch whose 256 x 256 tiles are whole rounds plus a few rows (4096 + 40 rows on 8192 x 8192)
 // is better run as two launches over consecutive rows: the row blocks that fill whole rounds with
 // the 256 x 256 tiles, and the rest with whatever the dispatcher picks for it -- 226 us against
@@ -949,8 +1026,9 @@ static int run_rows(int variant, const Args &a)
         if (a.sx) c.sx = a.sx + r0;
         if (a.Y) c.Y = a.Y + r0 * a.N;
         if (a.ACC) c.ACC = a.ACC + r0 * a.N;
+        const int runs = dispatched && a.M <= 16 ? in_place_of_stream16(variant, c) : variant;
         const PanelChoice panel = dispatched && is_few_tiles(variant) ? panel_instead_of_tiles(c) : PanelChoice{};
-        if (int rc = panel.form ? panel.form->launch(c, panel.S) : kVariants[variant].fn(c)) return rc;
+        if (int rc = panel.form ? panel.form->launch(c, panel.S) : kVariants[runs].fn(c)) return rc;
         need_max = std::max(need_max, need);
     }
     if (a.query) return *a.query = need_max, LQ_OK;
@@ -990,6 +1068,13 @@ static void launch_name(int variant, int M, int N, int K, char *text, size_t tex
     a.M = M, a.N = N, a.K = K, a.query = &unused;
     const bool dispatched = variant < 0;
     if (dispatched) variant = select_variant(M, N, K);
+    if (dispatched && M <= 16) {
+        const int runs = in_place_of_stream16(variant, a);
+        if (runs != variant) {
+            snprintf(text, text_bytes, "%s[as %s]", kVariants[variant].name, kVariants[runs].name);
+            return;
+        }
+    }
     PanelChoice panel{};
     if (kVariants[variant].fn == &launch_panel_auto) panel = choose_panel(M, N, K, workspace_limit(a));
     else if (dispatched && is_few_tiles(variant)) panel = panel_instead_of_tiles(a);

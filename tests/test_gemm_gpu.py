@@ -687,3 +687,34 @@ def test_every_dispatched_panel_form(M, N, K, form):
         assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g), ref), f"accumulators differ, call {rep}"
     Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
     H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
+
+
+# ---------------------------------------------------------------------------------------
+# What runs in place of the 16-row kernels of whole tiles: every form, with passes that are full, ragged and
+# not there at all, an odd tile count, and the edges of the rule
+# ---------------------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,form", [
+    (1, 64, 256, "stream16_h_w8_d2"), (16, 192, 4096, "stream16_h_w8_d2"), (5, 4096, 2304, "stream16_h_w8_d2"),
+    (3, 2112, 20480, "stream16_h_w8_d2"), (16, 64, 4352, "stream16_h_w8_d3"), (9, 320, 6144, "stream16_h_w8_d3"),
+    (4, 4160, 6144, "stream16_h_w8_d3"), (12, 64, 6400, "stream16_h_w8_d4"), (16, 2112, 8192, "stream16_h_w8_d4"),
+    (4, 8256, 7936, "stream16_h_w8_d4"), (13, 128, 6400, "stream16_h_w8_d2_s2"), (1, 64, 20480, "stream16_h_w8_d2_s2"),
+    (12, 192, 8448, "stream16_h_w8_d3_s2"), (2, 2048, 12544, "stream16_h_w8_d4_s2"), (12, 2112, 8448, "stream16_h_w16_d3"),
+    (7, 2112, 12544, "stream16_h_w16_d4"), (16, 4160, 8192, "panel_f1_m32"),
+    (1, 4224, 8448, "panel_f1_m32"), (5, 8256, 6400, "panel_f2_m32")])
+def test_every_form_in_place_of_the_16_row_kernels(M, N, K, form):
+    import torch
+
+    for g in (64, 128):
+        name, need = api.w4a8_describe_launch(M, N, K, g)
+        _say(f"up to 16 rows M={M} N={N} K={K} g={g} -> {name}, {need} bytes")
+        assert name.startswith("stream16_f") and name.endswith(f"[as {form}]") and (need > 0) == ("_s2" in form)
+        W = H.RandomWeights(N, K, g, seed=M)
+        X, sx = W.activations(M)
+        ref = W.product(X)
+        for rep in range(2):   # (the tickets reset themselves)
+            assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g), ref), f"accumulators differ, call {rep}"
+        # without room for slices the whole tiles run
+        nothing = torch.zeros(0, dtype=torch.uint8, device="cuda")
+        assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g, workspace=nothing), ref), "no workspace"
+        Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
+        H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
