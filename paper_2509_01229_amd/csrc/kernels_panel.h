@@ -88,7 +88,7 @@ __device__ __forceinline__ void panel_block(
     const uint32_t wl = lane * 16, pofl = j * (PB / 32);
 
     u32x4 wr[2][F][2];  // [parity of the unit]
-    uint32_t pr[2][F];
+    std::conditional_t<G128, uint16_t, uint32_t> pr[2][F];  // (widened where it is used: where it is loaded that would wait for it)
     // X of unit u straight into half `par` of the wave's region
     auto load_x = [&](int u, int par) {
 #pragma unroll
@@ -104,8 +104,10 @@ __device__ __forceinline__ void panel_block(
     };
     auto load_p = [&](int u, int par, int f, uint32_t off) {
         const int po = (min(f, nf - 1) * units + u) * PB;
-        pr[par][f] = G128 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(pbuf, off, po, 0)
-                          : __builtin_amdgcn_raw_buffer_load_b32(pbuf, off, po, 0);
+        if constexpr (G128)
+            pr[par][f] = __builtin_amdgcn_raw_buffer_load_b16(pbuf, off, po, 0);
+        else
+            pr[par][f] = __builtin_amdgcn_raw_buffer_load_b32(pbuf, off, po, 0);
     };
     auto load_unit_w = [&](int u, int par, uint32_t w_off, uint32_t p_off) {
 #pragma unroll
