@@ -5,34 +5,41 @@
 // ------------------------------------------------------------------------------------
 // A block owns 32 MF rows x F tiles (32 F channels) of the output and one of S slices of K; its
 // NW waves take the slice's units of 128 k round-robin, so a wave shares nothing with the others
-// until the end: no barrier in the loop.  No one unit of the CU is the bound: built without its loads the kernel
-// takes 20.6 us on 256 x 8192 x 8192 (of 26.5; F = 4, MF = 2), without dequantisation and MFMA 22.5, and 10.2 and
-// 12.5 of 13.7 on 45 x 13824 x 5120 (F = 2, MF = 2) -- the dequantisation of W for few rows, the way of X and W from
-// L2 (64 KB per us and CU, what a CU draws from beyond its L2) and 5 to 7 us of launch, first loads and sum, which
-// do not depend on K; hence forms from 1 x 1 to 4 x 4 accumulator tiles, which trade the volume of X and the
+// until the end: no barrier in the loop.  No one unit of the CU is the bound: of 256 x 8192 x 8192 (F = 4, MF = 2) the
+// 47.0 thousand cycles that a SIMD's two waves live hold 20.9 of vector and 16.4 of matrix instructions, of 45 x 13824 x
+// 5120 (F = 2, MF = 2) the 24.5 hold 7.3 and 5.1 (counters); the form before, with one set of W registers, took 20.6 of 26.5 us and
+// 10.2 of 13.7 without its loads, 22.5 and 12.5 without dequantisation and MFMA.  It is the dequantisation of W for few
+// rows, the way of X and W from L2 (64 KB per us and CU, what a CU draws from beyond its L2) and 5 to 7 us of launch,
+// first loads and sum, which do not depend on K; hence forms from 1 x 1 to 4 x 4 accumulator tiles, which trade the volume of X and the
 // repeated dequantisation against the sum over the waves and the number of blocks.  Two things keep the loads ahead:
 //   * W sits in two sets of registers: a unit's is loaded while the unit two before it is computed, as the
 //     registers of that one are used up;
 //   * X goes straight into LDS, into the half of the wave's region that the unit before the last has left, a
 //     whole unit ahead.
+// Against one set of W registers (loaded for the next unit) and X through registers, in us: 45 x 5120 x 5120 9.8 / 9.4, 45 x
+// 13824 x 5120 14.3 / 13.6, 128 x 4096 x 11008 16.5 / 15.5, 128 x 11008 x 4096 15.0 / 14.4, 24 x 8192 x 4096 7.3 / 6.9, 256 x
+// 8192 x 8192 26.7 / 25.6; 18000 calls of 17 to 512 rows 0.96 of the time (groups of 64 and 128 alike), at worst, with K =
+// 256, 3.2 / 3.4.
 // Starting every column group at another unit takes 1 to 3 us off large batches (35.8 to 32.9 us on 256 x 10240 x
 // 8192): rows are a power of two apart, and the blocks of an XCD would all ask the same channels of its L2.
-// The waves add their accumulators to the block's sums in LDS, each when it is through.  Measured against one set
-// of W registers (loaded for the next unit), X through registers and a sum of eight copies in LDS, in us: 45 x 5120 x
-// 5120 9.5 / 9.0, 45 x 13824 x 5120 13.7 / 13.0, 128 x 4096 x 11008 16.7 / 15.7, 24 x 8192 x 4096 8.7 / 8.1, 64 x 28672
-// x 8192 33.1 / 30.5; 128 x 11008 x 4096 and 256 x 8192 x 8192 (row tiles share W) equal to 1 %.
+// The sum is one of copies, each wave's in its own region; waves that add to one copy with LDS atomics, each when it is
+// through, take longer where K is short (one unit a wave, 32 x 32 6 %, 64 x 64 8 %; 3 x 4 tiles 5 % up to K = 6144) and as long
+// where it is not.
 // The code is written out per position of a unit (first of an odd count, pair in the loop, last two): a load that
 // may or may not have been issued would make the compiler wait for all of them.
 //
 // X: a load covers 8 whole rows (8 cache lines per KiB instead of the 32 of a fragment load).  Load i (i = 0 .. 4
 // MF - 1) fills the 1 KiB piece i of the region in lane order; lane p brings row 8 i + r, 16-byte column c with
 // r = (p >> 3) ^ (i & 1), c = (p & 7) ^ r.  Fragment row j' = 32 mf + j is then found in piece j' >> 3
-// at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): the fragment reads meet no bank conflicts (counted).
+// at 128 ((j & 7) ^ (piece & 1)) + 16 (column ^ (j & 7)): no bank conflict there or in the sum (counted, 0 on both shapes above).
 // ------------------------------------------------------------------------------------
-constexpr bool panel_sums_apart(int F, int NW, int MF) { return (2 * NW + F) * MF * 4096 <= 160 * 1024; }
-constexpr size_t panel_lds_bytes(int F, int NW, int MF)
+// A wave's region holds X of two units, and in the end its sums of up to two tiles.  With one tile and slices in which
+// no wave has a second unit half of that does, and short K on many channels has three blocks on a CU instead of
+// two (752 blocks of K = 256 5.5 us, with both halves and the sum of one copy 6.9).
+constexpr int panel_halves(int F, int NW, int units) { return F == 1 && units <= NW ? 1 : 2; }
+constexpr size_t panel_lds_bytes(int F, int NW, int MF, int units)
 {
-    return (size_t)(2 * NW + (panel_sums_apart(F, NW, MF) ? F : 0)) * MF * 4096;
+    return (size_t)panel_halves(F, NW, units) * NW * MF * 4096;
 }
 
 // ONCE = the weights are read by one row tile only (M <= 32 MF): loaded without keeping them in the
@@ -49,7 +56,7 @@ __device__ __forceinline__ void panel_block(
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials, int tile_group)
 {
-    extern __shared__ __attribute__((aligned(16))) int8_t panel_lds[];  // the waves' X regions and the block's sums
+    extern __shared__ __attribute__((aligned(16))) int8_t panel_lds[];  // the waves' regions: X, then their sums
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int j = lane & 31, kb = lane >> 5;
@@ -67,10 +74,8 @@ __device__ __forceinline__ void panel_block(
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[f][mf][r] = 0;
 
-    // X of two units in the wave's region; the sums behind all regions where there is room
-    constexpr bool kSumsApart = panel_sums_apart(F, NW, MF);
-    int8_t *const xregion = panel_lds + wave * (2 * MF * 4096);
-    int *const block_sums = reinterpret_cast<int *>(panel_lds + (kSumsApart ? 2 * NW * MF * 4096 : 0));  // [F][MF][register][lane]
+    const int halves = panel_halves(F, NW, u_end - u_begin);  // (the only one is that of parity 1)
+    int8_t *const xregion = panel_lds + wave * (halves * MF * 4096);
     const int8_t *const xfrag = xregion + (j >> 3) * 1024 + 128 * ((j & 7) ^ ((j >> 3) & 1));
     const uint32_t xlds = (uint32_t)(size_t)(__attribute__((address_space(3))) void *)xregion;
     const int rows = min(32 * MF, M - m0);
@@ -89,13 +94,13 @@ __device__ __forceinline__ void panel_block(
 
     u32x4 wr[2][F][2];  // [parity of the unit]
     std::conditional_t<G128, uint16_t, uint32_t> pr[2][F];  // (widened where it is used: where it is loaded that would wait for it)
-    // X of unit u straight into half `par` of the wave's region
+    // X of unit u straight into the half of the wave's region for parity `par`
     auto load_x = [&](int u, int par) {
 #pragma unroll
         for (int i = 0; i < 4 * MF; ++i)
             asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                          :
-                         : "v"(xoff[i]), "s"(xbase + (size_t)u * 128), "s"(xlds + par * (MF * 4096) + i * 1024)
+                         : "v"(xoff[i]), "s"(xbase + (size_t)u * 128), "s"(xlds + (1 - par) * (MF * 4096) + i * 1024)
                          : "memory", "m0");
     };
     // (off: the lane's offset, or kNoLoad)
@@ -147,7 +152,7 @@ __device__ __forceinline__ void panel_block(
         auto read_a = [&](int t, v4i (&to)[MF]) {
 #pragma unroll
             for (int mf = 0; mf < MF; ++mf)
-                to[mf] = *reinterpret_cast<const v4i *>(xfrag + (P * MF + mf) * 4096 + 16 * ((2 * t + kb) ^ (j & 7)));
+                to[mf] = *reinterpret_cast<const v4i *>(xfrag + ((1 - P) * MF + mf) * 4096 + 16 * ((2 * t + kb) ^ (j & 7)));
         };
         // phase ph (0..3) of the dequantisation of step (t, f): four independent instructions each
         auto build = [&](int t, int f, int ph, v4i &to) {
@@ -209,17 +214,9 @@ __device__ __forceinline__ void panel_block(
     // (an odd count: unit 0 goes first, on the second set of registers)
     const int count = (n + NW - 1) / NW, odd = count & 1;
     if (is_unit(0)) load_x(nth(0), odd);
-    load_unit_w(nth(odd), 0, is_unit(odd) ? wl : kNoLoad, is_unit(odd) ? pofl : kNoLoad);
+    if (count > 1) load_unit_w(nth(odd), 0, is_unit(odd) ? wl : kNoLoad, is_unit(odd) ? pofl : kNoLoad);
     load_unit_w(nth(odd ^ 1), 1, is_unit(odd ^ 1) ? wl : kNoLoad, is_unit(odd ^ 1) ? pofl : kNoLoad);
     __builtin_amdgcn_sched_barrier(0);
-    if (kSumsApart) {
-#pragma unroll
-        for (int z = 0; z < F * MF * 256; z += NW * 64)
-            if (z + (int)threadIdx.x < F * MF * 256) reinterpret_cast<v4i *>(block_sums)[z + threadIdx.x] = v4i{0, 0, 0, 0};
-        // (no wave adds before all are past this; the loads above need not have arrived)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    }
     const std::integral_constant<int, 0> c0{};
     const std::integral_constant<int, 1> c1{};
     const std::integral_constant<int, 3 * F> next_w{};
@@ -235,44 +232,39 @@ __device__ __forceinline__ void panel_block(
         load_scales();
     __builtin_amdgcn_sched_barrier(0);
 
-    if (!kSumsApart) {
-        __syncthreads();
-#pragma unroll
-        for (int z = 0; z < F * MF * 256; z += NW * 64)
-            if (z + (int)threadIdx.x < F * MF * 256) reinterpret_cast<v4i *>(block_sums)[z + threadIdx.x] = v4i{0, 0, 0, 0};
-        __syncthreads();
-    }
-    // Sum over the waves: each adds its accumulators to the block's sums in LDS as soon as it is through
-    // with its units.  Item it = (mf * 4 + q) * 64 + lane of a tile is rows 32 mf + 8 q + 4 (lane / 32)
-    // + 0..3 of the slot lane % 32.
+    // Sum over the waves through LDS, FG tiles at a time, each wave's in its own region (its reads of X are done).
+    // Element quadruple q of (tile, fragment) is 16 bytes per lane: item it = (mf * 4 + q) * 64 + lane of a tile is
+    // rows 32 mf + 8 q + 4 (lane / 32) + 0..3 of the slot lane % 32.
     constexpr int FG = F % 2 == 0 ? 2 : 1;
-    if (is_unit(0)) {
-        // (16 tiles fill the accumulation registers: their elements are read one at a time where they sit, behind the
-        // wait states that an MFMA's result needs)
-        if (F * MF == 16) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+    v4i *const red = reinterpret_cast<v4i *>(panel_lds);
+    v4i sums[F][PER];
 #pragma unroll
-        for (int f = 0; f < F; ++f)
+    for (int f0 = 0; f0 < F; f0 += FG) {
+        if (f0) __syncthreads();
+#pragma unroll
+        for (int g = 0; g < FG; ++g)
 #pragma unroll
             for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    int x = acc[f][mf][r];
-                    if (F * MF == 16) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[f][mf][r]));
-                    __hip_atomic_fetch_add(&block_sums[((f * MF + mf) * 16 + r) * 64 + lane], x, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                for (int q = 0; q < 4; ++q) {
+                    const v16i &t = acc[f0 + g][mf];
+                    red[(wave * halves + g) * ITEMS + (mf * 4 + q) * 64 + lane] =
+                        v4i{t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3]};
                 }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < FG; ++g)
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int it = threadIdx.x + i * NW * 64;
+                v4i s = {0, 0, 0, 0};
+                if (it < ITEMS) {
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) s += red[(w * halves + g) * ITEMS + it];
+                }
+                sums[f0 + g][i] = s;
+            }
     }
-    __syncthreads();
-    v4i sums[F][PER];
-#pragma unroll
-    for (int f = 0; f < F; ++f)
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int it = threadIdx.x + i * NW * 64;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                sums[f][i][e] = it < ITEMS ? block_sums[((f * MF * 4 + (it >> 6)) * 4 + e) * 64 + lane] : 0;
-        }
     if (S > 1) {
         // the partial tiles meet in memory: same protocol as stream16_block, 16 bytes per thread
         const size_t group_ints = (size_t)F * ITEMS * 4;
@@ -284,7 +276,7 @@ __device__ __forceinline__ void panel_block(
                 const int it = threadIdx.x + i * NW * 64;
                 if (it < ITEMS) store_sc1_x4(base + ks * group_ints + (size_t)(f * ITEMS + it) * 4, sums[f][i]);
             }
-        int *const s_last = reinterpret_cast<int *>(panel_lds);  // (X and sums are read)
+        int *const s_last = reinterpret_cast<int *>(panel_lds);  // (the sums are read before the barrier below)
         wait_vmcnt0();
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -249,7 +249,7 @@ static int launch_panel(const Args &a, int S)
     if (need > 0 && (!a.ws || a.ws_bytes < need))
         return fail(LQ_ERR_WORKSPACE, "split-K needs %zu bytes of workspace, got %zu", need, a.ws ? a.ws_bytes : 0);
     const dim3 grid((unsigned)(blocks_m * blocks_n * S)), block(NW * 64);
-    const size_t lds_bytes = panel_lds_bytes(F, NW, MF);
+    const size_t lds_bytes = panel_lds_bytes(F, NW, MF, (a.K / 128 + S - 1) / S);
     unsigned int *tickets = static_cast<unsigned int *>(a.ws);
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
     auto go = [&](auto kernel) {
@@ -1180,7 +1180,7 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
         if (blocks > 0x7fffffff) return fail(LQ_ERR_INVALID, "grouped GEMM too large for one launch");
         t.block_end[i] = (int)blocks;
     }
-    const size_t lds = panel_lds_bytes(F, 8, MF);
+    const size_t lds = panel_lds_bytes(F, 8, MF, a.K / 128);
     const dim3 grid((unsigned)blocks);
     auto go = [&](auto kernel) {
         return launch_checked("grouped panel", kernel, grid, dim3(512), lds, a.stream, t, a.p, a.N, a.K);

@@ -18,4 +18,13 @@ __device__ __forceinline__ __half scale_to_half(int acc, float sx, float sw) { r
         int32_t *, unsigned int *, int, int, int);
 PANEL(true)
 PANEL(false)
+
+// 32 x 32, one unit a wave: at 67 registers three blocks fit a CU, and its LDS has to let them
+static_assert(3 * panel_lds_bytes(1, 8, 1, 8) <= 160 * 1024);
+// every form fits, with one unit a wave and with more
+template <int F, int NW, int MF>
+constexpr bool fits = panel_lds_bytes(F, NW, MF, 1) <= 160 * 1024 && panel_lds_bytes(F, NW, MF, 1024) <= 160 * 1024 &&
+                      panel_lds_bytes(F, NW, MF, 1) >= (size_t)NW * (F % 2 == 0 ? 2 : 1) * MF * 4096;
+static_assert(fits<1, 8, 1> && fits<2, 8, 1> && fits<4, 8, 1> && fits<1, 8, 2> && fits<2, 8, 2> && fits<3, 8, 2> &&
+              fits<4, 8, 2> && fits<3, 4, 4> && fits<4, 4, 4>);
 }  // namespace lqq
