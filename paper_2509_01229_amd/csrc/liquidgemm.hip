@@ -308,6 +308,16 @@ static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
             if (us < best.us) best = PanelChoice{&f, S, us};
         }
     }
+    // Two exceptions, for launches of several rounds, which the fit prices alike whatever stays on a CU.  32 x 128 panels, one
+    // on a CU, run a round at a time: beyond one round 32 x 64 panels, two on a CU, are ahead (136 x 11520 x 2048 15.9 / 13.1 us,
+    // 390 such calls 1.05 / 0.91 of what the form with one set of W registers took).  32 x 32 panels of more than two rounds are
+    // behind them while a wave has no second unit (24 x 24064 x 256 5.5 / 5.2, 5.0 of that form; K = 512 5.7 / 5.4, 768 6.1 / 6.0,
+    // 1024 6.2 / 6.5).
+    if (best.form && best.S == 1 && best.form->MF == 1) {
+        const long long blocks = panel_blocks(M, N, best.form->F, 1);
+        if ((best.form->F == 4 && blocks > kAssumedCUs) || (best.form->F == 1 && blocks > 2 * kAssumedCUs && K <= 768))
+            best.form = &kPanelForms[1];
+    }
     return best;
 }
 // 17..64 rows: the form that choose_panel picks

@@ -253,3 +253,15 @@ def test_workload_names():
     for bad in ("bogus", "x_M3_N64", "x_M3_N64_K256_g32", "_M3_N64_K256"):
         with pytest.raises(KeyError):
             WL.by_name(bad)
+
+
+def test_panels_of_several_rounds():
+    """32 x 128 panels run one on a CU: beyond one round of them 32 x 64 panels take their place (15.9 against 13.1
+    us); so they do for 32 x 32 panels of more than two rounds while K is short (5.5 against 5.2 us)."""
+    name = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0]
+    for g in (64, 128):
+        assert name(136, 11520, 2048, g) == name(160, 11520, 2048, g) == name(136, 13056, 3072, g) == "panel_f2_m32"
+        assert name(28, 24576, 3584, g) == "panel_f4_m32"   # one round
+        for K in (256, 512, 768):
+            assert name(24, 24064, K, g) == "panel_f2_m32" and name(24, 8192, K, g) == "panel_f1_m32"
+        assert name(24, 24064, 1024, g) == "panel_f1_m32"
