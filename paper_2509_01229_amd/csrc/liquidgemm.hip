@@ -917,28 +917,34 @@ static int select_variant(int M, int N, int K)
 // Up to 16 rows: the kernel that runs where select_variant names a stream16 variant of whole tiles (that variant
 // itself where nothing is faster).  Measured on 52 weight shapes (N 1024..12288, K 2048..20480) at 1, 4, 8 and 16 rows and 20
 // (N to 28672, K to 28672) at 1, 4, 8, 12 and 16, 560 MB of weights in rotation, us whole tiles / what runs here:
-//   * up to 128 tiles of 32 channels, half tiles: 256 instead of 128 blocks at N = 4096, and no K slices.  At 4 rows 4096 x
-//     4096 5.1 / 4.2, 4096 x 11008 8.9 / 7.2, 4096 x 8192 8.0 / 5.8, 1024 x 4096 5.0 / 3.8, 4096 x 14336 10.5 / 8.4.  D is
+//   * up to 128 tiles of 32 channels and K from 2048 on, half tiles: 256 instead of 128 blocks at N = 4096, and no K slices.  At 4
+//     rows 4096 x 4096 5.3 / 4.5, 4096 x 11008 8.9 / 7.2, 4096 x 8192 7.9 / 5.9, 1024 x 4096 5.1 / 4.0, 4096 x 14336 10.5 / 8.2.  D is
 //     the number of units that leaves the fewest loads past the end: K / 128 units over 8 waves are at most 2 x 2, 2 x
 //     3 or 2 x 4 each (4096 x 5120: 4.9 with 3, 5.4 with 4), above that over 16 waves, with very long K 2 in any number of passes.
 //     X is read twice as often, so from 13 rows long K keeps whole tiles (4096 x 11008 at 16 rows 9.1, half tiles 9.3).
-//   * up to 64 tiles two slices of K fill the CUs where K is long (2048 x 14336 at 4 rows 8.1 / 7.2; one slice 7.6)
-//   * 129..384 tiles: with a whole number of passes and few rows half tiles again (8192 x 8192 at 4 rows 9.8 / 9.0, 10240 x
-//     8192 12.9 / 11.3), else up to 320 tiles the 32-row panels, whose loads run two units ahead (8192 x 11008 at 8
-//     rows 12.6 / 11.9, 10240 x 8192 at 16 13.5 / 12.8, 6656 x 16384 at 16 16.6 / 15.1; groups of 128: 12.7 / 12.3,
-//     13.3 / 13.1, 16.4 / 15.6).  K below 6144, up to 8 rows with K from 12288 and K beyond 16384 stay (5120 x
-//     5120 6.7 against 7.5, 5120 x 13824 at 8 rows 12.1 against 12.2, 8192 x 28672 at 16 rows, groups of 128, 25.7 against 26.5).
+//     Shorter K keeps them too: a wave of half tiles issues four units' loads whatever there is, and sixteen waves of a whole tile
+//     hold as many bytes in flight (up to 4 rows, up to 128 tiles, K = 256 3.0 / 3.4, 1024 3.25 / 3.55, 1536 3.60 / 3.64, 2048 3.76 / 3.67).
+//   * up to 64 tiles two slices of K fill the CUs where K is long (2048 x 14336 at 4 rows 8.3 / 7.2; one slice 7.6), with up to
+//     16 tiles for up to 10 rows (320 x 12544 at 12 rows 6.9 / 7.3)
+//   * 129..384 tiles: with a whole number of passes and few rows half tiles again (8192 x 8192 at 4 rows 9.3 / 8.7, 10240 x
+//     8192 12.7 / 11.0), else up to 320 tiles the 32-row panels, whose loads run two units ahead (8192 x 11008 at 8
+//     rows 12.5 / 11.7, 10240 x 8192 at 16 13.1 / 12.5, 6656 x 16384 at 16 16.2 / 15.0).  K below 6144, up to 8 rows with K from 12288
+//     and K beyond 16384 stay (5120 x 5120 6.7 against 7.5, 5120 x 13824 at 8 rows 12.1 against 12.2, 8192 x 28672 at 16 rows,
+//     groups of 128, 25.7 against 26.5), and 9 and 10 rows where all sixteen waves' loads are in flight at once (7360 x 7168 at 9 rows
+//     1.03 to 1.07 of the time on panels).
 static int in_place_of_stream16(int variant, const Args &a)
 {
     const int tiles = a.N / 32, M = a.M, K = a.K;
     const char *name = nullptr;
     if (tiles <= 128) {
-        if (K <= 4096) name = "stream16_h_w8_d2";
+        if (K < 2048) name = nullptr;
+        else if (K <= 4096) name = "stream16_h_w8_d2";
         else if (K <= 6144) name = "stream16_h_w8_d3";
         else if (K <= 8192) name = tiles <= 64 && M > 12 ? "stream16_h_w8_d2_s2" : "stream16_h_w8_d4";
         else if (tiles <= 64) {
-            if (K <= 12288) name = M <= 12 ? "stream16_h_w8_d3_s2" : nullptr;
-            else if (K <= 16384) name = M <= 12 ? "stream16_h_w8_d4_s2" : nullptr;
+            const int most = tiles <= 16 ? 10 : 12;
+            if (K <= 12288) name = M <= most ? "stream16_h_w8_d3_s2" : nullptr;
+            else if (K <= 16384) name = M <= most ? "stream16_h_w8_d4_s2" : nullptr;
             else if (K <= 20480) name = M <= 4 ? "stream16_h_w8_d2_s2" : nullptr;
         } else if (K <= 16384) {
             if (M <= 12) name = K <= 12288 ? "stream16_h_w16_d3" : "stream16_h_w16_d4";
@@ -948,7 +954,7 @@ static int in_place_of_stream16(int variant, const Args &a)
     } else if (tiles <= 384 && K >= 6144 && K <= 8192 && M <= 4) {
         name = K == 6144 ? "stream16_h_w8_d3" : "stream16_h_w8_d4";
     } else if (tiles <= 256) {
-        if (K > 6144 && K <= 16384 && (M >= 9 || (K > 8192 && K < 12288))) name = "panel_f1_m32";
+        if (K > 6144 && K <= 16384 && (M >= (K <= 8192 && K % 512 == 0 ? 11 : 9) || (K > 8192 && K < 12288))) name = "panel_f1_m32";
     } else if (tiles <= 320) {
         if (K >= 6144 && K < 12288 && (M >= 5 || K > 8192)) name = "panel_f2_m32";
     }

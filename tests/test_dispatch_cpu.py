@@ -265,3 +265,21 @@ def test_panels_of_several_rounds():
         for K in (256, 512, 768):
             assert name(24, 24064, K, g) == "panel_f2_m32" and name(24, 8192, K, g) == "panel_f1_m32"
         assert name(24, 24064, 1024, g) == "panel_f1_m32"
+
+
+def test_where_half_tiles_and_panels_are_behind_whole_tiles():
+    """Up to 16 rows whole tiles stay where they were found ahead: K below 2048, 9 and 10 rows on 129..256 tiles with
+    all of a wave's loads in flight, K slices of half tiles for more than 10 rows of up to 16 tiles."""
+    def runs(M, N, K):
+        name = api.w4a8_describe_launch(M, N, K, 64)[0]
+        return name.split("[as ")[1][:-1] if "[as " in name else None
+
+    for M in (1, 4, 9, 16):
+        assert [runs(M, N, K) for N in (64, 2048, 4096) for K in (256, 512, 1024, 1536, 1792)] == [None] * 15
+        assert runs(M, 64, 2048) == runs(M, 4096, 2048) == "stream16_h_w8_d2"
+    for M in (9, 10):
+        assert runs(M, 7360, 7168) is None and runs(M, 8192, 8192) is None and runs(M, 7360, 7424) == "panel_f1_m32"
+    assert runs(11, 7360, 7168) == runs(9, 7360, 8448) == "panel_f1_m32"
+    assert runs(12, 512, 8448) is None and runs(11, 512, 12544) is None
+    assert runs(10, 512, 8448) == runs(12, 576, 8448) == "stream16_h_w8_d3_s2"
+    assert runs(10, 512, 12544) == runs(12, 576, 12544) == "stream16_h_w8_d4_s2"

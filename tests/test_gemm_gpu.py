@@ -694,11 +694,11 @@ def test_every_dispatched_panel_form(M, N, K, form):
 # not there at all, an odd tile count, and the edges of the rule
 # ---------------------------------------------------------------------------------------
 @pytest.mark.parametrize("M,N,K,form", [
-    (1, 64, 256, "stream16_h_w8_d2"), (16, 192, 4096, "stream16_h_w8_d2"), (5, 4096, 2304, "stream16_h_w8_d2"),
+    (1, 64, 2048, "stream16_h_w8_d2"), (16, 192, 4096, "stream16_h_w8_d2"), (5, 4096, 2304, "stream16_h_w8_d2"),
     (3, 2112, 20480, "stream16_h_w8_d2"), (16, 64, 4352, "stream16_h_w8_d3"), (9, 320, 6144, "stream16_h_w8_d3"),
     (4, 4160, 6144, "stream16_h_w8_d3"), (12, 64, 6400, "stream16_h_w8_d4"), (16, 2112, 8192, "stream16_h_w8_d4"),
     (4, 8256, 7936, "stream16_h_w8_d4"), (13, 128, 6400, "stream16_h_w8_d2_s2"), (1, 64, 20480, "stream16_h_w8_d2_s2"),
-    (12, 192, 8448, "stream16_h_w8_d3_s2"), (2, 2048, 12544, "stream16_h_w8_d4_s2"), (12, 2112, 8448, "stream16_h_w16_d3"),
+    (12, 576, 8448, "stream16_h_w8_d3_s2"), (2, 2048, 12544, "stream16_h_w8_d4_s2"), (12, 2112, 8448, "stream16_h_w16_d3"),
     (7, 2112, 12544, "stream16_h_w16_d4"), (16, 4160, 8192, "panel_f1_m32"),
     (1, 4224, 8448, "panel_f1_m32"), (5, 8256, 6400, "panel_f2_m32")])
 def test_every_form_in_place_of_the_16_row_kernels(M, N, K, form):
