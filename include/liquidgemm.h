@@ -214,6 +214,11 @@ int w4a8_grouped_gemm(int E, const int *row_offsets, int N, int K, int group, co
                       const float *act_scales, const void *W_packed, const uint8_t *gparams,
                       const float *w_scales, uint16_t *Y, int32_t *ACC, void *hip_stream);
 
+/* The launches of w4a8_grouped_gemm for the given rows: "<kernel>[<experts> experts, <rows> rows]", joined by
+ * "+" in the order they run (an expert whose rows run on several kernels counts in each).  Host only; text is
+ * cut to text_bytes, always terminated; "" where no expert has rows. */
+int w4a8_describe_grouped(int E, const int *row_offsets, int N, int K, int group, char *text, size_t text_bytes);
+
 /* ------------------------------------------------------------------------------------
  * W8A8 reference (Sec. 3.2, Sec. 7.3: the baseline without dequantisation that W4A8 is
  * measured against): the same tiled kernel skeleton with INT8 weights fed to the MFMA as

@@ -82,6 +82,8 @@ def lib() -> ctypes.CDLL:
     L.w4a8_dequant_dump.argtypes = [vp, vp, i, i, i, vp, vp]
     L.w4a8_grouped_gemm.restype = i
     L.w4a8_grouped_gemm.argtypes = [i, ctypes.POINTER(ctypes.c_int), i, i, i, vp, vp, vp, vp, vp, vp, vp, vp]
+    L.w4a8_describe_grouped.restype = i
+    L.w4a8_describe_grouped.argtypes = [i, ctypes.POINTER(ctypes.c_int), i, i, i, ctypes.c_char_p, sz]
     L.w4a8_quantize_activations.restype = i
     L.w4a8_quantize_activations.argtypes = [i, i, vp, vp, vp, vp, vp]
     L.w8a8_pack_weights.restype = i
@@ -455,3 +457,11 @@ def w4a8_grouped_gemm(row_offsets, X, act_scales, W_packed, gparams, w_scales, N
         _dev(out_y, torch.float16, (M, N), "out_y") if want_y else None,
         _dev(out_acc, torch.int32, (M, N), "out_acc") if want_acc else None, _stream(stream)))
     return (out_y if want_y else None), (out_acc if want_acc else None)
+
+
+def w4a8_describe_grouped(row_offsets, N: int, K: int, group: int) -> str:
+    """The launches of w4a8_grouped_gemm for the given rows, "<kernel>[<experts> experts, <rows> rows]+..."."""
+    offs = [int(r) for r in row_offsets]
+    text = ctypes.create_string_buffer(320)
+    _check(lib().w4a8_describe_grouped(len(offs) - 1, (ctypes.c_int * len(offs))(*offs), N, K, group, text, len(text)))
+    return text.value.decode()

@@ -1104,25 +1104,35 @@ static void launch_name(int variant, int M, int N, int K, char *text, size_t tex
 
 // ------------------------------------------------------------------------------------
 // Grouped GEMM: experts are sorted by their number of rows into the three kernel families
-// (16-row stream kernel, 32- or 64-row panels, tiles), and each family that is not empty gets
-// one launch over all of its experts.
+// (16-row stream kernel, 32- or 64-row panels, tiles); large experts on up to two kinds of 256-row tiles
+// and what these leave over.  Each kernel that is needed gets one launch over all of its experts, or
+// ranges of their rows; at most five in all.
 // ------------------------------------------------------------------------------------
 struct GroupedArgs {
     int E, N, K, group;
     const int *row_offsets;  // host, E + 1
     GroupedPtrs p;
     hipStream_t stream;
+    char *text = nullptr;  // set: append the launches to it and launch nothing
+    size_t text_bytes = 0;
 };
 
 template <class Kernel, class... A>
-static int launch_checked(const char *what, Kernel kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st,
-                          A... args)
+static int grouped_launch(const GroupedArgs &a, const char *name, Kernel kernel, dim3 grid, dim3 block, size_t lds,
+                          const GroupTable &t, A... more)
 {
+    if (a.text) {
+        int rows = 0;
+        for (int i = 0; i < t.count; ++i) rows += t.rows[i];
+        const size_t at = strlen(a.text);
+        snprintf(a.text + at, a.text_bytes - at, "%s%s[%d experts, %d rows]", at ? "+" : "", name, t.count, rows);
+        return LQ_OK;
+    }
     if (int rc = allow_lds(kernel, lds)) return rc;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(kernel, grid, block, lds, st, args...);
+    hipLaunchKernelGGL(kernel, grid, block, lds, a.stream, t, a.p, a.N, a.K, more...);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(LQ_ERR_HIP, "launch of %s failed: %s", what, hipGetErrorString(e));
+    if (e != hipSuccess) return fail(LQ_ERR_HIP, "launch of %s failed: %s", name, hipGetErrorString(e));
     return LQ_OK;
 }
 
@@ -1148,10 +1158,8 @@ static int grouped_tiles_run(const GroupedArgs &a, GroupTable &big)
         }
         const dim3 grid((unsigned)big_blocks64);
         const size_t lds2 = std::max<size_t>(4 * (size_t)128 * kTilePitch, 64 * 1024);
-        return g128 ? launch_checked("grouped duo", w4a8_duo_grouped_kernel<true, 2, 64>, grid, dim3(512), lds2, a.stream,
-                                     big, a.p, a.N, a.K)
-                    : launch_checked("grouped duo", w4a8_duo_grouped_kernel<false, 2, 64>, grid, dim3(512), lds2, a.stream,
-                                     big, a.p, a.N, a.K);
+        return g128 ? grouped_launch(a, "duo_m64", w4a8_duo_grouped_kernel<true, 2, 64>, grid, dim3(512), lds2, big)
+                    : grouped_launch(a, "duo_m64", w4a8_duo_grouped_kernel<false, 2, 64>, grid, dim3(512), lds2, big);
     }
     const dim3 grid((unsigned)big_blocks);
     // as for single GEMMs: two k groups per block while the grid gives at most one block per CU
@@ -1170,22 +1178,16 @@ static int grouped_tiles_run(const GroupedArgs &a, GroupTable &big)
     }
     dl = dl && big_rows > 96ll * big.count;
     if (dl)
-        return g128 ? launch_checked("grouped duo", w4a8_duo_dl_grouped_kernel<true>, grid, dim3(256),
-                                     4 * (size_t)128 * 128, a.stream, big, a.p, a.N, a.K)
-                    : launch_checked("grouped duo", w4a8_duo_dl_grouped_kernel<false>, grid, dim3(256),
-                                     4 * (size_t)128 * 128, a.stream, big, a.p, a.N, a.K);
+        return g128 ? grouped_launch(a, "duo_dl_m128", w4a8_duo_dl_grouped_kernel<true>, grid, dim3(256), 4 * (size_t)128 * 128, big)
+                    : grouped_launch(a, "duo_dl_m128", w4a8_duo_dl_grouped_kernel<false>, grid, dim3(256), 4 * (size_t)128 * 128, big);
     if (kg2)
-        return g128 ? launch_checked("grouped duo", w4a8_duo_grouped_kernel<true, 2>, grid, dim3(512), lds2, a.stream, big,
-                                     a.p, a.N, a.K)
-                    : launch_checked("grouped duo", w4a8_duo_grouped_kernel<false, 2>, grid, dim3(512), lds2, a.stream, big,
-                                     a.p, a.N, a.K);
-    return g128 ? launch_checked("grouped duo", w4a8_duo_grouped_kernel<true, 1>, grid, dim3(256), lds1, a.stream, big,
-                                 a.p, a.N, a.K)
-                : launch_checked("grouped duo", w4a8_duo_grouped_kernel<false, 1>, grid, dim3(256), lds1, a.stream, big,
-                                 a.p, a.N, a.K);
+        return g128 ? grouped_launch(a, "duo_m128_g2", w4a8_duo_grouped_kernel<true, 2>, grid, dim3(512), lds2, big)
+                    : grouped_launch(a, "duo_m128_g2", w4a8_duo_grouped_kernel<false, 2>, grid, dim3(512), lds2, big);
+    return g128 ? grouped_launch(a, "duo_m128", w4a8_duo_grouped_kernel<true, 1>, grid, dim3(256), lds1, big)
+                : grouped_launch(a, "duo_m128", w4a8_duo_grouped_kernel<false, 1>, grid, dim3(256), lds1, big);
 }
 
-// Experts of up to 64 rows as panels: one launch for all of them.
+// Experts (or what they leave over) of up to 128 rows as panels: one launch for all of them.
 template <int F, int MF>
 static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
 {
@@ -1197,9 +1199,10 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
         t.block_end[i] = (int)blocks;
     }
     const size_t lds = panel_lds_bytes(F, 8, MF, a.K / 128);
+    static_assert((F == 2 && MF == 1) || (F == 4 && MF == 2), "the names below");
     const dim3 grid((unsigned)blocks);
     auto go = [&](auto kernel) {
-        return launch_checked("grouped panel", kernel, grid, dim3(512), lds, a.stream, t, a.p, a.N, a.K);
+        return grouped_launch(a, MF == 1 ? "panel_f2_m32" : "panel_f4_m64", kernel, grid, dim3(512), lds, t);
     };
     if (blocks == (long long)t.count * groups)  // one row tile each
         return a.group == 128 ? go(&w4a8_panel_grouped_kernel<F, MF, true, true>)
@@ -1274,10 +1277,9 @@ static int grouped_solo_run(const GroupedArgs &a, const GroupTable &t)
 {
     const dim3 grid((unsigned)std::min(t.block_end[t.count - 1], std::max(cu_count(), 1)));
     const size_t lds = 4 * (size_t)256 * 128 + 4 * 1024;
-    return a.group == 128 ? launch_checked("grouped solo", w4a8_solo_grouped_kernel<true, KG>, grid, dim3(256), lds, a.stream,
-                                           t, a.p, a.N, a.K)
-                          : launch_checked("grouped solo", w4a8_solo_grouped_kernel<false, KG>, grid, dim3(256), lds, a.stream,
-                                           t, a.p, a.N, a.K);
+    const char *name = KG == 1 ? "solo16_pt_m256" : "solo16_g2_m256";
+    return a.group == 128 ? grouped_launch(a, name, w4a8_solo_grouped_kernel<true, KG>, grid, dim3(256), lds, t)
+                          : grouped_launch(a, name, w4a8_solo_grouped_kernel<false, KG>, grid, dim3(256), lds, t);
 }
 // The larger experts' row blocks of 256: time (us) of 256 x 256 and of 256 x 128 tiles, from 65
 // calls on five weight shapes (2816 x 2048 to 4096 x 14336; 4 to 64 row blocks).  A round that leaves CUs
@@ -1343,15 +1345,11 @@ static int grouped_run(const GroupedArgs &a)
         const size_t lds = (size_t)(w4 ? 4 : 8) * 2 * 8 * 64 * sizeof(int);
         int rc;
         if (w4)
-            rc = g128 ? launch_checked("grouped stream16", w4a8_stream16_grouped_kernel<4, 1, true>, grid, dim3(256),
-                                       lds, a.stream, small, a.p, a.N, a.K, groups)
-                      : launch_checked("grouped stream16", w4a8_stream16_grouped_kernel<4, 1, false>, grid, dim3(256),
-                                       lds, a.stream, small, a.p, a.N, a.K, groups);
+            rc = g128 ? grouped_launch(a, "stream16_f2_w4", w4a8_stream16_grouped_kernel<4, 1, true>, grid, dim3(256), lds, small, groups)
+                      : grouped_launch(a, "stream16_f2_w4", w4a8_stream16_grouped_kernel<4, 1, false>, grid, dim3(256), lds, small, groups);
         else
-            rc = g128 ? launch_checked("grouped stream16", w4a8_stream16_grouped_kernel<8, 1, true>, grid, dim3(512),
-                                       lds, a.stream, small, a.p, a.N, a.K, groups)
-                      : launch_checked("grouped stream16", w4a8_stream16_grouped_kernel<8, 1, false>, grid, dim3(512),
-                                       lds, a.stream, small, a.p, a.N, a.K, groups);
+            rc = g128 ? grouped_launch(a, "stream16_f2_w8", w4a8_stream16_grouped_kernel<8, 1, true>, grid, dim3(512), lds, small, groups)
+                      : grouped_launch(a, "stream16_f2_w8", w4a8_stream16_grouped_kernel<8, 1, false>, grid, dim3(512), lds, small, groups);
         if (rc) return rc;
     }
     if (mid.count && (panel64 || !big.count)) {
@@ -1419,6 +1417,22 @@ static int grouped_run(const GroupedArgs &a)
     if (g2.count)
         if (int rc = grouped_solo_run<2>(a, g2)) return rc;
     return rest.count || mid.count ? grouped_few_rows_run(a, rest, mid) : LQ_OK;
+}
+
+static int check_grouped_shape(int E, const int *row_offsets, int N, int K, int group)
+{
+    if (E < 1 || E > kMaxExperts) return fail(LQ_ERR_INVALID, "E=%d out of range (1..%d)", E, kMaxExperts);
+    if (!shape_ok(N, K, group))
+        return fail(LQ_ERR_INVALID, "bad shape N=%d K=%d group=%d (need N%%64==0, K%%256==0, group 64|128, K<=131072)",
+                    N, K, group);
+    if (!row_offsets || row_offsets[0] != 0) return fail(LQ_ERR_INVALID, "row_offsets must start at 0");
+    for (int e = 0; e < E; ++e) {
+        if (row_offsets[e + 1] < row_offsets[e]) return fail(LQ_ERR_INVALID, "row_offsets must not decrease");
+        // the kernels address an expert's rows of X with 32-bit byte offsets
+        if ((long long)(row_offsets[e + 1] - row_offsets[e]) * K >= (1ll << 32))
+            return fail(LQ_ERR_INVALID, "expert %d has rows * K >= 2^32 bytes of X; split it into two experts", e);
+    }
+    return LQ_OK;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1633,17 +1647,7 @@ int w4a8_grouped_gemm(int E, const int *row_offsets, int N, int K, int group, co
                       const float *act_scales, const void *W_packed, const uint8_t *gparams,
                       const float *w_scales, uint16_t *Y, int32_t *ACC, void *hip_stream)
 {
-    if (E < 1 || E > kMaxExperts) return fail(LQ_ERR_INVALID, "E=%d out of range (1..%d)", E, kMaxExperts);
-    if (!shape_ok(N, K, group))
-        return fail(LQ_ERR_INVALID, "bad shape N=%d K=%d group=%d (need N%%64==0, K%%256==0, group 64|128, K<=131072)",
-                    N, K, group);
-    if (!row_offsets || row_offsets[0] != 0) return fail(LQ_ERR_INVALID, "row_offsets must start at 0");
-    for (int e = 0; e < E; ++e) {
-        if (row_offsets[e + 1] < row_offsets[e]) return fail(LQ_ERR_INVALID, "row_offsets must not decrease");
-        // the kernels address an expert's rows of X with 32-bit byte offsets
-        if ((long long)(row_offsets[e + 1] - row_offsets[e]) * K >= (1ll << 32))
-            return fail(LQ_ERR_INVALID, "expert %d has rows * K >= 2^32 bytes of X; split it into two experts", e);
-    }
+    if (int rc = check_grouped_shape(E, row_offsets, N, K, group)) return rc;
     if (row_offsets[E] == 0) return LQ_OK;
     if (!Y && !ACC) return fail(LQ_ERR_INVALID, "no output pointer");
     if (!X || !W_packed || !gparams) return fail(LQ_ERR_INVALID, "null input pointer");
@@ -1657,6 +1661,19 @@ int w4a8_grouped_gemm(int E, const int *row_offsets, int N, int K, int group, co
                       reinterpret_cast<__half *>(Y), ACC, (size_t)N * K / 32, (size_t)2 * N * K / group};
     a.stream = static_cast<hipStream_t>(hip_stream);
     return grouped_run(a);
+}
+
+int w4a8_describe_grouped(int E, const int *row_offsets, int N, int K, int group, char *text, size_t text_bytes)
+{
+    if (int rc = check_grouped_shape(E, row_offsets, N, K, group)) return rc;
+    char words[320] = "";
+    GroupedArgs a{};
+    a.E = E, a.N = N, a.K = K, a.group = group, a.row_offsets = row_offsets;
+    a.text = words, a.text_bytes = sizeof(words);
+    if (row_offsets[E] > 0)
+        if (int rc = grouped_run(a)) return rc;
+    if (text && text_bytes) snprintf(text, text_bytes, "%s", words);
+    return LQ_OK;
 }
 
 int w8a8_gemm(int M, int N, int K, const int8_t *X, const float *act_scales, const void *W8_packed,

@@ -283,3 +283,29 @@ def test_where_half_tiles_and_panels_are_behind_whole_tiles():
     assert runs(12, 512, 8448) is None and runs(11, 512, 12544) is None
     assert runs(10, 512, 8448) == runs(12, 576, 8448) == "stream16_h_w8_d3_s2"
     assert runs(10, 512, 12544) == runs(12, 576, 12544) == "stream16_h_w8_d4_s2"
+
+
+def _grouped(rows, N, K, g):
+    offsets = [0]
+    for r in rows:
+        offsets.append(offsets[-1] + r)
+    return api.w4a8_describe_grouped(offsets, N, K, g)
+
+
+def test_reported_grouped_launches():
+    """What w4a8_describe_grouped says a grouped call launches: every row exactly once, at most five launches."""
+    import re
+
+    assert _grouped([0, 0], 256, 512, 64) == ""
+    assert _grouped([3, 0, 16], 256, 512, 64) == "stream16_f2_w8[2 experts, 19 rows]"
+    assert _grouped([17, 32, 0, 1], 256, 512, 64) == "panel_f2_m32[3 experts, 50 rows]"
+    assert _grouped([40, 64, 9], 4096, 4096, 64) == "panel_f4_m64[3 experts, 113 rows]"
+    assert _grouped([760, 741, 768, 733, 742, 789, 722, 745], 4096, 14336, 64).startswith("solo16_")
+    for rows, N, K, g in [([1500, 20, 1537, 1400, 1700, 7], 4096, 4096, 64), ([1] * 64, 2816, 256, 128), ([129, 128, 127, 33, 257], 64, 256, 64),
+                          ([700, 5, 520, 900, 40, 256, 1000], 4160, 768, 128), ([90, 100, 3, 17, 65], 8192, 1024, 64)]:
+        parts = [re.fullmatch(r"([a-z0-9_]+)\[(\d+) experts, (\d+) rows\]", part) for part in _grouped(rows, N, K, g).split("+")]
+        assert all(parts) and len(parts) <= 5 and len({p[1] for p in parts}) == len(parts)
+        assert sum(int(p[3]) for p in parts) == sum(rows)
+    for E, offsets, N, K, g in [(2, [0, 3, 2], 256, 512, 64), (1, [1, 4], 256, 512, 64), (1, [0, 4], 100, 512, 64), (1, [0, 4], 256, 512, 32)]:
+        with pytest.raises(api.LiquidGemmError):
+            api.w4a8_describe_grouped(offsets, N, K, g)
