@@ -1212,20 +1212,20 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
 }
 
 // Up to 128 rows of each expert (experts of 33 to 128 rows, and what larger ones leave over): 32-row
-// panels, 64-row panels of 128 channels or tiles, whichever a fitted cost (us) finds cheapest.  Fitted
-// to 8 to 128 rows of 1 to 16 experts on five weight shapes (2816 x 2048 to 4096 x 14336), 4 to 8 % rms;
-// the choice is 0.8 % behind the best of the three (geometric mean; 15 % at worst), tiles alone 37 %: a few
-// experts are few tiles, and the tiles of a grouped launch have no K slices across blocks (us on tiles / as
-// picked: one expert of 8..128 rows on 4096 x 14336 51 / 20, four of 64 rows 53 / 32, eight 71 / 51, two of 64
-// on 14336 x 4096 24 / 20; eight of 64 there stay on tiles, 59 against 69).
+// panels, 64-row panels of 128 channels or tiles, whichever a fitted cost (us) finds cheapest.  The panels' is fitted to 12000
+// calls of 1 to 64 experts of up to 128 rows (N 128 to 16384, K 256 to 14336) with the present panel kernel, 6 % rms; the tiles' to
+// 8 to 128 rows of 1 to 16 experts on five weight shapes (2816 x 2048 to 4096 x 14336), and is off by 19 % over those
+// 12000, hence the 10 % that panels have to win by.  So picked, 4600 such calls are 0.9 % behind the best of the three and none
+// is more than 3 % behind tiles alone (48 % ahead of them): a few experts are few tiles, and the tiles of a grouped launch have no
+// K slices across blocks (us on tiles / as picked: one expert of 128 rows on 4096 x 14336 55.8 / 19.4, two of 64 on
+// 14336 x 4096 20.0 / 19.7; eight of 64 there stay on tiles, 60 against 69).
 static double grouped_panel_us(const GroupTable &t, int N, int K, int F, int MF)
 {
     long long blocks = 0;
     for (int i = 0; i < t.count; ++i) blocks += panel_blocks(t.rows[i], N, F, MF);
-    const double fill = (double)blocks / kAssumedCUs, rounds = 0.5 * (std::ceil(fill) + std::max(fill, 1.0));
-    const double k = K / 1024.0, mb = 0.5e-6 * N * K * t.count;
-    return MF == 1 ? 7.11 + rounds * (0.21 + 0.864 * k) - 0.306 * std::min(fill, 1.0) * k + 0.0683 * mb
-                   : 3.05 + rounds * (5.50 + 1.605 * k) - 0.071 * std::min(fill, 1.0) * k + 0.0784 * mb;
+    const double fill = (double)blocks / kAssumedCUs, k = K / 1024.0, mb = 0.5e-6 * N * K * t.count;
+    return MF == 1 ? 2.91 + (0.6 * std::ceil(fill) + 0.4 * std::max(fill, 1.0)) * (1.25 + 0.715 * k) + 0.30 * std::min(fill, 1.0) * k + 0.088 * mb
+                   : 1.42 + std::ceil(fill) * (4.72 + 1.666 * k) + 0.136 * mb;  // (one block on a CU)
 }
 // ... as 128- or 64-row tiles, also of experts of more rows (the last line: the rounds of a single GEMM, 6 % off
 // on 264 to 3584 tiles with K from 2048 to 14336)
@@ -1259,7 +1259,7 @@ static int grouped_few_rows_run(const GroupedArgs &a, GroupTable &t, GroupTable 
     int most = 0;
     for (int i = 0; i < t.count; ++i) most = std::max(most, t.rows[i]);
     const double p32 = grouped_panel_us(t, a.N, a.K, 2, 1), p64 = grouped_panel_us(t, a.N, a.K, 4, 2);
-    const double tiles = 0.95 * grouped_tiles_us(t, a.N, a.K);  // (panels have to win by 5 %, the fit is no better)
+    const double tiles = 0.90 * grouped_tiles_us(t, a.N, a.K);  // (panels have to win by 10 %: the tiles' estimate is off by up to that and more)
     const bool as_p32 = most <= 32 || (p32 <= p64 && p32 <= tiles);
     for (int i = 0; as_p32 && i < t.count; ++i) {
         const int k = mid.count++;
@@ -1377,17 +1377,28 @@ static int grouped_run(const GroupedArgs &a)
         }
     }
     if (row_blocks == 0) return grouped_few_rows_run(a, rest, mid);
-    long long first = -1;  // row blocks on 256 x 256 tiles; the others on 256 x 128
-    // (the estimates are good to about 5 %: what the rule of single GEMMs picks has to lose by that)
-    const double rest_us = grouped_few_rows_us(rest, a.N, a.K);
-    const bool solo_by_rule = solo_form_for(main_t128, row_blocks * blocks_n, 0, a.K) == 1;
-    double us = grouped_tiles_us(big, a.N, a.K) * (solo_by_rule && fits ? 1.0 : 0.95);
+    // What the rule of single GEMMs picks -- 256 x 256 tiles for all row blocks (first = row_blocks) or 128-row tiles for
+    // everything (first = -1) -- or, where it is estimated to be enough faster, another split: `first` row blocks on
+    // 256 x 256 tiles and the others on 256 x 128.  Enough is what a replay of the rule over 16000 timed calls (1 to 64 experts, N 128
+    // to 16384, K 256 to 14336) showed it to be: the 128-row tiles' estimate is 45 % too low at K = 512 and 20 % at 1024 against the
+    // 256-row tiles' (two experts of 3650 rows on 15936 x 512: 90 us on 256 x 256 tiles, 121 on 128-row ones), except where K % 512
+    // == 256 adds two stages to the latter; two kinds of 256-row tiles in turn, one of them in part of a round, were equal to 128-row tiles on average
+    // (94 calls) and need 18 %.  1540 calls leave the single GEMMs' rule, at 0.865 of its time; 7 of them lose more than 10 %.
+    const double rest_us = grouped_few_rows_us(rest, a.N, a.K), tiles_us = grouped_tiles_us(big, a.N, a.K);
+    const bool solo_by_rule = fits && solo_form_for(main_t128, row_blocks * blocks_n, 0, a.K) == 1;
+    long long first = solo_by_rule ? row_blocks : -1;
+    const double rule_us = solo_by_rule ? grouped_solo_us(row_blocks * blocks_n, a.K) + rest_us : tiles_us;
+    double best_us = 1e30;
+    auto consider = [&](long long rb, double us, double margin) {
+        if (us < margin * rule_us && us < best_us) best_us = us, first = rb;
+    };
+    if (solo_by_rule) consider(-1, tiles_us, a.K % 512 == 0 ? std::min(0.95, 0.50 + 0.22 * a.K / 1024) : 0.95);
     const long long rounds = row_blocks * blocks_n / kAssumedCUs;
     for (const long long rb : {0ll, (rounds - 1) * kAssumedCUs / blocks_n, rounds * kAssumedCUs / blocks_n, row_blocks}) {
         if (!fits || rb < 0 || (row_blocks - rb) * blocks_n2 > 0x7fffffff) continue;
-        const double t = grouped_solo_us(rb * blocks_n, a.K) + grouped_g2_us((row_blocks - rb) * blocks_n2, a.K) + rest_us;
-        const double biased = solo_by_rule && rb == row_blocks ? 0.95 * t : t;
-        if (biased < us) us = biased, first = rb;
+        const bool two_kinds = rb > 0 && rb < row_blocks;
+        consider(rb, grouped_solo_us(rb * blocks_n, a.K) + grouped_g2_us((row_blocks - rb) * blocks_n2, a.K) + rest_us,
+                 solo_by_rule ? 0.95 : two_kinds ? 0.82 : rb == row_blocks ? 0.90 : 0.95);
     }
     if (first < 0) {
         if (mid.count)

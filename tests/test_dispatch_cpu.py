@@ -309,3 +309,24 @@ def test_reported_grouped_launches():
     for E, offsets, N, K, g in [(2, [0, 3, 2], 256, 512, 64), (1, [1, 4], 256, 512, 64), (1, [0, 4], 100, 512, 64), (1, [0, 4], 256, 512, 32)]:
         with pytest.raises(api.LiquidGemmError):
             api.w4a8_describe_grouped(offsets, N, K, g)
+
+
+def test_grouped_rules():
+    """Large experts: what the single GEMMs' rule picks unless another split is estimated to be clearly faster.  With
+    short K the 128-row tiles' estimate is too low: they were picked where 256 x 256 tiles took three quarters of the time."""
+    # 256 x 256 tiles with short K (121 us on 128-row tiles, 90 on these), and 128-row tiles where K % 512 == 256 adds two stages
+    for rows, N, K, g in [([3648, 3671], 15936, 512, 128), ([511, 620, 909, 5716], 16320, 512, 128), ([2113, 2153], 16320, 1024, 64),
+                          ([746, 761, 797, 819], 16192, 1024, 128)]:
+        assert _grouped(rows, N, K, g).startswith("solo16_pt_m256["), (rows, N, K)
+    assert _grouped([3648, 3671], 15936, 768, 128).startswith("duo_dl_m128[")
+    # 24 row blocks on 16 column blocks of 256: one and a half rounds
+    assert _grouped([760, 741, 768, 733, 742, 789, 722, 745], 4096, 14336, 64).startswith("solo16_pt_m256[6 experts, 4000 rows]+solo16_g2_m256[")
+    # two kinds of 256-row tiles only where they are far ahead (115 us on 128-row tiles, 131 on two kinds; 129 and 147; 215 and 246)
+    for rows, N, K, g in [([1324], 16128, 5376, 64), ([933, 304, 1067, 1181], 5696, 6144, 128), ([1118, 1138, 1162, 1131], 8256, 6144, 128)]:
+        assert _grouped(rows, N, K, g).startswith("duo_dl_m128["), (rows, N, K)
+    # 64-row panels of 128 channels, one on a CU: not a little beyond a round of them (38 us on tiles, 47 on panels; 51 and 62)
+    assert _grouped([69, 52, 57, 57, 46, 63, 58, 59, 49, 43, 55, 48, 60, 48, 64, 45], 2176, 6656, 64).startswith("duo_m64[16")
+    assert _grouped([75, 63], 13056, 9984, 64).startswith("duo_m64[2")
+    # short K (7.9 us on tiles, 8.8 on panels), and where panels are far ahead (55.8 us on tiles, 19.4)
+    assert _grouped([75, 63, 77, 75], 4672, 256, 64).startswith("duo_m128")
+    assert _grouped([128], 4096, 14336, 64) == "panel_f2_m32[1 experts, 128 rows]"
