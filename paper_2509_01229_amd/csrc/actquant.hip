@@ -85,8 +85,9 @@ __device__ __forceinline__ float max_abs8(const float (&f)[8], float m)
 // reciprocal within one unit), hence they round to the same integer unless the product is within 3e-5
 // of a tie.  Only then (or where a value is not finite) that value is redone with the IEEE division,
 // so the result is always that of the division.  A wave of 512 values meets one 3 times in 100, and a small call
-// lasts as long as its slowest wave: redoing one value at a time, where it redid all 8 of the lane within
-// 1e-4 of a tie, takes 2.77 us to 2.50 on 128 x 4096, 3.55 to 3.17 on 128 x 8192, 8.3 to 7.7 on 1000 x 8192.
+// lasts as long as its slowest wave, hence a branch for each of the lane's values: redoing all 8 takes 1.02 to 1.06 of the
+// time (8000 calls).  Where most values are ties a loop over the lane's, one selected at a time, takes as long on
+// Gaussian values and up to twice as long on these (1311 x 27584 of halves 63 us, all 8 35.7, here 36.8).
 __device__ __forceinline__ uint2 round8(const float (&f)[8], float s, float rcp_s)
 {
     constexpr float kMagic = 0x1.8p23f;
@@ -99,15 +100,11 @@ __device__ __forceinline__ uint2 round8(const float (&f)[8], float s, float rcp_
         u[e] = __builtin_bit_cast(uint32_t, t);
     }
     // (a branch the compiler must not turn into divisions and selects for everybody)
-    while (__builtin_expect_with_probability(ties != 0, 0, 0.999)) {
-        const uint32_t first = ties & -ties;
-        float x = f[0];
+    if (__builtin_expect_with_probability(ties != 0, 0, 0.999)) {
 #pragma unroll
-        for (int e = 1; e < 8; ++e) x = first == 1u << e ? f[e] : x;
-        const uint32_t q = (uint32_t)(int)fminf(fmaxf(__builtin_rintf(x / s), -127.0f), 127.0f);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = first == 1u << e ? q : u[e];
-        ties ^= first;
+        for (int e = 0; e < 8; ++e)
+            if (__builtin_expect_with_probability((ties >> e) & 1, 0, 0.999))
+                u[e] = (uint32_t)(int)fminf(fmaxf(__builtin_rintf(f[e] / s), -127.0f), 127.0f);
     }
     uint32_t w[2];
 #pragma unroll
@@ -208,8 +205,10 @@ __global__ __launch_bounds__(kLongThreads) void quantize_act_long_kernel(
 //     token once.
 // About 10 instructions per element with smooth scales, 6 without; large calls move their bytes at
 // the rate of a copy or near it, small ones take the launch, one load and one store.
+// Without smooth scales eight waves a SIMD are asked for: 1024 threads of four pieces at 66 registers instead of 63 ran one
+// block on a CU instead of two, at up to 1.28 of the time.
 template <bool SMOOTH, int ITERS, int NT, bool SEVERAL>
-__global__ __launch_bounds__(NT) void quantize_act_rows_kernel(
+__global__ __launch_bounds__(NT, SMOOTH ? 1 : 8) void quantize_act_rows_kernel(
     int M, int K, int R, int lg_shares, const __half *__restrict__ X, const float *__restrict__ smooth,
     int8_t *__restrict__ Q, float *__restrict__ sx)
 {

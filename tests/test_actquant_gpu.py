@@ -311,3 +311,48 @@ def test_quantize_then_gemm_matches_oracle_chain():
     torch.cuda.synchronize()
     assert np.array_equal(ACC.cpu().numpy(), ACC_ref)
     H.assert_fp16_close(Y.cpu().numpy(), ref64, "chain")
+
+
+def _us(X16s, n=24, reps=9):
+    """Microseconds a call, from replays of a graph that takes the inputs in turn (the median replay)."""
+    import torch
+
+    outs = [(torch.empty(x.shape, dtype=torch.int8, device="cuda"), torch.empty(x.shape[0], device="cuda")) for x in X16s]
+
+    def calls():
+        for i in range(n):
+            api.w4a8_quantize_activations(X16s[i % len(X16s)], out_q=outs[i % len(X16s)][0], out_scales=outs[i % len(X16s)][1])
+
+    calls()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    times = []
+    for _ in range(reps + 1):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / n)
+    return sorted(times[1:])[reps // 2]
+
+
+@pytest.mark.parametrize("M,K", [(2854, 6264), (1311, 27584)])
+def test_tokens_full_of_ties_are_not_much_slower(M, K):
+    """Every value half an integer of scale 1, so that each needs the division.  A loop over a lane's ties, one selected at
+    a time, took 2.7 times as long as on Gaussian values; the divisions one by one or all 8 take 1.5 to 1.7 times."""
+    import torch
+
+    _say(f"actquant ties M={M} K={K}")
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    gauss = [torch.randn((M, K), device="cuda", generator=gen).half() for _ in range(4)]
+    ties = [torch.randint(-126, 126, (M, K), device="cuda", generator=gen).half() + 0.5 for _ in range(4)]
+    for x in ties:
+        x[:, 0] = 127
+    q, s = api.w4a8_quantize_activations(ties[0])
+    assert torch.equal(s, torch.ones_like(s)) and torch.equal(q, torch.round(ties[0].float()).to(torch.int8))
+    g, t = _us(gauss), _us(ties)
+    _say(f"  Gaussian {g:.1f} us, ties {t:.1f} us")
+    assert t < 2.1 * g
