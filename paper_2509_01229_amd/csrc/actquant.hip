@@ -310,8 +310,9 @@ static void launch_rows(int M, int K, int R, int lg_shares, const __half *X, con
 //     15.6), with three pieces each up to 6144 (11.9 on 4096 x 4104, 13.3 on 4096 x 5120; 512 threads of
 //     two pieces, nearly half of them past the end: 15.0 and 15.8) and four from there on (18.2 on 4096 x
 //     8192, 512 threads: 19.0; with 1024 tokens 7.7 and 7.5, hence from 2048 tokens), one up to 2048 columns
-//     (11.0 / 15.5 on 8192 x 2048); 768 threads of two pieces up to 12288 (36.8 on 6000 x 11008, 512 threads of
-//     three: 37.9); 512 threads above (40.2 / 43.5 on 6000 x 14336), three blocks
+//     (11.0 / 15.5 on 8192 x 2048); 512 threads of three up to 10240 (7880 x 8680 36.0; 768 threads of two, nearly
+//     a third of them past the end: 41.1; with 1536 tokens equal, hence from 2048), 768 threads of two pieces up to 12288 (36.8
+//     on 6000 x 11008, 512 threads of three: 37.9); 512 threads above (40.2 / 43.5 on 6000 x 14336), three blocks
 //     of them on a CU instead of four where the call moves more than the memory-side cache holds (72.3 / 74.5 on
 //     8192 x 16384, 62.5 / 64.2 on 8192 x 14336; below that four are ahead, 32.9 / 33.8 on 4096 x 16384);
 //   many tokens with smooth scales: from 1024 tokens on several tokens per block, as many as leave two
@@ -344,6 +345,7 @@ static void launch_quantize(int M, int K, const __half *X, const float *smooth, 
     if constexpr (!SMOOTH) {
         if (n8 <= 768 && M >= 1024) return launch_rows<SMOOTH, 3, 256>(M, K, 1, 0, X, smooth, Q, sx, st);
         if (n8 <= 1024 && M >= 2048) return launch_rows<SMOOTH, 4, 256>(M, K, 1, 0, X, smooth, Q, sx, st);
+        if (n8 > 1024 && n8 <= 1280 && M >= 2048) return launch_rows<SMOOTH, 3, 512>(M, K, 1, 0, X, smooth, Q, sx, st);
         if (n8 > 1536 && n8 <= 2048 && (size_t)M * K >= (96u << 20))
             return launch_rows<SMOOTH, 4, 512>(M, K, 1, 0, X, smooth, Q, sx, st, 48 * 1024);
     }

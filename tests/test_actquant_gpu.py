@@ -356,3 +356,16 @@ def test_tokens_full_of_ties_are_not_much_slower(M, K):
     g, t = _us(gauss), _us(ties)
     _say(f"  Gaussian {g:.1f} us, ties {t:.1f} us")
     assert t < 2.1 * g
+
+
+def test_block_shape_past_8192_columns():
+    """Many tokens of 8680 columns keep the pace of 8192.  768 threads of two pieces, nearly a third of them past the
+    end, took 1.05 to 1.11 of the time of 512 threads of three there."""
+    import torch
+
+    _say("actquant 7880 tokens of 8192 and 8680 columns")
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    a, b = ([torch.randn((7880, K), device="cuda", generator=gen).half() for _ in range(4)] for K in (8192, 8680))
+    t, u = _us(a) / 8192, _us(b) / 8680
+    _say(f"  {7880 * 3e-6 / t:.2f} and {7880 * 3e-6 / u:.2f} TB/s")
+    assert u < 1.025 * t
