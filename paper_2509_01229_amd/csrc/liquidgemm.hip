@@ -1018,6 +1018,12 @@ static int check_device_args(const Args &a)
     return LQ_OK;
 }
 
+static void panel_name(const PanelChoice &c, char *text, size_t text_bytes)
+{
+    const int n = snprintf(text, text_bytes, "panel_f%d_m%d", c.form->F, 32 * c.form->MF);
+    if (c.S > 1 && (size_t)n < text_bytes) snprintf(text + n, text_bytes - n, "_s%d", c.S);
+}
+
 static int run_rows(int variant, const Args &a)
 {
     const bool dispatched = variant < 0;
@@ -1033,6 +1039,8 @@ static int run_rows(int variant, const Args &a)
     // independent, so the result is that of one launch.
     const long long rows_max = ((1ll << 32) - 1) / a.K / 256 * 256;
     size_t need_max = 0;
+    int ran = variant;  // (for the error below)
+    PanelChoice ran_panel;
     for (long long r0 = 0; r0 < a.M; r0 += rows_max) {
         Args c = a;
         size_t need = 0;
@@ -1045,12 +1053,16 @@ static int run_rows(int variant, const Args &a)
         const int runs = dispatched && a.M <= 16 ? in_place_of_stream16(variant, c) : variant;
         const PanelChoice panel = dispatched && is_few_tiles(variant) ? panel_instead_of_tiles(c) : PanelChoice{};
         if (int rc = panel.form ? panel.form->launch(c, panel.S) : kVariants[runs].fn(c)) return rc;
+        ran = runs, ran_panel = panel;
         need_max = std::max(need_max, need);
     }
     if (a.query) return *a.query = need_max, LQ_OK;
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return fail(LQ_ERR_HIP, "launch of %s failed: %s", kVariants[variant].name, hipGetErrorString(e));
+    if (e != hipSuccess) {
+        char panel[32];
+        if (ran_panel.form) panel_name(ran_panel, panel, sizeof(panel));
+        return fail(LQ_ERR_HIP, "launch of %s failed: %s", ran_panel.form ? panel : kVariants[ran].name, hipGetErrorString(e));
+    }
     return LQ_OK;
 }
 
@@ -1094,12 +1106,10 @@ static void launch_name(int variant, int M, int N, int K, char *text, size_t tex
     PanelChoice panel{};
     if (kVariants[variant].fn == &launch_panel_auto) panel = choose_panel(M, N, K, workspace_limit(a));
     else if (dispatched && is_few_tiles(variant)) panel = panel_instead_of_tiles(a);
-    if (!panel.form)
-        snprintf(text, text_bytes, "%s", kVariants[variant].name);
-    else if (panel.S == 1)
-        snprintf(text, text_bytes, "panel_f%d_m%d", panel.form->F, 32 * panel.form->MF);
+    if (panel.form)
+        panel_name(panel, text, text_bytes);
     else
-        snprintf(text, text_bytes, "panel_f%d_m%d_s%d", panel.form->F, 32 * panel.form->MF, panel.S);
+        snprintf(text, text_bytes, "%s", kVariants[variant].name);
 }
 
 // ------------------------------------------------------------------------------------

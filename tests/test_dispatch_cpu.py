@@ -330,3 +330,18 @@ def test_grouped_rules():
     # short K (7.9 us on tiles, 8.8 on panels), and where panels are far ahead (55.8 us on tiles, 19.4)
     assert _grouped([75, 63, 77, 75], 4672, 256, 64).startswith("duo_m128")
     assert _grouped([128], 4096, 14336, 64) == "panel_f2_m32[1 experts, 128 rows]"
+
+
+def test_a_failed_launch_names_the_kernel_that_ran():
+    """Without a GPU every launch fails; the error names the kernel that was launched, not the one it stands for."""
+    import ctypes
+
+    import torch
+
+    if torch.cuda.is_available():
+        pytest.skip("the launches have to fail")
+    buf = ctypes.create_string_buffer(4096 + 16)
+    p = ctypes.c_void_p((ctypes.addressof(buf) + 15) // 16 * 16)   # (never read: nothing is launched)
+    for M, N, K, name in [(4, 4096, 4096, "stream16_h_w8_d2"), (4, 4096, 11008, "stream16_h_w16_d3"), (4, 4096, 1024, "stream16_f1_w16_s1")]:
+        with pytest.raises(api.LiquidGemmError, match=f"launch of {name} failed"):
+            api._check(api.lib().w4a8_gemm(M, N, K, 64, p, p, p, p, p, p, None, 0, None))
