@@ -444,21 +444,28 @@ def test_hip_graph_replays_of_split_k_kernels():
             assert torch.equal(other, eager2)
 
 
-def test_workspace_init_and_concurrent_streams():
+@pytest.mark.parametrize("M,N,K,g,kernel", [
+    (16, 2048, 8192, 64, "stream16_h_w8_d2_s2"), (8, 1024, 8448, 64, "stream16_h_w8_d3_s2"),   # half tiles with two K slices
+    (16, 2048, 12544, 64, "stream16_f1_w8"),       # whole tiles with two
+    (64, 1088, 6912, 64, "panel_f1_m32_s3"),       # panels with three
+    (70, 12672, 2304, 64, "duo_m64"),              # 64-row tiles
+])
+def test_workspace_init_and_concurrent_streams(M, N, K, g, kernel):
     """The split-K state lives in the caller's workspace: a dirty buffer works after
     w4a8_workspace_init, and calls that overlap on two streams, each with its own workspace,
     do not disturb each other."""
     import torch
 
-    M, N, K, g = 8, 1024, 8192, 64          # stream16 with grid split-K
-    assert api.w4a8_variant_name(api.w4a8_select_variant(M, N, K, g)).startswith("stream16")
+    name, used = api.w4a8_describe_launch(M, N, K, g)
+    _say(f"workspace and streams M={M} N={N} K={K} -> {name}, {used} bytes")
+    assert name.split("[as ")[-1].rstrip("]") == kernel and used > 32768   # (tickets and partial sums)
     P = H.Problem(N, K, g, seed=77)
     X, s_x = I.make_activations(M, K, seed=78)
     ACC_ref, _ = P.oracle_gemm(X, s_x)
     ref = torch.from_numpy(ACC_ref).cuda()
     dX = torch.from_numpy(X).cuda()
     need = api.w4a8_gemm_workspace_size(M, N, K, g)
-    assert need > 32768
+    assert need >= used
     _say("dirty workspace + init")
     dirty = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
     api.w4a8_workspace_init(dirty)

@@ -157,19 +157,29 @@ def test_grouped_full_size_layer_all_families():
                             f"expert {e}")
 
 
-@pytest.mark.parametrize("K", [1024, 768])
-def test_grouped_large_experts_take_256_row_tiles(K):
+def _kernels(rows, N, K, g):
+    """The kernels that a grouped call launches for these rows, in their order."""
+    text = api.w4a8_describe_grouped([0] + [int(v) for v in np.cumsum(rows)], N, K, g)
+    return [part.split("[")[0] for part in text.split("+")]
+
+
+@pytest.mark.parametrize("K,kernels", [
+    (1024, ["stream16_f2_w8", "solo16_pt_m256", "panel_f2_m32"]), (2304, ["stream16_f2_w8", "solo16_pt_m256", "panel_f2_m32"]),
+    (768, ["stream16_f2_w8", "duo_dl_m128"])])
+def test_grouped_large_experts_take_256_row_tiles(K, kernels):
     """Experts of several hundred rows on a layer wide enough that whole rounds of 256 x 256 tiles
     pay: the big experts run as one persistent launch of the one-wave-per-SIMD kernel over all of
     them (ragged last row tiles of 8, 132 and 188 rows, an expert of exactly 256 rows, tile
     boundaries between experts inside a block's stream), the small ones in their own families.
-    Also with K % 512 == 256 (two added stages of zero weights per tile).
+    Also with K % 512 == 256 (two added stages of zero weights per tile); with K = 768 these two are half of what
+    there is, and 128-row tiles are ahead.
     Checked in full against the exact float64 product of the oracle's dequantised weights."""
     import torch
 
     E, N, g = 7, 4096, 128
     rows = [700, 5, 520, 900, 40, 256, 1000]
     _say(f"grouped 256-row tiles E={E} N={N} K={K} rows={rows}")
+    assert _kernels(rows, N, K, g) == kernels
     Ws = [WL.make_weights(N, K, 0.02, seed=300 + e) for e in range(E)]
     packs = [api.liquidquant_pack_weights(W, g) for W in Ws]
     d_packed = torch.from_numpy(np.concatenate([p[0] for p in packs])).cuda()
@@ -207,19 +217,26 @@ def test_panel_groups(E, N, K, g, rows):
     Experts(E, N, K, g, seed=K).check(rows, seed=N, what=f"rows {rows}")
 
 
-@pytest.mark.parametrize("N,K,g,rows", [
-    # 24 row blocks: 16 on 256 x 256 tiles, 8 on 256 x 128; the rests of 1 and 120 rows join the expert of 20 as panels
-    (4096, 4096, 64, [1500, 20, 1537, 1400, 1700]),
-    (4096, 4864, 128, [1000, 900]),                # 256 x 128 tiles alone, K % 512 == 256
-    (4096, 4096, 64, [100, 12, 97, 128, 65]),      # 64-row panels of two row tiles, the smallest expert on 32-row panels
-    (8192, 1024, 128, [100, 97, 128, 66, 90, 100, 3, 120, 113]),   # tiles, and the smallest expert on panels
+@pytest.mark.parametrize("N,K,g,rows,kernels", [
+    # 20 row blocks: 14 on 256 x 256 tiles, 6 on 256 x 128 and a rest of 7 rows; the last tile of either kind has 64
+    # channels, K % 512 == 256 adds two stages of zero weights to both
+    (4416, 4864, 128, [1487, 1468, 1031, 173, 950], ["solo16_pt_m256", "solo16_g2_m256", "panel_f2_m32"]),
+    (2624, 1280, 64, [1185, 949, 647], ["solo16_g2_m256"]),   # 256 x 128 tiles alone, the same edges across experts
+    (3520, 4864, 64, [80, 607, 1355, 24, 636], ["solo16_g2_m256", "panel_f2_m32", "panel_f4_m64"]),   # rests on 64-row panels
+    (4864, 1024, 128, [367, 29, 457, 1373], ["solo16_pt_m256", "panel_f2_m32", "panel_f4_m64"]),
+    (4096, 4096, 64, [1500, 20, 1537, 1400, 1700], ["panel_f2_m32", "duo_dl_m128"]),   # rests of 1 and 120 rows in the tiles' launch
+    (4096, 4864, 128, [1000, 900], ["duo_m128_g2"]),
+    (4096, 4096, 64, [100, 12, 97, 128, 65], ["stream16_f2_w8", "panel_f4_m64"]),   # 64-row panels of two row tiles
+    (8192, 1024, 128, [100, 97, 128, 66, 90, 100, 3, 120, 113], ["stream16_f2_w8", "duo_m128_g2"]),
+    (4096, 8448, 128, [100, 12, 97, 128, 65], ["panel_f2_m32", "panel_f4_m64"]),   # long K: the smallest expert on 32-row panels
 ])
-def test_row_blocks_and_rests(N, K, g, rows):
+def test_row_blocks_and_rests(N, K, g, rows, kernels):
     """Larger experts as two kinds of 256-row tiles and what they leave over, against the float64 product
     (exact: |ACC| < 2^53) of the weights that the layout hook dequantises."""
     import torch
 
     _say(f"grouped row blocks N={N} K={K} g={g} rows={rows}")
+    assert _kernels(rows, N, K, g) == kernels
     E = len(rows)
     cb, gb = api.liquidquant_packed_size(N, K, g)
     gen = torch.Generator(device="cuda").manual_seed(K)

@@ -25,15 +25,18 @@ def test_static_workspace_entry_point_matches_w4a8_gemm():
 
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
-    # 256-row tiles with K slices (a matrix of partial sums per slice: nearly all of the built-in
-    # workspace), the 128-row tiled kernel with K slices, then the 64-row and 16-row stream kernels
-    # with K slices (smaller each time), then a shape that uses no workspace at all
-    cases = [(256, 6144, 16384, 128), (200, 1024, 4096, 128), (48, 4096, 2048, 64), (8, 1024, 8192, 64),
-             (4096 + 40, 512, 512, 64)]
-    for M, N, K, g in cases:
-        picked = api.w4a8_variant_name(api.w4a8_select_variant(M, N, K, g))
+    # 256-row tiles with K slices (a matrix of partial sums per slice and no tickets), then kernels that exchange partial
+    # tiles by tickets: 64-row tiles, 64- and 32-row panels, half and whole tiles of the 16-row kernel, half
+    # tiles again -- the tickets of each lie among those of the one before --, then a shape that uses no workspace at all
+    cases = [(256, 6144, 16384, 128, "solo16_g2_sk_m256"), (70, 12672, 2304, 64, "duo_m64"), (300, 1024, 8192, 128, "panel_f2_m64_s3"),
+             (64, 1088, 6912, 64, "panel_f1_m32_s3"), (16, 2048, 12544, 64, "stream16_f1_w8"), (16, 2048, 8192, 64, "stream16_h_w8_d2_s2"),
+             (8, 1024, 8448, 64, "stream16_h_w8_d3_s2"), (4096 + 40, 512, 512, 64, "duo_m64")]
+    for i, (M, N, K, g, kernel) in enumerate(cases):
+        name, used = api.w4a8_describe_launch(M, N, K, g)
         need = api.w4a8_gemm_workspace_size(M, N, K, g)
-        _say(f"static workspace: M={M} N={N} K={K} g={g} -> {picked} (caller workspace {need} bytes)")
+        _say(f"static workspace: M={M} N={N} K={K} g={g} -> {name}, {used} bytes (caller workspace {need})")
+        assert name.split("[as ")[-1].rstrip("]") == kernel
+        assert (used > 32768 if i < len(cases) - 1 else used == 0) and used <= need
         P = H.Problem(N, K, g, seed=M)
         X, s_x = I.make_activations(M, K, outlier_frac=0.01, seed=M + 7)
         dX, dsx = torch.from_numpy(X).cuda(), torch.from_numpy(s_x).cuda()
