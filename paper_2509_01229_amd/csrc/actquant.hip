@@ -316,8 +316,8 @@ static void launch_rows(int M, int K, int R, int lg_shares, const __half *X, con
 //     of them on a CU instead of four where the call moves more than the memory-side cache holds (72.3 / 74.5 on
 //     8192 x 16384, 62.5 / 64.2 on 8192 x 14336; below that four are ahead, 32.9 / 33.8 on 4096 x 16384);
 //   many tokens with smooth scales: from 1024 tokens on several tokens per block, as many as leave two
-//     blocks of 1024 threads per CU (one where a thread holds two pieces: 98 registers) -- 20.1 / 26.8
-//     on 4096 x 8192 (5.0 TB/s, a copy runs at 5.2), 38 / 60 on 4096 x 16384, 9.3 / 11.2 on 1024 x 8192;
+//     blocks of 1024 threads per CU (one where a thread holds two pieces: 93 registers) -- 18.8 / 26.8
+//     on 4096 x 8192 (5.35 TB/s; a copy, which writes as much as it reads, 5.2), 38 / 60 on 4096 x 16384, 9.3 / 11.2 on 1024 x 8192;
 //     with at most 2048 columns a token is too short for that (16.0 / 20.2 on 8192 x 2048);
 //   few tokens: at most two pieces per thread up to 1536 pieces of a token (45 x 5120 2.64 to 2.30, 200 x 11008
 //     4.5 to 3.9 against blocks of 512 threads) and beyond 128 tokens up to 2048 (200 x 14336 5.0 to 4.3); up to

@@ -278,10 +278,10 @@ struct PanelChoice {
 };
 // The form and the number of K slices for a shape.  The time of a form is linear in what it does,
 // fitted to 14 row counts (17 to 512) x 17 weight shapes (1024 to 28672 channels and k) x all forms
-// and 1 to 4 slices, 8 % rms.  Audited on 19 row counts x 23 weight shapes (channels and k up to 28672, 550 MB of
-// weights in rotation): at 17..64 rows the form it picks is 1.4 % behind the best one (geometric mean) and at
-// worst 14 % (33 x 4096 x 14336: 14.8 against 13.0 us), at 65..512 rows 0.4 % and 9 %; 12 and 19 % ahead of the
-// 32- and 64-row kernels that prefetched one unit, and nowhere more than 1 % behind them:
+// and 1 to 4 slices of the panel kernel with one set of W registers, 8 % rms.  Audited with the present kernel on 2200 calls of 17 to 512
+// rows (channels from 1024, k from 2048, to 28672 each, weights from HBM): the form it picks is 0.5 % behind the best one at 17..32 rows, 0.8 %
+// at 33..64, 1.4 to 2.0 % above (geometric means; 24 % at worst).  It never picks 32 x 64 and 128 x 128, the best in 7 and 4 % of them.
+// (One block of 32 x 64 fits a CU with its 128 KB of LDS, two of 32 x 32.)
 //   2.26 us of launch and first loads
 //   + 0.61 us per accumulator tile (32 x 32) of a block: the sum over the waves and the epilogue
 //   + 9.8 ns per KB of X and 19.1 ns per KB of W that a CU takes in (X comes from L2; W is also dequantised)
@@ -667,8 +667,9 @@ static bool prefer_64_row_tiles(int M, int N, int K)
 // Where the dispatcher arrives at duo_m64 or duo_m128 it runs a panel form instead if that is estimated to
 // be faster (a null form: it is not).  The estimate of the tiles is 2.5 us below its terms (the fits above
 // include more launch time) and low by up to half for some shapes, by 18 % on average; with a factor of
-// 1.15 the choice is 0.8 % from the better of both over 128 shapes of 96 to 512 rows (256 x 8192 x 8192:
-// 27.2 against 30.6 us, 128 x 4096 x 11008: 15.8 against 21.2, 192 x 5120 x 5120: 12.8 against 18.3).  With
+// 1.15 the choice was 0.8 % from the better of both over 128 shapes of 96 to 512 rows (256 x 8192 x 8192:
+// 27.2 against 30.6 us, 128 x 4096 x 11008: 15.8 against 21.2, 192 x 5120 x 5120: 12.8 against 18.3); the panel kernel is
+// 4 to 8 % faster since, and over 1300 calls of 65 to 512 rows what runs is 4 to 6 % behind the best form or tile.  With
 // more rows and more than 64 tiles of 128 x 256 the tiles stay ahead (384 x 6144 x 2048: 12.9 against 14.8 us,
 // 1024 x 3072 x 3072: 17.5 against 18.9; with 64 tiles 500 x 4096 x 4096: 18.6 against 15.3).
 static double few_tiles_us(int M, int N, int K);

@@ -55,7 +55,7 @@ class Experts:
 
 CASES = [
     # E, N, K, g, rows per expert
-    (5, 256, 512, 64, [3, 0, 20, 40, 200]),        # all three families and an empty expert
+    (5, 256, 512, 64, [3, 0, 20, 40, 200]),        # panels, tiles and an empty expert
     (8, 448, 768, 128, [1, 16, 7, 0, 2, 16, 9, 4]),  # decode-like: every expert small
     (3, 320, 1024, 64, [130, 77, 300]),            # only tiled experts, ragged rows, N tail
     (4, 128, 256, 64, [32, 17, 33, 31]),           # around the family boundaries, one k unit
@@ -125,8 +125,8 @@ def test_grouped_interface_limits():
 
 
 def test_grouped_full_size_layer_all_families():
-    """A layer of realistic width (N = K = 4096, 8 experts) with expert sizes in every kernel
-    family, checked in full: per expert the float64 BLAS product of the oracle's dequantised
+    """A layer of realistic width (N = K = 4096, 8 experts) with experts of 5 to 700 rows, on the 16-row
+    kernel and on tiles, checked in full: per expert the float64 BLAS product of the oracle's dequantised
     weights is exact (|ACC| < 2^53)."""
     import torch
 
@@ -209,8 +209,8 @@ def test_grouped_large_experts_take_256_row_tiles(K, kernels):
     (3, 192, 8192, 128, [1, 9, 16]),               # ... long K: also for the smallest experts
     (3, 320, 768, 128, [33, 64, 5]),               # 64-row panels of 128 channels, a ragged last column group
     (6, 5824, 256, 64, [40, 3, 31, 17, 64, 1]),    # more blocks than one round: 32-row panels, two row tiles for some
-    (6, 5824, 256, 128, [40, 33, 64, 50, 20, 1]),  # ... most experts above 32 rows: panels and tiles
-    (3, 320, 512, 64, [65, 40, 20]),               # an expert of more than 64 rows: panels up to 32 rows only
+    (6, 5824, 256, 128, [40, 33, 64, 50, 20, 1]),  # ... most experts above 32 rows: panels of both heights
+    (3, 320, 512, 64, [65, 40, 20]),               # an expert of more than 64 rows: three row tiles of 32
 ])
 def test_panel_groups(E, N, K, g, rows):
     _say(f"panel groups E={E} N={N} K={K} g={g} rows={rows}")
