@@ -358,6 +358,19 @@ def test_tokens_full_of_ties_are_not_much_slower(M, K):
     assert t < 2.1 * g
 
 
+@pytest.mark.parametrize("M,K", [(2047, 8200), (2048, 8200), (2049, 10240), (2048, 10248), (2050, 9000)])
+def test_edges_of_three_pieces(M, K):
+    """512 threads of three pieces from 2048 tokens and 8200 to 10240 columns, 768 of two around that."""
+    _say(f"actquant three pieces M={M} K={K}")
+    X16 = WL.make_activations_f16(M, K, outlier_frac=0.001, seed=K)
+    X16[:, :1024] = (np.arange(1024) % 255 - 127).astype(np.float16) / 2
+    X16[0::2, 1] = 127.0
+    q_ref, s_ref = O.quantize_activations(X16, None)
+    q, s = _run(X16, None)
+    assert np.array_equal(s.view(np.uint32), s_ref.view(np.uint32)), "per-token scales differ"
+    assert np.array_equal(q, q_ref), f"{np.count_nonzero(q != q_ref)} codes differ"
+
+
 def test_block_shape_past_8192_columns():
     """Many tokens of 8680 columns keep the pace of 8192.  768 threads of two pieces, nearly a third of them past the
     end, took 1.05 to 1.11 of the time of 512 threads of three there."""
