@@ -379,6 +379,6 @@ def test_block_shape_past_8192_columns():
     _say("actquant 7880 tokens of 8192 and 8680 columns")
     gen = torch.Generator(device="cuda").manual_seed(1)
     a, b = ([torch.randn((7880, K), device="cuda", generator=gen).half() for _ in range(4)] for K in (8192, 8680))
-    t, u = _us(a) / 8192, _us(b) / 8680
+    t, u = (min(v) for v in zip(*((_us(a) / 8192, _us(b) / 8680) for _ in range(4))))   # (in turn: the clocks drift)
     _say(f"  {7880 * 3e-6 / t:.2f} and {7880 * 3e-6 / u:.2f} TB/s")
     assert u < 1.025 * t
