@@ -51,6 +51,14 @@ __device__ __forceinline__ buf_t make_buf(const void *p, uint32_t bytes)
 }
 constexpr uint32_t kNoLoad = 1u << 30;
 
+// First unit of slice ks of S (ks = S: the end).  What stands between a kernel's start and its first load counts in
+// full where the whole launch takes 4 to 15 us: 64-bit divisions here and by the divisors of the block ids, with their branches, were
+// 0.1 to 0.4 us of it (24 x 5120 x 5120 7.4 / 7.1 us, 45 x 5120 x 5120 9.7 / 9.3, 4 x 4096 x 4096 4.3 / 4.2).
+__device__ __forceinline__ int slice_begin(int units, int ks, int S)
+{
+    return S == 1 ? units * ks : (int)((unsigned)units * (unsigned)ks / (unsigned)S);  // (K <= 2^17: below 2^32)
+}
+
 // Where a block works: gx = its tile group (or output tile) among gnx, ks = its slice of S
 // K slices.  Plain launches take these from the grid (blockIdx.x, gridDim.x, blockIdx.y,
 // gridDim.y); grouped launches compute them per expert.

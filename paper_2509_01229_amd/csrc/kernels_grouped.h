@@ -42,12 +42,19 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_grouped_kernel(const Gr
 }
 
 // The entry that block `lid` belongs to: one lane per entry compares, instead of a walk through the
-// table (one dependent scalar load after the other, which a short block of a late entry waits for).
+// table (one dependent scalar load after the other, which a short block of a late entry waits for).  The lanes hold the
+// rest of their entries by then, so that nothing else is loaded once the entry is known.
 static_assert(kMaxExperts == 64, "one lane per entry");
-__device__ __forceinline__ int entry_of(const GroupTable &g, int lid)
+struct GroupEntry {
+    int first, expert, row_off, rows;  // (first: the entry's first block)
+};
+__device__ __forceinline__ GroupEntry entry_of(const GroupTable &g, int lid)
 {
     const int lane = threadIdx.x & 63;
-    return __popcll(__ballot(lane < g.count - 1 && lid >= g.block_end[lane]));
+    const int end = g.block_end[lane], expert = g.expert[lane], row_off = g.row_off[lane], rows = g.rows[lane];
+    const int i = __popcll(__ballot(lane < g.count - 1 && lid >= end));
+    return GroupEntry{i ? __builtin_amdgcn_readlane(end, i - 1) : 0, __builtin_amdgcn_readlane(expert, i),
+                      __builtin_amdgcn_readlane(row_off, i), __builtin_amdgcn_readlane(rows, i)};
 }
 
 // block_end counts row tiles x column groups of every entry.  As in w4a8_panel_kernel each XCD gets a
@@ -58,11 +65,11 @@ __global__ __launch_bounds__(512) void w4a8_panel_grouped_kernel(const GroupTabl
     const int total = g.block_end[g.count - 1];
     const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
     const int lid = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
-    const int i = entry_of(g, lid);
-    const int local = lid - (i ? g.block_end[i - 1] : 0);
-    const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
+    const GroupEntry en = entry_of(g, lid);
+    const int local = lid - en.first, M = en.rows, e = en.expert, r0 = en.row_off;
     const int blocks_m = (M + 32 * MF - 1) / (32 * MF), groups = (N / 32 + F - 1) / F;
-    panel_block<F, 8, MF, G128, ONCE>(Place{local / blocks_m, groups, 0, 1, nullptr}, local % blocks_m, M, N, K,
+    const int gx = blocks_m == 1 ? local : (int)((unsigned)local / (unsigned)blocks_m);
+    panel_block<F, 8, MF, G128, ONCE>(Place{gx, groups, 0, 1, nullptr}, local - gx * blocks_m, M, N, K,
                                 p.X + (size_t)r0 * K, p.sx + r0, p.Wp + e * p.w_stride, p.gp + e * p.gp_stride,
                                 p.sw + (size_t)e * N, p.Y ? p.Y + (size_t)r0 * N : nullptr,
                                 p.ACC ? p.ACC + (size_t)r0 * N : nullptr, nullptr, 0);

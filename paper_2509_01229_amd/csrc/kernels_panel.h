@@ -64,7 +64,7 @@ __device__ __forceinline__ void panel_block(
     const int t0 = pl.gx * F;
     const int m0 = bm * (32 * MF);
     const int S = pl.S, ks = pl.ks;
-    const int u_begin = (int)((long long)units * ks / S), u_end = (int)((long long)units * (ks + 1) / S);
+    const int u_begin = slice_begin(units, ks, S), u_end = slice_begin(units, ks + 1, S);
 
     v16i acc[F][MF];
 #pragma unroll
@@ -132,8 +132,10 @@ __device__ __forceinline__ void panel_block(
             for (int e = 0; e < 4; ++e) pre_sx[i][e] = sx[min(m0 + 8 * ((wave + i * NW) % (MF * 4)) + 4 * kb + e, M - 1)];
     };
     // The units of this wave are wave + k NW of the slice (in an order that starts elsewhere for every column
-    // group), k = 0 .. count - 1; only the last may be past the end (is_unit).
-    const int n = u_end - u_begin, rot = (int)(((unsigned)pl.gx * NW) % (unsigned)n);
+    // group, a 24th of the way further on; multiplied out, as a division would stand before the first load -- us with
+    // steps of NW units modulo n / of a 24th / of the golden ratio: 256 x 8192 x 8192 25.9 / 25.3 / 25.4, 509 x 4096 x 11008 31.3 /
+    // 31.3 / 32.5), k = 0 .. count - 1; only the last may be past the end (is_unit).
+    const int n = u_end - u_begin, rot = (int)__umulhi((unsigned)pl.gx * (0xFFFFFFFFu / 24), (unsigned)n);
     auto is_unit = [&](int k) { return wave + k * NW < n; };
     auto nth = [&](int k) {
         const int i = min(wave + k * NW, n - 1);
@@ -347,14 +349,21 @@ __global__ __launch_bounds__(NW * 64) void w4a8_panel_kernel(
     int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials,
-    unsigned int *__restrict__ tickets, int blocks_m, int blocks_n, int S)
+    unsigned int *__restrict__ tickets, int /*blocks_m*/, int /*blocks_n*/, int /*S*/)
 {
+    // The command processor hands over the first 14 dwords of the arguments in registers (build.py), as far as `sw`; the first load
+    // from the others waits for memory.  So nothing that the first addresses need is taken from those: the row tiles and column
+    // groups follow from M and N, K slices are the grid's second dimension, and S - 1 sits in the low bits of N, a multiple of
+    // 64 (us without / with this, 64 x 8192 x 8192 13.8 / 13.5, 45 x 5120 x 13824 14.6 / 14.5, 128 x 11008 x 4096 14.4 / 14.0).
+    const int S = (N & 63) + 1;
+    N &= ~63;
+    const int blocks_m = (int)(((unsigned)M + 32 * MF - 1) / (32 * MF)), blocks_n = (int)(((unsigned)N / 32 + F - 1) / F);
     // Consecutive block ids go to different XCDs: each XCD gets a run of logical ids, whose row tiles
     // of one column group are neighbours and find its weights in that XCD's L2.
-    const int total = blocks_m * blocks_n * S;
+    const int total = blocks_m * blocks_n;
     const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
     const int lid = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
-    const int tg = lid / S, ks = lid % S;
-    panel_block<F, NW, MF, G128, ONCE>(Place{tg / blocks_m, blocks_n, ks, S, tickets}, tg % blocks_m, M, N, K, X, sx, Wp, gp,
-                                       sw, Y, ACC, partials, tg);
+    const int gx = blocks_m == 1 ? lid : (int)((unsigned)lid / (unsigned)blocks_m);
+    panel_block<F, NW, MF, G128, ONCE>(Place{gx, blocks_n, (int)blockIdx.y, S, tickets}, lid - gx * blocks_m, M, N, K, X, sx, Wp, gp,
+                                       sw, Y, ACC, partials, lid);
 }

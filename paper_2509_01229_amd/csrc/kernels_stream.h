@@ -109,7 +109,7 @@ __device__ __forceinline__ void stream16_block(
     const int steps = units / UU;               // pipeline steps of UU units
     const int chunks_per_tile = K >> 6;
     const int S = pl.S, ks = pl.ks;
-    const int u_begin = (int)((long long)steps * ks / S), u_end = (int)((long long)steps * (ks + 1) / S);
+    const int u_begin = slice_begin(steps, ks, S), u_end = slice_begin(steps, ks + 1, S);
 
     v4i acc[F][2];
 #pragma unroll
@@ -121,21 +121,11 @@ __device__ __forceinline__ void stream16_block(
     // the k-block order that regroup_16x16 produces.  Lanes past M read row M-1.
     const int8_t *xrow = X + (size_t)min(lane & 15, M - 1) * K + kstep16_offset(lane >> 4);
 
-    // The outputs this thread will finish (idx = threadIdx.x + i * blockDim.x) are known
-    // now: fetch their scales here, so that the epilogue does not end on a cold load.
+    // The outputs this thread will finish (idx = threadIdx.x + i * blockDim.x) are known now: their scales
+    // are fetched behind the first unit, so that the epilogue does not end on a cold load.
     constexpr int OUTS = (VALS * 64 + NW * 64 - 1) / (NW * 64);
     auto chan = [&](int v, int l) { return channel_of(t0 + (v >> 3), 16 * ((v >> 2) & 1) + (l & 15)); };
     float pre_sx[OUTS], pre_sw[OUTS];
-    if (Y) {
-#pragma unroll
-        for (int i = 0; i < OUTS; ++i) {
-            const int idx = threadIdx.x + i * NW * 64;
-            const int v = min(idx >> 6, VALS - 1), l = idx & 63;
-            pre_sx[i] = sx[min(4 * (l >> 4) + (v & 3), M - 1)];
-            pre_sw[i] = sw[chan(v, l)];
-        }
-    }
-
     auto load_unit = [&](int u, Stream16Regs<F, UU, G128> &r) {
 #pragma unroll
         for (int f = 0; f < F; ++f) {
@@ -170,6 +160,15 @@ __device__ __forceinline__ void stream16_block(
     Stream16Regs<F, UU, G128> cur, nxt;
     int u = u_begin + wave;
     if (u < u_end) load_unit(u, cur);
+    if (Y) {
+#pragma unroll
+        for (int i = 0; i < OUTS; ++i) {
+            const int idx = threadIdx.x + i * NW * 64;
+            const int v = min(idx >> 6, VALS - 1), l = idx & 63;
+            pre_sx[i] = sx[min(4 * (l >> 4) + (v & 3), M - 1)];
+            pre_sw[i] = sw[chan(v, l)];
+        }
+    }
     for (; u < u_end; u += NW) {
         const bool more = (u + NW) < u_end;
         if (more) load_unit(u + NW, nxt);
@@ -190,12 +189,14 @@ __device__ __forceinline__ void stream16_block(
 
 template <int F, int NW, int UU, bool G128>
 __global__ __launch_bounds__(NW * 64) void w4a8_stream16_kernel(
-    int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
+    int M, int N, int K, int S, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials,
     unsigned int *__restrict__ tickets)
 {
-    stream16_block<F, NW, UU, G128>(grid_place(tickets), M, N, K, X, sx, Wp, gp, sw, Y, ACC, partials);
+    // (the arguments up to sw, all that the first loads need, come in registers: see w4a8_panel_kernel)
+    const Place pl{(int)blockIdx.x, N / (32 * F), (int)blockIdx.y, S, tickets};
+    stream16_block<F, NW, UU, G128>(pl, M, N, K, X, sx, Wp, gp, sw, Y, ACC, partials);
 }
 
 
@@ -227,7 +228,7 @@ __device__ __forceinline__ void stream16_half_block(
     const int tile = pl.gx >> 1, slot = 16 * (pl.gx & 1) + (lane & 15);
     const int chunk = lane >> 5, kb = (lane >> 4) & 1;
     const int units = K >> 7;
-    const int u_begin = (int)((long long)units * pl.ks / pl.S), u_end = (int)((long long)units * (pl.ks + 1) / pl.S);
+    const int u_begin = slice_begin(units, pl.ks, pl.S), u_end = slice_begin(units, pl.ks + 1, pl.S);
     constexpr int PB = G128 ? 64 : 128;  // parameter bytes of a tile's unit
     const buf_t wbuf = make_buf(Wp + (size_t)tile * (K >> 6) * 64, (uint32_t)K * 16u);
     const buf_t pbuf = make_buf(gp + (size_t)tile * units * PB, (uint32_t)units * PB);
@@ -290,10 +291,11 @@ __device__ __forceinline__ void stream16_half_block(
 
 template <int NW, int D, bool G128>
 __global__ __launch_bounds__(NW * 64) void w4a8_stream16_half_kernel(
-    int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
+    int M, int N, int K, int S, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials,
     unsigned int *__restrict__ tickets)
 {
-    stream16_half_block<NW, D, G128>(grid_place(tickets), M, N, K, X, sx, Wp, gp, sw, Y, ACC, partials);
+    const Place pl{(int)blockIdx.x, N / 16, (int)blockIdx.y, S, tickets};
+    stream16_half_block<NW, D, G128>(pl, M, N, K, X, sx, Wp, gp, sw, Y, ACC, partials);
 }

@@ -193,11 +193,11 @@ static int launch_stream16(const Args &a)
     if (a.group == 128) {
         if (int rc = allow_lds(&w4a8_stream16_kernel<F, NW, UU, true>, lds_bytes)) return rc;
         hipLaunchKernelGGL((w4a8_stream16_kernel<F, NW, UU, true>), grid, block, lds_bytes, a.stream, a.M, a.N,
-                           a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
+                           a.K, S, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
     } else {
         if (int rc = allow_lds(&w4a8_stream16_kernel<F, NW, UU, false>, lds_bytes)) return rc;
         hipLaunchKernelGGL((w4a8_stream16_kernel<F, NW, UU, false>), grid, block, lds_bytes, a.stream, a.M, a.N,
-                           a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
+                           a.K, S, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC, partials, tickets);
     }
     return LQ_OK;
 }
@@ -216,7 +216,7 @@ static int launch_stream16_half(const Args &a)
     unsigned int *tickets = static_cast<unsigned int *>(a.ws);
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(groups, S), dim3(NW * 64), 0, a.stream, a.M, a.N, a.K, a.X, a.sx, a.Wp, a.gp, a.sw,
+        hipLaunchKernelGGL(kernel, dim3(groups, S), dim3(NW * 64), 0, a.stream, a.M, a.N, a.K, S, a.X, a.sx, a.Wp, a.gp, a.sw,
                            a.Y, a.ACC, partials, tickets);
         return (int)LQ_OK;
     };
@@ -248,13 +248,13 @@ static int launch_panel(const Args &a, int S)
     if (a.query) return *a.query = need, LQ_OK;
     if (need > 0 && (!a.ws || a.ws_bytes < need))
         return fail(LQ_ERR_WORKSPACE, "split-K needs %zu bytes of workspace, got %zu", need, a.ws ? a.ws_bytes : 0);
-    const dim3 grid((unsigned)(blocks_m * blocks_n * S)), block(NW * 64);
+    const dim3 grid((unsigned)(blocks_m * blocks_n), (unsigned)S), block(NW * 64);
     const size_t lds_bytes = panel_lds_bytes(F, NW, MF, (a.K / 128 + S - 1) / S);
     unsigned int *tickets = static_cast<unsigned int *>(a.ws);
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
     auto go = [&](auto kernel) {
         if (int rc = allow_lds(kernel, lds_bytes)) return rc;
-        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, a.stream, a.M, a.N, a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC,
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, a.stream, a.M, a.N | (S - 1), a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC,
                            partials, tickets, blocks_m, blocks_n, S);
         return (int)LQ_OK;
     };
