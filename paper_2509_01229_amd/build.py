@@ -1,4 +1,5 @@
-"""Build the C-ABI library paper_2509_01229_amd/libliquidgemm.so with hipcc for gfx950.
+"""Build the C-ABI library paper_2509_01229_amd/libliquidgemm.so with hipcc for gfx950, and the native half of the
+Python binding, paper_2509_01229_amd/_binding.so, with g++.
 
 `python -m paper_2509_01229_amd.build` compiles csrc/*.hip and csrc/*.cpp in-tree.
 """
@@ -48,6 +49,30 @@ def check_compiler() -> None:
         "VALIDATED_COMPILERS in paper_2509_01229_amd/build.py.")
 
 
+def build_binding(verbose: bool = False, out: str = os.path.join(PKG, "_binding.so")) -> str:
+    """The native module of api.py: host code against the installed torch and Python."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    libs = cpp_extension.library_paths(device_type="cpu")
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"],
+           *(f for p in [*cpp_extension.include_paths(device_type="cpu"), os.path.join(rocm, "include")] for f in ("-isystem", p)),
+           "-o", out, os.path.join(CSRC, "binding.cpp"), *(f"-L{p}" for p in libs),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed building _binding.so")
+    return out
+
+
 def build_library(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
     check_compiler()
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
@@ -90,4 +115,5 @@ def kernel_resource_usage(stderr_text: str) -> dict:
 
 
 if __name__ == "__main__":
+    print(build_binding(verbose=True))
     print(build_library(verbose=True))
