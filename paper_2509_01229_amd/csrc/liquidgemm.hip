@@ -915,50 +915,81 @@ static int select_variant(int M, int N, int K)
     return find_variant(prefer_64_row_tiles(M, N, K) ? "duo_m64" : "duo_m128");
 }
 
-// Up to 16 rows: the kernel that runs where select_variant names a stream16 variant of whole tiles (that variant
-// itself where nothing is faster).  Measured on 52 weight shapes (N 1024..12288, K 2048..20480) at 1, 4, 8 and 16 rows and 20
-// (N to 28672, K to 28672) at 1, 4, 8, 12 and 16, 560 MB of weights in rotation, us whole tiles / what runs here:
-//   * up to 128 tiles of 32 channels and K from 2048 on, half tiles: 256 instead of 128 blocks at N = 4096, and no K slices.  At 4
-//     rows 4096 x 4096 5.3 / 4.5, 4096 x 11008 8.9 / 7.2, 4096 x 8192 7.9 / 5.9, 1024 x 4096 5.1 / 4.0, 4096 x 14336 10.5 / 8.2.  D is
-//     the number of units that leaves the fewest loads past the end: K / 128 units over 8 waves are at most 2 x 2, 2 x
-//     3 or 2 x 4 each (4096 x 5120: 4.9 with 3, 5.4 with 4), above that over 16 waves, with very long K 2 in any number of passes.
-//     X is read twice as often, so from 13 rows long K keeps whole tiles (4096 x 11008 at 16 rows 9.1, half tiles 9.3).
-//     Shorter K keeps them too: a wave of half tiles issues four units' loads whatever there is, and sixteen waves of a whole tile
-//     hold as many bytes in flight (up to 4 rows, up to 128 tiles, K = 256 3.0 / 3.4, 1024 3.25 / 3.55, 1536 3.60 / 3.64, 2048 3.76 / 3.67).
-//   * up to 64 tiles two slices of K fill the CUs where K is long (2048 x 14336 at 4 rows 8.3 / 7.2; one slice 7.6), with up to
-//     16 tiles for up to 10 rows (320 x 12544 at 12 rows 6.9 / 7.3)
-//   * 129..384 tiles: with a whole number of passes and few rows half tiles again (8192 x 8192 at 4 rows 9.3 / 8.7, 10240 x
-//     8192 12.7 / 11.0), else up to 320 tiles the 32-row panels, whose loads run two units ahead (8192 x 11008 at 8
-//     rows 12.5 / 11.7, 10240 x 8192 at 16 13.1 / 12.5, 6656 x 16384 at 16 16.2 / 15.0).  K below 6144, up to 8 rows with K from 12288
-//     and K beyond 16384 stay (5120 x 5120 6.7 against 7.5, 5120 x 13824 at 8 rows 12.1 against 12.2, 8192 x 28672 at 16 rows,
-//     groups of 128, 25.7 against 26.5), and 9 and 10 rows where all sixteen waves' loads are in flight at once (7360 x 7168 at 9 rows
-//     1.03 to 1.07 of the time on panels).
+// Up to 16 rows: the form that runs where select_variant names a stream16 variant of whole tiles (null: that variant itself).
+// From 8000 random calls (N 1024..28672, K 2048..28672, groups of 64 and 128, 1 to 16 rows, weights from HBM), all forms of each timed in
+// turn; the figures are times against what ran before (geometric means).  What decides: how evenly the blocks fill 256
+// CUs, and how many bytes a CU has in flight (64 to 128 KB; sixteen waves of one tile, or panels two units ahead, hold
+// most).  Half tiles do where all of a wave's units are in flight at once: 32 units of K in two passes of two, 48 of three,
+// 64 of four.  Fewer than 32 tiles keep the rules of an audit of their own (N from 64).
+static const char *form_up_to_16_rows(int M, int N, int K)
+{
+    const int tiles = N / 32;
+    const bool some = tiles >= 32;  // (N >= 1024)
+    if (tiles <= 128) {
+        // 256 instead of 128 blocks at N = 4096 and no K slices: at 4 rows 4096 x 4096 5.3 / 4.5 us, 4096 x 11008 8.9 / 7.2, 1024 x
+        // 4096 5.1 / 4.0.  Shorter K keeps whole tiles: a wave of half tiles issues four units' loads whatever there is (K =
+        // 256 3.0 / 3.4, 1536 3.60 / 3.64, 2048 3.76 / 3.67).  X is read twice as often, so from 13 rows long K keeps whole tiles too.
+        if (K < 2048) return nullptr;
+        if (K <= 4096) return "stream16_h_w8_d2";
+        if (K <= 6144) return "stream16_h_w8_d3";
+        // two units a pass in four passes against four in two: 0.97 up to 4 rows, 0.98 up to 8, equal above
+        if (K <= 8192) return tiles <= 64 && M > 12 ? "stream16_h_w8_d2_s2" : M <= 8 && some ? "stream16_h_w8_d2" : "stream16_h_w8_d4";
+        if (tiles <= 64) {
+            // two slices of K fill the CUs (2048 x 14336 at 4 rows 8.3 / 7.2; one slice 7.6), with up to 16 tiles for up to 10 rows (320 x
+            // 12544 at 12 rows 6.9 / 7.3); up to 4 rows and K = 12288 one slice is ahead (0.90 to 0.96)
+            const int most = tiles <= 16 ? 10 : 12;
+            if (K <= 12288) return M <= 4 && some ? "stream16_h_w8_d2" : M <= most ? "stream16_h_w8_d3_s2" : nullptr;
+            if (K <= 16384) return M <= most ? "stream16_h_w8_d4_s2" : nullptr;
+            return (M <= 4 && K <= 20480) || (M <= 8 && some) ? "stream16_h_w8_d2_s2" : nullptr;  // (beyond 20480: 0.88 / 0.93 up to 4 / 8 rows)
+        }
+        if (K <= 16384) {
+            if (M <= 4 && K <= 10240) return "stream16_h_w8_d2";  // (0.96; beyond equal to three units in sixteen waves)
+            return M > 12 ? nullptr : K <= 12288 ? "stream16_h_w16_d3" : "stream16_h_w16_d4";
+        }
+        return M <= 8 ? "stream16_h_w8_d2" : nullptr;  // (0.78 / 0.85 up to 4 / 8 rows)
+    }
+    if (tiles <= 256) {
+        // one block a CU or less: up to 8 rows sixteen waves of one tile (K 4352..5888 0.91 / 0.93 up to 4 / 8 rows, 6400..8192 0.96 /
+        // 0.92, 8704..12032 0.94 / 0.96), above 32-row panels (K 5376..6144 0.97, beyond 16384 0.95), but not for 9 and 10 rows where
+        // all sixteen waves' loads are in flight at once (7360 x 7168 at 9 rows 1.03 to 1.07 of the time on panels)
+        if (M <= 8) {
+            if (K <= 4096 || K >= 12288) return nullptr;
+            if (K == 6144) return M <= 4 ? "stream16_h_w8_d3" : nullptr;
+            if (M <= 4 && K > 7680 && K <= 8192) return "stream16_h_w8_d4";  // (7936 and 8192: 1.03 on whole tiles)
+            return K == 8448 ? "panel_f1_m32" : "stream16_f1_w16_s1";  // (at 8448 0.95 as at 8704)
+        }
+        if (K > 16384 || (K > 8192 && K < 12288)) return "panel_f1_m32";
+        return K >= 5376 && M >= (K <= 8192 && K % 512 == 0 ? 11 : 9) ? "panel_f1_m32" : nullptr;
+    }
+    if (tiles <= 384) {
+        // half tiles where K is close below 4096 or 6144 (4 x 11008 x 4096 8.1 / 7.25 us; K = 3072 0.97, 2816 1.01; at 5 to 8 rows
+        // from 3584 on), else panels of 32 x 64 (K to 6144 0.96, to 12288 0.95, beyond 0.88 to 0.97)
+        if (K <= 4096) return (M <= 4 && K >= 3072) || (M <= 8 && K >= 3584) ? "stream16_h_w8_d2" : nullptr;
+        if (M <= 4 && K >= 4864 && K <= 8192) return K <= 6144 ? "stream16_h_w8_d3" : "stream16_h_w8_d4";
+        return "panel_f2_m32";
+    }
+    if (tiles <= 512) {
+        // up to 224 blocks of two tiles the same panels (0.94 to 0.98), up to 256 of them only for few rows (0.97)
+        if (K <= 4096) return nullptr;
+        if (tiles <= 448) return "panel_f2_m32";
+        return M > 4 ? nullptr : K <= 8192 ? "stream16_f1_w8" : "panel_f2_m32";
+    }
+    if (K < 2048) return nullptr;
+    if (tiles <= 768) {
+        // blocks of two tiles are two on some CUs and one on others (257..384 of them); one tile a block is at most three on
+        // every CU: 0.80 to 0.86 for K to 6144, beyond with sixteen waves 0.82 to 0.85 up to 8 rows; with more, 0.87 to K = 8192, panels
+        // of 32 x 32 0.86 to 0.88 and two slices of K 0.83 to 0.86 (12 x 24192 x 11776 33.2 / 29.1 us)
+        if (K <= 6144) return "stream16_f1_w8";
+        if (M <= 8 || K <= 8192) return "stream16_f1_w16_s1";
+        return K <= 16384 ? "panel_f1_m32" : "stream16_f2_w8_s2";
+    }
+    if (tiles <= 896)  // (0.92 and 0.94; 0.96 to 0.98: 16 x 28672 x 8192 25.3 / 24.6 us)
+        return M <= 8 && K <= 4096 ? "stream16_f1_w8" : "panel_f2_m32";
+    return nullptr;
+}
 static int in_place_of_stream16(int variant, const Args &a)
 {
-    const int tiles = a.N / 32, M = a.M, K = a.K;
-    const char *name = nullptr;
-    if (tiles <= 128) {
-        if (K < 2048) name = nullptr;
-        else if (K <= 4096) name = "stream16_h_w8_d2";
-        else if (K <= 6144) name = "stream16_h_w8_d3";
-        else if (K <= 8192) name = tiles <= 64 && M > 12 ? "stream16_h_w8_d2_s2" : "stream16_h_w8_d4";
-        else if (tiles <= 64) {
-            const int most = tiles <= 16 ? 10 : 12;
-            if (K <= 12288) name = M <= most ? "stream16_h_w8_d3_s2" : nullptr;
-            else if (K <= 16384) name = M <= most ? "stream16_h_w8_d4_s2" : nullptr;
-            else if (K <= 20480) name = M <= 4 ? "stream16_h_w8_d2_s2" : nullptr;
-        } else if (K <= 16384) {
-            if (M <= 12) name = K <= 12288 ? "stream16_h_w16_d3" : "stream16_h_w16_d4";
-        } else if (K <= 20480 && M <= 4) {
-            name = "stream16_h_w8_d2";
-        }
-    } else if (tiles <= 384 && K >= 6144 && K <= 8192 && M <= 4) {
-        name = K == 6144 ? "stream16_h_w8_d3" : "stream16_h_w8_d4";
-    } else if (tiles <= 256) {
-        if (K > 6144 && K <= 16384 && (M >= (K <= 8192 && K % 512 == 0 ? 11 : 9) || (K > 8192 && K < 12288))) name = "panel_f1_m32";
-    } else if (tiles <= 320) {
-        if (K >= 6144 && K < 12288 && (M >= 5 || K > 8192)) name = "panel_f2_m32";
-    }
+    const char *name = form_up_to_16_rows(a.M, a.N, a.K);
     if (!name) return variant;
     const int other = find_variant(name);
     Args query = a;

@@ -725,3 +725,32 @@ def test_every_form_in_place_of_the_16_row_kernels(M, N, K, form):
         assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g, workspace=nothing), ref), "no workspace"
         Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
         H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
+
+
+# ---------------------------------------------------------------------------------------
+# ... and at the edges of the rules for N from 1024 on: the forms that fill the CUs best, with odd tile counts, ragged
+# last passes and, where K slices are picked, no room for them
+# ---------------------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,form", [
+    (1, 1024, 8448, "stream16_h_w8_d2"), (8, 1024, 20736, "stream16_h_w8_d2_s2"), (8, 2112, 16640, "stream16_h_w8_d2"),
+    (3, 4160, 4352, "stream16_f1_w16_s1"), (8, 8192, 12032, "stream16_f1_w16_s1"), (11, 4160, 5632, "panel_f1_m32"),
+    (16, 4160, 16640, "panel_f1_m32"), (4, 8256, 3072, "stream16_h_w8_d2"), (8, 12288, 3584, "stream16_h_w8_d2"),
+    (4, 12288, 4864, "stream16_h_w8_d3"), (16, 12288, 4352, "panel_f2_m32"), (9, 14336, 4352, "panel_f2_m32"),
+    (4, 16384, 4352, "stream16_f1_w8"), (16, 16448, 2048, "stream16_f1_w8"), (8, 16448, 6400, "stream16_f1_w16_s1"),
+    (16, 24576, 8192, "stream16_f1_w16_s1"), (9, 16448, 8448, "panel_f1_m32"), (16, 16448, 16640, "stream16_f2_w8_s2"),
+    (8, 24640, 4096, "stream16_f1_w8"), (16, 28672, 2304, "panel_f2_m32")])
+def test_forms_for_up_to_16_rows_of_many_channels(M, N, K, form):
+    import torch
+
+    g = 64 if K % 512 else 128
+    name, need = api.w4a8_describe_launch(M, N, K, g)
+    _say(f"up to 16 rows M={M} N={N} K={K} g={g} -> {name}, {need} bytes")
+    assert name.endswith(f"[as {form}]") and (need > 0) == ("_s2" in form)
+    W = H.RandomWeights(N, K, g, seed=M)
+    X, sx = W.activations(M)
+    ref = W.product(X)
+    nothing = torch.zeros(0, dtype=torch.uint8, device="cuda")
+    for ws in (None, None, nothing):   # (the tickets reset themselves)
+        assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g, workspace=ws), ref)
+    Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
+    H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
