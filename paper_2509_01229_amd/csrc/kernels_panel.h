@@ -132,10 +132,8 @@ __device__ __forceinline__ void panel_block(
             for (int e = 0; e < 4; ++e) pre_sx[i][e] = sx[min(m0 + 8 * ((wave + i * NW) % (MF * 4)) + 4 * kb + e, M - 1)];
     };
     // The units of this wave are wave + k NW of the slice (in an order that starts elsewhere for every column
-    // group, a 24th of the way further on; multiplied out, as a division would stand before the first load -- us with
-    // steps of NW units modulo n / of a 24th / of the golden ratio: 256 x 8192 x 8192 25.9 / 25.3 / 25.4, 509 x 4096 x 11008 31.3 /
-    // 31.3 / 32.5), k = 0 .. count - 1; only the last may be past the end (is_unit).
-    const int n = u_end - u_begin, rot = (int)__umulhi((unsigned)pl.gx * (0xFFFFFFFFu / 24), (unsigned)n);
+    // group), k = 0 .. count - 1; only the last may be past the end (is_unit).
+    const int n = u_end - u_begin, rot = (int)(((unsigned)pl.gx * NW) % (unsigned)n);
     auto is_unit = [&](int k) { return wave + k * NW < n; };
     auto nth = [&](int k) {
         const int i = min(wave + k * NW, n - 1);
@@ -287,29 +285,40 @@ __device__ __forceinline__ void panel_block(
         }
         __syncthreads();
         if (!*s_last) return;
-        for (int k2 = 0; k2 < S; ++k2) {
-            if (k2 == ks) continue;
-            const unsigned long long *other = reinterpret_cast<const unsigned long long *>(base + k2 * group_ints);
-            unsigned long long v[F][PER][2];
+        // Up to three slices at a time (as far as there are registers), all their loads on the way before the first is added: one after the other each
+        // was a trip to memory of its own (24 x 4096 x 16384 in four slices 12.8 / 12.3 us).
+        constexpr int AT = F * PER >= 8 ? 1 : 3;
+        for (int k0 = 1; k0 < S; k0 += AT) {
+            unsigned long long v[AT][F][PER][2];
 #pragma unroll
-            for (int f = 0; f < F; ++f)
+            for (int q = 0; q < AT; ++q) {
+                if (k0 + q >= S) continue;
+                const int k2 = ks + k0 + q - (ks + k0 + q >= S ? S : 0);
+                const unsigned long long *other = reinterpret_cast<const unsigned long long *>(base + k2 * group_ints);
 #pragma unroll
-                for (int i = 0; i < PER; ++i) {
-                    const int it = min((int)threadIdx.x + i * NW * 64, ITEMS - 1);
+                for (int f = 0; f < F; ++f)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        v[f][i][h] = __hip_atomic_load(other + (size_t)(f * ITEMS + it) * 2 + h, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                }
+                    for (int i = 0; i < PER; ++i) {
+                        const int it = min((int)threadIdx.x + i * NW * 64, ITEMS - 1);
 #pragma unroll
-            for (int f = 0; f < F; ++f)
-#pragma unroll
-                for (int i = 0; i < PER; ++i)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        sums[f][i][2 * h] += (int)(uint32_t)v[f][i][h];
-                        sums[f][i][2 * h + 1] += (int)(uint32_t)(v[f][i][h] >> 32);
+                        for (int h = 0; h < 2; ++h)
+                            v[q][f][i][h] = __hip_atomic_load(other + (size_t)(f * ITEMS + it) * 2 + h, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT);
                     }
+            }
+#pragma unroll
+            for (int q = 0; q < AT; ++q) {
+                if (k0 + q >= S) continue;
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+#pragma unroll
+                    for (int i = 0; i < PER; ++i)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            sums[f][i][2 * h] += (int)(uint32_t)v[q][f][i][h];
+                            sums[f][i][2 * h + 1] += (int)(uint32_t)(v[q][f][i][h] >> 32);
+                        }
+            }
         }
         if (threadIdx.x == 0)  // ready for the next call
             __hip_atomic_store(&pl.tickets[tile_group], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -353,17 +362,18 @@ __global__ __launch_bounds__(NW * 64) void w4a8_panel_kernel(
 {
     // The command processor hands over the first 14 dwords of the arguments in registers (build.py), as far as `sw`; the first load
     // from the others waits for memory.  So nothing that the first addresses need is taken from those: the row tiles and column
-    // groups follow from M and N, K slices are the grid's second dimension, and S - 1 sits in the low bits of N, a multiple of
-    // 64 (us without / with this, 64 x 8192 x 8192 13.8 / 13.5, 45 x 5120 x 13824 14.6 / 14.5, 128 x 11008 x 4096 14.4 / 14.0).
+    // groups follow from M and N, and S - 1 sits in the low bits of N, a multiple of 64 (us without / with this, 64 x 8192 x 8192
+    // 13.8 / 13.5, 45 x 5120 x 13824 14.6 / 14.5, 128 x 11008 x 4096 14.4 / 14.0).  Divisions only where there is something to divide.
     const int S = (N & 63) + 1;
     N &= ~63;
     const int blocks_m = (int)(((unsigned)M + 32 * MF - 1) / (32 * MF)), blocks_n = (int)(((unsigned)N / 32 + F - 1) / F);
     // Consecutive block ids go to different XCDs: each XCD gets a run of logical ids, whose row tiles
-    // of one column group are neighbours and find its weights in that XCD's L2.
-    const int total = blocks_m * blocks_n;
+    // of one column group are neighbours and find its weights in that XCD's L2 (and the slices of a tile end together).
+    const int total = blocks_m * blocks_n * S;
     const int xcd = blockIdx.x & 7, per = total >> 3, rem = total & 7;
     const int lid = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
-    const int gx = blocks_m == 1 ? lid : (int)((unsigned)lid / (unsigned)blocks_m);
-    panel_block<F, NW, MF, G128, ONCE>(Place{gx, blocks_n, (int)blockIdx.y, S, tickets}, lid - gx * blocks_m, M, N, K, X, sx, Wp, gp,
-                                       sw, Y, ACC, partials, lid);
+    const int tg = S == 1 ? lid : (int)((unsigned)lid / (unsigned)S);
+    const int gx = blocks_m == 1 ? tg : (int)((unsigned)tg / (unsigned)blocks_m);
+    panel_block<F, NW, MF, G128, ONCE>(Place{gx, blocks_n, lid - tg * S, S, tickets}, tg - gx * blocks_m, M, N, K, X, sx, Wp, gp,
+                                       sw, Y, ACC, partials, tg);
 }

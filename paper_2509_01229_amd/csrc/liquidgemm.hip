@@ -248,7 +248,7 @@ static int launch_panel(const Args &a, int S)
     if (a.query) return *a.query = need, LQ_OK;
     if (need > 0 && (!a.ws || a.ws_bytes < need))
         return fail(LQ_ERR_WORKSPACE, "split-K needs %zu bytes of workspace, got %zu", need, a.ws ? a.ws_bytes : 0);
-    const dim3 grid((unsigned)(blocks_m * blocks_n), (unsigned)S), block(NW * 64);
+    const dim3 grid((unsigned)(blocks_m * blocks_n * S)), block(NW * 64);
     const size_t lds_bytes = panel_lds_bytes(F, NW, MF, (a.K / 128 + S - 1) / S);
     unsigned int *tickets = static_cast<unsigned int *>(a.ws);
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
