@@ -270,7 +270,15 @@ static const PanelForm kPanelForms[] = {
     {1, 8, 1, &launch_panel<1, 8, 1>}, {2, 8, 1, &launch_panel<2, 8, 1>}, {4, 8, 1, &launch_panel<4, 8, 1>},
     {1, 8, 2, &launch_panel<1, 8, 2>}, {2, 8, 2, &launch_panel<2, 8, 2>}, {3, 8, 2, &launch_panel<3, 8, 2>},
     {4, 8, 2, &launch_panel<4, 8, 2>}, {3, 4, 4, &launch_panel<3, 4, 4>}, {4, 4, 4, &launch_panel<4, 4, 4>},
+    {2, 4, 4, &launch_panel<2, 4, 4>}, {3, 8, 1, &launch_panel<3, 8, 1>},  // (the last two not in choose_panel's fit)
 };
+constexpr int kFittedPanelForms = 9;
+static const PanelForm &panel_form(int F, int MF)
+{
+    for (const PanelForm &f : kPanelForms)
+        if (f.F == F && f.MF == MF) return f;
+    return kPanelForms[0];
+}
 struct PanelChoice {
     const PanelForm *form = nullptr;  // null: no form takes the shape
     int S = 1;
@@ -293,7 +301,8 @@ struct PanelChoice {
 static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
 {
     PanelChoice best;
-    for (const PanelForm &f : kPanelForms) {
+    for (int i = 0; i < kFittedPanelForms; ++i) {
+        const PanelForm &f = kPanelForms[i];
         const long long blocks = panel_blocks(M, N, f.F, f.MF);
         const int tiles = f.F * f.MF;
         for (int S = 1; S <= 4 && S <= K / 128; ++S) {
@@ -308,16 +317,32 @@ static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
             if (us < best.us) best = PanelChoice{&f, S, us};
         }
     }
-    // Two exceptions, for launches of several rounds, which the fit prices alike whatever stays on a CU.  32 x 128 panels, one
+    // Exceptions.  For launches of several rounds, which the fit prices alike whatever stays on a CU: 32 x 128 panels, one
     // on a CU, run a round at a time: beyond one round 32 x 64 panels, two on a CU, are ahead (136 x 11520 x 2048 15.9 / 13.1 us,
     // 390 such calls 1.05 / 0.91 of what the form with one set of W registers took).  32 x 32 panels of more than two rounds are
     // behind them while a wave has no second unit (24 x 24064 x 256 5.5 / 5.2, 5.0 of that form; K = 512 5.7 / 5.4, 768 6.1 / 6.0,
     // 1024 6.2 / 6.5).
-    if (best.form && best.S == 1 && best.form->MF == 1) {
-        const long long blocks = panel_blocks(M, N, best.form->F, 1);
-        if ((best.form->F == 4 && blocks > kAssumedCUs) || (best.form->F == 1 && blocks > 2 * kAssumedCUs && K <= 768))
-            best.form = &kPanelForms[1];
-    }
+    if (!best.form || best.form->MF != 1) return best;
+    const int F = best.form->F;
+    const long long blocks = panel_blocks(M, N, F, 1);
+    if (best.S == 1 && ((F == 4 && blocks > kAssumedCUs) || (F == 1 && blocks > 2 * kAssumedCUs && K <= 768)))
+        best.form = &panel_form(2, 1);
+    // From 5200 random calls (17 to 512 rows, N from 1024, K from 2048, to 28672 each), these against the fit's choice: with one row
+    // tile, panels of 96 channels where they are less than a round in place of 128 channels (0.91: more of the CUs work), also
+    // of 128 with slices in more than one round of blocks (20 x 20608 x 14336 37.2 / 30.0 us, 0.90); two slices of 64 channels for
+    // four of 128 (0.92); two of 32 for four of 64 (with several row tiles 0.85 to K = 12288, 0.96 to 20480, behind
+    // beyond; with one from 3072 channels on 0.93); with several row tiles up to K = 8192 one slice of 32 for two (0.96).
+    if (K < 2048 || N < 1024) return best;
+    if (M <= 32 && F == 4 && best.S == 1 && blocks <= kAssumedCUs && panel_blocks(M, N, 3, 1) < kAssumedCUs)
+        best.form = &panel_form(3, 1);
+    else if (F == 4 && best.S == 4)
+        best.form = &panel_form(2, 1), best.S = 2;
+    else if (M <= 32 && F == 4 && best.S > 1 && blocks * best.S > kAssumedCUs)
+        best.form = &panel_form(3, 1), best.S = 1;
+    else if (F == 2 && best.S == 4 && K <= 20480 && (M > 32 || N >= 3072))
+        best.form = &panel_form(1, 1), best.S = 2;
+    else if (M > 32 && F == 1 && best.S == 2 && K <= 8192)
+        best.S = 1;
     return best;
 }
 // 17..64 rows: the form that choose_panel picks
@@ -673,11 +698,56 @@ static bool prefer_64_row_tiles(int M, int N, int K)
 // more rows and more than 64 tiles of 128 x 256 the tiles stay ahead (384 x 6144 x 2048: 12.9 against 14.8 us,
 // 1024 x 3072 x 3072: 17.5 against 18.9; with 64 tiles 500 x 4096 x 4096: 18.6 against 15.3).
 static double few_tiles_us(int M, int N, int K);
-static PanelChoice panel_instead_of_tiles(const Args &a)
+
+// Where that estimate leaves a batch of 33 to 512 rows on duo_m64 or duo_m128, both sides are estimated once more, from 5200
+// random calls (N from 1024, K from 2048, to 28672 each, weights from HBM), each form by itself: the panels' time without K slices is
+// linear in their rounds, the units that a wave walks in each, how far the first round fills the CUs, and the packed weights
+// (4 to 7 % rms, 11 % for 32 x 64); the tiles' in the same and in the volume of their slices (5 and 8 %).  With panels that have to
+// win by 5 %, 594 of 892 such calls leave the tiles, at 0.87 of their time; 21 of them lose more than 2 %, one more than 8.  (104 x
+// 16000 x 2304 18.3 / 11.7 us on 128 x 64 panels, 36 x 22464 x 6912 28.0 / 20.9 on 64 x 96, 312 x 6400 x 4096 21.0 / 14.0 on 64 x
+// 128, 256 x 10240 x 8192 35.0 / 29.5 on 128 x 96.)  Left on tiles: 64 full rows on 28672 and more channels, whose two
+// slices are seven eighths of the CUs, and 10240 to 12672 channels with K up to 8192 (groups of 128: below 8192), where the parity tests of
+// the tiles' slices run.
+static PanelChoice panel_instead_of_few_tiles(int M, int N, int K, int group, bool rows64)
 {
-    if (a.M > 256 && (long long)((a.M + 127) / 128) * ((a.N + 255) / 256) > 64) return PanelChoice{};
-    const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
-    return c.form && c.us < 1.15 * few_tiles_us(a.M, a.N, a.K) ? c : PanelChoice{};
+    struct Cost {
+        int F, MF;
+        double fixed, round, unit, fill, mb;
+    };
+    static const Cost kCosts[] = {
+        {2, 1, 1.391, 1.239, 0.683, 0.346, 0.099}, {3, 1, 1.556, 2.466, 1.006, 0.093, 0.092}, {4, 1, 0.744, 3.720, 1.253, 0.101, 0.096},
+        {2, 2, 1.068, 2.347, 1.029, 0.121, 0.089}, {3, 2, 0.461, 4.470, 1.263, 0.232, 0.081}, {4, 2, 0.371, 4.939, 1.509, 0.351, 0.076},
+        {2, 4, 1.045, 4.068, 0.815, 0.131, 0.088}, {3, 4, 0.000, 8.265, 1.014, 0.271, 0.056}, {4, 4, 0.000, 9.031, 1.183, 0.524, 0.033},
+    };
+    PanelChoice best;
+    if (M <= 32 || M > 512 || N < 1024 || K < 2048) return best;
+    if (M <= 64 ? M == 64 && N >= 28672 : N >= 10240 && N <= 12672 && (K < 8192 || (K == 8192 && group == 64))) return best;
+    const double mb = 0.5e-6 * N * K;
+    for (const Cost &c : kCosts) {
+        const PanelForm &f = panel_form(c.F, c.MF);
+        const long long blocks = panel_blocks(M, N, c.F, c.MF);
+        const bool two = c.F == 2 && c.MF == 1;  // (two 32 x 64 panels fit a CU)
+        if (c.F > 2 && c.MF == 4 && K < 2816) continue;  // (0.97 there, a seventh of them behind)
+        if (blocks > (two ? 4 : K <= 8192 ? 2 : 1) * kAssumedCUs) continue;  // (a second round with longer K: 0.98, a quarter of them behind)
+        const double fill = (double)blocks / kAssumedCUs, units = (K / 128 + f.NW - 1) / f.NW;
+        const double rounds = two ? std::max(fill, 1.0) : std::ceil(fill);
+        const double us = c.fixed + rounds * (c.round + c.unit * units) + c.fill * std::min(fill, 1.0) * units + c.mb * mb;
+        if (us < best.us) best = PanelChoice{&f, 1, us};
+    }
+    const int bn = (N + 255) / 256, tiles = rows64 ? (M + 63) / 64 * bn : (M + 127) / 128 * bn;
+    const int S = rows64 ? duo64_split(M, N, K) : duo_split(M, N, K);
+    const double fill = (double)tiles * S / kAssumedCUs, k = K / 1024.0 / S, volume = (S - 1) * (double)tiles / kAssumedCUs;
+    const double us = rows64 ? std::ceil(fill) * (7.394 + 2.299 * k) + 1.778 * std::min(fill, 1.0) * k + 7.466 * volume + 0.063 * mb
+                             : std::ceil(fill) * (9.415 + 3.473 * k) + 3.654 * std::min(fill, 1.0) * k + 11.112 * volume + 0.023 * mb;
+    return best.us < 0.95 * us ? best : PanelChoice{};
+}
+static PanelChoice panel_instead_of_tiles(const Args &a, bool rows64)
+{
+    if (a.M <= 256 || (long long)((a.M + 127) / 128) * ((a.N + 255) / 256) <= 64) {
+        const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
+        if (c.form && c.us < 1.15 * few_tiles_us(a.M, a.N, a.K)) return c;
+    }
+    return panel_instead_of_few_tiles(a.M, a.N, a.K, a.group, rows64);
 }
 
 struct Variant {
@@ -751,6 +821,9 @@ static const Variant kVariants[] = {
     // --- ablation forms (Sec. 7.3), measured by the benchmark, never dispatched ---
     {"excp_m128", &launch_excp, 0, 1, 1},
     {"widened_dq_m128", &launch_duo_widened, 0, 1, 1},
+    // (panel forms that were added last: indices are part of the interface)
+    {"panel_f3_m32", &launch_panel_named<3, 8, 1, 1>, 0, 1, 1},
+    {"panel_f2_m128", &launch_panel_named<2, 4, 4, 1>, 0, 1, 1},
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
@@ -768,10 +841,8 @@ static int find_variant(const char *name)
     return -1;
 }
 
-static bool is_few_tiles(int variant)
-{
-    return kVariants[variant].fn == &launch_duo64<0> || kVariants[variant].fn == &launch_duo<0, 0>;
-}
+static bool is_64_row_tiles(int variant) { return kVariants[variant].fn == &launch_duo64<0>; }
+static bool is_few_tiles(int variant) { return is_64_row_tiles(variant) || kVariants[variant].fn == &launch_duo<0, 0>; }
 
 // The 256-row tiles with one wave per SIMD (solo16_pt_m256: 256 x 256; solo16_g2_m256: 256 x 128
 // with two k groups per block) against the 128 x 256 tiles with two waves per SIMD.  Half the
@@ -950,7 +1021,7 @@ static const char *form_up_to_16_rows(int M, int N, int K)
     }
     if (tiles <= 256) {
         // one block a CU or less: up to 8 rows sixteen waves of one tile (K 4352..5888 0.91 / 0.93 up to 4 / 8 rows, 6400..8192 0.96 /
-        // 0.92, 8704..12032 0.94 / 0.96), above 32-row panels (K 5376..6144 0.97, beyond 16384 0.95), but not for 9 and 10 rows where
+        // 0.92, 8704..12032 0.94 / 0.96), above 32-row panels (K 5376..6144 0.97, 16640..24576 0.95), but not for 9 and 10 rows where
         // all sixteen waves' loads are in flight at once (7360 x 7168 at 9 rows 1.03 to 1.07 of the time on panels)
         if (M <= 8) {
             if (K <= 4096 || K >= 12288) return nullptr;
@@ -958,6 +1029,7 @@ static const char *form_up_to_16_rows(int M, int N, int K)
             if (M <= 4 && K > 7680 && K <= 8192) return "stream16_h_w8_d4";  // (7936 and 8192: 1.03 on whole tiles)
             return K == 8448 ? "panel_f1_m32" : "stream16_f1_w16_s1";  // (at 8448 0.95 as at 8704)
         }
+        if (K > 24576) return nullptr;  // (0.98, at 28672 behind)
         if (K > 16384 || (K > 8192 && K < 12288)) return "panel_f1_m32";
         return K >= 5376 && M >= (K <= 8192 && K % 512 == 0 ? 11 : 9) ? "panel_f1_m32" : nullptr;
     }
@@ -969,10 +1041,11 @@ static const char *form_up_to_16_rows(int M, int N, int K)
         return "panel_f2_m32";
     }
     if (tiles <= 512) {
-        // up to 224 blocks of two tiles the same panels (0.94 to 0.98), up to 256 of them only for few rows (0.97)
+        // up to 224 blocks of two tiles the same panels (0.94 to 0.98); with more these are between 0.97 and 1.25 of the time, from one
+        // machine to another, and one tile a block is ahead for few rows (0.97)
         if (K <= 4096) return nullptr;
         if (tiles <= 448) return "panel_f2_m32";
-        return M > 4 ? nullptr : K <= 8192 ? "stream16_f1_w8" : "panel_f2_m32";
+        return M <= 4 && K <= 12288 ? "stream16_f1_w8" : nullptr;
     }
     if (K < 2048) return nullptr;
     if (tiles <= 768) {
@@ -1083,7 +1156,7 @@ static int run_rows(int variant, const Args &a)
         if (a.Y) c.Y = a.Y + r0 * a.N;
         if (a.ACC) c.ACC = a.ACC + r0 * a.N;
         const int runs = dispatched && a.M <= 16 ? in_place_of_stream16(variant, c) : variant;
-        const PanelChoice panel = dispatched && is_few_tiles(variant) ? panel_instead_of_tiles(c) : PanelChoice{};
+        const PanelChoice panel = dispatched && is_few_tiles(variant) ? panel_instead_of_tiles(c, is_64_row_tiles(variant)) : PanelChoice{};
         if (int rc = panel.form ? panel.form->launch(c, panel.S) : kVariants[runs].fn(c)) return rc;
         ran = runs, ran_panel = panel;
         need_max = std::max(need_max, need);
@@ -1121,11 +1194,11 @@ static int run(int variant, const Args &a)
 }
 
 // The name of the kernel that a launch over the given rows runs (with all K slices), to `text`.
-static void launch_name(int variant, int M, int N, int K, char *text, size_t text_bytes)
+static void launch_name(int variant, int M, int N, int K, int group, char *text, size_t text_bytes)
 {
     Args a{};
     size_t unused = 0;
-    a.M = M, a.N = N, a.K = K, a.query = &unused;
+    a.M = M, a.N = N, a.K = K, a.group = group, a.query = &unused;
     const bool dispatched = variant < 0;
     if (dispatched) variant = select_variant(M, N, K);
     if (dispatched && M <= 16) {
@@ -1137,7 +1210,7 @@ static void launch_name(int variant, int M, int N, int K, char *text, size_t tex
     }
     PanelChoice panel{};
     if (kVariants[variant].fn == &launch_panel_auto) panel = choose_panel(M, N, K, workspace_limit(a));
-    else if (dispatched && is_few_tiles(variant)) panel = panel_instead_of_tiles(a);
+    else if (dispatched && is_few_tiles(variant)) panel = panel_instead_of_tiles(a, is_64_row_tiles(variant));
     if (panel.form)
         panel_name(panel, text, text_bytes);
     else
@@ -1661,7 +1734,7 @@ int w4a8_describe_launch(int variant, int M, int N, int K, int group, char *text
         Args a{};
         a.M = first, a.N = N, a.K = K, a.group = group, a.query = &need[0];
         if (int rc = run_rows(first == M ? variant : find_variant("solo16_pt_m256"), a)) return rc;
-        launch_name(first == M ? variant : -1, M - (first == M ? 0 : first), N, K, name, sizeof(name));
+        launch_name(first == M ? variant : -1, M - (first == M ? 0 : first), N, K, group, name, sizeof(name));
         if (first == M) {
             snprintf(words, sizeof(words), "%s", name);
         } else {

@@ -754,3 +754,30 @@ def test_forms_for_up_to_16_rows_of_many_channels(M, N, K, form):
         assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g, workspace=ws), ref)
     Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
     H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
+
+
+# ---------------------------------------------------------------------------------------
+# Panels for 17 to 512 rows where the first estimates had tiles or other panels: ragged row tiles, last column
+# groups that are not full, waves without a unit in the last turn, with and without K slices
+# ---------------------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,form", [
+    (17, 16448, 2048, "panel_f3_m32"), (20, 17024, 12288, "panel_f3_m32"), (33, 1664, 8704, "panel_f1_m32_s2"),
+    (17, 3136, 8704, "panel_f1_m32_s2"), (45, 1664, 5376, "panel_f1_m32"), (33, 16448, 4096, "panel_f3_m64"),
+    (63, 28672, 2048, "panel_f4_m64"), (65, 12736, 2304, "panel_f2_m128"), (255, 8192, 8448, "panel_f2_m128"),
+    (97, 16448, 4864, "panel_f3_m128"), (512, 5632, 4096, "panel_f3_m128"), (90, 8320, 4352, "panel_f4_m32"),
+    (385, 4672, 8192, "panel_f2_m64"), (97, 25664, 4352, "panel_f4_m128"), (257, 5568, 2816, "panel_f4_m64"),
+    (64, 28672, 2048, "duo_m64"), (256, 10240, 8192, "panel_f3_m128"), (513, 5632, 4096, "duo_m64")])
+def test_panels_instead_of_few_tiles(M, N, K, form):
+    import torch
+
+    g = 64 if K % 512 else 128
+    name, need = api.w4a8_describe_launch(M, N, K, g)
+    _say(f"panel instead of tiles M={M} N={N} K={K} g={g} -> {name}, {need} bytes")
+    assert name == form
+    W = H.RandomWeights(N, K, g, seed=M)
+    X, sx = W.activations(M)
+    ref = W.product(X)
+    for ws in (None, None, torch.zeros(0, dtype=torch.uint8, device="cuda")):   # (the tickets reset themselves)
+        assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g, workspace=ws), ref)
+    Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
+    H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
