@@ -35,7 +35,7 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_grouped_kernel(const Gr
 {
     const int i = blockIdx.x / groups, gx = blockIdx.x % groups;
     const int e = g.expert[i], r0 = g.row_off[i];
-    stream16_block<2, NW, UU, G128>(Place{gx, groups, 0, 1, nullptr}, g.rows[i], N, K, p.X + (size_t)r0 * K, p.sx + r0,
+    stream16_block<2, NW, UU, G128, true>(Place{gx, groups, 0, 1, nullptr}, g.rows[i], N, K, p.X + (size_t)r0 * K, p.sx + r0,
                                     p.Wp + e * p.w_stride, p.gp + e * p.gp_stride, p.sw + (size_t)e * N,
                                     p.Y ? p.Y + (size_t)r0 * N : nullptr, p.ACC ? p.ACC + (size_t)r0 * N : nullptr,
                                     nullptr);
@@ -43,7 +43,8 @@ __global__ __launch_bounds__(NW * 64) void w4a8_stream16_grouped_kernel(const Gr
 
 // The entry that block `lid` belongs to: one lane per entry compares, instead of a walk through the
 // table (one dependent scalar load after the other, which a short block of a late entry waits for).  The lanes hold the
-// rest of their entries by then, so that nothing else is loaded once the entry is known.
+// rest of their entries by then, so that nothing else is loaded once the entry is known (tiles of 64 experts: 256 rows each on 1408 x 2048
+// 67.0 / 63.9 us, 16 of 60 rows on 4096 x 2560 24.3 / 23.3).
 static_assert(kMaxExperts == 64, "one lane per entry");
 struct GroupEntry {
     int first, expert, row_off, rows;  // (first: the entry's first block)
@@ -81,10 +82,8 @@ __global__ __launch_bounds__(256 * KG, KG == 1 ? 2 : 1) void w4a8_duo_grouped_ke
                                                                                      const GroupedPtrs p, int N,
                                                                                      int K)
 {
-    int i = 0;
-    while (i < g.count - 1 && (int)blockIdx.x >= g.block_end[i]) ++i;
-    const int local = (int)blockIdx.x - (i ? g.block_end[i - 1] : 0);
-    const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
+    const GroupEntry en = entry_of(g, (int)blockIdx.x);
+    const int local = (int)blockIdx.x - en.first, M = en.rows, e = en.expert, r0 = en.row_off;
     // row tiles of one column block are neighbours, so they meet on the expert's W columns
     const int blocks_m = (M + TM - 1) / TM;
     const int bm = local % blocks_m, bn = local / blocks_m;
@@ -100,10 +99,8 @@ template <bool G128>
 __global__ __launch_bounds__(256, 2) void w4a8_duo_dl_grouped_kernel(const GroupTable g, const GroupedPtrs p, int N,
                                                                      int K)
 {
-    int i = 0;
-    while (i < g.count - 1 && (int)blockIdx.x >= g.block_end[i]) ++i;
-    const int local = (int)blockIdx.x - (i ? g.block_end[i - 1] : 0);
-    const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
+    const GroupEntry en = entry_of(g, (int)blockIdx.x);
+    const int local = (int)blockIdx.x - en.first, M = en.rows, e = en.expert, r0 = en.row_off;
     const int blocks_m = (M + 127) >> 7;
     const int bm = local % blocks_m, bn = local / blocks_m;
     const Place pl{0, 1, 0, 1, nullptr};
@@ -126,18 +123,26 @@ __global__ __launch_bounds__(256, 2) void w4a8_duo_dl_grouped_kernel(const Group
 // one persistent stream: resident blocks walk the tiles of every expert, with 256 x 256 tiles (KG = 1)
 // prefetching across the boundaries between them.  block_end counts 256 x 256 / KG tiles here.
 struct SoloGrouped {
-    const GroupTable &g;
     const GroupedPtrs &p;
-    int N, K, blocks_n;
+    int N, K, blocks_n, total;
+    int end, expert, row_off, rows;  // this lane's entry: nothing is loaded when a tile is looked up, in the middle of the stage loop
+    __device__ __forceinline__ SoloGrouped(const GroupTable &g, const GroupedPtrs &ptrs, int n, int k, int tn)
+        : p(ptrs), N(n), K(k), blocks_n((n + tn - 1) / tn), total(g.block_end[g.count - 1])
+    {
+        const int lane = threadIdx.x & 63;
+        end = lane < g.count ? g.block_end[lane] : 0x7fffffff;
+        expert = g.expert[lane], row_off = g.row_off[lane], rows = g.rows[lane];
+        asm volatile("" : "+v"(end), "+v"(expert), "+v"(row_off), "+v"(rows));  // (here, and not at each use)
+    }
     __device__ __forceinline__ int slices() const { return 1; }
-    __device__ __forceinline__ int tiles() const { return g.block_end[g.count - 1]; }
+    __device__ __forceinline__ int tiles() const { return total; }
     __device__ __forceinline__ SoloTile tile(int lid, int G) const
     {
-        lid = solo_xcd_order(lid, tiles(), G);
-        int i = 0;
-        while (i < g.count - 1 && lid >= g.block_end[i]) ++i;
-        const int local = lid - (i ? g.block_end[i - 1] : 0);
-        const int M = g.rows[i], e = g.expert[i], r0 = g.row_off[i];
+        lid = solo_xcd_order(lid, total, G);
+        const int i = __popcll(__ballot(lid >= end));
+        const int local = lid - (i ? __builtin_amdgcn_readlane(end, i - 1) : 0);
+        const int M = __builtin_amdgcn_readlane(rows, i), e = __builtin_amdgcn_readlane(expert, i);
+        const int r0 = __builtin_amdgcn_readlane(row_off, i);
         int bm, bn;
         solo_coords(local, (M + 255) / 256, blocks_n, bm, bn);
         return SoloTile{M,
@@ -156,6 +161,5 @@ struct SoloGrouped {
 template <bool G128, int KG>
 __global__ __launch_bounds__(256, 1) void w4a8_solo_grouped_kernel(const GroupTable g, const GroupedPtrs p, int N, int K)
 {
-    constexpr int TN = 256 / KG;
-    solo16_body<G128, KG>(SoloGrouped{g, p, N, K, (N + TN - 1) / TN}, N, K);
+    solo16_body<G128, KG>(SoloGrouped(g, p, N, K, 256 / KG), N, K);
 }

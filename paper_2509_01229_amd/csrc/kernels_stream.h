@@ -109,7 +109,7 @@ __device__ __forceinline__ void stream16_finish(
     }
 }
 
-template <int F, int NW, int UU, bool G128>
+template <int F, int NW, int UU, bool G128, bool SCALES_FIRST = false>
 __device__ __forceinline__ void stream16_block(
     const Place pl, int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
@@ -137,10 +137,22 @@ __device__ __forceinline__ void stream16_block(
     const int8_t *xrow = X + (size_t)min(lane & 15, M - 1) * K + kstep16_offset(lane >> 4);
 
     // The outputs this thread will finish (idx = threadIdx.x + i * blockDim.x) are known now: their scales
-    // are fetched behind the first unit, so that the epilogue does not end on a cold load.
+    // are fetched behind the first unit, so that the epilogue does not end on a cold load -- or ahead of it in a grouped launch,
+    // where several rounds of blocks share a CU and the scales are what the end of a short block waits for (8 experts of 9 rows on 12480 x
+    // 768 12.0 us, behind the first unit 12.7; plain launches 7 x 13824 x 2560 6.7 ahead, 6.3 behind).
     constexpr int OUTS = (VALS * 64 + NW * 64 - 1) / (NW * 64);
     auto chan = [&](int v, int l) { return channel_of(t0 + (v >> 3), 16 * ((v >> 2) & 1) + (l & 15)); };
     float pre_sx[OUTS], pre_sw[OUTS];
+    auto load_scales = [&] {
+        if (!Y) return;
+#pragma unroll
+        for (int i = 0; i < OUTS; ++i) {
+            const int idx = threadIdx.x + i * NW * 64;
+            const int v = min(idx >> 6, VALS - 1), l = idx & 63;
+            pre_sx[i] = sx[min(4 * (l >> 4) + (v & 3), M - 1)];
+            pre_sw[i] = sw[chan(v, l)];
+        }
+    };
     auto load_unit = [&](int u, Stream16Regs<F, UU, G128> &r) {
 #pragma unroll
         for (int f = 0; f < F; ++f) {
@@ -174,16 +186,9 @@ __device__ __forceinline__ void stream16_block(
 
     Stream16Regs<F, UU, G128> cur, nxt;
     int u = u_begin + wave;
+    if (SCALES_FIRST) load_scales();
     if (u < u_end) load_unit(u, cur);
-    if (Y) {
-#pragma unroll
-        for (int i = 0; i < OUTS; ++i) {
-            const int idx = threadIdx.x + i * NW * 64;
-            const int v = min(idx >> 6, VALS - 1), l = idx & 63;
-            pre_sx[i] = sx[min(4 * (l >> 4) + (v & 3), M - 1)];
-            pre_sw[i] = sw[chan(v, l)];
-        }
-    }
+    if (!SCALES_FIRST) load_scales();
     for (; u < u_end; u += NW) {
         const bool more = (u + NW) < u_end;
         if (more) load_unit(u + NW, nxt);

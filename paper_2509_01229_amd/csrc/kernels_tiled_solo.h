@@ -51,12 +51,14 @@ __device__ __forceinline__ int solo_xcd_order(int lid, int tiles, int G)
 __device__ __forceinline__ void solo_coords(int lid, int blocks_m, int blocks_n, int &bm, int &bn)
 {
     constexpr int GM = 4;
-    const int per_group = GM * blocks_n;
-    const int first = (lid / per_group) * GM;
-    const int gsz = min(blocks_m - first, GM);
-    const int in_group = lid % per_group;
-    bm = first + in_group % gsz;
-    bn = in_group / gsz;
+    // (no division where there is none to do: these stand before a block's first load and, at the end of a tile, in the stage loop)
+    const unsigned per_group = (unsigned)(GM * blocks_n);
+    const unsigned group = blocks_m <= GM ? 0u : (unsigned)lid / per_group;
+    const unsigned in_group = (unsigned)lid - group * per_group;
+    const int first = (int)group * GM, gsz = min(blocks_m - first, GM);
+    const unsigned q = gsz == GM ? in_group / GM : gsz == 1 ? in_group : in_group / (unsigned)gsz;
+    bm = first + (int)(in_group - q * (unsigned)gsz);
+    bn = (int)q;
 }
 // The tiles of one GEMM.  With S > 1 every tile is computed in S equal K slices by S blocks,
 // slice ks writing its INT32 partial sums to matrix ks of ACC ([S][M][N]; Y is null then) for
@@ -79,7 +81,7 @@ struct SoloDense {
         int bm, bn;
         const int per_slice = blocks_m * blocks_n;
         const int item = solo_xcd_order(lid, tiles(), G);  // an XCD's items: one slice (or part of one) of all tiles
-        const int ks = item / per_slice;
+        const int ks = S == 1 ? 0 : item / per_slice;
         solo_coords(item - ks * per_slice, blocks_m, blocks_n, bm, bn);
         return SoloTile{M, bm, bn, ks, X, sx, Wp, gp, sw, Y, ACC + (size_t)ks * M * N};
     }

@@ -61,7 +61,7 @@ __device__ __forceinline__ void solo16_body(const Src &src, const int N, const i
     // number is 2 mod 4 (K % 512 == 256, one slice), two stages are added whose loads re-read the
     // last real stage and whose group parameters are replaced, as they arrive, by those of an
     // all-zero group (s = 0, a = 128: (code * 0 + 128) XOR 0x80 = 0) -- they add nothing.
-    const int stages_real = (K >> 7) / src.slices();
+    const int stages_real = src.slices() == 1 ? K >> 7 : (K >> 7) / src.slices();
     const int stages = (stages_real + 3) & ~3;
     const bool has_pad = stages != stages_real;
     constexpr uint32_t kZeroGroup = G128 ? 0x8000u : 0x80008000u;
@@ -172,8 +172,6 @@ __device__ __forceinline__ void solo16_body(const Src &src, const int N, const i
             asm volatile("" : "+a"(acc[i >> 2][i & 3]));
         });
     };
-    clear_acc();
-    asm volatile("s_nop 3" ::: "memory");  // (accumulation registers written by moves: wait states before an MFMA reads them)
     auto acc_elem = [&](int tf, int f, int v) {
         int x;
         asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[tf][f][v]));
@@ -487,6 +485,9 @@ __device__ __forceinline__ void solo16_body(const Src &src, const int N, const i
 #pragma unroll
             for (int i = 0; i < 4; ++i) issue_x1(2, i);
         }
+        // (behind the loads, not ahead of them: 256 moves are 0.4 us -- 1024 x 8192 x 8192 54.6 / 54.2 us, 1000 x 6208 x 1280 16.3 / 16.1)
+        clear_acc();
+        asm volatile("s_nop 3" ::: "memory");  // (accumulation registers written by moves: wait states before an MFMA reads them)
         // X(0) of this wave is in LDS, W(0) in its registers
         arrive_w(std::integral_constant<int, KG == 2 ? 2 * PER_STAGE : PER_STAGE + 4>{}, wr[0], pr[0]);
         asm volatile("s_barrier" ::: "memory");
@@ -569,8 +570,10 @@ __device__ __forceinline__ void solo16_body(const Src &src, const int N, const i
             }
             __syncthreads();  // the ring is read; the next tile's fill may overwrite it
         }
-        clear_acc();
-        asm volatile("s_nop 3" ::: "memory");
+        if constexpr (KG == 1) {
+            clear_acc();
+            asm volatile("s_nop 3" ::: "memory");
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
     // the prefetches past the last stage write LDS too: they must have landed before the block ends
@@ -579,9 +582,9 @@ __device__ __forceinline__ void solo16_body(const Src &src, const int N, const i
 
 template <bool G128, int KG = 1>
 __global__ __launch_bounds__(256, 1) void w4a8_solo16_pt_kernel(
-    int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
-    const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
-    __half *__restrict__ Y, int32_t *__restrict__ ACC, int blocks_m, int blocks_n, int S)
+    int M, int N, int K, int blocks_m, int blocks_n, int S, const int8_t *__restrict__ X, const u32x4 *__restrict__ Wp,
+    const uint8_t *__restrict__ gp, const float *__restrict__ sx, const float *__restrict__ sw, __half *__restrict__ Y,
+    int32_t *__restrict__ ACC)  // (what the first loads need comes first: the first 14 dwords are in registers from the start)
 {
     solo16_body<G128, KG>(SoloDense{M, N, X, sx, Wp, gp, sw, Y, ACC, blocks_m, blocks_n, S}, N, K);
 }

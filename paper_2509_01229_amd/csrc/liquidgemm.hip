@@ -585,11 +585,11 @@ static int launch_solo_pt(const Args &a)
         if (a.group == 128) {
             if (int rc = allow_lds(w4a8_solo16_pt_kernel<true, KG>, lds_bytes)) return rc;
             hipLaunchKernelGGL((w4a8_solo16_pt_kernel<true, KG>), dim3((unsigned)grid), dim3(256), lds_bytes, a.stream, a.M,
-                               a.N, a.K, a.X, a.sx, a.Wp, a.gp, a.sw, Y, ACC, blocks_m, blocks_n, S);
+                               a.N, a.K, blocks_m, blocks_n, S, a.X, a.Wp, a.gp, a.sx, a.sw, Y, ACC);
         } else {
             if (int rc = allow_lds(w4a8_solo16_pt_kernel<false, KG>, lds_bytes)) return rc;
             hipLaunchKernelGGL((w4a8_solo16_pt_kernel<false, KG>), dim3((unsigned)grid), dim3(256), lds_bytes, a.stream, a.M,
-                               a.N, a.K, a.X, a.sx, a.Wp, a.gp, a.sw, Y, ACC, blocks_m, blocks_n, S);
+                               a.N, a.K, blocks_m, blocks_n, S, a.X, a.Wp, a.gp, a.sx, a.sw, Y, ACC);
         }
     } else if (a.group == 128) {
         if (int rc = allow_lds(w4a8_solo_pt_kernel<true, KG>, lds_bytes)) return rc;

@@ -257,6 +257,17 @@ def test_row_blocks_and_rests(N, K, g, rows, kernels):
         H.assert_fp16_close(Y[lo:hi].cpu().numpy(), ref.cpu().numpy(), f"expert {e}")
 
 
+@pytest.mark.parametrize("N,K,g,rows,kernels", [
+    (256, 512, 64, [(37 * e) % 190 for e in range(64)], ["panel_f2_m32", "duo_m64"]),    # 52 of 64 experts in the tiles' table
+    (1024, 512, 64, [65 + (37 * e) % 64 for e in range(64)], ["duo_m128_g2"]),           # the whole table
+    (2048, 768, 64, [1280, 0, 1536, 1792] + [256] * 20, ["duo_dl_m128"]),
+    (1024, 4096, 64, [200] * 24 + [0] * 3 + [256] * 8, ["solo16_g2_m256"]),              # ... one tile at a time
+    (4096, 1024, 64, [1280, 0, 1536, 1792, 2048], ["solo16_pt_m256"]),   # row blocks in fours, the last of them 1, 2, 3 and 4
+])
+def test_many_experts_in_the_tiles_table(N, K, g, rows, kernels):
+    test_row_blocks_and_rests(N, K, g, rows, kernels)
+
+
 @pytest.mark.parametrize("E,N,K,g,rows", [
     (64, 192, 256, 64, [(7 * e) % 33 for e in range(64)]),       # the whole table: panels of up to 32 rows
     (64, 192, 512, 128, [5 + (11 * e) % 60 for e in range(64)]),  # ... 33..64 rows: one or two row tiles an expert
