@@ -214,7 +214,8 @@ int w4a8_grouped_gemm(int E, const int *row_offsets, int N, int K, int group, co
                       const float *act_scales, const void *W_packed, const uint8_t *gparams,
                       const float *w_scales, uint16_t *Y, int32_t *ACC, void *hip_stream);
 
-/* The launches of w4a8_grouped_gemm for the given rows: "<kernel>[<experts> experts, <rows> rows]", joined by
+/* The launches of w4a8_grouped_gemm for the given rows: "<kernel>[<experts> experts, <rows> rows]", or with
+ * ", as <form>" behind the rows where another form of the kernel runs (32-row panels of few blocks), joined by
  * "+" in the order they run (an expert whose rows run on several kernels counts in each).  Host only; text is
  * cut to text_bytes, always terminated; "" where no expert has rows. */
 int w4a8_describe_grouped(int E, const int *row_offsets, int N, int K, int group, char *text, size_t text_bytes);

@@ -502,7 +502,7 @@ def w4a8_grouped_gemm(row_offsets, X, act_scales, W_packed, gparams, w_scales, N
 
 
 def w4a8_describe_grouped(row_offsets, N: int, K: int, group: int) -> str:
-    """The launches of w4a8_grouped_gemm for the given rows, "<kernel>[<experts> experts, <rows> rows]+..."."""
+    """The launches of w4a8_grouped_gemm for the given rows, "<kernel>[<experts> experts, <rows> rows]+..." ("..., as <form>]": another form)."""
     offs = [int(r) for r in row_offsets]
     text = ctypes.create_string_buffer(320)
     _check(lib().w4a8_describe_grouped(len(offs) - 1, (ctypes.c_int * len(offs))(*offs), N, K, group, text, len(text)))

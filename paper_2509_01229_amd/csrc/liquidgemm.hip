@@ -1240,7 +1240,9 @@ static int grouped_launch(const GroupedArgs &a, const char *name, Kernel kernel,
         int rows = 0;
         for (int i = 0; i < t.count; ++i) rows += t.rows[i];
         const size_t at = strlen(a.text);
-        snprintf(a.text + at, a.text_bytes - at, "%s%s[%d experts, %d rows]", at ? "+" : "", name, t.count, rows);
+        const char *as = strchr(name, '[');  // ("<kernel>[as <form>]")
+        snprintf(a.text + at, a.text_bytes - at, "%s%.*s[%d experts, %d rows%s%s", at ? "+" : "",
+                 (int)(as ? as - name : (ptrdiff_t)strlen(name)), name, t.count, rows, as ? ", " : "", as ? as + 1 : "]");
         return LQ_OK;
     }
     if (int rc = allow_lds(kernel, lds)) return rc;
@@ -1303,6 +1305,10 @@ static int grouped_tiles_run(const GroupedArgs &a, GroupTable &big)
 }
 
 // Experts (or what they leave over) of up to 128 rows as panels: one launch for all of them.
+// 32-row panels of 64 channels that are half a round of blocks or less run on 32 channels a block instead where K is long: a CU takes in
+// weights at some 60 KB per us, however few others do (25000 calls of 1 to 16 experts, 8 to 128 blocks of 64 channels: 0.79 of the time with K above
+// 8448, 0.83 from 4352 on and none slower but by noise; at K = 3072 0.95 and one call in five slower, at 2048 1.01; from 129 blocks on, where
+// 32 channels make more than one round, 1.03 to 1.19).  27 rows on 4096 x 14336, what eight experts of some 750 leave over: 17.3 -> 13.3 us.
 template <int F, int MF>
 static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
 {
@@ -1313,11 +1319,14 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
         if (blocks > 0x7fffffff) return fail(LQ_ERR_INVALID, "grouped GEMM too large for one launch");
         t.block_end[i] = (int)blocks;
     }
+    if constexpr (F == 2)
+        if (a.K > 4096 && 2 * blocks <= kAssumedCUs) return grouped_panel_run<1, 1>(a, t);
     const size_t lds = panel_lds_bytes(F, 8, MF, a.K / 128);
-    static_assert((F == 2 && MF == 1) || (F == 4 && MF == 2), "the names below");
+    static_assert((F <= 2 && MF == 1) || (F == 4 && MF == 2), "the names below");
     const dim3 grid((unsigned)blocks);
     auto go = [&](auto kernel) {
-        return grouped_launch(a, MF == 1 ? "panel_f2_m32" : "panel_f4_m64", kernel, grid, dim3(512), lds, t);
+        return grouped_launch(a, F == 1 ? "panel_f2_m32[as panel_f1_m32]" : MF == 1 ? "panel_f2_m32" : "panel_f4_m64", kernel, grid,
+                              dim3(512), lds, t);
     };
     if (blocks == (long long)t.count * groups)  // one row tile each
         return a.group == 128 ? go(&w4a8_panel_grouped_kernel<F, MF, true, true>)

@@ -257,6 +257,19 @@ def test_row_blocks_and_rests(N, K, g, rows, kernels):
         H.assert_fp16_close(Y[lo:hi].cpu().numpy(), ref.cpu().numpy(), f"expert {e}")
 
 
+@pytest.mark.parametrize("N,K,g,rows,form", [
+    (4096, 4352, 64, [17, 0, 32], "panel_f1_m32"),        # 128 blocks of 64 channels, the shortest K; a last turn without units for all waves
+    (4160, 4352, 64, [17, 0, 32], None),                  # 130
+    (4096, 4096, 64, [17, 0, 32], None),
+    (64, 14336, 128, [1, 3, 0, 16], "panel_f1_m32"),
+    (1600, 4352, 64, [40, 66], "panel_f1_m32"),   # 125: two and three row tiles an expert, the last of one with 2 rows
+])
+def test_few_panels_of_long_k_take_32_channels(N, K, g, rows, form):
+    text = api.w4a8_describe_grouped([0] + [int(v) for v in np.cumsum(rows)], N, K, g)
+    assert text == f"panel_f2_m32[{sum(r > 0 for r in rows)} experts, {sum(rows)} rows" + (f", as {form}]" if form else "]")
+    test_row_blocks_and_rests(N, K, g, rows, ["panel_f2_m32"])
+
+
 @pytest.mark.parametrize("N,K,g,rows,kernels", [
     (256, 512, 64, [(37 * e) % 190 for e in range(64)], ["panel_f2_m32", "duo_m64"]),    # 52 of 64 experts in the tiles' table
     (1024, 512, 64, [65 + (37 * e) % 64 for e in range(64)], ["duo_m128_g2"]),           # the whole table
