@@ -262,6 +262,7 @@ def test_row_blocks_and_rests(N, K, g, rows, kernels):
     (4160, 4352, 64, [17, 0, 32], None),                  # 130
     (4096, 4096, 64, [17, 0, 32], None),
     (64, 14336, 128, [1, 3, 0, 16], "panel_f1_m32"),
+    (1024, 4352, 128, [1, 16, 7, 2, 0, 12, 9, 3, 16], "panel_f1_m32"),   # 128 blocks of experts of up to 16 rows
     (1600, 4352, 64, [40, 66], "panel_f1_m32"),   # 125: two and three row tiles an expert, the last of one with 2 rows
 ])
 def test_few_panels_of_long_k_take_32_channels(N, K, g, rows, form):
