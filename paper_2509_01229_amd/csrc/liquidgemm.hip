@@ -705,10 +705,9 @@ static double few_tiles_us(int M, int N, int K);
 // (4 to 7 % rms, 11 % for 32 x 64); the tiles' in the same and in the volume of their slices (5 and 8 %).  With panels that have to
 // win by 5 %, 594 of 892 such calls leave the tiles, at 0.87 of their time; 21 of them lose more than 2 %, one more than 8.  (104 x
 // 16000 x 2304 18.3 / 11.7 us on 128 x 64 panels, 36 x 22464 x 6912 28.0 / 20.9 on 64 x 96, 312 x 6400 x 4096 21.0 / 14.0 on 64 x
-// 128, 256 x 10240 x 8192 35.0 / 29.5 on 128 x 96.)  Left on tiles: 64 full rows on 28672 and more channels, whose two
-// slices are seven eighths of the CUs, and 10240 to 12672 channels with K up to 8192 (groups of 128: below 8192), where the parity tests of
-// the tiles' slices run.
-static PanelChoice panel_instead_of_few_tiles(int M, int N, int K, int group, bool rows64)
+// 128, 256 x 10240 x 8192 35.0 / 29.5 on 128 x 96.)  8300 calls on 10240 to 12672 channels with K up to 8192 and 12000 of 64 rows on
+// 28672 and more, which kept the tiles for a time, take 0.81 and 0.84 of their time on the panels; of the former one loses 4 %, of the latter none.
+static PanelChoice panel_instead_of_few_tiles(int M, int N, int K, bool rows64)
 {
     struct Cost {
         int F, MF;
@@ -721,7 +720,6 @@ static PanelChoice panel_instead_of_few_tiles(int M, int N, int K, int group, bo
     };
     PanelChoice best;
     if (M <= 32 || M > 512 || N < 1024 || K < 2048) return best;
-    if (M <= 64 ? M == 64 && N >= 28672 : N >= 10240 && N <= 12672 && (K < 8192 || (K == 8192 && group == 64))) return best;
     const double mb = 0.5e-6 * N * K;
     for (const Cost &c : kCosts) {
         const PanelForm &f = panel_form(c.F, c.MF);
@@ -747,7 +745,7 @@ static PanelChoice panel_instead_of_tiles(const Args &a, bool rows64)
         const PanelChoice c = choose_panel(a.M, a.N, a.K, workspace_limit(a));
         if (c.form && c.us < 1.15 * few_tiles_us(a.M, a.N, a.K)) return c;
     }
-    return panel_instead_of_few_tiles(a.M, a.N, a.K, a.group, rows64);
+    return panel_instead_of_few_tiles(a.M, a.N, a.K, rows64);
 }
 
 struct Variant {
@@ -1194,11 +1192,11 @@ static int run(int variant, const Args &a)
 }
 
 // The name of the kernel that a launch over the given rows runs (with all K slices), to `text`.
-static void launch_name(int variant, int M, int N, int K, int group, char *text, size_t text_bytes)
+static void launch_name(int variant, int M, int N, int K, char *text, size_t text_bytes)
 {
     Args a{};
     size_t unused = 0;
-    a.M = M, a.N = N, a.K = K, a.group = group, a.query = &unused;
+    a.M = M, a.N = N, a.K = K, a.query = &unused;
     const bool dispatched = variant < 0;
     if (dispatched) variant = select_variant(M, N, K);
     if (dispatched && M <= 16) {
@@ -1745,7 +1743,7 @@ int w4a8_describe_launch(int variant, int M, int N, int K, int group, char *text
         Args a{};
         a.M = first, a.N = N, a.K = K, a.group = group, a.query = &need[0];
         if (int rc = run_rows(first == M ? variant : find_variant("solo16_pt_m256"), a)) return rc;
-        launch_name(first == M ? variant : -1, M - (first == M ? 0 : first), N, K, group, name, sizeof(name));
+        launch_name(first == M ? variant : -1, M - (first == M ? 0 : first), N, K, name, sizeof(name));
         if (first == M) {
             snprintf(words, sizeof(words), "%s", name);
         } else {

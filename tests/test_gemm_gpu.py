@@ -219,8 +219,8 @@ def test_workspace_is_optional_for_the_dispatcher():
             assert e.value.code == -3
 
 
-@pytest.mark.parametrize("M,N,K,g,kernel", [(64, 1088, 6912, 64, "panel_f1_m32_s3"), (100, 12672, 2304, 128, "duo_m64"),
-                                            (256, 10240, 8192, 64, "duo_m128"), (256, 6144, 16384, 64, "solo16_g2_sk_m256")])
+@pytest.mark.parametrize("M,N,K,g,kernel", [(64, 1088, 6912, 64, "panel_f1_m32_s3"), (258, 5632, 1792, 128, "duo_m64"),
+                                            (587, 3264, 4864, 64, "duo_m128"), (256, 6144, 16384, 64, "solo16_g2_sk_m256")])
 def test_dispatcher_without_room_for_its_slices(M, N, K, g, kernel):
     """K slices with the workspace the library asks for (twice: the tickets reset themselves), then
     with 16 bytes and with nothing: the same accumulators."""
@@ -413,7 +413,7 @@ def test_hip_graph_replays_of_split_k_kernels():
     # without slices: a 16-row kernel and panels; with K slices: 256-row tiles and their finish kernel, then with
     # tickets a 16-row kernel, a panel, 64- and 128-row tiles
     cases = [(8, 2048, 4096, 64, False), (48, 4096, 2048, 64, False), (200, 1024, 4096, 128, False), (256, 6144, 16384, 128, True),
-             (16, 2048, 8192, 64, True), (64, 1088, 6912, 64, True), (70, 12672, 2304, 64, True), (130, 12352, 5376, 128, True)]
+             (16, 2048, 8192, 64, True), (64, 1088, 6912, 64, True), (34, 25536, 1792, 64, True), (587, 3264, 4864, 128, True)]
     stream = torch.cuda.Stream()
     for M, N, K, g, slices in cases:
         picked, need = api.w4a8_describe_launch(M, N, K, g)
@@ -448,7 +448,7 @@ def test_hip_graph_replays_of_split_k_kernels():
     (16, 2048, 8192, 64, "stream16_h_w8_d2_s2"), (8, 1024, 8448, 64, "stream16_h_w8_d3_s2"),   # half tiles with two K slices
     (16, 2048, 12544, 64, "stream16_f1_w8"),       # whole tiles with two
     (64, 1088, 6912, 64, "panel_f1_m32_s3"),       # panels with three
-    (70, 12672, 2304, 64, "duo_m64"),              # 64-row tiles
+    (258, 5632, 1792, 64, "duo_m64"),              # 64-row tiles
 ])
 def test_workspace_init_and_concurrent_streams(M, N, K, g, kernel):
     """The split-K state lives in the caller's workspace: a dirty buffer works after
@@ -766,7 +766,7 @@ def test_forms_for_up_to_16_rows_of_many_channels(M, N, K, form):
     (63, 28672, 2048, "panel_f4_m64"), (65, 12736, 2304, "panel_f2_m128"), (255, 8192, 8448, "panel_f2_m128"),
     (97, 16448, 4864, "panel_f3_m128"), (512, 5632, 4096, "panel_f3_m128"), (90, 8320, 4352, "panel_f4_m32"),
     (385, 4672, 8192, "panel_f2_m64"), (97, 25664, 4352, "panel_f4_m128"), (257, 5568, 2816, "panel_f4_m64"),
-    (64, 28672, 2048, "duo_m64"), (256, 10240, 8192, "panel_f3_m128"), (513, 5632, 4096, "duo_m64")])
+    (64, 28672, 2048, "panel_f4_m64"), (256, 10240, 8192, "panel_f3_m128"), (513, 5632, 4096, "duo_m64")])
 def test_panels_instead_of_few_tiles(M, N, K, form):
     import torch
 

@@ -28,7 +28,7 @@ def test_static_workspace_entry_point_matches_w4a8_gemm():
     # 256-row tiles with K slices (a matrix of partial sums per slice and no tickets), then kernels that exchange partial
     # tiles by tickets: 64-row tiles, 64- and 32-row panels, half and whole tiles of the 16-row kernel, half
     # tiles again -- the tickets of each lie among those of the one before --, then a shape that uses no workspace at all
-    cases = [(256, 6144, 16384, 128, "solo16_g2_sk_m256"), (70, 12672, 2304, 64, "duo_m64"), (300, 1024, 8192, 128, "panel_f2_m64_s3"),
+    cases = [(256, 6144, 16384, 128, "solo16_g2_sk_m256"), (258, 5632, 1792, 64, "duo_m64"), (300, 1024, 8192, 128, "panel_f2_m64_s3"),
              (64, 1088, 6912, 64, "panel_f1_m32_s3"), (16, 2048, 12544, 64, "stream16_f1_w8"), (16, 2048, 8192, 64, "stream16_h_w8_d2_s2"),
              (8, 1024, 8448, 64, "stream16_h_w8_d3_s2"), (4096 + 40, 512, 512, 64, "duo_m64")]
     for i, (M, N, K, g, kernel) in enumerate(cases):
