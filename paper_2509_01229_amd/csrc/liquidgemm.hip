@@ -1019,13 +1019,14 @@ static const char *form_up_to_16_rows(int M, int N, int K)
     }
     if (tiles <= 256) {
         // one block a CU or less: up to 8 rows sixteen waves of one tile (K 4352..5888 0.91 / 0.93 up to 4 / 8 rows, 6400..8192 0.96 /
-        // 0.92, 8704..12032 0.94 / 0.96), above 32-row panels (K 5376..6144 0.97, 16640..24576 0.95), but not for 9 and 10 rows where
+        // 0.92, 8448..12032 0.94 / 0.96: 32-row panels 1.06 / 1.03 of it at 8448, 1.07 / 1.05 at 8960), above 32-row panels (K 5376..6144 0.97, 16640..24576 0.95), but not for 9 and 10 rows where
         // all sixteen waves' loads are in flight at once (7360 x 7168 at 9 rows 1.03 to 1.07 of the time on panels)
         if (M <= 8) {
             if (K <= 4096 || K >= 12288) return nullptr;
-            if (K == 6144) return M <= 4 ? "stream16_h_w8_d3" : nullptr;
-            if (M <= 4 && K > 7680 && K <= 8192) return "stream16_h_w8_d4";  // (7936 and 8192: 1.03 on whole tiles)
-            return K == 8448 ? "panel_f1_m32" : "stream16_f1_w16_s1";  // (at 8448 0.95 as at 8704)
+            // ... but half tiles where their passes are full or nearly so: two of three units for 46 to 48 units (0.96 / 0.97 up to 4
+            // / 8 rows; 44 units 1.02 / 1.04), up to 4 rows two of four for 62 to 64 (0.97; 56 to 60 units 1.03 to 1.04)
+            if (K > 5632 && K <= 6144) return "stream16_h_w8_d3";
+            return M <= 4 && K > 7680 && K <= 8192 ? "stream16_h_w8_d4" : "stream16_f1_w16_s1";
         }
         if (K > 24576) return nullptr;  // (0.98, at 28672 behind)
         if (K > 16384 || (K > 8192 && K < 12288)) return "panel_f1_m32";

@@ -304,6 +304,18 @@ def test_where_half_tiles_and_panels_are_behind_whole_tiles():
     assert runs(10, 512, 12544) == runs(12, 576, 12544) == "stream16_h_w8_d4_s2"
 
 
+def test_up_to_8_rows_of_one_tile_a_block_go_by_ranges_of_k():
+    """129..256 tiles: sixteen waves of one tile, half tiles where their passes are full or nearly so; no single K is an exception."""
+    runs = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0].split("[as ")[-1].rstrip("]")
+    for g in (64, 128):
+        for N in (4160, 8192):
+            for M in (1, 4, 5, 8):
+                assert {runs(M, N, K, g) for K in range(8448, 12288, 256)} == {"stream16_f1_w16_s1"}
+                assert {runs(M, N, K, g) for K in (5888, 6144)} == {"stream16_h_w8_d3"}
+                assert {runs(M, N, K, g) for K in (4352, 5632, 6400, 7680)} == {"stream16_f1_w16_s1"}
+                assert {runs(M, N, K, g) for K in (7936, 8192)} == {"stream16_h_w8_d4" if M <= 4 else "stream16_f1_w16_s1"}
+
+
 def _grouped(rows, N, K, g):
     offsets = [0]
     for r in rows:

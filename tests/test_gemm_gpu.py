@@ -707,7 +707,7 @@ def test_every_dispatched_panel_form(M, N, K, form):
     (4, 8256, 7936, "stream16_h_w8_d4"), (13, 128, 6400, "stream16_h_w8_d2_s2"), (1, 64, 20480, "stream16_h_w8_d2_s2"),
     (12, 576, 8448, "stream16_h_w8_d3_s2"), (2, 2048, 12544, "stream16_h_w8_d4_s2"), (12, 2112, 8448, "stream16_h_w16_d3"),
     (7, 2112, 12544, "stream16_h_w16_d4"), (16, 4160, 8192, "panel_f1_m32"),
-    (1, 4224, 8448, "panel_f1_m32"), (5, 8256, 6400, "panel_f2_m32")])
+    (9, 4224, 8448, "panel_f1_m32"), (5, 8256, 6400, "panel_f2_m32")])
 def test_every_form_in_place_of_the_16_row_kernels(M, N, K, form):
     import torch
 
@@ -733,7 +733,7 @@ def test_every_form_in_place_of_the_16_row_kernels(M, N, K, form):
 # ---------------------------------------------------------------------------------------
 @pytest.mark.parametrize("M,N,K,form", [
     (1, 1024, 8448, "stream16_h_w8_d2"), (8, 1024, 20736, "stream16_h_w8_d2_s2"), (8, 2112, 16640, "stream16_h_w8_d2"),
-    (3, 4160, 4352, "stream16_f1_w16_s1"), (8, 8192, 12032, "stream16_f1_w16_s1"), (11, 4160, 5632, "panel_f1_m32"),
+    (1, 4224, 8448, "stream16_f1_w16_s1"), (8, 4160, 5888, "stream16_h_w8_d3"), (3, 4160, 4352, "stream16_f1_w16_s1"), (8, 8192, 12032, "stream16_f1_w16_s1"), (11, 4160, 5632, "panel_f1_m32"),
     (16, 4160, 16640, "panel_f1_m32"), (4, 8256, 3072, "stream16_h_w8_d2"), (8, 12288, 3584, "stream16_h_w8_d2"),
     (4, 12288, 4864, "stream16_h_w8_d3"), (16, 12288, 4352, "panel_f2_m32"), (9, 14336, 4352, "panel_f2_m32"),
     (4, 16384, 4352, "stream16_f1_w8"), (16, 16448, 2048, "stream16_f1_w8"), (8, 16448, 6400, "stream16_f1_w16_s1"),
