@@ -330,14 +330,15 @@ static PanelChoice choose_panel(int M, int N, int K, size_t ws_limit)
     // From 5200 random calls (17 to 512 rows, N from 1024, K from 2048, to 28672 each), these against the fit's choice: with one row
     // tile, panels of 96 channels where they are less than a round in place of 128 channels (0.91: more of the CUs work), also
     // of 128 with slices in more than one round of blocks (20 x 20608 x 14336 37.2 / 30.0 us, 0.90); two slices of 64 channels for
-    // four of 128 (0.92); two of 32 for four of 64 (with several row tiles 0.85 to K = 12288, 0.96 to 20480, behind
-    // beyond; with one from 3072 channels on 0.93); with several row tiles up to K = 8192 one slice of 32 for two (0.96).
+    // four of 128 up to K = 40960 (0.92 to 28672, 0.96 beyond; 0.98 to 49152, behind from there on: 88 x 2432 x 124928 64.7 /
+    // 73.2 us); two of 32 for four of 64 (with several row tiles 0.85 to K = 12288, 0.96 to 20480, behind beyond; with one from 3072
+    // channels on 0.93); with several row tiles up to K = 8192 one slice of 32 for two (0.96).
     if (K < 2048 || N < 1024) return best;
     if (M <= 32 && F == 4 && best.S == 1 && blocks <= kAssumedCUs && panel_blocks(M, N, 3, 1) < kAssumedCUs)
         best.form = &panel_form(3, 1);
-    else if (F == 4 && best.S == 4)
-        best.form = &panel_form(2, 1), best.S = 2;
-    else if (M <= 32 && F == 4 && best.S > 1 && blocks * best.S > kAssumedCUs)
+    else if (F == 4 && best.S == 4) {
+        if (K <= 40960) best.form = &panel_form(2, 1), best.S = 2;
+    } else if (M <= 32 && F == 4 && best.S > 1 && blocks * best.S > kAssumedCUs)
         best.form = &panel_form(3, 1), best.S = 1;
     else if (F == 2 && best.S == 4 && K <= 20480 && (M > 32 || N >= 3072))
         best.form = &panel_form(1, 1), best.S = 2;

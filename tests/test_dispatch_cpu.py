@@ -286,6 +286,14 @@ def test_panels_instead_of_few_tiles_by_estimate_alone():
         assert name(256, 10240, 8192, g) == "panel_f3_m128" and name(130, 12352, 5376, g) == "panel_f2_m32"
 
 
+def test_four_slices_of_wide_panels_with_very_long_k():
+    """Two K slices of 32 x 64 panels stand in for four of 32 x 128 up to K = 40960 and are behind them beyond 49152."""
+    name = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0]
+    for g in (64, 128):
+        for M, N in ((88, 2432), (32, 5952), (32, 7040)):
+            assert name(M, N, 40960, g) == "panel_f2_m32_s2" and name(M, N, 114688, g) == name(M, N, 65536, g) == "panel_f4_m32_s4"
+
+
 def test_where_half_tiles_and_panels_are_behind_whole_tiles():
     """Up to 16 rows whole tiles stay where they were found ahead: K below 2048, 9 and 10 rows on 129..256 tiles with
     all of a wave's loads in flight, K slices of half tiles for more than 10 rows of up to 16 tiles."""
