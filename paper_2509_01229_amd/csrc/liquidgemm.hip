@@ -1000,6 +1000,7 @@ static const char *form_up_to_16_rows(int M, int N, int K)
         // 4096 5.1 / 4.0.  Shorter K keeps whole tiles: a wave of half tiles issues four units' loads whatever there is (K =
         // 256 3.0 / 3.4, 1536 3.60 / 3.64, 2048 3.76 / 3.67).  X is read twice as often, so from 13 rows long K keeps whole tiles too.
         if (K < 2048) return nullptr;
+        const int few = K <= 49152 ? 8 : 7;  // (beyond 8 rows are behind, 1.01 over 64 calls, 7 rows 0.95)
         if (K <= 4096) return "stream16_h_w8_d2";
         if (K <= 6144) return "stream16_h_w8_d3";
         // two units a pass in four passes against four in two: 0.97 up to 4 rows, 0.98 up to 8, equal above
@@ -1010,13 +1011,13 @@ static const char *form_up_to_16_rows(int M, int N, int K)
             const int most = tiles <= 16 ? 10 : 12;
             if (K <= 12288) return M <= 4 && some ? "stream16_h_w8_d2" : M <= most ? "stream16_h_w8_d3_s2" : nullptr;
             if (K <= 16384) return M <= most ? "stream16_h_w8_d4_s2" : nullptr;
-            return (M <= 4 && K <= 20480) || (M <= 8 && some) ? "stream16_h_w8_d2_s2" : nullptr;  // (beyond 20480: 0.88 / 0.93 up to 4 / 8 rows)
+            return (M <= 4 && K <= 20480) || (M <= few && some) ? "stream16_h_w8_d2_s2" : nullptr;  // (beyond 20480: 0.88 / 0.93 up to 4 / 8 rows)
         }
         if (K <= 16384) {
             if (M <= 4 && K <= 10240) return "stream16_h_w8_d2";  // (0.96; beyond equal to three units in sixteen waves)
             return M > 12 ? nullptr : K <= 12288 ? "stream16_h_w16_d3" : "stream16_h_w16_d4";
         }
-        return M <= 8 ? "stream16_h_w8_d2" : nullptr;  // (0.78 / 0.85 up to 4 / 8 rows)
+        return M <= few ? "stream16_h_w8_d2" : nullptr;  // (0.78 / 0.85 up to 4 / 8 rows)
     }
     if (tiles <= 256) {
         // one block a CU or less: up to 8 rows sixteen waves of one tile (K 4352..5888 0.91 / 0.93 up to 4 / 8 rows, 6400..8192 0.96 /

@@ -312,6 +312,17 @@ def test_where_half_tiles_and_panels_are_behind_whole_tiles():
     assert runs(10, 512, 12544) == runs(12, 576, 12544) == "stream16_h_w8_d4_s2"
 
 
+def test_half_tiles_of_8_rows_end_at_very_long_k():
+    """Up to 128 tiles with K beyond 49152: 7 rows are ahead on half tiles, 8 rows on whole ones."""
+    runs = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0]
+    for g in (64, 128):
+        for N, form in ((1344, "stream16_h_w8_d2_s2"), (4032, "stream16_h_w8_d2")):
+            for M, K in ((8, 49152), (7, 49408), (7, 129536), (1, 131072)):
+                assert runs(M, N, K, g).endswith(f"[as {form}]"), (M, N, K)
+            for K in (49408, 66048, 129536):
+                assert runs(8, N, K, g) == "stream16_f1_w8", (N, K)
+
+
 def test_up_to_8_rows_of_one_tile_a_block_go_by_ranges_of_k():
     """129..256 tiles: sixteen waves of one tile, half tiles where their passes are full or nearly so; no single K is an exception."""
     runs = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0].split("[as ")[-1].rstrip("]")
