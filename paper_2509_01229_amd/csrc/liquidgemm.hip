@@ -154,6 +154,8 @@ static int allow_lds(Kernel kernel, size_t bytes)
     return allow_lds_once(reinterpret_cast<const void *>(kernel), bytes);
 }
 
+constexpr long long kAssumedCUs = 256;  // the shape rules of the dispatcher are written for the MI355X
+
 // Grid-level split of K for the 16-row kernel, each wave keeping at least two units of 128 k.
 static int stream_split(int N, int K, int F, int NW)
 {
@@ -187,7 +189,12 @@ static int launch_stream16(const Args &a)
         need = 0;
     }
     const dim3 grid(groups, S), block(NW * 64);
-    const size_t lds_bytes = (size_t)NW * F * 8 * 64 * sizeof(int);
+    size_t lds_bytes = (size_t)NW * F * 8 * 64 * sizeof(int);
+    // Two tiles in four waves: with groups of 64 the registers let five blocks on a CU (four with 128), which is ahead where five
+    // hold them all (15 x 76416 x 9472 75.4 / 67.8 us) and behind where a few are left for a round of their own; four at a time, by the LDS
+    // that they ask for, are more even there (more than 5 to 6 blocks a CU 0.99 of the time to K = 4352, 0.97 to 6400, 0.95 beyond; 4 x 93056 x
+    // 9728 86.1 / 79.2 us).
+    if (NW == 4 && groups > 5 * kAssumedCUs && groups <= 6 * kAssumedCUs) lds_bytes = std::max<size_t>(lds_bytes, 36 << 10);
     unsigned int *tickets = static_cast<unsigned int *>(a.ws);
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
     if (a.group == 128) {
@@ -225,7 +232,6 @@ static int launch_stream16_half(const Args &a)
 
 // Panel kernel: 32 MF rows x 32 F channels per block, S slices of K across blocks, NW waves per
 // block (two per SIMD while the accumulators leave room for that, i.e. up to 64 rows).
-constexpr long long kAssumedCUs = 256;  // the shape rules of the dispatcher are written for the MI355X
 static long long panel_blocks(int M, int N, int F, int MF)
 {
     return (long long)((M + 32 * MF - 1) / (32 * MF)) * ((N / 32 + F - 1) / F);

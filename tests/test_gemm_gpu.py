@@ -756,6 +756,23 @@ def test_forms_for_up_to_16_rows_of_many_channels(M, N, K, form):
     H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
 
 
+@pytest.mark.parametrize("M,N,K", [(16, 81920, 2048), (1, 81984, 2304), (9, 98304, 2048), (16, 98368, 2304)])
+def test_two_tile_blocks_at_the_edges_of_four_to_a_cu(M, N, K):
+    """More than five blocks a CU, up to six: the launch asks for LDS that it does not use."""
+    import torch
+
+    for g in (64, 128):
+        name, _ = api.w4a8_describe_launch(M, N, K, g)
+        _say(f"two tiles in four waves M={M} N={N} K={K} g={g} -> {name}")
+        assert name == "stream16_f2_w4"
+        W = H.RandomWeights(N, K, g, seed=M)
+        X, sx = W.activations(M)
+        ref = W.product(X)
+        assert torch.equal(api.w4a8_gemm_i32(X, W.codes, W.gparams, N, K, g), ref)
+        Y = api.w4a8_gemm(X, sx, W.codes, W.gparams, W.scales, N, K, g)
+        H.assert_fp16_close(Y.cpu().numpy(), O.scale_epilogue_f64(ref.cpu().numpy(), sx.cpu().numpy(), W.scales.cpu().numpy()), name)
+
+
 # ---------------------------------------------------------------------------------------
 # Panels for 17 to 512 rows where the first estimates had tiles or other panels: ragged row tiles, last column
 # groups that are not full, waves without a unit in the last turn, with and without K slices
