@@ -122,6 +122,7 @@ __global__ __launch_bounds__(256, 2) void w4a8_duo_dl_grouped_kernel(const Group
 // The 256-row tiles (one wave per SIMD, see kernels_tiled_solo16.h) of all experts of a launch as
 // one persistent stream: resident blocks walk the tiles of every expert, with 256 x 256 tiles (KG = 1)
 // prefetching across the boundaries between them.  block_end counts 256 x 256 / KG tiles here.
+template <int KG>
 struct SoloGrouped {
     const GroupedPtrs &p;
     int N, K, blocks_n, total;
@@ -144,7 +145,7 @@ struct SoloGrouped {
         const int M = __builtin_amdgcn_readlane(rows, i), e = __builtin_amdgcn_readlane(expert, i);
         const int r0 = __builtin_amdgcn_readlane(row_off, i);
         int bm, bn;
-        solo_coords(local, (M + 255) / 256, blocks_n, bm, bn);
+        solo_coords<KG>(local, (M + 255) / 256, blocks_n, bm, bn);
         return SoloTile{M,
                         bm,
                         bn,
@@ -161,5 +162,5 @@ struct SoloGrouped {
 template <bool G128, int KG>
 __global__ __launch_bounds__(256, 1) void w4a8_solo_grouped_kernel(const GroupTable g, const GroupedPtrs p, int N, int K)
 {
-    solo16_body<G128, KG>(SoloGrouped(g, p, N, K, 256 / KG), N, K);
+    solo16_body<G128, KG>(SoloGrouped<KG>(g, p, N, K, 256 / KG), N, K);
 }

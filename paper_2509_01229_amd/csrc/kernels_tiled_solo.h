@@ -48,10 +48,22 @@ __device__ __forceinline__ int solo_xcd_order(int lid, int tiles, int G)
 {
     return (tiles & 7) == 0 && (G & 7) == 0 ? (lid & 7) * (tiles >> 3) + (lid >> 3) : lid;
 }
+// 256 x 128 tiles (KG = 2) look a tile up before its first load: no division where there is none to do (K = 256 to 1280 0.98 of the
+// time of the divisions).  256 x 256 tiles do so in the stage loop, which the branches lengthen: K up to 1280 1.007 with them against
+// 0.999 with the divisions, beyond 1.004 (1750 and 550 calls).
+template <int KG>
 __device__ __forceinline__ void solo_coords(int lid, int blocks_m, int blocks_n, int &bm, int &bn)
 {
     constexpr int GM = 4;
-    // (no division where there is none to do: these stand before a block's first load and, at the end of a tile, in the stage loop)
+    if constexpr (KG == 1) {
+        const int per_group = GM * blocks_n;
+        const int first = (lid / per_group) * GM;
+        const int gsz = min(blocks_m - first, GM);
+        const int in_group = lid % per_group;
+        bm = first + in_group % gsz;
+        bn = in_group / gsz;
+        return;
+    }
     const unsigned per_group = (unsigned)(GM * blocks_n);
     const unsigned group = blocks_m <= GM ? 0u : (unsigned)lid / per_group;
     const unsigned in_group = (unsigned)lid - group * per_group;
@@ -64,6 +76,7 @@ __device__ __forceinline__ void solo_coords(int lid, int blocks_m, int blocks_n,
 // slice ks writing its INT32 partial sums to matrix ks of ACC ([S][M][N]; Y is null then) for
 // splitk_finish_kernel to add up: the form for outputs with too few tiles for the chip
 // (Sec. 3.2: the batch sizes between the memory-bound and the compute-bound regime).
+template <int KG>
 struct SoloDense {
     int M, N;
     const int8_t *X;
@@ -82,7 +95,7 @@ struct SoloDense {
         const int per_slice = blocks_m * blocks_n;
         const int item = solo_xcd_order(lid, tiles(), G);  // an XCD's items: one slice (or part of one) of all tiles
         const int ks = S == 1 ? 0 : item / per_slice;
-        solo_coords(item - ks * per_slice, blocks_m, blocks_n, bm, bn);
+        solo_coords<KG>(item - ks * per_slice, blocks_m, blocks_n, bm, bn);
         return SoloTile{M, bm, bn, ks, X, sx, Wp, gp, sw, Y, ACC + (size_t)ks * M * N};
     }
 };
@@ -597,7 +610,7 @@ __global__ __launch_bounds__(256, 1) void w4a8_solo_pt_kernel(
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int blocks_m, int blocks_n, int S)
 {
-    solo_body<G128, KG>(SoloDense{M, N, X, sx, Wp, gp, sw, Y, ACC, blocks_m, blocks_n, S}, N, K);
+    solo_body<G128, KG>(SoloDense<KG>{M, N, X, sx, Wp, gp, sw, Y, ACC, blocks_m, blocks_n, S}, N, K);
 }
 
 // Adds up the S partial matrices of a launch with K slices and finishes the outputs like the

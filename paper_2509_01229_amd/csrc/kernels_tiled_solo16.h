@@ -586,5 +586,5 @@ __global__ __launch_bounds__(256, 1) void w4a8_solo16_pt_kernel(
     const uint8_t *__restrict__ gp, const float *__restrict__ sx, const float *__restrict__ sw, __half *__restrict__ Y,
     int32_t *__restrict__ ACC)  // (what the first loads need comes first: the first 14 dwords are in registers from the start)
 {
-    solo16_body<G128, KG>(SoloDense{M, N, X, sx, Wp, gp, sw, Y, ACC, blocks_m, blocks_n, S}, N, K);
+    solo16_body<G128, KG>(SoloDense<KG>{M, N, X, sx, Wp, gp, sw, Y, ACC, blocks_m, blocks_n, S}, N, K);
 }
