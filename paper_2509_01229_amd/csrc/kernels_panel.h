@@ -355,17 +355,15 @@ __device__ __forceinline__ void panel_block(
 
 template <int F, int NW, int MF, bool G128, bool ONCE>
 __global__ __launch_bounds__(NW * 64) void w4a8_panel_kernel(
-    int M, int N, int K, const int8_t *__restrict__ X, const float *__restrict__ sx,
+    int M, int N, int K, int S, const int8_t *__restrict__ X, const float *__restrict__ sx,
     const u32x4 *__restrict__ Wp, const uint8_t *__restrict__ gp, const float *__restrict__ sw,
     __half *__restrict__ Y, int32_t *__restrict__ ACC, int32_t *__restrict__ partials,
-    unsigned int *__restrict__ tickets, int /*blocks_m*/, int /*blocks_n*/, int /*S*/)
+    unsigned int *__restrict__ tickets)
 {
     // The command processor hands over the first 14 dwords of the arguments in registers (build.py), as far as `sw`; the first load
     // from the others waits for memory.  So nothing that the first addresses need is taken from those: the row tiles and column
-    // groups follow from M and N, and S - 1 sits in the low bits of N, a multiple of 64 (us without / with this, 64 x 8192 x 8192
-    // 13.8 / 13.5, 45 x 5120 x 13824 14.6 / 14.5, 128 x 11008 x 4096 14.4 / 14.0).  Divisions only where there is something to divide.
-    const int S = (N & 63) + 1;
-    N &= ~63;
+    // groups follow from M and N (us without / with this, 64 x 8192 x 8192 13.8 / 13.5, 45 x 5120 x 13824 14.6 / 14.5, 128 x 11008 x
+    // 4096 14.4 / 14.0).  Divisions only where there is something to divide.
     const int blocks_m = (int)(((unsigned)M + 32 * MF - 1) / (32 * MF)), blocks_n = (int)(((unsigned)N / 32 + F - 1) / F);
     // Consecutive block ids go to different XCDs: each XCD gets a run of logical ids, whose row tiles
     // of one column group are neighbours and find its weights in that XCD's L2 (and the slices of a tile end together).

@@ -260,8 +260,8 @@ static int launch_panel(const Args &a, int S)
     int32_t *partials = a.ws ? reinterpret_cast<int32_t *>(static_cast<char *>(a.ws) + kTicketBytes) : nullptr;
     auto go = [&](auto kernel) {
         if (int rc = allow_lds(kernel, lds_bytes)) return rc;
-        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, a.stream, a.M, a.N | (S - 1), a.K, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC,
-                           partials, tickets, blocks_m, blocks_n, S);
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, a.stream, a.M, a.N, a.K, S, a.X, a.sx, a.Wp, a.gp, a.sw, a.Y, a.ACC,
+                           partials, tickets);
         return (int)LQ_OK;
     };
     if (blocks_m == 1)
