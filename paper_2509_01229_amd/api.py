@@ -2,7 +2,8 @@
 
 The calls of a serving loop -- activation quantisation, GEMM, grouped GEMM -- first go to a native module
 (csrc/binding.cpp), which checks, allocates and launches where everything is as it usually is and leaves all else to
-the ctypes path below: a token through one 4096 x 4096 projection takes 10.5 us in place of 30.
+the ctypes path below: a token through one 4096 x 4096 projection takes 10.5 us in place of 30.  The module is built against
+one torch and one Python; without it, or with another, every call takes the ctypes path, and the first one says so.
 
 Host entry points take and return numpy arrays; device entry points take torch tensors
 that live on the GPU (torch is used for device memory and streams, nothing else) and
@@ -14,6 +15,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 import numpy as np
 
@@ -21,7 +24,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 # LIQUIDGEMM_LIB lets tools load another build of the same library (e.g. an experiment build)
 LIB_PATH = os.environ.get("LIQUIDGEMM_LIB") or os.path.join(_PKG, "libliquidgemm.so")
 _lib = None
-_native = None  # the native module, bound to _lib
+_native = None  # the native module, bound to _lib, or what stands in for it
 
 LQ_OK = 0
 LQ_ERR_INVALID, LQ_ERR_ALIGN, LQ_ERR_WORKSPACE, LQ_ERR_HIP = -1, -2, -3, -4
@@ -38,11 +41,10 @@ def lib() -> ctypes.CDLL:
     global _lib
     if _lib is not None:
         return _lib
-    for path in (LIB_PATH, os.path.join(_PKG, "_binding.so")):
-        if not os.path.exists(path):
-            raise FileNotFoundError(
-                f"{path} is missing: build it with `python -m paper_2509_01229_amd.build` "
-                "(there is no CPU fallback for the GEMM path)")
+    if not os.path.exists(LIB_PATH):
+        raise FileNotFoundError(
+            f"{LIB_PATH} is missing: build it with `python -m paper_2509_01229_amd.build` "
+            "(there is no CPU fallback for the GEMM path)")
     # torch ships its own HIP runtime; load it first so that the library binds to the
     # same runtime that owns the device pointers and streams it is handed.
     import torch  # noqa: F401
@@ -105,11 +107,40 @@ def lib() -> ctypes.CDLL:
     return L
 
 
-def _bind(L) -> None:
-    """Hand the native module the entry points of the loaded library."""
-    global _native
-    from . import _binding
+class _NoNative:
+    """Stands in for the native module where there is none for this torch and Python: declines every call, and says why once."""
 
+    def __init__(self, why):
+        self._why = why
+
+    def _decline(self, *args):
+        if self._why:
+            why, self._why = self._why, None
+            warnings.warn(f"no native module for this Python and torch ({why}): calls go through ctypes, 20 us more each; "
+                          "build it with `python -m paper_2509_01229_amd.build`", RuntimeWarning, stacklevel=3)
+
+    gemm = quantize = grouped = _decline
+
+
+def native_built_for() -> str:
+    """The Python and torch that a native module has to be built against to be used here."""
+    import torch
+
+    return f"Python {sys.version_info[0]}.{sys.version_info[1]}, torch {torch.__version__}"
+
+
+def _bind(L) -> None:
+    """Hand the native module, if there is one, the entry points of the loaded library."""
+    global _native
+    try:
+        from . import _binding
+
+        built_for = getattr(_binding, "built_for", "another version of this package")
+        if built_for != native_built_for():
+            raise ImportError(f"_binding.so is built for {built_for}, this is {native_built_for()}")
+    except ImportError as e:
+        _native = _NoNative(str(e))
+        return
     address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
     _binding.bind(address(L.w4a8_gemm), address(L.w4a8_gemm_workspace_size), address(L.w4a8_quantize_activations),
                   address(L.w4a8_grouped_gemm), address(L.liquidquant_packed_size))

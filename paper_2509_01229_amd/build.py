@@ -56,9 +56,12 @@ def build_binding(verbose: bool = False, out: str = os.path.join(PKG, "_binding.
     import torch
     from torch.utils import cpp_extension
 
+    from . import api
+
     libs = cpp_extension.library_paths(device_type="cpu")
     rocm = os.path.dirname(os.path.dirname(HIPCC))
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f'-DBUILT_FOR="{api.native_built_for()}"',
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
            "-I", sysconfig.get_paths()["include"],
            *(f for p in [*cpp_extension.include_paths(device_type="cpu"), os.path.join(rocm, "include")] for f in ("-isystem", p)),
@@ -115,5 +118,5 @@ def kernel_resource_usage(stderr_text: str) -> dict:
 
 
 if __name__ == "__main__":
-    print(build_binding(verbose=True))
     print(build_library(verbose=True))
+    print(build_binding(verbose=True))

@@ -212,4 +212,10 @@ PyModuleDef module{PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__binding()
+{
+    PyObject *const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", BUILT_FOR) == 0) return m;  // (api.py looks at it before the first call)
+    Py_XDECREF(m);
+    return nullptr;
+}

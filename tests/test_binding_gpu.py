@@ -155,3 +155,41 @@ def test_what_the_native_module_leaves_alone():
     for offs in ((0, 4), [0], [0, 2.0], [0, True], [0, 2 ** 70], [0] * 70, []):
         assert api._native.grouped(offs, X, s, W, W, s, 64, 256, 64, None, None) is None
     assert api._native.gemm() is None and api._native.quantize(X) is None and api._native.grouped(1) is None
+
+
+@pytest.mark.parametrize("what", ["missing", "of another torch"])
+def test_without_a_native_module_for_this_torch(monkeypatch, what):
+    """Only the calls that would use it notice, and they run on the ctypes path: the host functions need the C library alone."""
+    import sys
+    import types
+    import warnings
+
+    import paper_2509_01229_amd as package
+
+    monkeypatch.setattr(api, "_native", None)
+    monkeypatch.setattr(api, "_lib", None)
+    monkeypatch.delattr(package, "_binding", raising=False)
+    other = types.ModuleType("paper_2509_01229_amd._binding")
+    other.built_for = "Python 3.9, torch 1.0"
+    monkeypatch.setitem(sys.modules, "paper_2509_01229_amd._binding", None if what == "missing" else other)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        packed, gparams = api.liquidquant_pack_from_i8(np.ones((64, 256), np.int8), 64)
+        assert packed.size == 64 * 256 // 2 and api.w4a8_describe_launch(8, 64, 256, 64)[0]
+    import torch
+
+    X = torch.zeros((4, 256), dtype=torch.int8)   # (on the host: the ctypes path refuses it)
+    with pytest.warns(RuntimeWarning, match="no native module"):
+        with pytest.raises(TypeError):
+            api.w4a8_gemm(X, torch.ones(4), X, X, torch.ones(64), 64, 256, 64)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        for call in (lambda: api.w4a8_gemm(X, torch.ones(4), X, X, torch.ones(64), 64, 256, 64), lambda: api.w4a8_quantize_activations(X.half()),
+                     lambda: api.w4a8_grouped_gemm([0, 4], X, torch.ones(4), X, X, torch.ones(1, 64), 64, 256, 64)):
+            with pytest.raises(TypeError):
+                call()
+
+
+def test_the_built_native_module_is_used():
+    api.lib()
+    assert api._native.__name__ == "paper_2509_01229_amd._binding" and api._native.built_for == api.native_built_for()
