@@ -102,9 +102,9 @@ PyObject *quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (rc != LQ_OK) return PyLong_FromLong(rc);
     PyObject *const pq = a[2] != Py_None ? (Py_INCREF(a[2]), a[2]) : THPVariable_Wrap(std::move(q));
     PyObject *const ps = a[3] != Py_None ? (Py_INCREF(a[3]), a[3]) : THPVariable_Wrap(std::move(s));
-    PyObject *const both = PyTuple_New(2);
-    PyTuple_SET_ITEM(both, 0, pq);
-    PyTuple_SET_ITEM(both, 1, ps);
+    PyObject *const both = pq && ps ? PyTuple_Pack(2, pq, ps) : nullptr;
+    Py_XDECREF(pq);
+    Py_XDECREF(ps);
     return both;
     END_HANDLE_TH_ERRORS
 }
