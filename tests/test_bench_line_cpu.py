@@ -2,6 +2,8 @@
 import json
 
 import bench
+from paper_2509_01229_amd import api
+from paper_2509_01229_amd import workloads as WL
 
 
 def test_result_line_is_short_and_complete():
@@ -26,3 +28,12 @@ def test_result_line_is_short_and_complete():
     assert all(line[k] == out[k] for k in contract)
     assert line["curve_N8192_K8192"][0] == [4096, 12345.678, 0.1234]
     assert len(json.dumps(line)) < 1950
+
+
+def test_traffic_is_that_of_the_kernels_that_run():
+    """The result line's two kernels have a measured traffic under the names that the library reports for them."""
+    for name in ("prefill_M4096_N8192_K8192", bench.HBM_WORKLOAD):
+        s = WL.by_name(name)
+        kernel = api.w4a8_describe_launch(s.M, s.N, s.K, s.group)[0]
+        traffic = bench.measured_traffic(name, kernel)
+        assert traffic and traffic >= bench.algorithmic_bytes(s.M, s.N, s.K, s.group), kernel
