@@ -1063,8 +1063,12 @@ static const char *form_up_to_16_rows(int M, int N, int K)
         if (M <= 8 || K <= 8192) return "stream16_f1_w16_s1";
         return K <= 16384 ? "panel_f1_m32" : "stream16_f2_w8_s2";
     }
-    if (tiles <= 896)  // (0.92 and 0.94; 0.96 to 0.98: 16 x 28672 x 8192 25.3 / 24.6 us)
-        return M <= 8 && K <= 4096 ? "stream16_f1_w8" : "panel_f2_m32";
+    if (tiles <= 896) {
+        // (0.92 and 0.94; 0.96 to 0.98: 16 x 28672 x 8192 25.3 / 24.6 us; from 9 rows on K = 2048, which has eight waves a block before
+        // it, 1.02 on panels)
+        if (M <= 8 && K <= 4096) return "stream16_f1_w8";
+        return K <= 2048 ? nullptr : "panel_f2_m32";
+    }
     return nullptr;
 }
 static int in_place_of_stream16(int variant, const Args &a)

@@ -312,6 +312,15 @@ def test_where_half_tiles_and_panels_are_behind_whole_tiles():
     assert runs(10, 512, 12544) == runs(12, 576, 12544) == "stream16_h_w8_d4_s2"
 
 
+def test_two_tile_blocks_of_eight_waves_keep_k_up_to_2048():
+    """769..896 tiles from 9 rows on: panels for K from 2304 on, where these blocks have four waves."""
+    runs = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0]
+    for g in (64, 128):
+        for M, N in ((9, 24640), (16, 28672)):
+            assert runs(M, N, 2048, g) == "stream16_f2_w8" and runs(M, N, 2304, g) == "stream16_f2_w4[as panel_f2_m32]"
+        assert runs(8, 28672, 2048, g) == "stream16_f2_w8[as stream16_f1_w8]"
+
+
 def test_half_tiles_of_8_rows_end_at_very_long_k():
     """Up to 128 tiles with K beyond 49152: 7 rows are ahead on half tiles, 8 rows on whole ones."""
     runs = lambda M, N, K, g: api.w4a8_describe_launch(M, N, K, g)[0]
