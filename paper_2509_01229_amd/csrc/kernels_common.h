@@ -60,8 +60,8 @@ __device__ __forceinline__ int slice_begin(int units, int ks, int S)
 }
 
 // Where a block works: gx = its tile group (or output tile) among gnx, ks = its slice of S
-// K slices.  Plain launches take these from the grid (blockIdx.x, gridDim.x, blockIdx.y,
-// gridDim.y); grouped launches compute them per expert.
+// K slices.  The tiled kernels' plain launches take these from the grid (blockIdx.x, gridDim.x, blockIdx.y, gridDim.y), the 16-row
+// kernels and panels from it and their arguments; grouped launches compute them per expert.
 struct Place {
     int gx, gnx, ks, S;
     unsigned int *tickets;  // arrival tickets of the split-K groups (unused when S == 1)

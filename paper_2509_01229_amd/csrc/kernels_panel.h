@@ -9,7 +9,7 @@
 // 47.0 thousand cycles that a SIMD's two waves live hold 20.9 of vector and 16.4 of matrix instructions, of 45 x 13824 x
 // 5120 (F = 2, MF = 2) the 24.5 hold 7.3 and 5.1 (counters); the form before, with one set of W registers, took 20.6 of 26.5 us and
 // 10.2 of 13.7 without its loads, 22.5 and 12.5 without dequantisation and MFMA.  It is the dequantisation of W for few
-// rows, the way of X and W from L2 (64 KB per us and CU, what a CU draws from beyond its L2) and 5 to 7 us of launch,
+// rows, the way of X and W to the CU (X in pieces of rows 55 to 60 KB per us and CU also from L2, however many are in flight, whole KiBs 115) and 5 to 7 us of launch,
 // first loads and sum, which do not depend on K; hence forms from 1 x 1 to 4 x 4 accumulator tiles, which trade the volume of X and the
 // repeated dequantisation against the sum over the waves and the number of blocks.  Two things keep the loads ahead:
 //   * W sits in two sets of registers: a unit's is loaded while the unit two before it is computed, as the

@@ -294,8 +294,8 @@ struct PanelChoice {
 // fitted to 14 row counts (17 to 512) x 17 weight shapes (1024 to 28672 channels and k) x all forms
 // and 1 to 4 slices of the panel kernel with one set of W registers, 8 % rms.  Audited with the present kernel on 2200 calls of 17 to 512
 // rows (channels from 1024, k from 2048, to 28672 each, weights from HBM): the form it picks is 0.5 % behind the best one at 17..32 rows, 0.8 %
-// at 33..64, 1.4 to 2.0 % above (geometric means; 24 % at worst).  It never picks 32 x 64 and 128 x 128, the best in 7 and 4 % of them.
-// (One block of 32 x 64 fits a CU with its 128 KB of LDS, two of 32 x 32.)
+// at 33..64, 1.4 to 2.0 % above (geometric means; 24 % at worst).  The fit itself never picks 32 x 64 and 128 x 128, the best in 7 and 4 % of
+// them; the exceptions behind it and panel_instead_of_few_tiles do.
 //   2.26 us of launch and first loads
 //   + 0.61 us per accumulator tile (32 x 32) of a block: the sum over the waves and the epilogue
 //   + 9.8 ns per KB of X and 19.1 ns per KB of W that a CU takes in (X comes from L2; W is also dequantised)
@@ -1042,7 +1042,8 @@ static const char *form_up_to_16_rows(int M, int N, int K)
     }
     if (tiles <= 384) {
         // half tiles where K is close below 4096 or 6144 (4 x 11008 x 4096 8.1 / 7.25 us; K = 3072 0.97, 2816 1.01; at 5 to 8 rows
-        // from 3584 on), else panels of 32 x 64 (K to 6144 0.96, to 12288 0.95, beyond 0.88 to 0.97)
+        // from 3584 on), else panels of 32 x 64 (K to 6144 0.96, to 12288 0.95, beyond 0.88 to 0.97; above 28672 0.90 over 948 calls, but 13 of
+        // them more than 4 % behind, at worst 6 x 11776 x 73728 87 / 103 us)
         if (K <= 4096) return (M <= 4 && K >= 3072) || (M <= 8 && K >= 3584) ? "stream16_h_w8_d2" : nullptr;
         if (M <= 4 && K >= 4864 && K <= 8192) return K <= 6144 ? "stream16_h_w8_d3" : "stream16_h_w8_d4";
         return "panel_f2_m32";
@@ -1353,7 +1354,8 @@ static int grouped_panel_run(const GroupedArgs &a, GroupTable &t)
 // 12000, hence the 10 % that panels have to win by.  So picked, 4600 such calls are 0.9 % behind the best of the three and none
 // is more than 3 % behind tiles alone (48 % ahead of them): a few experts are few tiles, and the tiles of a grouped launch have no
 // K slices across blocks (us on tiles / as picked: one expert of 128 rows on 4096 x 14336 55.8 / 19.4, two of 64 on
-// 14336 x 4096 20.0 / 19.7; eight of 64 there stay on tiles, 60 against 69).
+// 14336 x 4096 20.0 / 19.7; eight of 64 there stay on tiles, 60 against 69).  32-row panels are priced as of 64 channels; where
+// grouped_panel_run takes 32 a block they run in about 0.8 of that, so tiles are taken a little too often there.
 static double grouped_panel_us(const GroupTable &t, int N, int K, int F, int MF)
 {
     long long blocks = 0;
