@@ -248,7 +248,7 @@ template <int F, int NW, int MF>
 static int launch_panel(const Args &a, int S)
 {
     const int blocks_m = (a.M + 32 * MF - 1) / (32 * MF), blocks_n = (a.N / 32 + F - 1) / F;
-    S = std::max(1, std::min(S, a.K / 128));
+    S = std::max(1, std::min({S, a.K / 128, kMaxPanelSlices}));
     if (S > 1 && blocks_m * blocks_n > kMaxTicketGroups) S = 1;
     const size_t need = panel_ws_bytes(blocks_m * blocks_n, F, MF, S);
     if (a.query) return *a.query = need, LQ_OK;
